@@ -185,6 +185,8 @@ def _engine(case):
         extra = case["turns"] * (case["steps"] + case["tokens"])
     if case["kind"] == "append":
         longest = case["context"]
+    if case["kind"] == "score":
+        longest = max(o + case["turns"] * (g + o) for g, o in _turns(case))
     room = longest + extra + grow + 16
     n = case["batch"] * (2 if case["kind"] == "append" else 1) + case.get("arrivals", 0)
     config = (room, HELD * n, HELD * (n * (room // 16 + 2)), rl.FLAG_FP8_KV_CACHE if case.get("cache8") else 0)
