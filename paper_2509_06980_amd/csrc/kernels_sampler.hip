@@ -9,14 +9,24 @@
 // The log-prob is t_id * ln 2 - ln(sum e_i).  This file must be compiled with
 // -ffp-contract=off: a fused multiply-add would change the weights' bits.
 //
-// Three launches over segments of RL_SAMPLER_SEG logits: per-segment max, per-segment weight sums,
-// then one workgroup per row locates the segment and the token inside it.
+// Launches: per-segment maxima (segments of RL_SAMPLER_SEG logits; left out where the lm-head has left
+// maxima of its own), weight sums of the segments, then one workgroup per row that locates the segment
+// and the token inside it.
 #include "../../include/rl_rollout.h"
 #include "kernels.h"
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
-__device__ __forceinline__ void exp2_weight(float z, float m, float c, float& e, uint64_t& w) {
+// x = e * 2^32 (exact scaling) and w = floor(x).  e < 1 except at the maximum, where it is exactly 1 (or
+// 1 by rounding just below it), so w fits 32 bits except there: w is converted as one 32-bit integer
+// that saturates at the largest float below 2^32, and the caller adds the missing kTop where
+// x >= 2^32.  A 64-bit conversion takes three times the instructions and had made the weights pass
+// bound by its arithmetic (128 x 151 936 logits: 30 us, 78 MB).  A NaN gives weight 0.
+constexpr float kTwo32 = 4294967296.0f;
+constexpr uint32_t kTop = 256;
+__device__ __forceinline__ void exp2_weight(float z, float m, float c, float& x, uint32_t& w) {
   const float C1 = 0x1.62e430p-1f, C2 = 0x1.ebfc40p-3f, C3 = 0x1.c69f6ap-5f, C4 = 0x1.3c4a8ap-7f,
               C5 = 0x1.4ca4ccp-10f, C6 = 0x1.b4d1e4p-13f;
   float t = __fmul_rn(__fsub_rn(z, m), c);
@@ -29,13 +39,9 @@ __device__ __forceinline__ void exp2_weight(float z, float m, float c, float& e,
   p = __fadd_rn(__fmul_rn(p, r), C2);
   p = __fadd_rn(__fmul_rn(p, r), C1);
   p = __fadd_rn(__fmul_rn(p, r), 1.0f);
-  if (n < -40.0f) {
-    e = 0.f;
-    w = 0;
-  } else {
-    e = ldexpf(p, (int)n);
-    w = (uint64_t)__fmul_rn(e, 4294967296.0f);
-  }
+  x = __builtin_amdgcn_ldexpf(p, (int)fmaxf(n, -64.0f) + 32);
+  if (n < -40.0f) x = 0.f;
+  w = (uint32_t)__builtin_amdgcn_fmed3f(x, 0.f, 4294967040.0f);
 }
 
 __host__ __device__ __forceinline__ uint32_t splitmix_u32(uint64_t seed, int32_t traj, int32_t pos) {
@@ -51,21 +57,49 @@ extern "C" uint32_t rl_uniform_u32(uint64_t seed, int32_t traj_id, int32_t posit
   return splitmix_u32(seed, traj_id, position);
 }
 
-// grid (nseg, rows), block 256
-__global__ void seg_max_kernel(const float* __restrict__ z, size_t ldz, int V,
-                               float* __restrict__ segmax, int32_t* __restrict__ segarg) {
+// The 16 logits of a thread in segment `seg`: VEC (rows of whole, aligned 16-byte pieces): four pieces
+// per thread, all requested before the first use; otherwise single logits.  The order of a thread's
+// logits is ascending either way.
+template <bool VEC>
+__device__ __forceinline__ int seg_index(int seg, int tid, int i) {
+  return VEC ? seg * RL_SAMPLER_SEG + ((i >> 2) * 256 + tid) * 4 + (i & 3) : seg * RL_SAMPLER_SEG + i * 256 + tid;
+}
+__device__ __forceinline__ bool s_whole(int seg, int V) { return (int64_t)(seg + 1) * RL_SAMPLER_SEG <= V; }
+template <bool VEC>
+__device__ __forceinline__ void seg_load(const float* __restrict__ zr, int V, int seg, int tid, float (&v)[16]) {
+  if (VEC) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int idx = seg_index<true>(seg, tid, 4 * i);
+      const float4 q = *(const float4*)(zr + (idx < V ? idx : 0));
+      v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      const int idx = seg_index<false>(seg, tid, i);
+      v[i] = zr[idx < V ? idx : 0];
+    }
+  }
+}
+
+// grid (nseg, rows), block 256.  Bound by the read of the logits: 14.1 us for 128 x 151 936 (5.5 TB/s;
+// 22.9 us with one 4-byte read at a time).
+template <bool VEC>
+__global__ __launch_bounds__(256) void seg_max_kernel(const float* __restrict__ z, size_t ldz, int V,
+                                                      float* __restrict__ segmax,
+                                                      int32_t* __restrict__ segarg) {
   __shared__ float sv[4];
   __shared__ int si[4];
   int seg = blockIdx.x, row = blockIdx.y, nseg = gridDim.x;
-  const float* zr = z + (size_t)row * ldz;
+  float v[16];
+  seg_load<VEC>(z + (size_t)row * ldz, V, seg, threadIdx.x, v);
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  for (int i = 0; i < RL_SAMPLER_SEG / 256; i++) {
-    int idx = seg * RL_SAMPLER_SEG + i * 256 + threadIdx.x;
-    if (idx < V) {
-      float v = zr[idx];
-      if (v > best || (v == best && idx < bi)) { best = v; bi = idx; }
-    }
+#pragma unroll
+  for (int i = 0; i < 16; i++) {
+    const int idx = seg_index<VEC>(seg, threadIdx.x, i);
+    if (idx < V && (v[i] > best || (v[i] == best && idx < bi))) { best = v[i]; bi = idx; }
   }
   for (int o = 32; o > 0; o >>= 1) {
     float ov = __shfl_xor(best, o, 64);
@@ -82,133 +116,225 @@ __global__ void seg_max_kernel(const float* __restrict__ z, size_t ldz, int V,
   }
 }
 
-// grid rows, block 256: the row maximum from the per-strip maxima that the lm-head epilogue left,
-// written into every per-segment slot of the row, so that the two kernels below find it where
-// seg_max_kernel would have put the segment maxima (the maximum does not depend on the order of
-// the reduction: same bits either way).  The arg-max is not formed (sampling does not need it).
-__global__ void row_max_kernel(const float* __restrict__ stripmax, int nstrips, int nseg,
-                               float* __restrict__ segmax, int32_t* __restrict__ segarg) {
-  __shared__ float red[4];
-  const int row = blockIdx.x;
-  const float* p = stripmax + (size_t)row * nstrips;
-  float m = -INFINITY;
-  for (int j = threadIdx.x; j < nstrips; j += 256) m = fmaxf(m, p[j]);
-  m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  for (int k = threadIdx.x; k < nseg; k += 256) {
-    segmax[(size_t)row * nseg + k] = m;
-    segarg[(size_t)row * nseg + k] = 0;
-  }
-}
-
-// grid (nseg, rows), block 256
-__global__ void seg_weight_kernel(const float* __restrict__ z, size_t ldz, int V, float c,
-                                  const float* __restrict__ segmax, uint64_t* __restrict__ segw,
-                                  float* __restrict__ sege) {
+// grid (ceil(nseg / spw), rows), block 256: weight sums of up to spw consecutive segments of a row.
+// The row maximum is first reduced from `maxima` (nmax per row: the lm-head's strip maxima, or the
+// segment maxima): several segments per workgroup, so that reading the maxima stays a small part of
+// its work and needs no launch of its own.  The next segment's logits are requested before the
+// current one's arithmetic.  128 x 151 936 logits: 20.4 us from segment maxima, 23 us from 4748 strip
+// maxima (30 us, and 38 + 8 us with a launch of its own for the maxima, before); bound by about 28
+// vector instructions per logit.  put_max: the maximum is left in the row's segmax entries for the last
+// kernel (strip maxima; with segment maxima they hold it already).
+template <bool VEC>
+__global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict__ z, size_t ldz, int V, float c,
+                                                         const float* maxima, int nmax, int spw, int nseg, int put_max,
+                                                         float* segmax, uint64_t* __restrict__ segw,
+                                                         float* __restrict__ sege) {
+  __shared__ float sm[4];
   __shared__ uint64_t sw[4];
   __shared__ float se[4];
-  int seg = blockIdx.x, row = blockIdx.y, nseg = gridDim.x;
+  const int row = blockIdx.y, tid = threadIdx.x;
+  const int s0 = blockIdx.x * spw, s1 = min(s0 + spw, nseg);
   const float* zr = z + (size_t)row * ldz;
+  float v[16];
+  seg_load<VEC>(zr, V, s0, tid, v);
   float m = -INFINITY;
-  for (int k = 0; k < nseg; k++) m = fmaxf(m, segmax[(size_t)row * nseg + k]);
-  uint64_t ws = 0;
-  float es = 0.f;
-  for (int i = 0; i < RL_SAMPLER_SEG / 256; i++) {
-    int idx = seg * RL_SAMPLER_SEG + i * 256 + threadIdx.x;
-    if (idx < V) {
-      float e;
-      uint64_t w;
-      exp2_weight(zr[idx], m, c, e, w);
-      ws += w;
-      es = __fadd_rn(es, e);
-    }
+  const float* mr = maxima + (size_t)row * nmax;
+  for (int k = tid; k < nmax; k += 256 * 8) {      // eight independent reads in flight
+    float q[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) q[j] = mr[min(k + 256 * j, nmax - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; j++) m = fmaxf(m, q[j]);
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    ws += __shfl_xor(ws, o, 64);
-    es = __fadd_rn(es, __shfl_xor(es, o, 64));
-  }
-  if ((threadIdx.x & 63) == 0) { sw[threadIdx.x >> 6] = ws; se[threadIdx.x >> 6] = es; }
+  m = wave_max(m);
+  if ((tid & 63) == 0) sm[tid >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    segw[(size_t)row * nseg + seg] = sw[0] + sw[1] + sw[2] + sw[3];
-    sege[(size_t)row * nseg + seg] = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3]));
+  m = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+  for (int seg = s0; seg < s1; seg++) {
+    float nx[16];
+    if (seg + 1 < s1) seg_load<VEC>(zr, V, seg + 1, tid, nx);
+    uint64_t ws = 0;
+    float es = 0.f;
+    float xm = 0.f;
+    if (s_whole(seg, V)) {              // no element of the segment lies behind the row's end
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        float x;
+        uint32_t w;
+        exp2_weight(v[i], m, c, x, w);
+        ws += w;
+        es = __fadd_rn(es, x);
+        xm = fmaxf(xm, x);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        float x;
+        uint32_t w;
+        exp2_weight(v[i], m, c, x, w);
+        const bool in = seg_index<VEC>(seg, tid, i) < V;
+        ws += in ? w : 0u;
+        es = __fadd_rn(es, in ? x : 0.f);
+        xm = in ? fmaxf(xm, x) : xm;
+      }
+    }
+    if (__any(xm >= kTwo32)) {          // the row's maximum is among the wave's elements
+#pragma unroll
+      for (int i = 0; i < 16; i++) {
+        float x;
+        uint32_t w;
+        exp2_weight(v[i], m, c, x, w);
+        if (x >= kTwo32 && seg_index<VEC>(seg, tid, i) < V) ws += kTop;
+      }
+    }
+    if (seg + 1 < s1) {
+#pragma unroll
+      for (int i = 0; i < 16; i++) v[i] = nx[i];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      ws += __shfl_xor(ws, o, 64);
+      es = __fadd_rn(es, __shfl_xor(es, o, 64));
+    }
+    if (seg > s0) __syncthreads();      // the previous segment's sums have been read
+    if ((tid & 63) == 0) { sw[tid >> 6] = ws; se[tid >> 6] = es; }
+    __syncthreads();
+    if (tid == 0) {
+      segw[(size_t)row * nseg + seg] = sw[0] + sw[1] + sw[2] + sw[3];
+      sege[(size_t)row * nseg + seg] = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3])) * 0x1p-32f;
+      if (put_max) segmax[(size_t)row * nseg + seg] = m;
+    }
   }
 }
 
-// grid rows, block 256
-__global__ void sample_final_kernel(const float* __restrict__ z, size_t ldz, int V, float c,
-                                    int greedy, int nseg, const float* __restrict__ segmax,
-                                    const int32_t* __restrict__ segarg,
-                                    const uint64_t* __restrict__ segw,
-                                    const float* __restrict__ sege, const uint32_t* __restrict__ u32,
-                                    uint64_t seed, const int32_t* __restrict__ row_traj,
-                                    const int32_t* __restrict__ row_newpos,
-                                    const int32_t* __restrict__ forced,
-                                    const uint8_t* __restrict__ out_mask,
-                                    int32_t* __restrict__ ids_out, float* __restrict__ logp_out) {
-  __shared__ uint64_t tsum[256];
-  __shared__ int chosen;
-  int row = blockIdx.x, tid = threadIdx.x;
-  const float* zr = z + (size_t)row * ldz;
-  float m = -INFINITY;
-  int arg = 0;
-  uint64_t W = 0;
-  float E = 0.f;
-  for (int k = 0; k < nseg; k++) {
-    float v = segmax[(size_t)row * nseg + k];
-    if (v > m) { m = v; arg = segarg[(size_t)row * nseg + k]; }   // first segment wins ties
-    W += segw[(size_t)row * nseg + k];
-    E = __fadd_rn(E, sege[(size_t)row * nseg + k]);
+// Inclusive sum over the workgroup's 256 threads; *total gets the sum of all.  tmp: 4 entries of LDS.
+__device__ __forceinline__ uint64_t block_scan(uint64_t x, uint64_t* tmp, uint64_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    uint64_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  int id;
-  if (forced) {
-    id = forced[row];
-  } else if (greedy) {
-    id = arg;
-  } else {
-    uint32_t u = u32 ? u32[row] : splitmix_u32(seed, row_traj[row], row_newpos[row]);
-    uint64_t hi = __umul64hi(W, (uint64_t)u), lo = W * (uint64_t)u;
-    uint64_t r = (hi << 32) | (lo >> 32);          // floor(u * W / 2^32) < W
-    int s = 0;
-    uint64_t pre = 0;
-    for (; s < nseg - 1; s++) {
-      uint64_t w = segw[(size_t)row * nseg + s];
-      if (pre + w > r) break;
-      pre += w;
+  __syncthreads();                      // an earlier use of tmp is over
+  if (lane == 63) tmp[wave] = x;
+  __syncthreads();
+  uint64_t before = 0;
+  for (int k = 0; k < wave; k++) before += tmp[k];
+  *total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  return x + before;
+}
+
+// grid rows, block 256.  A chain of three dependent reads (segment sums, the chosen segment's logits,
+// none for the log-prob): the sums over segments and the two searches are spread over the lanes (128
+// rows: 15.1 -> 6.6 us).
+template <bool VEC>
+__global__ __launch_bounds__(256) void sample_final_kernel(
+    const float* __restrict__ z, size_t ldz, int V, float c, int greedy, int nseg,
+    const float* __restrict__ segmax, const int32_t* __restrict__ segarg, const uint64_t* __restrict__ segw,
+    const float* __restrict__ sege, const uint32_t* __restrict__ u32, uint64_t seed,
+    const int32_t* __restrict__ row_traj, const int32_t* __restrict__ row_newpos,
+    const int32_t* __restrict__ forced, const uint8_t* __restrict__ out_mask, int32_t* __restrict__ ids_out,
+    float* __restrict__ logp_out) {
+  __shared__ uint64_t tmp[4], s_pre;
+  __shared__ float sm[4], se[4], s_z;
+  __shared__ int sa[4], s_seg, s_id;
+  const int row = blockIdx.x, tid = threadIdx.x;
+  const float* zr = z + (size_t)row * ldz;
+  const size_t r0 = (size_t)row * nseg;
+  float m = -INFINITY, E = 0.f;
+  int arg = 0x7fffffff;
+  uint64_t W = 0;
+  for (int k = tid; k < nseg; k += 256) {
+    const float v = segmax[r0 + k];
+    if (greedy) {
+      const int a = segarg[r0 + k];
+      if (v > m || (v == m && a < arg)) { m = v; arg = a; }
+    } else {
+      m = fmaxf(m, v);
     }
-    uint64_t rl = r - pre;                         // target inside segment s
-    const int PER = RL_SAMPLER_SEG / 256;          // 16 consecutive logits per thread
-    int base = s * RL_SAMPLER_SEG + tid * PER;
+    W += segw[r0 + k];
+    E = __fadd_rn(E, sege[r0 + k]);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(m, o, 64);
+    const int oa = __shfl_xor(arg, o, 64);
+    if (greedy ? (ov > m || (ov == m && oa < arg)) : ov > m) { m = ov; arg = oa; }
+    E = __fadd_rn(E, __shfl_xor(E, o, 64));
+    W += __shfl_xor(W, o, 64);
+  }
+  if ((tid & 63) == 0) { sm[tid >> 6] = m; sa[tid >> 6] = arg; se[tid >> 6] = E; tmp[tid >> 6] = W; }
+  if (tid == 0) { s_seg = nseg - 1; s_id = -1; }
+  __syncthreads();
+  m = sm[0];
+  arg = sa[0];
+  for (int k = 1; k < 4; k++)
+    if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
+  E = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3]));
+  W = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  int id;
+  float zid = 0.f;
+  if (forced || greedy) {
+    id = forced ? forced[row] : (arg == 0x7fffffff ? 0 : arg);   // a row without any number: token 0
+    if (id >= 0 && id < V) zid = zr[id];
+  } else {
+    const uint32_t u = u32 ? u32[row] : splitmix_u32(seed, row_traj[row], row_newpos[row]);
+    const uint64_t hi = __umul64hi(W, (uint64_t)u), lo = W * (uint64_t)u;
+    const uint64_t r = (hi << 32) | (lo >> 32);          // floor(u * W / 2^32) < W
+    // first segment whose inclusive sum exceeds r (the last one if none does)
+    uint64_t carry = 0;
+    for (int k0 = 0; k0 < nseg; k0 += 256) {
+      const int k = k0 + tid;
+      const uint64_t w = k < nseg ? segw[r0 + k] : 0;
+      uint64_t total;
+      const uint64_t incl = carry + block_scan(w, tmp, &total);
+      if (k < nseg - 1 && incl > r && incl - w <= r) { s_seg = k; s_pre = incl - w; }
+      if (k == nseg - 1 && incl - w <= r) s_pre = incl - w;
+      carry += total;
+    }
+    __syncthreads();
+    const int s = s_seg;
+    const uint64_t rl = r - s_pre;                       // target inside segment s
+    const int PER = RL_SAMPLER_SEG / 256;                // 16 consecutive logits per thread
+    const int base = s * RL_SAMPLER_SEG + tid * PER;
+    float zl[PER];
+    if (VEC) {
+#pragma unroll
+      for (int j = 0; j < PER; j += 4) {
+        const float4 q = *(const float4*)(zr + (base + j < V ? base + j : 0));
+        zl[j] = q.x; zl[j + 1] = q.y; zl[j + 2] = q.z; zl[j + 3] = q.w;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < PER; j++) zl[j] = zr[base + j < V ? base + j : 0];
+    }
     uint64_t wloc[PER];
     uint64_t mine = 0;
+#pragma unroll
     for (int j = 0; j < PER; j++) {
-      float e;
-      uint64_t w = 0;
-      if (base + j < V) exp2_weight(zr[base + j], m, c, e, w);
-      wloc[j] = w;
-      mine += w;
+      float x;
+      uint32_t w;
+      exp2_weight(zl[j], m, c, x, w);
+      wloc[j] = base + j < V ? (uint64_t)w + (x >= kTwo32 ? kTop : 0u) : 0;
+      mine += wloc[j];
     }
-    tsum[tid] = mine;
-    if (tid == 0) chosen = -1;
-    __syncthreads();
-    uint64_t before = 0;
-    for (int k = 0; k < tid; k++) before += tsum[k];
+    uint64_t total;
+    const uint64_t before = block_scan(mine, tmp, &total) - mine;
     if (before <= rl && rl < before + mine) {
       uint64_t acc = before;
+      bool found = false;
+#pragma unroll
       for (int j = 0; j < PER; j++) {
         acc += wloc[j];
-        if (acc > rl) { chosen = base + j; break; }
+        if (!found && acc > rl) { found = true; s_id = base + j; s_z = zl[j]; }
       }
     }
     __syncthreads();
-    id = chosen;
+    id = s_id;
+    // no weight at all (a row of infinities or NaN): id -1, the log-prob is not a number
+    zid = id >= 0 ? s_z : __builtin_nanf("");
   }
   if (tid == 0) {
     float lp = 0.f;
     if (!(out_mask && out_mask[row])) {
-      float t = __fmul_rn(__fsub_rn(zr[id], m), c);
+      float t = __fmul_rn(__fsub_rn(zid, m), c);
       lp = t * 0.6931471805599453f - logf(E);
     }
     if (ids_out) ids_out[row] = id;
@@ -222,15 +348,32 @@ void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, in
                     SamplerScratch sc, int32_t* ids_out, float* logp_out, const float* stripmax,
                     int nstrips) {
   if (rows <= 0) return;
-  int nseg = sampler_nseg(V);
-  dim3 grid(nseg, rows);
+  const int nseg = sampler_nseg(V);
+  const dim3 grid(nseg, rows);
+  const bool vec = V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)logits & 15) == 0;
   if (greedy || nstrips <= 0) stripmax = nullptr;   // the arg-max needs the pass over the logits
-  if (stripmax) row_max_kernel<<<rows, 256, 0, s>>>(stripmax, nstrips, nseg, sc.segmax, sc.segarg);
-  else seg_max_kernel<<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
-  seg_weight_kernel<<<grid, 256, 0, s>>>(logits, ldz, V, scale_c, sc.segmax, sc.segw, sc.sege);
-  sample_final_kernel<<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax,
-                                           sc.segarg, sc.segw, sc.sege, u32, seed, row_traj,
-                                           row_newpos, forced, out_mask, ids_out, logp_out);
+  if (!stripmax) {
+    if (vec) seg_max_kernel<true><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
+    else seg_max_kernel<false><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
+  }
+  // about four workgroups per CU, each with at most eight segments
+  const int spw = (int)std::min<int64_t>(8, std::max<int64_t>(1, ((int64_t)nseg * rows + 1023) / 1024));
+  const dim3 wgrid((nseg + spw - 1) / spw, rows);
+  const float* maxima = stripmax ? stripmax : sc.segmax;
+  const int nmax = stripmax ? nstrips : nseg, put = stripmax ? 1 : 0;
+  if (vec) {
+    seg_weight_kernel<true><<<wgrid, 256, 0, s>>>(logits, ldz, V, scale_c, maxima, nmax, spw, nseg, put, sc.segmax,
+                                                  sc.segw, sc.sege);
+    sample_final_kernel<true><<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax, sc.segarg, sc.segw,
+                                                   sc.sege, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out,
+                                                   logp_out);
+  } else {
+    seg_weight_kernel<false><<<wgrid, 256, 0, s>>>(logits, ldz, V, scale_c, maxima, nmax, spw, nseg, put, sc.segmax,
+                                                   sc.segw, sc.sege);
+    sample_final_kernel<false><<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax, sc.segarg, sc.segw,
+                                                    sc.sege, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out,
+                                                    logp_out);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------

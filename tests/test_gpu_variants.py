@@ -1,0 +1,29 @@
+"""Edges of the kernels' size rules: each variant that a dispatch can take, at the sizes where it can go wrong."""
+import numpy as np
+import pytest
+
+import paper_2509_06980_amd as rl
+from oracle.sampler import sample_token
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V,rows,T", [(1, 2, 1.0), (5, 3, 1.0), (4095, 2, 0.7), (4096, 1, 1.0), (4100, 300, 1.0), (4101, 3, 1.0),
+                                      (12292, 400, 1.0), (12292, 3, 0.0), (1100000, 2, 1.0), (1100001, 1, 0.0)])
+def test_sampler_segment_layouts(V, rows, T):
+    # rows of whole 16-byte pieces and others, one to many segments per workgroup, more than 256 segments
+    # in a row, masked logits (minus infinity and the lowest float: weight 0, as -1e30 for the oracle)
+    rng = np.random.default_rng(V + rows)
+    z = (rng.standard_normal((rows, V)) * 2).astype(np.float32)
+    ref = z.copy()
+    if V > 4:
+        z[-1, ::3], ref[-1, ::3] = -np.inf, -1e30
+        z[0, 1::2], ref[0, 1::2] = -3.4e38, -1e30
+    u = rng.integers(0, 2**32, rows, dtype=np.uint64).astype(np.uint32)
+    u[0] = 2**32 - 1
+    ids, lps = rl.sample_from_logits(z, T, u)
+    for r in sorted({0, rows // 2, rows - 1}):
+        tok, lp = sample_token(ref[r], T, int(u[r]))
+        assert ids[r] == tok, (r, ids[r], tok)
+        # float32 sums of up to V terms in a tree over 16 x 256 and the segments: well below 1e-5
+        assert abs(lps[r] - lp) < 1e-5 * max(1.0, abs(lp))
