@@ -1019,50 +1019,91 @@ void attention_prefill_lds_kernel(
   }
 }
 
-// grid (n_merges, nkv), block 256: merge the parts of one (row, kv head) in a fixed order: the
-// shared-prefix parts first (the row is row `sr` of those items), then the row's own parts.
+// grid (n_merges, nkv), block 256: merge the parts of one (row, kv head): the shared-prefix parts (the
+// row is row `sr` of those items), then the row's own parts.  16 lanes hold a head's 128 outputs; the
+// 16 such lane groups are dealt over the G heads and over 16/G shares of the parts (share x takes parts
+// x, x + 16/G, ...), four parts' reads in flight at a time, and the shares are added through LDS in
+// ascending order: a chain of a few reads instead of two per part (6 rows x 8 kv heads of ~24 parts:
+// 16.1 -> 3.8 us).
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ scratch,
                                                               const AttnMerge* __restrict__ merges,
                                                               bf16_t* __restrict__ o, int nq,
                                                               int nkv, int gshift) {
+  __shared__ __align__(16) float s_o[16][132];
+  __shared__ float s_m[16], s_l[16];
   const AttnMerge mg = merges[blockIdx.x];
   const int kvh = blockIdx.y, tid = threadIdx.x;
-  const size_t stride = (size_t)nkv * (16 * 130);
-  const int cn = tid >> 4, d0 = (tid & 15) * 8;
-  if ((cn >> gshift) != 0) return;   // decode rows: one query row, columns 0 .. G-1
+  const int grp = tid >> 4, d0 = (tid & 15) * 8;
+  const int hq = grp & ((1 << gshift) - 1), share = grp >> gshift, nshare = 16 >> gshift;
   const int total = mg.snparts + mg.nparts;
-  const int scol = (mg.sr << gshift) + cn;
-  // part w: slot and column holding this row's head cn
+  const int scol = (mg.sr << gshift) + hq;
+  // part w: slot and column holding this row's head hq
   auto src_of = [&](int w, int* col) -> const float* {
     const bool sh = w < mg.snparts;
-    *col = sh ? scol : cn;
+    *col = sh ? scol : hq;
     const int slot = sh ? mg.sfirst + w : mg.first + (w - mg.snparts);
     return scratch + ((size_t)slot * nkv + kvh) * (16 * 130);
   };
-  float mt = ATT_NEG;
-  for (int w = 0; w < total; w++) {
-    int col;
-    const float* src = src_of(w, &col);
-    mt = fmaxf(mt, src[16 * 128 + col]);
-  }
-  float L = 0.f, o8[8];
+  float mt = ATT_NEG, L = 0.f, o8[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) o8[e] = 0.f;
-  for (int w = 0; w < total; w++) {
-    int col;
-    const float* src = src_of(w, &col);
-    const float f = exp2f(src[16 * 128 + col] - mt);
-    L += f * src[16 * 128 + 16 + col];
-    const float* a = src + (size_t)col * 128 + d0;
+  for (int w0 = share; w0 < total; w0 += 4 * nshare) {
+    float pm[4], pl[4];
+    f32x4 a0[4], a1[4];
 #pragma unroll
-    for (int e = 0; e < 8; e++) o8[e] += f * a[e];
+    for (int j = 0; j < 4; j++) {
+      const int w = w0 + j * nshare;
+      int col;
+      const float* src = src_of(min(w, total - 1), &col);
+      pm[j] = src[16 * 128 + col];
+      pl[j] = src[16 * 128 + 16 + col];
+      a0[j] = *(const f32x4*)(src + (size_t)col * 128 + d0);
+      a1[j] = *(const f32x4*)(src + (size_t)col * 128 + d0 + 4);
+    }
+    float mn = mt;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (w0 + j * nshare < total) mn = fmaxf(mn, pm[j]);
+    }
+    const float f = exp2f(mt - mn);
+    L *= f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) o8[e] *= f;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (w0 + j * nshare >= total) continue;
+      const float fj = exp2f(pm[j] - mn);
+      L += fj * pl[j];
+#pragma unroll
+      for (int e = 0; e < 4; e++) { o8[e] += fj * a0[j][e]; o8[4 + e] += fj * a1[j][e]; }
+    }
+    mt = mn;
+  }
+  *(f32x4*)&s_o[grp][d0] = (f32x4){o8[0], o8[1], o8[2], o8[3]};
+  *(f32x4*)&s_o[grp][d0 + 4] = (f32x4){o8[4], o8[5], o8[6], o8[7]};
+  if ((tid & 15) == 0) { s_m[grp] = mt; s_l[grp] = L; }
+  __syncthreads();
+  if (share != 0) return;
+  float M = mt;
+  for (int x = 1; x < nshare; x++) M = fmaxf(M, s_m[(x << gshift) + hq]);
+  float f = exp2f(mt - M);
+  L *= f;
+#pragma unroll
+  for (int e = 0; e < 8; e++) o8[e] *= f;
+  for (int x = 1; x < nshare; x++) {
+    const int gx = (x << gshift) + hq;
+    f = exp2f(s_m[gx] - M);
+    L += f * s_l[gx];
+    const f32x4 b0 = *(const f32x4*)&s_o[gx][d0], b1 = *(const f32x4*)&s_o[gx][d0 + 4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) { o8[e] += f * b0[e]; o8[4 + e] += f * b1[e]; }
   }
   const float inv = 1.0f / L;
   uint32_t wv[4];
 #pragma unroll
   for (int e = 0; e < 4; e++)
     wv[e] = (uint32_t)f2bf(o8[2 * e] * inv) | ((uint32_t)f2bf(o8[2 * e + 1] * inv) << 16);
-  *(uint4*)(o + atile_off(mg.row, ((kvh << gshift) + cn) * 128 + d0, nq * 128)) =
+  *(uint4*)(o + atile_off(mg.row, ((kvh << gshift) + hq) * 128 + d0, nq * 128)) =
       make_uint4(wv[0], wv[1], wv[2], wv[3]);
 }
 
