@@ -411,9 +411,8 @@ void add_items(rl_model* m, Staging& st, int row0, int cnt, int slot, int pos0) 
   }
 }
 
-// Decode items: one row per trajectory.  Contexts are cut into parts of about equal page count so
-// that ~kAttnTargetWgs workgroups share the keys / values evenly whatever the mix of lengths; a
-// part never gets fewer than 16 pages.
+// Decode items: one row per trajectory.  Contexts are cut into parts of about equal page count where
+// that pays (see below); a part gets at least 8 pages (ragged batches: 16).
 // Shared-prefix ("cascade") mode: trajectories of the step whose leading pages are the same physical
 // pages (a forked group) get those pages read once per 16/G members by a gather item; each member
 // then covers only its own remainder and a merge record joins the two.
@@ -458,26 +457,39 @@ int add_decode_items(rl_model* m, Staging& st, const std::vector<Traj*>& ts) {  
   int64_t total_pages = 0;
   for (int i = 0; i < n; i++) total_pages += st.pos[i] / RL_PAGE + 1 - own_lo[i];
   for (auto& b : blocks) total_pages += b.pages;
-  // Contexts of about equal length are cut into parts only when that is expected to pay.  Uncut, the launch lasts as long as
-  // its longest item streams on one workgroup (about 0.28 us per 16-token page of one kv head) or
-  // as long as all pages take at the bandwidth of the chip (1.37 ns per page and kv head at
-  // 6 TB/s), whichever is more; cut into ~kAttnTargetWgs even shares it is bandwidth bound but
-  // pays for the merge launch, the partial results and the shorter loops (about 19 us in all).
-  // Constants fitted on the 4B shape at 4 to 96 trajectories and contexts of 512 to 6144 tokens
-  // (break-even at 12 trajectories of 2048 tokens and at 21 of 6144); always cutting below 1024
-  // (trajectory, kv head) pairs cost 5-15 % of the decode step at 32 to 56 equal trajectories,
-  // never cutting 23 % at 8 trajectories of 6144 tokens.
+  // Contexts of about equal length: the number of parts that a cost estimate finds cheapest.  With W
+  // workgroups (one per part and kv head) on 256 CUs, R = ceil(W / 256) of them share a CU and the
+  // launch lasts as long as a CU needs for its R parts: per 16-token page and kv head 0.18 us where a
+  // workgroup has its CU to itself (0.205 us shared; 8-bit cache 0.135 / 0.12), or the page's share
+  // of the bandwidth when all CUs stream (0.31 us, 0.165), plus 8.3 us for the launch (10.7 with the
+  // merge) and 3 us for every further part on a CU.  Fitted on the 4B shape at 1 to 48 trajectories
+  // and contexts of 200 to 8000 tokens, in each of which it is within a few percent of the best of
+  // eight cuts (1 x 800: 17.8 -> 12.2 us against no cut, 4 x 8000: 38.1 -> 31.5 and 16 x 8000: 96.7
+  // -> 87.4 against shares for 1024 workgroups).
   int pages_max = 0;
   for (int i = 0; i < n; i++) pages_max = std::max(pages_max, st.pos[i] / RL_PAGE + 1 - own_lo[i]);
   for (auto& b : blocks) pages_max = std::max(pages_max, b.pages);
-  const double units = (double)total_pages * m->md.nkv;
-  const int n_items = n + (int)blocks.size();
+  const int nkv = m->md.nkv, n_items = n + (int)blocks.size();
   const bool alike = (int64_t)pages_max * n_items * 2 <= total_pages * 3;   // longest <= 1.5 x average
   int chunk;
   if (alike) {
-    const bool cut = m->mfma && 0.28 * pages_max > 0.00137 * units + 19.0;
-    chunk = cut ? (int)std::max<int64_t>(16, (total_pages * m->md.nkv + kAttnTargetWgs - 1) / kAttnTargetWgs)
-                : std::max(16, pages_max);
+    chunk = std::max(16, pages_max);
+    const double t_own = m->md.kv_fp8 ? 0.135 : 0.18, t_shared = m->md.kv_fp8 ? 0.12 : 0.205;
+    const double t_all = m->md.kv_fp8 ? 0.165 : 0.31;
+    double best = 0.0;
+    // parts for at most ~kAttnTargetWgs workgroups, of at least 8 pages
+    const int pmax = m->mfma ? std::max(1, std::min(kAttnTargetWgs / (n_items * nkv), pages_max / 8)) : 1;
+    for (int p = 1; p <= pmax; p++) {
+      const int c = p == 1 ? std::max(16, pages_max) : std::max(8, (pages_max + p - 1) / p);
+      int64_t W = 0;
+      for (int i = 0; i < n; i++) W += (st.pos[i] / RL_PAGE + 1 - own_lo[i] + c - 1) / c;
+      for (auto& b : blocks) W += (b.pages + c - 1) / c;
+      W *= nkv;
+      const int64_t R = (W + 255) / 256;
+      const double t = std::max(R > 1 ? t_shared : t_own, t_all * (double)W / (256.0 * R));
+      const double cost = (p == 1 ? 8.3 : 10.7) + 3.0 * (R - 1) + R * c * t;
+      if (p == 1 || cost < best) { best = cost; chunk = c; }
+    }
   } else {
     // ragged lengths: even shares; with 512 or more (trajectory, kv head) pairs only what is
     // longer than twice the average is cut

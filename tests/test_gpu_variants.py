@@ -4,6 +4,7 @@ import pytest
 
 import paper_2509_06980_amd as rl
 from oracle.sampler import sample_token
+from synthetic import SHAPES, make_weight_blob
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +28,26 @@ def test_sampler_segment_layouts(V, rows, T):
         assert ids[r] == tok, (r, ids[r], tok)
         # float32 sums of up to V terms in a tree over 16 x 256 and the segments: well below 1e-5
         assert abs(lps[r] - lp) < 1e-5 * max(1.0, abs(lp))
+
+
+@pytest.mark.parametrize("name", ["small-g1", "small-g2", "small-d128", "small-g8"])
+@pytest.mark.parametrize("lens", [[15], [256, 250], [127, 128, 129], [700], [1023, 900, 800], [40, 1000]])
+def test_decode_attention_cuts_and_merges(name, lens):
+    # contexts around the sizes at which a row is cut into parts (1 to 8 parts, equal and ragged batches),
+    # every number of lane groups that share a row's parts (G = 1, 2, 4, 8), against the shape-generic kernels
+    shape = SHAPES[name]
+    blob = make_weight_blob(shape, seed=3, weight_std=0.03, gain_std=0.1)
+    kw = dict(max_context=1100, max_trajectories=4, kv_pool_pages=280)
+    a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
+    rng = np.random.default_rng(sum(lens))
+    toks = rng.integers(0, shape.vocab, sum(lens))
+    ids = list(range(len(lens)))
+    for e in (a, b):
+        e.append_observation(ids, toks, lens)
+    for step in range(2):
+        forced = rng.integers(0, shape.vocab, len(lens))
+        la, lb = (e.decode_step_forced(ids, 1.0, forced) for e in (a, b))
+        assert np.abs(la - lb).max() < 3e-2          # two bf16 paths, the bound of the parity tests
+    za, zb = a.debug_logits(ids[-1]), b.debug_logits(ids[-1])
+    assert np.abs(za - zb).max() < 3e-2
+    a.close(), b.close()
