@@ -193,8 +193,8 @@ void forward_generic(rl_model* m, int M, const RowMeta& r) {
     launch_qkrope<TW, TA, TA, false>(s, m->qkv, 1, 0, (const TW*)w.gq, (const TW*)w.gk, m->rope_cs,
                                      r.pos, r.slot, m->page_table, (TA*)m->qb, m->pools[l], md, M);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
-    launch_attention_generic<TA, TA, false>(s, (const TA*)m->qb, m->pools[l], r.pos, r.slot,
-                                            m->page_table, (TA*)m->xo, md, M, false);
+    launch_attention_generic<TA, TA>(s, (const TA*)m->qb, m->pools[l], r.pos, r.slot, m->page_table,
+                                     (TA*)m->xo, md, M);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
     launch_gemm_generic<TA, TW>(s, (const TA*)m->xo, (const TW*)w.wo, m->h, M, H, qw, true);
     launch_rmsnorm<TW, TA>(s, m->h, (const TW*)w.g_post, (TA*)m->xa, M, H, md.eps, false);

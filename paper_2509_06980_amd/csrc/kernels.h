@@ -74,10 +74,10 @@ void launch_add_rmsnorm(hipStream_t s, float* h, const float* parts, int n_part,
                         const bf16_t* g, bf16_t* out, int M, int H, float eps,
                         const int32_t* rows = nullptr);
 
-template <typename TA, typename TKV, bool SWZ>
+template <typename TA, typename TKV>
 void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int32_t* row_pos,
                               const int32_t* row_slot, const int32_t* page_table, TA* o,
-                              const ModelDims& md, int M, bool o_atile);
+                              const ModelDims& md, int M);
 
 // m = silu(gu[:, :I]) * gu[:, I:]
 template <typename TA>

@@ -204,6 +204,75 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const TA* __restrict_
     }
 }
 
+// The same product on the fp32 matrix instruction (16x16x4: exact fp32 products, fp32 accumulation), for
+// rows of whole 4-element pieces.  A wave forms 16 R rows x 16 columns with no LDS in its loop: lane
+// (i = lane % 16, g = lane / 16) reads four consecutive k of row (column) i at k0 + 4 g and feeds
+// component c of both operands to MFMA c, whose k index is then k0 + 4 g + c on either side.  The four
+// waves of a workgroup take every fourth 16-k step, several steps in flight, and wave r adds the four
+// sums of row block r in ascending order.  At the few rows of a decode step a launch is
+// a chain of memory round trips, not arithmetic: K / 128 of them here, against K / 16 with two barriers
+// each in the tile kernel above, which keeps the shapes whose rows are not whole pieces (4 rows: K = 256
+// 30 -> 3.3 us, K = 688 85 -> 5.1 us; 51 200 rows at hidden 1024, fp32: a two-layer prefill 138 -> 95 ms).
+template <typename TA, typename TW, int R>
+__global__ __launch_bounds__(256) void gemm_mfma32_kernel(const TA* __restrict__ A, const TW* __restrict__ W,
+                                                          float* __restrict__ C, int M, int N, int K,
+                                                          int accumulate) {
+  __shared__ f32x4 red[R][4][64];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * R);
+  const TW* w = W + (size_t)min(n0 + i, N - 1) * K;      // rows and columns past the end: repeated, not stored
+  const TA* a[R];
+#pragma unroll
+  for (int r = 0; r < R; r++) a[r] = A + (size_t)min(m0 + 16 * r + i, M - 1) * K;
+  f32x4 acc[R];
+#pragma unroll
+  for (int r = 0; r < R; r++) acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  constexpr int U = R == 1 ? 4 : 2;                      // 16-k steps in flight
+  for (int k0 = wave * 16; k0 < K; k0 += 64 * U) {
+    float wv[U][4], av[U][R][4];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int k = k0 + 64 * u + 4 * g;
+      const bool in = k < K;                             // K % 4 == 0: a piece is inside or outside as a whole
+#pragma unroll
+      for (int e = 0; e < 4; e++) wv[u][e] = 0.f;
+      if (in) ld4(w + k, wv[u][0], wv[u][1], wv[u][2], wv[u][3]);
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) av[u][r][e] = 0.f;
+        if (in) ld4(a[r] + k, av[u][r][0], av[u][r][1], av[u][r][2], av[u][r][3]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int r = 0; r < R; r++)
+          acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][r][e], wv[u][e], acc[r], 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < R; r++) red[r][wave][lane] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    if (wave != (r & 3)) continue;
+    // the same order for every row: a row's bits do not depend on where it lies in the batch
+    const f32x4 v = ((red[r][0][lane] + red[r][1][lane]) + red[r][2][lane]) + red[r][3][lane];
+    const int n = n0 + i;
+    if (n >= N) continue;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int row = m0 + 16 * r + 4 * g + e;
+      if (row < M) {
+        float* c = C + (size_t)row * N + n;
+        *c = accumulate ? *c + v[e] : v[e];
+      }
+    }
+  }
+}
+
 // grid (M, nq + 2 nkv), block 64
 template <typename TW, typename TA, typename TKV, bool SWZ>
 __global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t part_stride,
@@ -259,58 +328,91 @@ __global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t 
   }
 }
 
-// grid (M, nq), block 64: one wave per (row, q head); tokens in blocks of 64, online softmax
-template <typename TA, typename TKV, bool SWZ, bool OATILE>
-__global__ void attention_generic_kernel(const TA* __restrict__ q, const TKV* __restrict__ kpool,
-                                         const TKV* __restrict__ vpool,
-                                         const int32_t* __restrict__ row_pos,
-                                         const int32_t* __restrict__ row_slot,
-                                         const int32_t* __restrict__ page_table,
-                                         TA* __restrict__ o, int nq, int nkv, int d,
-                                         int pt_stride) {
-  __shared__ float qs[128];
-  __shared__ float ps[64];
-  int row = blockIdx.x, qh = blockIdx.y, kvh = qh / (nq / nkv);
-  int pos = row_pos[row];
+// grid (M, nq), block 256: one workgroup per (row, q head).  Sixteen groups of 16 lanes: group g takes
+// the tokens at offset g of every page, lane `sub` of it holds a sixteenth of the head (VEC, head_dim a
+// multiple of 4: dims 64 j + 4 sub .. + 3, one 16-byte read each in fp32; else dims 16 j + sub), so that
+// a wave reads whole rows.  Four pages' page ids, keys and values are requested before the first use;
+// every group keeps an online softmax of its own and the sixteen are joined through LDS.  A chain of
+// one memory round trip per 64 tokens (4 rows x 4 heads at 32 to 104 tokens: 13.7 -> 5.0 us; 64 rows at 800
+// tokens, head_dim 64: a decode step of 2 layers 1200 -> 202 us together with the product above; one
+// wave had read a token's dims one after the other).
+template <typename TA, typename TKV, bool VEC>
+__global__ __launch_bounds__(256) void attention_generic_kernel(
+    const TA* __restrict__ q, const TKV* __restrict__ kpool, const TKV* __restrict__ vpool,
+    const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_slot,
+    const int32_t* __restrict__ page_table, TA* __restrict__ o, int nq, int nkv, int d, int pt_stride) {
+  __shared__ float s_m[16], s_l[16], s_acc[16][129];
+  const int row = blockIdx.x, qh = blockIdx.y, kvh = qh / (nq / nkv);
+  const int tid = threadIdx.x, grp = tid >> 4, sub = tid & 15;
+  const int pos = row_pos[row], npages = pos / RL_PAGE + 1;
   const int32_t* pt = page_table + (size_t)row_slot[row] * pt_stride;
-  for (int e = threadIdx.x; e < d; e += 64) qs[e] = ldf(q + (size_t)row * nq * d + (size_t)qh * d + e);
-  __syncthreads();
-  float scale = 1.0f / sqrtf((float)d);
-  float m = -INFINITY, l = 0.f, acc[2] = {0.f, 0.f};
-  for (int t0 = 0; t0 <= pos; t0 += 64) {
-    int t = t0 + threadIdx.x;
-    float sc = -INFINITY;
-    if (t <= pos) {
-      const TKV* kb = kpool + ((size_t)pt[t >> 4] * nkv + kvh) * (RL_PAGE * d);
-      float dot = 0.f;
-      for (int e = 0; e < d; e++) dot += qs[e] * ldf(kb + kblk_off<SWZ>(t & 15, e, d));
-      sc = dot * scale;
-    }
-    float mn = fmaxf(m, wave_max(sc));
-    float p = (t <= pos) ? expf(sc - mn) : 0.f;
-    float alpha = expf(m - mn);       // m = -inf on the first block: exp(-inf) = 0
-    l = l * alpha + wave_sum(p);
-    m = mn;
-    __syncthreads();
-    ps[threadIdx.x] = p;
-    __syncthreads();
-    int nt = min(64, pos + 1 - t0);
-    int c = 0;
-    for (int e = threadIdx.x; e < d; e += 64, c++) {
-      float a = acc[c] * alpha;
-      for (int j = 0; j < nt; j++) {
-        int tt = t0 + j;
-        const TKV* vb = vpool + ((size_t)pt[tt >> 4] * nkv + kvh) * (RL_PAGE * d);
-        a += ps[j] * ldf(vb + vblk_off<SWZ>(tt & 15, e, d));
+  auto dim = [&](int j) { return VEC ? (j >> 2) * 64 + sub * 4 + (j & 3) : j * 16 + sub; };
+  auto load8 = [&](const auto* p, float (&x)[8]) {     // the lane's dims of one row of d elements
+    if constexpr (VEC) {
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        const int e = j * 64 + sub * 4;
+        x[4 * j] = x[4 * j + 1] = x[4 * j + 2] = x[4 * j + 3] = 0.f;
+        if (e < d) ld4(p + e, x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]);
       }
-      acc[c] = a;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; j++) x[j] = j * 16 + sub < d ? ldf(p + j * 16 + sub) : 0.f;
     }
+  };
+  float qv[8], acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  load8(q + (size_t)row * nq * d + (size_t)qh * d, qv);
+  const float scale = 1.0f / sqrtf((float)d);
+  float m = -INFINITY, l = 0.f;
+  for (int p0 = 0; p0 < npages; p0 += 4) {
+    float k[4][8], v[4][8], sc[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {      // past the end: the last page again, masked below
+      const size_t off = (((size_t)pt[min(p0 + u, npages - 1)] * nkv + kvh) * RL_PAGE + grp) * d;
+      load8(kpool + off, k[u]);
+      load8(vpool + off, v[u]);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      float dot = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; j++) dot += qv[j] * k[u][j];
+#pragma unroll
+      for (int x = 8; x > 0; x >>= 1) dot += __shfl_xor(dot, x, 16);
+      sc[u] = dot * scale;
+      if ((p0 + u) * RL_PAGE + grp <= pos) mx = fmaxf(mx, sc[u]);
+    }
+    const float mn = fmaxf(m, mx);
+    const float alpha = m == -INFINITY ? 0.f : expf(m - mn);
+    l *= alpha;
+#pragma unroll
+    for (int j = 0; j < 8; j++) acc[j] *= alpha;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if ((p0 + u) * RL_PAGE + grp > pos) continue;     // slots behind the row's position may hold anything
+      const float pr = expf(sc[u] - mn);
+      l += pr;
+#pragma unroll
+      for (int j = 0; j < 8; j++) acc[j] += pr * v[u][j];
+    }
+    m = mn;
   }
-  int c = 0;
-  for (int e = threadIdx.x; e < d; e += 64, c++) {
-    float y = acc[c] / l;
-    if (OATILE) stf(o + atile_off(row, qh * d + e, nq * d), y);
-    else stf(o + (size_t)row * nq * d + (size_t)qh * d + e, y);
+#pragma unroll
+  for (int j = 0; j < 8; j++)
+    if (dim(j) < d) s_acc[grp][dim(j)] = acc[j];
+  if (sub == 0) { s_m[grp] = m; s_l[grp] = l; }
+  __syncthreads();
+  if (tid < d) {
+    float M = s_m[0];
+    for (int g = 1; g < 16; g++) M = fmaxf(M, s_m[g]);
+    float L = 0.f, y = 0.f;
+    for (int g = 0; g < 16; g++) {
+      const float f = s_m[g] == -INFINITY ? 0.f : expf(s_m[g] - M);
+      L += f * s_l[g];
+      y += f * s_acc[g][tid];
+    }
+    stf(o + (size_t)row * nq * d + (size_t)qh * d + tid, y / L);
   }
 }
 
@@ -363,6 +465,15 @@ template <typename TA, typename TW>
 void launch_gemm_generic(hipStream_t s, const TA* A, const TW* W, float* C, int M, int N, int K,
                          bool accumulate) {
   if (M <= 0) return;
+  const bool vec = K % 4 == 0 && ((uintptr_t)A % (4 * sizeof(TA))) == 0 && ((uintptr_t)W % (4 * sizeof(TW))) == 0;
+  if (vec) {
+    if (M <= 16)
+      gemm_mfma32_kernel<TA, TW, 1><<<dim3((N + 15) / 16, 1), 256, 0, s>>>(A, W, C, M, N, K, accumulate ? 1 : 0);
+    else
+      gemm_mfma32_kernel<TA, TW, 4><<<dim3((N + 15) / 16, (M + 63) / 64), 256, 0, s>>>(A, W, C, M, N, K,
+                                                                                       accumulate ? 1 : 0);
+    return;
+  }
   dim3 grid((N + 63) / 64, (M + 63) / 64);
   gemm_generic_kernel<TA, TW><<<grid, 256, 0, s>>>(A, W, C, M, N, K, accumulate ? 1 : 0);
 }
@@ -506,24 +617,23 @@ template void launch_qkrope<float, float, float, false>(hipStream_t, const float
 template void launch_qkrope<bf16_t, bf16_t, bf16_t, false>(hipStream_t, const float*, int, size_t, const bf16_t*, const bf16_t*, const float*, const int32_t*, const int32_t*, const int32_t*, bf16_t*, KvPool, const ModelDims&, int);
 template void launch_qkrope<bf16_t, bf16_t, bf16_t, true>(hipStream_t, const float*, int, size_t, const bf16_t*, const bf16_t*, const float*, const int32_t*, const int32_t*, const int32_t*, bf16_t*, KvPool, const ModelDims&, int);
 
-template <typename TA, typename TKV, bool SWZ>
+template <typename TA, typename TKV>
 void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int32_t* row_pos,
                               const int32_t* row_slot, const int32_t* page_table, TA* o,
-                              const ModelDims& md, int M, bool o_atile) {
+                              const ModelDims& md, int M) {
   if (M <= 0) return;
   dim3 grid(M, md.nq);
-  if (o_atile)
-    attention_generic_kernel<TA, TKV, SWZ, true><<<grid, 64, 0, s>>>(
+  if (md.d % 4 == 0)     // rows of whole 4-element pieces: pools and q are allocated on 256-byte boundaries
+    attention_generic_kernel<TA, TKV, true><<<grid, 256, 0, s>>>(
         q, (const TKV*)pool.k, (const TKV*)pool.v, row_pos, row_slot, page_table, o, md.nq, md.nkv,
         md.d, md.max_pages_per_traj);
   else
-    attention_generic_kernel<TA, TKV, SWZ, false><<<grid, 64, 0, s>>>(
+    attention_generic_kernel<TA, TKV, false><<<grid, 256, 0, s>>>(
         q, (const TKV*)pool.k, (const TKV*)pool.v, row_pos, row_slot, page_table, o, md.nq, md.nkv,
         md.d, md.max_pages_per_traj);
 }
-template void launch_attention_generic<float, float, false>(hipStream_t, const float*, KvPool, const int32_t*, const int32_t*, const int32_t*, float*, const ModelDims&, int, bool);
-template void launch_attention_generic<bf16_t, bf16_t, false>(hipStream_t, const bf16_t*, KvPool, const int32_t*, const int32_t*, const int32_t*, bf16_t*, const ModelDims&, int, bool);
-template void launch_attention_generic<bf16_t, bf16_t, true>(hipStream_t, const bf16_t*, KvPool, const int32_t*, const int32_t*, const int32_t*, bf16_t*, const ModelDims&, int, bool);
+template void launch_attention_generic<float, float>(hipStream_t, const float*, KvPool, const int32_t*, const int32_t*, const int32_t*, float*, const ModelDims&, int);
+template void launch_attention_generic<bf16_t, bf16_t>(hipStream_t, const bf16_t*, KvPool, const int32_t*, const int32_t*, const int32_t*, bf16_t*, const ModelDims&, int);
 
 template <typename TA>
 void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool atile) {

@@ -29,6 +29,16 @@ __host__ __device__ __forceinline__ bf16_t f2bf(float f) {
 
 __device__ __forceinline__ float ldf(const float* p) { return *p; }
 __device__ __forceinline__ float ldf(const bf16_t* p) { return bf2f(*p); }
+// four consecutive elements, aligned to their size
+__device__ __forceinline__ void ld4(const float* p, float& a, float& b, float& c, float& d) {
+  const float4 q = *(const float4*)p;
+  a = q.x; b = q.y; c = q.z; d = q.w;
+}
+__device__ __forceinline__ void ld4(const bf16_t* p, float& a, float& b, float& c, float& d) {
+  const uint2 q = *(const uint2*)p;
+  a = bf2f((bf16_t)(q.x & 0xffff)); b = bf2f((bf16_t)(q.x >> 16));
+  c = bf2f((bf16_t)(q.y & 0xffff)); d = bf2f((bf16_t)(q.y >> 16));
+}
 __device__ __forceinline__ void stf(float* p, float v) { *p = v; }
 __device__ __forceinline__ void stf(bf16_t* p, float v) { *p = f2bf(v); }
 

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
+from oracle import OracleEngine
 from oracle.sampler import sample_token
 from synthetic import SHAPES, make_weight_blob
 
@@ -51,3 +52,27 @@ def test_decode_attention_cuts_and_merges(name, lens):
     za, zb = a.debug_logits(ids[-1]), b.debug_logits(ids[-1])
     assert np.abs(za - zb).max() < 3e-2
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("change", [dict(), dict(hidden=260, intermediate=700, vocab=4100), dict(hidden=250, head_dim=62, vocab=4090),
+                                    dict(head_dim=68), dict(head_dim=128, n_q_heads=2), dict(n_kv_heads=4, head_dim=6)])
+@pytest.mark.parametrize("lens", [[1], [16, 1], [65], [17, 64, 130], [2] * 17])
+def test_fp32_products_and_attention_at_the_edges(change, lens):
+    # one and several 16-row blocks, K and N that end inside a block, rows that are no whole 4-element
+    # pieces (the tile kernel, the scalar attention reads), contexts around pages and groups of four pages
+    shape = SHAPES["tiny"].replace(n_layers=1, **change)
+    blob = make_weight_blob(shape, seed=4, weight_std=0.05, gain_std=0.1)
+    kw = dict(max_context=160, max_trajectories=20, kv_pool_pages=80)
+    o, g = OracleEngine(blob, **kw), rl.RolloutEngine(blob, **kw)
+    rng = np.random.default_rng(sum(lens))
+    ids = list(range(len(lens)))
+    toks = rng.integers(0, shape.vocab, sum(lens))
+    forced = rng.integers(0, shape.vocab, len(lens))
+    for e in (o, g):
+        e.append_observation(ids, toks, lens)
+    lo, lg = (e.decode_step_forced(ids, 1.0, forced) for e in (o, g))
+    assert np.abs(lo - lg).max() < 1e-4              # the fp32 bound of the parity tests
+    for i in (ids[0], ids[-1]):
+        assert np.abs(o.debug_logits(i) - g.debug_logits(i)).max() < 1e-4
+    assert np.abs(o.recompute_logprobs(ids, 1.0) - g.recompute_logprobs(ids, 1.0)).max() < 1e-4
+    g.close()
