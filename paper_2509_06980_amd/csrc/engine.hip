@@ -204,27 +204,6 @@ void forward_generic(rl_model* m, int M, const RowMeta& r) {
   }
 }
 
-// Split-K factor of a weight-streaming GEMM (tile 128 x 128, 4 waves).  Measured on MI355X: one CU
-// sustains only ~20 GB/s of HBM reads, so a decode GEMM wants a workgroup on every CU: aim for
-// ~240 workgroups, at least four 64-k chunks per split, at most kMaxSplits partial sums (each
-// costs M x N floats of traffic; 8 measured best in the full decode step).  Prefill-sized GEMMs already have many row tiles.
-struct GemmPlan { int nw, splits; };
-const int kMaxSplits = 8;
-// part_rows: rows the partial-sum buffers hold (every split-K slice takes M of them)
-GemmPlan plan_gemm(int M, int N, int K, bool can_split, size_t part_rows) {
-  const int target = 240, max_splits = kMaxSplits;
-  int tiles = ((N + 127) / 128) * ((M + 127) / 128);
-  int s = 1;
-  if (can_split && M <= 1024 && tiles < target) {   // decode steps, mixed steps and small appends
-    s = (target + tiles / 2) / tiles;
-    s = std::min({s, max_splits, std::max(1, K / 256), (int)std::min<size_t>(part_rows / (size_t)M, 64)});
-  }
-  // narrow outputs (small models): 64-column tiles when 128-column tiles times slices leave more
-  // than half of the CUs without a workgroup
-  s = std::max(1, s);
-  return GemmPlan{tiles * s < 160 && N <= 8192 && M <= 128 ? 2 : 4, s};
-}
-
 // Leaves the last down-projection as m->pending_parts partial sums in m->ph (added by the next
 // add_rmsnorm: the next layer's, or the final norm before the lm-head).
 void forward_mfma(rl_model* m, int M, const RowMeta& r) {
@@ -232,16 +211,28 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   const ModelDims& md = m->md;
   int H = md.H, qw = md.nq * md.d, kvw = md.nkv * md.d, I = md.I, QW = qw + 2 * kvw;
   launch_embed<bf16_t>(s, (const bf16_t*)m->embed, r.tok, m->h, M, H);
+  // the same for every layer
+  const GemmPlan pq = plan_gemm(M, QW, H, EPI_STORE, m->part_rows), po = plan_gemm(M, H, qw, EPI_STORE, m->part_rows);
+  const GemmPlan pg = plan_gemm(M, 2 * I, H, EPI_SWIGLU, m->part_rows), pd = plan_gemm(M, H, I, EPI_STORE, m->part_rows);
+  // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
+  // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
+  const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
+  const bool fused_qkv = pf.nbw == 4 && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
     launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
-    GemmPlan pq = plan_gemm(M, QW, H, true, m->part_rows);
-    int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE,
-                              pq.splits, pq.nw);
-    launch_qkrope<bf16_t, bf16_t, bf16_t, true>(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq,
-                                                (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot,
-                                                m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
+    if (fused_qkv) {
+      const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
+                       (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,
+                       md.max_pages_per_traj, md.eps};
+      launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, qa);
+    } else {
+      int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, pq);
+      launch_qkrope<bf16_t, bf16_t, bf16_t, true>(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq,
+                                                  (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot,
+                                                  m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
+    }
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
     launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.items, r.n_items, r.merges, r.n_merges,
                           r.rowlist, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, r.prefill);
@@ -249,15 +240,10 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.pf_items, r.n_pf_items, nullptr, 0,
                             nullptr, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, true);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
-    GemmPlan po = plan_gemm(M, H, qw, true, m->part_rows);
-    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, m->ph, M, H, qw, EPI_STORE,
-                              po.splits, po.nw);
+    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, m->ph, M, H, qw, EPI_STORE, po);
     launch_add_rmsnorm(s, m->h, m->ph, so, (size_t)M * H, (const bf16_t*)w.g_post, (bf16_t*)m->xa, M, H, md.eps);
-    GemmPlan pg = plan_gemm(M, 2 * I, H, false, m->part_rows);
-    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, 1, pg.nw);
-    GemmPlan pd = plan_gemm(M, H, I, true, m->part_rows);
-    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, m->ph, M, H, I, EPI_STORE,
-                            pd.splits, pd.nw);
+    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, pg);
+    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, m->ph, M, H, I, EPI_STORE, pd);
   }
   m->pending_parts = pend;
 }
@@ -287,9 +273,8 @@ void lm_head_rows(rl_model* m, int M, int r0, int R, bool norm_done, int norm_ro
       launch_lm_head_logits(s, (const bf16_t*)m->xa + (size_t)r0 * md.H, (const bf16_t*)m->lm_head,
                             m->logits, R, md.V, md.H, stripmax);
     } else {
-      GemmPlan pl = plan_gemm(R, md.V, md.H, false, m->part_rows);
       launch_gemm_mfma(s, (const bf16_t*)m->xa + (size_t)r0 * md.H, (const bf16_t*)m->lm_head, m->logits,
-                       R, md.V, md.H, EPI_STORE, 1, pl.nw);
+                       R, md.V, md.H, EPI_STORE, plan_gemm(R, md.V, md.H, EPI_STORE, 0));
     }
   } else if (m->bf16) {
     if (!norm_done)

@@ -84,14 +84,32 @@ template <typename TA>
 void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool atile);
 
 // ---- MFMA kernels (bf16, head_dim 128) -------------------------------------------------------
-enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4 };
+enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4, EPI_QKV = 5, EPI_QKV8 = 6 };
+// Kernel and K-slices of one product (see plan_gemm's definition).  nbw: 0 = 128-row tiles of 32 * nw
+// columns, 4 / 5 = 256-row tiles of 64 * nbw columns.  cost: estimate in us, comparable between plans.
+struct GemmPlan { int nbw, nw, splits; double cost; };
+const int kMaxSplits = 8;
+// part_rows: rows the partial-sum buffer holds (every K-slice takes M of them)
+GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows);
 // A: bf16 A-tile layout [ceil(M/128)*128, K]; Wp: repacked weights (see repack kernel).
-// EPI_STORE: split-K slice z writes its fp32 partial sum to C + z * M * N (row-major [M, N]); the
-// consumer adds the `splits` partials.  EPI_SWIGLU (splits = 1): C is bf16 A-tile [.., N/2], gate
-// and up interleaved in 16-column groups.  nw = waves per workgroup (2 or 4): tile 128 x 32*nw.
-// K % 64 == 0, N % 32 == 0.  Returns the number of splits actually used.
-int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N,
-                     int K, int epilogue, int splits, int nw);
+// EPI_STORE: K-slice z writes its fp32 partial sum to C + z * M * N (row-major [M, N]); the consumer
+// adds the partials.  EPI_SWIGLU (one slice): C is bf16 A-tile [.., N/2], gate and up interleaved in
+// groups of 8 rows.  K % 64 == 0, N % 32 == 0.  Returns the number of slices actually used.
+int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
+                     const GemmPlan& plan);
+// QKV projection with QK-norm, RoPE and the cache write in its epilogue (head_dim 128): what the
+// projection followed by launch_qkrope leaves, without the fp32 projection in memory.
+struct QkvArgs {
+  const bf16_t *gq, *gk;
+  const float* rope_cs;
+  const int32_t *row_pos, *row_slot, *page_table;
+  bf16_t* qout;
+  void *kpool, *vpool;
+  int nq, nkv, qk_norm, pt_stride;
+  float eps;
+};
+void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int N, int K, bool kv_fp8,
+                     const QkvArgs& q);
 // lm-head fused with the log-softmax of the masked log-prob pass: for each of the M rows of A
 // (bf16 A-tile layout) lp[row] = log softmax(z / T)[tgt[row]] with z = A[row] . Wp^T (V logits, never
 // stored) and scale_c = log2(e) / T.  part: scratch of M * (V / 32) float pairs; zt: M floats.
@@ -102,10 +120,10 @@ void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, in
 // which the sampler takes the row maximum without a pass over the logits.  V % 32 == 0.
 void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* logits, int M,
                            int V, int K, float* stripmax);
-// W[N,K] row-major -> operand strips.  interleave16: rows come from two matrices Wg, Wu
-// ([N/2,K] each) interleaved in groups of 16 (gate, up, gate, up, ...).
+// W[N,K] row-major -> operand strips.  interleave8: rows come from two matrices Wg, Wu
+// ([N/2,K] each) interleaved in groups of 8 (gate, up, gate, up, ...).
 void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16_t* Wp, int N,
-                          int K, bool interleave16);
+                          int K, bool interleave8);
 
 // paged GQA attention over work items; q bf16 row-major [M, nq*128]; o bf16 A-tile [.., nq*128].
 // Decode (prefill = false): single-row items, possibly cut into parts; scratch: fp32

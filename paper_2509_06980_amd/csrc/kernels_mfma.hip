@@ -3,6 +3,9 @@
 // Generate / Update steps, Section 2.3.2) for head_dim 128 and tile-aligned widths.
 #include "kernels.h"
 
+#include <algorithm>
+#include <atomic>
+
 // =============================================================================================
 // Weight repack: W[N,K] row-major -> [K/64 chunks][N/32 strips][4 k-blocks][64 lanes][8].  One
 // (chunk, strip) cell is 4 KB: four 32x32x16 MFMA column operands in lane order
@@ -11,7 +14,7 @@
 // every wave's stream at a multiple of K * 64 bytes and piles them onto a few memory channels.
 // =============================================================================================
 __global__ void repack_weight_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ Wu,
-                                     bf16_t* __restrict__ Wp, int N, int K, int interleave16) {
+                                     bf16_t* __restrict__ Wp, int N, int K, int interleave8) {
   size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int NB = N / 32;
   size_t total = (size_t)NB * (K / 16) * 64;
@@ -25,9 +28,9 @@ __global__ void repack_weight_kernel(const bf16_t* __restrict__ W, const bf16_t*
   int n = nb * 32 + (lane & 31);
   int k = chunk * 64 + kb4 * 16 + (lane >> 5) * 8;
   const bf16_t* src;
-  if (interleave16) {
-    int grp = n >> 4;                       // even groups: gate rows, odd groups: up rows
-    int srow = (grp >> 1) * 16 + (n & 15);
+  if (interleave8) {
+    int grp = n >> 3;                       // even groups: gate rows, odd groups: up rows
+    int srow = (grp >> 1) * 8 + (n & 7);
     src = ((grp & 1) ? Wu : W) + (size_t)srow * K + k;
   } else {
     src = W + (size_t)n * K + k;
@@ -36,10 +39,10 @@ __global__ void repack_weight_kernel(const bf16_t* __restrict__ W, const bf16_t*
 }
 
 void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16_t* Wp, int N,
-                          int K, bool interleave16) {
+                          int K, bool interleave8) {
   size_t total = (size_t)(N / 32) * (K / 16) * 64;
   repack_weight_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(W, Wu, Wp, N, K,
-                                                                        interleave16 ? 1 : 0);
+                                                                        interleave8 ? 1 : 0);
 }
 
 // =============================================================================================
@@ -55,6 +58,7 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // fetched, staged and multiplied.  At decode sizes a workgroup's time follows the bytes its CU
 // fetches, and the A chunk is half of them, so small batches gain most of what they leave out
 // (rows <= 32: gate-up 30.7 -> 23.6 us, down 18.3 -> 13.0 us); results per row are unchanged.
+// EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.
 // EPI_LSE (lm-head of the masked log-prob pass): the product is formed transposed (weights as the
 // MFMA row operand; both operands have the same lane layout, so swapping them costs nothing), which
 // puts 16 vocabulary entries of one batch row into the registers of a lane.  The epilogue reduces
@@ -65,6 +69,54 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // step), written to zt[row * (N / 32) + strip]: the sampler gets the row maximum it needs before
 // any weight can be formed from V / 32 numbers per row instead of a pass over the logits.
 // =============================================================================================
+// SwiGLU of one transposed 32x32 block (EPI_SWIGLU forms the product with the weights as the row
+// operand): lane l holds, for batch row l % 32, weight rows (i / 4) * 8 + (l / 32) * 4 + i % 4, and the
+// repack puts 8 gate rows before the 8 up rows of the same units: gate and up of a unit are in the same
+// lane (registers i and i + 4), every lane works, and four consecutive units leave as one 8-byte store
+// (32 rows x 16 bytes of the A-tile layout contiguous).  With gate and up in different lanes, half the
+// lanes idle and 2-byte stores the epilogue had cost 24 us per round of 256 x 256 tiles.
+template <typename F>
+__device__ __forceinline__ void swiglu_block(F val, bf16_t* __restrict__ out, int row, int M, int nb, int lane,
+                                             int width) {
+  if (row >= M) return;
+#pragma unroll
+  for (int p = 0; p < 2; p++) {
+    uint32_t y[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float v = val(8 * p + e), u = val(8 * p + 4 + e);
+      y[e] = f2bf(v / (1.0f + __expf(-v)) * u);
+    }
+    *(uint2*)(out + atile_off(row, nb * 16 + p * 8 + (lane >> 5) * 4, width)) =
+        make_uint2(y[0] | (y[1] << 16), y[2] | (y[3] << 16));
+  }
+}
+// Log-softmax statistics of one transposed 32x32 block: lane l holds 16 vocabulary entries of batch row
+// l % 32; its half of the strip and the other lane half's are joined with one swap.
+template <typename F>
+__device__ __forceinline__ void lse_block(F val, float2* __restrict__ P, float* __restrict__ zt,
+                                          const int32_t* __restrict__ tgt, int row, int M, int nb, int NB, int lane,
+                                          float scale_c) {
+  float mx = val(0);
+#pragma unroll
+  for (int i = 1; i < 16; i++) mx = fmaxf(mx, val(i));
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  float sm = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; i++) sm += exp2f((val(i) - mx) * scale_c);
+  sm += __shfl_xor(sm, 32, 64);
+  if (row >= M) return;
+  if (lane < 32) P[(size_t)row * NB + nb] = make_float2(mx, sm);
+  const int t = tgt[row];
+  if ((t >> 5) == nb && ((t >> 2) & 1) == (lane >> 5)) {
+    const int isel = ((t & 31) >> 3) * 4 + (t & 3);
+    float z = val(0);
+#pragma unroll
+    for (int i = 1; i < 16; i++) z = isel == i ? val(i) : z;
+    zt[row] = z;
+  }
+}
+
 template <int EPI, int D, int NW, int MB>
 __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
                                                             const bf16_t* __restrict__ Wp,
@@ -131,7 +183,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
       bf16x8 b = __builtin_bit_cast(bf16x8, bcur[kk]);                      \
       _Pragma("unroll") for (int mb = 0; mb < MB; mb++) {                   \
         bf16x8 a = __builtin_bit_cast(bf16x8, av[kk * 4 + mb]);             \
-        acc[mb] = EPI == EPI_LSE                                            \
+        acc[mb] = EPI == EPI_LSE || EPI == EPI_SWIGLU                       \
                       ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, acc[mb], 0, 0, 0) \
                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[mb], 0, 0, 0); \
       }                                                                     \
@@ -152,31 +204,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 #undef GEMM_LOAD
 #undef GEMM_STAGE
   if (!active) return;
-  if (EPI == EPI_LSE) {
-    // acc[mb][i] = z[batch row mb*32 + lane%32][vocab nb*32 + (i/4)*8 + (lane/32)*4 + i%4]
-    float2* P = (float2*)Cv;
+  if (EPI == EPI_LSE || EPI == EPI_SWIGLU) {
+    // acc[mb][i] belongs to batch row mb*32 + lane%32 and weight row nb*32 + (i/4)*8 + (lane/32)*4 + i%4
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
       const int row = mt * 128 + mb * 32 + (lane & 31);
-      float mx = acc[mb][0];
-#pragma unroll
-      for (int i = 1; i < 16; i++) mx = fmaxf(mx, acc[mb][i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      float sm = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i++) sm += exp2f((acc[mb][i] - mx) * scale_c);
-      sm += __shfl_xor(sm, 32, 64);
-      if (row < M) {
-        if (lane < 32) P[(size_t)row * NB + nb] = make_float2(mx, sm);
-        const int t = tgt[row];
-        if ((t >> 5) == nb && ((t >> 2) & 1) == (lane >> 5)) {
-          const int isel = ((t & 31) >> 3) * 4 + (t & 3);
-          float z = acc[mb][0];
-#pragma unroll
-          for (int i = 1; i < 16; i++) z = isel == i ? acc[mb][i] : z;
-          zt[row] = z;
-        }
-      }
+      auto val = [&](int i) { return acc[mb][i]; };
+      if (EPI == EPI_SWIGLU) swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
+      else lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
     }
     return;
   }
@@ -227,14 +262,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
     for (int i = 0; i < 16; i++) {
       int row = mt * 128 + mb * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
       float v = acc[mb][i];
-      if (EPI == EPI_SWIGLU) {
-        float u = __shfl_xor(v, 16, 64);            // lanes 0..15 of a half: gate; 16..31: up
-        if ((lane & 16) == 0 && row < M) {
-          float y = v / (1.0f + __expf(-v)) * u;
-          int j = nb * 16 + (lane & 15);
-          ((bf16_t*)Cv)[atile_off(row, j, N >> 1)] = f2bf(y);
-        }
-      } else if (row < M) {
+      if (row < M) {
         __builtin_nontemporal_store(v, &Cp[(size_t)row * N + col]);   // leaves the L2 early instead of at the end of the kernel
       }
     }
@@ -242,26 +270,31 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 }
 
 // =============================================================================================
-// GEMM for many rows (chunked prefill, teacher-forced passes) and wide outputs: tile 256 x 256,
-// 4 waves as 2 x 2, wave tile 128 x 128 (16 accumulators of 32x32).  Per 16-k step a wave reads 4
-// row and 4 column operands from LDS for 16 MFMAs, so an operand byte fetched through the L1 feeds
-// twice the MFMAs of the 128 x 128 kernel above.  Both operands are staged through LDS (double
-// buffered, 2 x 64 KB).
-// The loop is one steady stream: a chunk is 16 pieces of 16 bytes per thread, and every group of
-// 4 MFMAs carries one global load (a piece 24 groups = 1.5 chunks ahead of the store that needs
-// it, in a ring of 32 register slots), the LDS stores of the next chunk (all done by group 11),
-// and two of the eight LDS operand reads of the next 16-k step.  The workgroup barrier sits in
-// front of group 12: by then the next chunk is complete in the other buffer and this buffer has
-// been read out, so groups 12-15 already fetch the next chunk's first operands and no LDS latency
-// is exposed at the chunk boundary.  A burst of 16 loads per thread at the top of every chunk
-// (all 256 workgroups at about the same time) instead of this even stream costs 17-26 %.
-// sched_group_barrier pins the interleaving (MFMA, load, MFMA, stores, MFMA, reads, MFMA).
-// XCD-aware tile numbering (xcd_tile256) is worth another 1.5-3 %.
-// The k order per output element is that of the 128 x 128 kernel: results are bit-identical.
-// Measured at 8192 rows (us, before -> after the steady stream): N = 6144 K = 2560 310 -> 266,
-// N = 19456 K = 2560 1010 -> 843, N = 24576 K = 4096 1800 -> 1462, N = 4096 K = 12288 830 -> 656;
-// N = 2560 stays with the kernel above (320 workgroups on 256 CUs).  K / 64 must be even; no
-// split-K.
+// GEMM for many rows (chunked prefill, teacher-forced passes, mixed steps): tile 256 x 64*NBW, 4 waves
+// as 2 x 2, wave tile 128 x 32*NBW (NBW = 4: 256 columns, 16 accumulators of 32x32; NBW = 5: 320 columns,
+// 20 of them).  Per 16-k step a wave reads 4 row and NBW column operands from LDS for 4*NBW MFMAs.
+// Both operands go from memory straight into LDS (16-byte buffer loads with the LDS destination; no
+// staging registers, no LDS stores in the instruction stream) as chunks of 32 k in a ring of four
+// stages, three and a half chunks ahead.  The loop is one steady stream: every group of NBW MFMAs
+// carries one such load, and the next step's operands are read in the first three of four groups, so
+// that the wait in front of the barrier (group 4 of a chunk's 8: the next chunk is complete, this one
+// is read out) finds them there.  The loads are issued from inline assembly because the compiler
+// otherwise waits for all of them before any LDS read; every wait on them is the explicit vmcnt
+// below: the loads return in order, so "at most 2 chunks outstanding" means the next chunk has landed.
+// Before the epilogue all are drained (nothing may land in LDS that is no longer ours).
+// The fifth accumulator column lives in vector registers: 320 accumulator registers exceed the 256
+// accumulation registers, and the builtin, which takes all of its kind from one file, then copies.
+// blockIdx.z selects a K-slice (EPI_STORE only); each slice stores its own partial sum.
+// The k order per output element is that of the 128 x 128 kernel: with one slice the bits are the same.
+// EPI_QKV / EPI_QKV8 (bf16 / 8-bit cache; NBW = 4: a wave's 128 columns are one head): the product is
+// formed transposed, which leaves a row's 128 dims of the head in two lanes, RoPE partners in the
+// same lane; the per-head norm (one swap), RoPE and the writes to q and the paged cache happen in
+// the epilogue, so the fp32 projection (201 MB at 8192 x 6144) is neither stored nor read back.
+// Measured at 8192 rows in the pass (us; before: register staging, 256-column tiles or 128 x 128):
+// gate-up N = 19456 K = 2560 with SwiGLU 880 -> 690, down N = 2560 K = 9728 443 -> 308 (1.41 PFLOP/s
+// alone), O N = 2560 K = 4096 192 -> 138, QKV N = 6144 K = 2560 with norm, RoPE and cache write
+// 244 + 80 -> 271, lm-head with log-softmax at 1536 rows (N = 151936) 1709 -> 1034.
+// XCD-aware tile numbering (xcd_tile256).  K % 64 == 0, N % 32 == 0.
 // =============================================================================================
 // Tile of a workgroup: the hardware hands workgroups to the 8 XCDs round-robin by linear index
 // and each XCD has its own L2.  XCD x works through a contiguous range of a sequence that walks
@@ -279,154 +312,246 @@ __device__ __forceinline__ void xcd_tile256(int id, int tiles_m, int tiles_n, in
   *tn = within / gm;
 }
 
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm256_mfma_kernel(const bf16_t* __restrict__ A,
-                                                      const bf16_t* __restrict__ Wp,
-                                                      void* __restrict__ Cv, int M, int N, int K) {
-  extern __shared__ u32x4 smem[];            // [2][A: 2048 | B: 2048] pieces of 16 bytes
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int NB = N >> 5;
-  const int nchunks = K >> 6;
-  const int mtiles128 = (M + 127) >> 7;
-  int bx, by;
-  xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
-  const int mt0 = by * 2, mt1 = min(mt0 + 1, mtiles128 - 1);   // second half clamped (results dropped)
-  const u32x4* Ag0 = (const u32x4*)(A + (size_t)mt0 * K * 128);
-  const u32x4* Ag1 = (const u32x4*)(A + (size_t)mt1 * K * 128);
-  const int strip0 = bx * 8;
-  // weight pieces of this thread: 2048 pieces per chunk = 8 strips x 256; piece p = i * 256 + tid
-  // strips past the end (N not a multiple of 256) are clamped to the last one; results dropped
-  const int nvalid = min(8, NB - strip0);
-  const int wbase = strip0 * 256 + tid;
-  const u32x4* Wg = (const u32x4*)Wp;
-  f32x16 acc[4][4];
+// QK-norm, RoPE and the writes of one head (EPI_QKV) for batch row `row`: val(b, i) is dim
+// 32 b + (i / 4) * 8 + (lane / 32) * 4 + i % 4 of the head.  The same arithmetic as qkrope128_kernel;
+// only the order of the sum of squares differs.
+template <bool FP8, typename F>
+__device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row, int M, int hd, int lane) {
+  const int h4 = (lane >> 5) * 4;
+  float ss = 0.f;
 #pragma unroll
-  for (int a = 0; a < 4; a++)
+  for (int b = 0; b < 4; b++)
+#pragma unroll
+    for (int i = 0; i < 16; i++) ss += val(b, i) * val(b, i);
+  ss += __shfl_xor(ss, 32, 64);
+  if (row >= M) return;
+  const int pos = q.row_pos[row], tok = pos & (RL_PAGE - 1);
+  const bool is_q = hd < q.nq, is_v = hd >= q.nq + q.nkv;
+  size_t blk = 0;
+  if (!is_q) {
+    const int page = q.page_table[(size_t)q.row_slot[row] * q.pt_stride + (pos >> 4)];
+    blk = ((size_t)page * q.nkv + (is_v ? hd - q.nq - q.nkv : hd - q.nq)) * (RL_PAGE * 128);
+  }
+  if (is_v) {
 #pragma unroll
     for (int b = 0; b < 4; b++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) acc[a][b][e] = 0.f;
-  // the 16 pieces of a thread and chunk: 0-3 rows 0-127, 4-7 rows 128-255, 8-15 the 8 strips;
-  // chunks past the end are clamped to the last one (re-reads that hit in cache, never used)
-  auto piece_src = [&](int chunk, int p) -> const u32x4* {
-    const int cl = min(chunk, nchunks - 1);
-    if (p < 4) return Ag0 + (size_t)cl * 1024 + p * 256 + tid;
-    if (p < 8) return Ag1 + (size_t)cl * 1024 + (p - 4) * 256 + tid;
-    return Wg + (size_t)cl * NB * 256 + wbase + min(p - 8, nvalid - 1) * 256;
-  };
-  auto piece_dst = [&](int buf, int p) -> u32x4* {
-    return smem + buf * 4096 + (p < 8 ? p * 256 : 2048 + (p - 8) * 256) + tid;
-  };
-  constexpr int DIST = 24;                   // groups between a piece's load and the group of piece p's store
-  u32x4 rs[32];                              // ring: the load of group T (counted from chunk 0) lands in slot T % 32
-  u32x4 av[2][4], bv[2][4];
-  {
-    u32x4 t0[16];
-#pragma unroll
-    for (int p = 0; p < 16; p++) t0[p] = *piece_src(0, p);
-#pragma unroll
-    for (int q = 0; q < DIST; q++) rs[(q + 32 - DIST) & 31] = *piece_src(1 + (q >> 4), q & 15);
-#pragma unroll
-    for (int p = 0; p < 16; p++) *piece_dst(0, p) = t0[p];
-  }
-  __syncthreads();
-  {
-    const u32x4* as_ = smem + wm * 1024;
-    const u32x4* bs_ = smem + 2048 + wn * 1024;
-#pragma unroll
-    for (int x = 0; x < 4; x++) { av[0][x] = as_[x * 64 + lane]; bv[0][x] = bs_[(x * 4) * 64 + lane]; }
-  }
-  for (int c = 0; c < nchunks; c += 2) {   // nchunks is even (checked by the launcher)
-#pragma unroll
-    for (int it2 = 0; it2 < 2; it2++) {
-      const int i = c + it2;               // chunk being multiplied; it sits in LDS buffer it2
-      const u32x4* as_cur = smem + it2 * 4096 + wm * 1024;
-      const u32x4* bs_cur = smem + it2 * 4096 + 2048 + wn * 1024;
-      const u32x4* as_nxt = smem + (1 - it2) * 4096 + wm * 1024;
-      const u32x4* bs_nxt = smem + (1 - it2) * 4096 + 2048 + wn * 1024;
-#pragma unroll
-      for (int g = 0; g < 16; g++) {
-        const int kk = g >> 2, a = g & 3;
-        if (g == 12) __syncthreads();      // chunk i + 1 is complete in the other buffer; this one is read out
-        rs[(16 * it2 + g) & 31] = *piece_src(i + 1 + ((g + DIST) >> 4), (g + DIST) & 15);
-        // stores of chunk i + 1: pieces p with 3 p / 4 == g (16 pieces over groups 0-11)
-#pragma unroll
-        for (int p = 0; p < 16; p++)
-          if ((3 * p) / 4 == g) *piece_dst(1 - it2, p) = rs[(16 * it2 + p + 32 - DIST) & 31];
-        // operands of the next 16-k step
-        if (kk < 3) {
-          av[(kk + 1) & 1][a] = as_cur[((kk + 1) * 4 + a) * 64 + lane];
-          bv[(kk + 1) & 1][a] = bs_cur[(a * 4 + kk + 1) * 64 + lane];
-        } else {
-          av[0][a] = as_nxt[a * 64 + lane];
-          bv[0][a] = bs_nxt[(a * 4) * 64 + lane];
-        }
-#pragma unroll
-        for (int b = 0; b < 4; b++)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[kk & 1][a]),
-                                                              __builtin_bit_cast(bf16x8, bv[kk & 1][b]),
-                                                              acc[a][b], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);   // LDS stores
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      }
-    }
-  }
-  float* Cp = (float*)Cv;
-#pragma unroll
-  for (int b = 0; b < 4; b++) {
-    const int nb = strip0 + wn * 4 + b;
-    if (nb >= NB) continue;
-    const int col = nb * 32 + (lane & 31);
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      const int mtile = wm == 0 ? mt0 : mt0 + 1;
-      if (mtile >= mtiles128) continue;
-#pragma unroll
       for (int i = 0; i < 16; i++) {
-        int row = mtile * 128 + a * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-        float v = acc[a][b][i];
-        if (EPI == EPI_SWIGLU) {
-          float u = __shfl_xor(v, 16, 64);
-          if ((lane & 16) == 0 && row < M) {
-            float y = v / (1.0f + __expf(-v)) * u;
-            int j = nb * 16 + (lane & 15);
-            ((bf16_t*)Cv)[atile_off(row, j, N >> 1)] = f2bf(y);
+        const int d = 32 * b + (i >> 2) * 8 + h4 + (i & 3);
+        if (FP8) ((uint8_t*)q.vpool)[blk + vswz8_off(tok, d)] = f2e4m3(val(b, i));
+        else ((bf16_t*)q.vpool)[blk + vswz_off(tok, d)] = f2bf(val(b, i));
+      }
+    return;
+  }
+  const bf16_t* g = is_q ? q.gq : q.gk;
+  const float inv = q.qk_norm ? 1.0f / sqrtf(ss / 128.0f + q.eps) : 1.0f;
+#pragma unroll
+  for (int b = 0; b < 2; b++)
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      const int d = 32 * b + c * 8 + h4;                 // dims d .. d + 3 and their partners d + 64 ..
+      const float4 cs0 = *(const float4*)(q.rope_cs + ((size_t)pos * 64 + d) * 2);
+      const float4 cs1 = *(const float4*)(q.rope_cs + ((size_t)pos * 64 + d) * 2 + 4);
+      const float co[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sn[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
+      float gl[4] = {1.f, 1.f, 1.f, 1.f}, gh[4] = {1.f, 1.f, 1.f, 1.f};
+      if (q.qk_norm) {
+        ld4(g + d, gl[0], gl[1], gl[2], gl[3]);
+        ld4(g + d + 64, gh[0], gh[1], gh[2], gh[3]);
+      }
+      float y1[4], y2[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        float x1 = val(b, 4 * c + e), x2 = val(b + 2, 4 * c + e);
+        if (q.qk_norm) { x1 = x1 * inv * gl[e]; x2 = x2 * inv * gh[e]; }
+        y1[e] = x1 * co[e] - x2 * sn[e];
+        y2[e] = x2 * co[e] + x1 * sn[e];
+      }
+      if (FP8 && !is_q) {
+        uint8_t* k8 = (uint8_t*)q.kpool + blk;
+        *(uint32_t*)(k8 + kswz8_off(tok, d)) = f2e4m3x4(y1[0], y1[1], y1[2], y1[3]);
+        *(uint32_t*)(k8 + kswz8_off(tok, d + 64)) = f2e4m3x4(y2[0], y2[1], y2[2], y2[3]);
+        continue;
+      }
+      const uint2 w1 = make_uint2((uint32_t)f2bf(y1[0]) | ((uint32_t)f2bf(y1[1]) << 16),
+                                  (uint32_t)f2bf(y1[2]) | ((uint32_t)f2bf(y1[3]) << 16));
+      const uint2 w2 = make_uint2((uint32_t)f2bf(y2[0]) | ((uint32_t)f2bf(y2[1]) << 16),
+                                  (uint32_t)f2bf(y2[2]) | ((uint32_t)f2bf(y2[3]) << 16));
+      if (is_q) {
+        bf16_t* dst = q.qout + ((size_t)row * q.nq + hd) * 128 + d;
+        *(uint2*)dst = w1;
+        *(uint2*)(dst + 64) = w2;
+      } else {
+        bf16_t* kb = (bf16_t*)q.kpool + blk;
+        *(uint2*)(kb + kswz_off(tok, d)) = w1;
+        *(uint2*)(kb + kswz_off(tok, d + 64)) = w2;
+      }
+    }
+}
+
+template <int EPI, int NBW>
+__global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
+                                                       void* __restrict__ Cv, int M, int N, int K,
+                                                       int chunks_per_split, const int32_t* __restrict__ tgt,
+                                                       float* __restrict__ zt, float scale_c, QkvArgs qkv) {
+  constexpr bool TR = EPI != EPI_STORE;       // weights as the row operand
+  constexpr int NS = 2 * NBW;                 // strips of the tile
+  constexpr int PW = 4 + NBW;                 // 1 KB pieces per wave and chunk
+  constexpr int BUF = (16 + 4 * NBW) * 1024;  // bytes of a stage: 16 row pieces, then [strip][kb]
+  extern __shared__ u32x4 smem[];             // 4 stages
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int NB = N >> 5, nch = K >> 5;
+  const int mtiles128 = (M + 127) >> 7;
+  const int c0 = blockIdx.z * chunks_per_split, c1 = min(c0 + chunks_per_split, nch);
+  int bx, by;
+  xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
+  const int mt0 = by * 2, mt1 = min(mt0 + 1, mtiles128 - 1);   // second half clamped (results dropped)
+  const int strip0 = bx * NS;
+  auto rsrc_of = [](const void* p, unsigned bytes) {
+    const uint64_t a = (uint64_t)p;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
+    r[2] = __builtin_amdgcn_readfirstlane(bytes);
+    r[3] = 0x00027000u;
+    return r;
+  };
+  const u32x4 ra = rsrc_of(A + (size_t)mt0 * K * 128, (unsigned)(mt1 - mt0 + 1) * (unsigned)K * 256u);
+  const u32x4 rb = rsrc_of(Wp, (unsigned)N * (unsigned)K * 2u);
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const int voff = lane * 16;
+  const unsigned a_rt1 = (unsigned)(mt1 - mt0) * (unsigned)K * 256u;
+  // piece j of this wave of chunk c (past the end of the slice: its last chunk again, never read)
+  auto dma = [&](int c, int j) {
+    const int cl = min(c, c1 - 1);
+    const unsigned dst = lds0 + (unsigned)(c & 3) * BUF + (unsigned)(j * 4 + wave) * 1024u;
+    unsigned so;
+    if (j < 4) {
+      so = ((j >> 1) ? a_rt1 : 0u) + (unsigned)((2 * cl + (j & 1)) * 4 + wave) * 1024u;
+    } else {     // strips past the end (N not a multiple of the tile): the last one again, results dropped
+      const int st = min(strip0 + 2 * (j - 4) + (wave >> 1), NB - 1);
+      so = ((unsigned)(cl >> 1) * NB + st) * 4096u + (cl & 1) * 2048u + (wave & 1) * 1024u;
+    }
+    const u32x4 r = j < 4 ? ra : rb;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff),
+                 "s"(r), "s"(so)
+                 : "memory");
+  };
+  f32x16 acc[4][4], acc5[4];
+#pragma unroll
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      acc5[a][e] = 0.f;
+#pragma unroll
+      for (int b = 0; b < 4; b++) acc[a][b][e] = 0.f;
+    }
+  u32x4 av[2][4], bv[2][NBW];
+  const u32x4* As = smem + (wm * 8) * 64 + lane;               // [kb][32-row block]
+  const u32x4* Bs = smem + (16 + wn * NBW * 2) * 64 + lane;    // [strip][kb]
+#pragma unroll
+  for (int c = 0; c < 3; c++)
+#pragma unroll
+    for (int j = 0; j < PW; j++) dma(c0 + c, j);
+#pragma unroll
+  for (int j = 0; j < 4; j++) dma(c0 + 3, j);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PW + 4) : "memory");
+  __builtin_amdgcn_s_barrier();
+  {
+    const int base = (c0 & 3) * (BUF / 16);
+#pragma unroll
+    for (int x = 0; x < 4; x++) av[0][x] = As[base + x * 64];
+#pragma unroll
+    for (int x = 0; x < NBW; x++) bv[0][x] = Bs[base + x * 128];
+  }
+  for (int c = c0; c < c1; c++) {
+    const int cur = (c & 3) * (BUF / 16), nxt = ((c + 1) & 3) * (BUF / 16);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < 8; g++) {
+      const int a = g & 3, st = g >> 2;
+      if (g == 4) {      // chunk c + 1 has landed for every wave, chunk c is read out by every wave
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * PW) : "memory");
+        __builtin_amdgcn_s_barrier();
+      }
+      const int base = st == 0 ? cur : nxt, kb = st == 0 ? 1 : 0;
+      auto rd = [&](int q) {      // operand q of the next 16-k step
+        if (q < 4) av[1 - st][q] = As[base + (kb * 4 + q) * 64];
+        else bv[1 - st][q - 4] = Bs[base + ((q - 4) * 2 + kb) * 64];
+      };
+      if (a == 0) { rd(4); rd(0); rd(5); }
+      if (a == 1) { rd(6); rd(7); rd(1); }
+      if (a == 2) { rd(2); rd(3); if (NBW == 5) rd(8); }
+      if (st == 0) {
+        dma(c + 3, 4 + a);
+        if (NBW == 5 && a == 3) dma(c + 3, 8);
+      } else {
+        dma(c + 4, a);
+      }
+#pragma unroll
+      for (int b = 0; b < 4; b++)
+        acc[a][b] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bv[st][b]),
+                                                                 __builtin_bit_cast(bf16x8, av[st][a]), acc[a][b], 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[st][a]),
+                                                                 __builtin_bit_cast(bf16x8, bv[st][b]), acc[a][b], 0, 0, 0);
+      if (NBW == 5) {
+        if (TR) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(bv[st][NBW - 1]), "v"(av[st][a]));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(av[st][a]), "v"(bv[st][NBW - 1]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // all loads into LDS are done; the last assembly MFMAs' results may be read
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15"
+               : "+v"(acc5[0]), "+v"(acc5[1]), "+v"(acc5[2]), "+v"(acc5[3])::"memory");
+  float* Cp = (float*)Cv + (size_t)blockIdx.z * M * N;
+#pragma unroll
+  for (int a = 0; a < 4; a++) {
+    const int mtile = wm == 0 ? mt0 : mt0 + 1;
+    if (mtile >= mtiles128) continue;
+    const int row0 = mtile * 128 + a * 32, row = row0 + (lane & 31);
+    if constexpr (EPI == EPI_QKV || EPI == EPI_QKV8) {
+      if (strip0 + wn * 4 < NB)
+        qkv_head<EPI == EPI_QKV8>([&](int b, int i) { return acc[a][b][i]; }, qkv, row, M, (strip0 >> 2) + wn, lane);
+    } else {
+#pragma unroll
+      for (int b = 0; b < NBW; b++) {
+        const int nb = strip0 + wn * NBW + b;
+        if (nb >= NB) continue;
+        auto val = [&](int i) { return b < 4 ? acc[a][b & 3][i] : acc5[a][i]; };
+        if constexpr (EPI == EPI_SWIGLU) {
+          swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
+        } else if constexpr (EPI == EPI_LSE) {
+          lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
+        } else {
+          const int col = nb * 32 + (lane & 31);
+#pragma unroll
+          for (int i = 0; i < 16; i++) {
+            const int r = row0 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+            if (r < M) __builtin_nontemporal_store(val(i), &Cp[(size_t)r * N + col]);
           }
-        } else if (row < M) {
-          __builtin_nontemporal_store(v, &Cp[(size_t)row * N + col]);
         }
       }
     }
+    __builtin_amdgcn_sched_barrier(0);      // one row block's values in flight at a time
   }
 }
 
-// M > 128: with one row tile the wide tile computes rows that are not there (the lm-head of a single
-// row at N = 151 936, K = 1024: 116 us, and 57 us with the 128-row kernel's 32-row instance)
-static bool use_gemm256(int M, int N, int K, int epilogue, int splits) {
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  return M > 128 && splits == 1 && (epilogue == EPI_STORE || epilogue == EPI_SWIGLU) && N >= 4096 && N % 32 == 0 &&
-         (K / 64) % 2 == 0 && K >= 128 && tiles >= 512;
-}
-
-static void launch_gemm256(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N,
-                           int K, int epilogue) {
-  static bool attr_set = false;      // 128 KB of dynamic LDS need the opt-in once per process
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm256_mfma_kernel<EPI_STORE>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
-    (void)hipFuncSetAttribute((const void*)gemm256_mfma_kernel<EPI_SWIGLU>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 131072);
-    attr_set = true;
+template <int EPI, int NBW>
+static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
+                       const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
+  constexpr int lds = 4 * (16 + 4 * NBW) * 1024;       // above 64 KB: needs the opt-in, once per device
+  static std::atomic<uint64_t> done{0};
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  const uint64_t bit = 1ull << (dev & 63);
+  if (!(done.load(std::memory_order_acquire) & bit)) {
+    (void)hipFuncSetAttribute((const void*)gemm_dma_kernel<EPI, NBW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    done.fetch_or(bit, std::memory_order_release);
   }
-  dim3 grid((N + 255) / 256, (M + 255) / 256, 1);
-  if (epilogue == EPI_STORE) gemm256_mfma_kernel<EPI_STORE><<<grid, 256, 131072, s>>>(A, Wp, C, M, N, K);
-  else gemm256_mfma_kernel<EPI_SWIGLU><<<grid, 256, 131072, s>>>(A, Wp, C, M, N, K);
+  const int cps = (K / 32 + splits - 1) / splits;
+  dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 255) / 256, splits);
+  gemm_dma_kernel<EPI, NBW><<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
 }
 
 template <int D, int NW, int MB>
@@ -438,41 +563,76 @@ static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t*
     gemm_mfma_kernel<EPI_SWIGLU, D, NW, MB><<<grid, 64 * NW, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
 }
 
-// depth = chunks in flight per workgroup (2 or 4)
-int launch_gemm_mfma_cfg(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N,
-                         int K, int epilogue, int splits, int nw, int depth) {
+// Which kernel and how many K-slices.  At most 128 rows (decode): the weight-streaming kernel with
+// enough K-slices for ~240 workgroups (one CU sustains only ~20 GB/s of HBM reads), at least four 64-k
+// chunks per slice, at most kMaxSplits partial sums (each costs M x N floats of traffic; 8 measured
+// best in the full decode step); narrow outputs of small models take 64-column tiles when 128-column
+// tiles times slices leave more than half of the CUs without a workgroup.
+// More rows: the cheapest by estimate (us).  A round is 256 workgroups, one per CU.  256-row tiles cost
+// per 32-k chunk 0.43 us with most CUs idle to 0.73 us with all of them busy (320 columns: 1.25 times
+// that), 4 to 16 us per round to store a tile, and further partial sums are read at 5 TB/s; 128 x 128
+// tiles cost 0.62 us per 64-k chunk and round, 0.59 us from the second round on (several to a CU).
+// Fitted on N = 2048 to 6144, K = 640 to 9728, 64 to 1280 tiles; e.g. 8192 x 2560 x 9728: 320 columns make
+// one full round of 256 tiles (289 us) where 256 columns make two (398 us, a quarter of the second
+// used); 587 x 2560 x 9728: eight slices of 256-column tiles.
+GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
+  const bool can_split = epilogue == EPI_STORE;
+  const int tiles = ((N + 127) / 128) * ((M + 127) / 128);
+  const int most = can_split ? (int)std::min<size_t>(kMaxSplits, std::max<size_t>(1, part_rows / (size_t)std::max(M, 1))) : 1;
+  int s = 1;
+  if (can_split && M <= 1024 && tiles < 240)
+    s = std::max(1, std::min({(240 + tiles / 2) / tiles, most, std::max(1, K / 256)}));
+  GemmPlan best{0, tiles * s < 160 && N <= 8192 && M <= 128 ? 2 : 4, s, 0.0};
+  auto read_back = [&](int sp) { return (sp - 1) * (double)M * N * 4.0 / 5.0e6; };
+  const int rounds = (tiles * s + 255) / 256;
+  best.cost = 7.0 + rounds * (rounds > 1 ? 0.59 : 0.62) * ((K / 64 + s - 1) / s) + read_back(s);
+  if (M <= 128 || (size_t)N * K * 2 >= 0x7fff0000ull) return best;
+  for (int nbw = 4; nbw <= (epilogue == EPI_STORE || epilogue == EPI_SWIGLU ? 5 : 4); nbw++)
+    for (int sp = 1; sp <= std::min(most, std::max(1, K / 256)); sp++) {
+      const int t = ((N / 32 + 2 * nbw - 1) / (2 * nbw)) * ((M + 255) / 256) * sp, r = (t + 255) / 256;
+      const double fill = t / (256.0 * r), w = nbw / 4.0;
+      const int cps = (K / 32 + sp - 1) / sp;
+      const double cost = 3.0 + r * (cps * w * (0.43 + 0.30 * fill) + 4.0 + 10.0 * w * fill) + read_back(sp);
+      if (cost < best.cost) best = GemmPlan{nbw, 4, (K / 32 + cps - 1) / cps, cost};
+    }
+  return best;
+}
+
+int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
+                     const GemmPlan& plan) {
   if (M <= 0) return 0;
-  int nchunks = K / 64;
-  if (splits < 1 || epilogue == EPI_SWIGLU) splits = 1;
-  if (splits > nchunks) splits = nchunks;
-  if (nw == 4 && depth == 2 && use_gemm256(M, N, K, epilogue, splits)) {
-    launch_gemm256(s, A, Wp, C, M, N, K, epilogue);
-    return 1;
+  if (plan.nbw > 0) {
+    const QkvArgs none{};
+    if (epilogue == EPI_STORE && plan.nbw == 4) launch_dma<EPI_STORE, 4>(s, A, Wp, C, M, N, K, plan.splits, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 5>(s, A, Wp, C, M, N, K, plan.splits, nullptr, nullptr, 0.f, none);
+    else if (plan.nbw == 4) launch_dma<EPI_SWIGLU, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    else launch_dma<EPI_SWIGLU, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    return plan.splits;
   }
-  int cps = (nchunks + splits - 1) / splits;
+  const int nchunks = K / 64, nw = plan.nw;
+  int splits = epilogue == EPI_SWIGLU ? 1 : std::max(1, std::min(plan.splits, nchunks));
+  const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
   dim3 grid((N + 32 * nw - 1) / (32 * nw), (M + 127) / 128, splits);
+  // two chunks in flight: fewer registers, more resident workgroups (measured best at M = 128)
   const int mb = M <= 32 ? 1 : M <= 64 ? 2 : 4;    // row blocks in use (one row tile when < 4)
-  if (nw == 2 && depth == 2) {
+  if (nw == 2) {
     if (mb == 1) gemm_launch<2, 2, 1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
     else if (mb == 2) gemm_launch<2, 2, 2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
     else gemm_launch<2, 2, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  } else if (nw == 2) {
-    gemm_launch<4, 2, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  } else if (depth == 2) {
+  } else {
     if (mb == 1) gemm_launch<2, 4, 1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
     else if (mb == 2) gemm_launch<2, 4, 2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
     else gemm_launch<2, 4, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  } else {
-    gemm_launch<4, 4, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
   }
   return splits;
 }
 
-int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N,
-                     int K, int epilogue, int splits, int nw) {
-  // two chunks in flight: fewer registers, more resident workgroups (measured best at M = 128)
-  return launch_gemm_mfma_cfg(s, A, Wp, C, M, N, K, epilogue, splits, nw, 2);
+void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int N, int K, bool kv_fp8,
+                     const QkvArgs& q) {
+  if (M <= 0) return;
+  if (kv_fp8) launch_dma<EPI_QKV8, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+  else launch_dma<EPI_QKV, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
 }
 
 // lm-head of a decode step: logits[M, V] (fp32, row-major) and stripmax[M, V / 32].
@@ -521,8 +681,12 @@ __global__ __launch_bounds__(256) void lse_finish_kernel(const float2* __restric
 void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int V, int K,
                             const int32_t* tgt, float scale_c, float* part, float* zt, float* lp) {
   if (M <= 0) return;
-  dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
-  gemm_mfma_kernel<EPI_LSE, 2, 4, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
+  if (plan_gemm(M, V, K, EPI_LSE, 0).nbw == 4) {
+    launch_dma<EPI_LSE, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
+  } else {
+    dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
+    gemm_mfma_kernel<EPI_LSE, 2, 4, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
+  }
   lse_finish_kernel<<<M, 256, 0, s>>>((const float2*)part, zt, V / 32, scale_c, lp);
 }
 

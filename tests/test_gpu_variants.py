@@ -76,3 +76,38 @@ def test_fp32_products_and_attention_at_the_edges(change, lens):
         assert np.abs(o.debug_logits(i) - g.debug_logits(i)).max() < 1e-4
     assert np.abs(o.recompute_logprobs(ids, 1.0) - g.recompute_logprobs(ids, 1.0)).max() < 1e-4
     g.close()
+
+
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("change,lens,sampled", [
+    (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [2048, 2049], 2),   # 4095 rows, last tile one row short
+    (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [3713], 2),         # 30 row tiles of 128 (29 + 1 row)
+    (dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=32768), [5, 3000], 130),    # 10 heads, 320-column tiles, odd strips
+    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [300, 288], 1),     # K-slices of 256-row tiles
+])
+def test_many_row_products(change, lens, sampled, kv8):
+    # the 256-row tiles (256 and 320 columns, K-slices, SwiGLU, QK-norm + RoPE + cache write and log-softmax
+    # in the epilogue) at row counts and widths that end inside a tile, against the shape-generic kernels
+    shape = SHAPES["small-d128"].replace(n_layers=1, **change)
+    blob = make_weight_blob(shape, seed=6, weight_std=0.02, gain_std=0.1)
+    kw = dict(max_context=4096, max_trajectories=4, kv_pool_pages=400)
+    a = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, **kw)
+    b = rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
+    rng = np.random.default_rng(sum(lens))
+    ids = list(range(len(lens)))
+    toks = rng.integers(0, shape.vocab, sum(lens))
+    for e in (a, b):
+        e.append_observation(ids, toks, lens)
+    for _ in range(sampled):
+        forced = rng.integers(0, shape.vocab, len(lens))
+        for e in (a, b):
+            e.decode_step_forced(ids, 1.0, forced)
+    # two bf16 paths over one layer: the bound of the parity tests, on logits of standard deviation up to 1;
+    # the 8-bit cache moves keys and values by up to 2^-4, attenuated by the average over the context
+    tol = 3e-2 if not kv8 else 0.25
+    za, zb = a.debug_logits(ids[-1]), b.debug_logits(ids[-1])
+    assert np.abs(za - zb).max() < tol * max(1.0, float(zb.std()))
+    ra, rb = a.recompute_logprobs(ids, 1.0), b.recompute_logprobs(ids, 1.0)
+    assert np.abs(ra - rb).max() < tol
+    assert np.array_equal(ra, a.recompute_logprobs(ids, 1.0))        # the same bits again
+    a.close(), b.close()
