@@ -217,7 +217,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
   // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
   const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
-  const bool fused_qkv = pf.nbw == 4 && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
+  const bool fused_qkv = pf.kind == GEMM_TILE256 && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];

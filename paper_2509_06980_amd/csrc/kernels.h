@@ -85,9 +85,11 @@ void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool ati
 
 // ---- MFMA kernels (bf16, head_dim 128) -------------------------------------------------------
 enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4, EPI_QKV = 5, EPI_QKV8 = 6 };
-// Kernel and K-slices of one product (see plan_gemm's definition).  nbw: 0 = 128-row tiles of 32 * nw
-// columns, 4 / 5 = 256-row tiles of 64 * nbw columns.  cost: estimate in us, comparable between plans.
-struct GemmPlan { int nbw, nw, splits; double cost; };
+// Kernel and K-slices of one product (see plan_gemm's definition).  width: GEMM_TILE256: 64-column groups
+// of the tile (4 or 5); GEMM_DECODE: 16-column blocks of the tile (2, 4, 5 or 6).  cost: estimate in us,
+// comparable between plans of as many rows.
+enum GemmKind { GEMM_TILE128 = 0, GEMM_TILE256 = 1, GEMM_DECODE = 2 };
+struct GemmPlan { int kind, width, splits; double cost; };
 const int kMaxSplits = 8;
 // part_rows: rows the partial-sum buffer holds (every K-slice takes M of them)
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows);

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 // =============================================================================================
 // Weight repack: W[N,K] row-major -> [K/64 chunks][N/32 strips][4 k-blocks][64 lanes][8].  One
@@ -278,10 +279,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 // stages, three and a half chunks ahead.  The loop is one steady stream: every group of NBW MFMAs
 // carries one such load, and the next step's operands are read in the first three of four groups, so
 // that the wait in front of the barrier (group 4 of a chunk's 8: the next chunk is complete, this one
-// is read out) finds them there.  The loads are issued from inline assembly because the compiler
-// otherwise waits for all of them before any LDS read; every wait on them is the explicit vmcnt
-// below: the loads return in order, so "at most 2 chunks outstanding" means the next chunk has landed.
-// Before the epilogue all are drained (nothing may land in LDS that is no longer ours).
+// is read out) finds them there.  The loads return in order, so "at most 2 chunks outstanding" means
+// that the next chunk has landed; before the epilogue all are drained.
 // The fifth accumulator column lives in vector registers: 320 accumulator registers exceed the 256
 // accumulation registers, and the builtin, which takes all of its kind from one file, then copies.
 // blockIdx.z selects a K-slice (EPI_STORE only); each slice stores its own partial sum.
@@ -388,6 +387,26 @@ __device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row, int M
     }
 }
 
+// Buffer descriptor of `bytes` bytes at p in scalar registers (p and bytes are the same in every lane).
+__device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
+  const uint64_t a = (uint64_t)p;
+  u32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+  r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
+  r[2] = __builtin_amdgcn_readfirstlane(bytes);
+  r[3] = 0x00027000u;
+  return r;
+}
+// One load of 16 bytes per lane straight into LDS (lane l's piece at lds + 16 l).  Inline assembly: after
+// the builtin the compiler waits for all such loads before any LDS read.  Whoever uses it waits with an
+// explicit vmcnt (the loads return in order), puts a barrier before other waves read, and drains all of
+// them before the workgroup ends.  Pieces whose offset lies behind the buffer's end arrive as zeros.
+__device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, unsigned soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
+               "s"(soff)
+               : "memory");
+}
+
 template <int EPI, int NBW>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K,
@@ -407,17 +426,8 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
   xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
   const int mt0 = by * 2, mt1 = min(mt0 + 1, mtiles128 - 1);   // second half clamped (results dropped)
   const int strip0 = bx * NS;
-  auto rsrc_of = [](const void* p, unsigned bytes) {
-    const uint64_t a = (uint64_t)p;
-    u32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
-    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
-    r[2] = __builtin_amdgcn_readfirstlane(bytes);
-    r[3] = 0x00027000u;
-    return r;
-  };
-  const u32x4 ra = rsrc_of(A + (size_t)mt0 * K * 128, (unsigned)(mt1 - mt0 + 1) * (unsigned)K * 256u);
-  const u32x4 rb = rsrc_of(Wp, (unsigned)N * (unsigned)K * 2u);
+  const u32x4 ra = buffer_rsrc(A + (size_t)mt0 * K * 128, (unsigned)(mt1 - mt0 + 1) * (unsigned)K * 256u);
+  const u32x4 rb = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
   const int voff = lane * 16;
   const unsigned a_rt1 = (unsigned)(mt1 - mt0) * (unsigned)K * 256u;
@@ -432,10 +442,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
       const int st = min(strip0 + 2 * (j - 4) + (wave >> 1), NB - 1);
       so = ((unsigned)(cl >> 1) * NB + st) * 4096u + (cl & 1) * 2048u + (wave & 1) * 1024u;
     }
-    const u32x4 r = j < 4 ? ra : rb;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff),
-                 "s"(r), "s"(so)
-                 : "memory");
+    load_to_lds(dst, voff, j < 4 ? ra : rb, so);
   };
   f32x16 acc[4][4], acc5[4];
 #pragma unroll
@@ -537,63 +544,219 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
   }
 }
 
-template <int EPI, int NBW>
-static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
-                       const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
-  constexpr int lds = 4 * (16 + 4 * NBW) * 1024;       // above 64 KB: needs the opt-in, once per device
-  static std::atomic<uint64_t> done{0};
+// More than 64 KB of dynamic LDS need an opt-in, once per kernel and device.
+static void set_lds_limit(std::atomic<uint64_t>& done, const void* kernel, int bytes) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   const uint64_t bit = 1ull << (dev & 63);
-  if (!(done.load(std::memory_order_acquire) & bit)) {
-    (void)hipFuncSetAttribute((const void*)gemm_dma_kernel<EPI, NBW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    done.fetch_or(bit, std::memory_order_release);
-  }
+  if (done.load(std::memory_order_acquire) & bit) return;
+  (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  done.fetch_or(bit, std::memory_order_release);
+}
+
+template <int EPI, int NBW>
+static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
+                       const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
+  constexpr int lds = 4 * (16 + 4 * NBW) * 1024;
+  static std::atomic<uint64_t> done{0};
+  set_lds_limit(done, (const void*)gemm_dma_kernel<EPI, NBW>, lds);
   const int cps = (K / 32 + splits - 1) / splits;
   dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 255) / 256, splits);
   gemm_dma_kernel<EPI, NBW><<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
 }
 
-template <int D, int NW, int MB>
+// =============================================================================================
+// GEMM for decode batches of 33 to 128 rows and, where the estimate says so, fewer: tile 64 * RB rows
+// (RB = 1 or 2 16-row blocks per wave) x 16 * CB columns.  What bounds these products is what one CU can
+// fetch: about 27 GB/s of weights from HBM and 125 GB/s of activations, which every workgroup needs
+// whole, from L2.  So the work is cut for 256 equal workgroups (CB = 2, 4, 5 or 6, times K-slices: 80
+// columns of the 4B gate-up make 244, where 128-column tiles leave 104 CUs idle), and both operands
+// stream straight into an LDS ring of NST stages of SK k, NST - 1 ahead, with one barrier per stage and
+// no staging registers.  A block is 16 rows (columns) x 32 k in operand order, gathered from the 32-row
+// layout by the lanes' offsets.  The product is formed transposed: four consecutive columns of a row
+// per lane, stored as 16 bytes; SwiGLU needs one swap of lane halves.
+// Rows are whole-wave work with no sum across waves: a row's bits do not depend on its place.
+// us at 128 / 64 rows, the 128-column kernel -> this: gate-up N = 19456 K = 2560 28.8 -> 26.0 / 23.4 -> 19.0,
+// down N = 2560 K = 9728 17.9 -> 15.9 / 14.1 -> 11.9, O N = 2560 K = 4096 9.9 -> 8.5 / 7.9 -> 6.7, QKV
+// N = 6144 K = 2560 11.7 -> 10.7 / 8.6 -> 8.4; 0.6B shape: gate-up 11.3 -> 7.2 / 7.5 -> 5.7, down 7.0 -> 4.4 /
+// 4.8 -> 3.6.  Deeper rings gain nothing; leaving out the loads behind the slice with a branch costs
+// 10 % (the loop falls apart into blocks).
+// =============================================================================================
+template <int EPI, int RB, int CB, int SK, int NST>
+__global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
+                                                       void* __restrict__ Cv, int M, int N, int K, int splits,
+                                                       int stages_per_split) {
+  constexpr int KB = SK / 32;                    // 32-k steps of a stage
+  constexpr int NA = 4 * RB * KB, NW = CB * KB;  // blocks
+  constexpr int PW = (NA + NW) / 4;
+  static_assert((NST - 2) * PW <= 63 && NST <= 7, "wait counter");
+  static_assert((NA + NW) % 4 == 0, "even");
+  constexpr int BUF = (NA + NW) * 1024;
+  extern __shared__ u32x4 smem[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int tile = blockIdx.x / splits, split = blockIdx.x - tile * splits;
+  const int NB = N >> 5, N16 = N >> 4, nst = K / SK;
+  const int s0 = split * stages_per_split, s1 = min(s0 + stages_per_split, nst);
+  const u32x4 ra = buffer_rsrc(A, (unsigned)K * 256u), rw = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const int lp = ((lane & 15) + (((lane >> 4) & 1) << 5)) << 4;
+  const int lw = ((lane >> 5) << 10) + lp, la = ((lane >> 5) << 12) + lp;
+  // piece j of this wave of stage s: block id j * 4 + wave, weight blocks first; stages behind the slice
+  // are asked for behind the buffer's end: no memory traffic, and the count of loads stays the same
+  auto dma = [&](int s, int j) {
+    const int sl = min(s, s1 - 1), id = j * 4 + wave;
+    const unsigned dst = lds0 + (unsigned)((s - s0) % NST) * BUF + (unsigned)id * 1024u;
+    if (id < NW) {
+      const int t = sl * KB + id / CB, c16 = min(tile * CB + id % CB, N16 - 1);   // columns past the end: dropped
+      load_to_lds(dst, s < s1 ? lw : 0x7fff0000, rw,
+                  ((unsigned)(t >> 1) * NB + (c16 >> 1)) * 4096u + (t & 1) * 2048u + (c16 & 1) * 256u);
+    } else {
+      const int x = id - NW, r = x % (4 * RB), t = sl * KB + x / (4 * RB);
+      load_to_lds(dst, s < s1 ? la : 0x7fff0000, ra, (unsigned)t * 8192u + (r >> 1) * 1024u + (r & 1) * 256u);
+    }
+  };
+  f32x4 acc[CB][RB];
+#pragma unroll
+  for (int c = 0; c < CB; c++)
+#pragma unroll
+    for (int r = 0; r < RB; r++) acc[c][r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < NST - 1; p++)
+#pragma unroll
+    for (int j = 0; j < PW; j++) dma(s0 + p, j);
+  int buf = 0;
+  for (int s = s0; s < s1; s++) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * PW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    const u32x4* B = smem + buf * (BUF / 16) + lane;
+    buf = buf + 1 == NST ? 0 : buf + 1;
+    u32x4 w[2][CB], a[2][RB];
+    auto rd = [&](int k) {
+#pragma unroll
+      for (int c = 0; c < CB; c++) w[k & 1][c] = B[(k * CB + c) * 64];
+#pragma unroll
+      for (int r = 0; r < RB; r++) a[k & 1][r] = B[(NW + k * 4 * RB + wave * RB + r) * 64];
+    };
+    rd(0);
+#pragma unroll
+    for (int k = 0; k < KB; k++) {
+      if (k + 1 < KB) rd(k + 1);
+#pragma unroll
+      for (int j = 0; j < PW; j++)
+        if (j * KB / PW == k ) dma(s + NST - 1, j);
+#pragma unroll
+      for (int c = 0; c < CB; c++)
+#pragma unroll
+        for (int r = 0; r < RB; r++)
+          acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[k & 1][c]),
+                                                              __builtin_bit_cast(bf16x8, a[k & 1][r]), acc[c][r], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < RB; r++) {
+    const int row = (wave * RB + r) * 16 + (lane & 15);
+#pragma unroll
+    for (int c = 0; c < CB; c++) {
+      const int c16 = tile * CB + c;
+      if (c16 >= N16) continue;
+      f32x4 v = acc[c][r];
+      if (EPI == EPI_SWIGLU) {
+        f32x4 up;
+#pragma unroll
+        for (int i = 0; i < 4; i++) up[i] = __shfl_xor(v[i], 32, 64);
+        if (lane < 32 && row < M) {
+          uint32_t y[4];
+#pragma unroll
+          for (int i = 0; i < 4; i++) y[i] = f2bf(v[i] / (1.0f + __expf(-v[i])) * up[i]);
+          *(uint2*)((bf16_t*)Cv + atile_off(row, c16 * 8 + 4 * (lane >> 4), N >> 1)) =
+              make_uint2(y[0] | (y[1] << 16), y[2] | (y[3] << 16));
+        }
+      } else if (row < M) {
+        float* C = (float*)Cv + (size_t)split * M * N;
+        __builtin_nontemporal_store(v, (f32x4*)(C + (size_t)row * N + c16 * 16 + 4 * (lane >> 4)));
+      }
+    }
+  }
+}
+
+template <int EPI, int CB>
+static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits) {
+  constexpr int SK = CB == 5 ? 128 : 64, NST = CB == 5 ? 3 : 4;   // CB = 5: whole rounds of 4 waves need 128 k
+  const int rb = M <= 64 ? 1 : 2, lds = NST * (4 * rb + CB) * (SK / 32) * 1024;
+  static std::atomic<uint64_t> done[2];
+  auto go = [&](auto kernel) {
+    set_lds_limit(done[rb - 1], (const void*)kernel, lds);
+    const int sps = (K / SK + splits - 1) / splits;
+    kernel<<<(N / 16 + CB - 1) / CB * splits, 256, lds, s>>>(A, Wp, C, M, N, K, splits, sps);
+  };
+  if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST>);
+  else go(gemm_decode_kernel<EPI, 2, CB, SK, NST>);
+}
+
+template <int MB>
 static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t* Wp, void* C, int M,
                         int N, int K, int epilogue, int cps) {
   if (epilogue == EPI_STORE)
-    gemm_mfma_kernel<EPI_STORE, D, NW, MB><<<grid, 64 * NW, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
+    gemm_mfma_kernel<EPI_STORE, 2, 4, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
   else
-    gemm_mfma_kernel<EPI_SWIGLU, D, NW, MB><<<grid, 64 * NW, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
+    gemm_mfma_kernel<EPI_SWIGLU, 2, 4, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
 }
 
-// Which kernel and how many K-slices.  At most 128 rows (decode): the weight-streaming kernel with
-// enough K-slices for ~240 workgroups (one CU sustains only ~20 GB/s of HBM reads), at least four 64-k
-// chunks per slice, at most kMaxSplits partial sums (each costs M x N floats of traffic; 8 measured
-// best in the full decode step); narrow outputs of small models take 64-column tiles when 128-column
-// tiles times slices leave more than half of the CUs without a workgroup.
-// More rows: the cheapest by estimate (us).  A round is 256 workgroups, one per CU.  256-row tiles cost
-// per 32-k chunk 0.43 us with most CUs idle to 0.73 us with all of them busy (320 columns: 1.25 times
-// that), 4 to 16 us per round to store a tile, and further partial sums are read at 5 TB/s; 128 x 128
-// tiles cost 0.62 us per 64-k chunk and round, 0.59 us from the second round on (several to a CU).
-// Fitted on N = 2048 to 6144, K = 640 to 9728, 64 to 1280 tiles; e.g. 8192 x 2560 x 9728: 320 columns make
-// one full round of 256 tiles (289 us) where 256 columns make two (398 us, a quarter of the second
-// used); 587 x 2560 x 9728: eight slices of 256-column tiles.
+// Which kernel and how many K-slices: the cheapest by estimate (us), over at most kMaxSplits slices of
+// at least 256 k.  Further partial sums cost their stores and their reading at 5 TB/s.
+// At most 128 rows: per round of 256 workgroups the time of a workgroup's weight bytes at 27 GB/s and of
+// its activation bytes at 125 GB/s, plus 2.2 us (decode kernel) or 3.2 us (128-column kernel, which
+// fetches only the 32-row blocks in use; it stays the better one where its 128 columns times slices
+// make whole rounds: 8B down at N = 4096 K = 12288, 12 rows 18.6 against 22.4 us with 64 columns).
+// More rows: a round is 256 workgroups, one per CU.  256-row tiles cost per 32-k chunk 0.43 us with most
+// CUs idle to 0.73 us with all of them busy (320 columns: 1.25 times that) and 4 to 16 us per round to
+// store a tile; 128 x 128 tiles cost 0.62 us per 64-k chunk and round, 0.59 us from the second round on
+// (several to a CU).  Fitted on N = 2048 to 6144, K = 640 to 9728, 64 to 1280 tiles; e.g. 8192 x 2560 x
+// 9728: 320 columns make one full round of 256 tiles (289 us) where 256 columns make two (398 us).
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
   const bool can_split = epilogue == EPI_STORE;
-  const int tiles = ((N + 127) / 128) * ((M + 127) / 128);
-  const int most = can_split ? (int)std::min<size_t>(kMaxSplits, std::max<size_t>(1, part_rows / (size_t)std::max(M, 1))) : 1;
+  int most = can_split ? (int)std::min<size_t>(kMaxSplits, std::max<size_t>(1, part_rows / (size_t)std::max(M, 1))) : 1;
+  most = std::min(most, std::max(1, K / 256));
+  const bool wide = (size_t)N * K * 2 >= 0x7fff0000ull;      // beyond a buffer descriptor's signed offsets
+  const double part = (double)M * N * 4.0 / 5.0e6;           // one partial sum, stored or read
+  const int tiles = ((N + 127) / 128) * ((M + 127) / 128), nch = K / 64;
+  GemmPlan best{GEMM_TILE128, 0, 1, 1e30};
+  auto offer = [&](int kind, int width, int splits, double cost) {
+    if (cost < best.cost) best = GemmPlan{kind, width, splits, cost};
+  };
+  if (M <= 128) {
+    const double arow = (M <= 32 ? 32 : M <= 64 ? 64 : 128) * 2.0, adec = (M <= 64 ? 64 : 128) * 2.0;
+    for (int sp = 1; sp <= most; sp++) {
+      const int cps = (nch + sp - 1) / sp, r = (tiles * sp + 255) / 256;
+      offer(GEMM_TILE128, 0, sp, 3.2 + r * cps * 64 * (256 / 27.0e3 + arow / 125.0e3) + (2 * sp - 1) * part);
+      if (wide || (epilogue != EPI_STORE && epilogue != EPI_SWIGLU)) continue;
+      for (int cb : {2, 4, 5, 6}) {
+        const int sk = cb == 5 ? 128 : 64;
+        if (K % sk != 0) continue;
+        const int k = (K / sk + sp - 1) / sp * sk, rd = ((N / 16 + cb - 1) / cb * sp + 255) / 256;
+        offer(GEMM_DECODE, cb, sp, 2.2 + rd * k * (32 * cb / 27.0e3 + adec / 125.0e3) + (2 * sp - 1) * part);
+      }
+    }
+    if (best.kind == GEMM_DECODE) {     // no empty slices
+      const int st = K / (best.width == 5 ? 128 : 64), sps = (st + best.splits - 1) / best.splits;
+      best.splits = (st + sps - 1) / sps;
+    }
+    return best;
+  }
   int s = 1;
-  if (can_split && M <= 1024 && tiles < 240)
-    s = std::max(1, std::min({(240 + tiles / 2) / tiles, most, std::max(1, K / 256)}));
-  GemmPlan best{0, tiles * s < 160 && N <= 8192 && M <= 128 ? 2 : 4, s, 0.0};
-  auto read_back = [&](int sp) { return (sp - 1) * (double)M * N * 4.0 / 5.0e6; };
+  if (M <= 1024 && tiles < 240) s = std::max(1, std::min((240 + tiles / 2) / tiles, most));
   const int rounds = (tiles * s + 255) / 256;
-  best.cost = 7.0 + rounds * (rounds > 1 ? 0.59 : 0.62) * ((K / 64 + s - 1) / s) + read_back(s);
-  if (M <= 128 || (size_t)N * K * 2 >= 0x7fff0000ull) return best;
+  offer(GEMM_TILE128, 0, s, 7.0 + rounds * (rounds > 1 ? 0.59 : 0.62) * ((nch + s - 1) / s) + (s - 1) * part);
+  if (wide) return best;
   for (int nbw = 4; nbw <= (epilogue == EPI_STORE || epilogue == EPI_SWIGLU ? 5 : 4); nbw++)
-    for (int sp = 1; sp <= std::min(most, std::max(1, K / 256)); sp++) {
+    for (int sp = 1; sp <= most; sp++) {
       const int t = ((N / 32 + 2 * nbw - 1) / (2 * nbw)) * ((M + 255) / 256) * sp, r = (t + 255) / 256;
       const double fill = t / (256.0 * r), w = nbw / 4.0;
       const int cps = (K / 32 + sp - 1) / sp;
-      const double cost = 3.0 + r * (cps * w * (0.43 + 0.30 * fill) + 4.0 + 10.0 * w * fill) + read_back(sp);
-      if (cost < best.cost) best = GemmPlan{nbw, 4, (K / 32 + cps - 1) / cps, cost};
+      offer(GEMM_TILE256, nbw, (K / 32 + cps - 1) / cps,
+            3.0 + r * (cps * w * (0.43 + 0.30 * fill) + 4.0 + 10.0 * w * fill) + (sp - 1) * part);
     }
   return best;
 }
@@ -601,30 +764,36 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
 int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
                      const GemmPlan& plan) {
   if (M <= 0) return 0;
-  if (plan.nbw > 0) {
+  const int width = plan.width, sp = plan.splits;
+  if (plan.kind == GEMM_TILE256) {
     const QkvArgs none{};
-    if (epilogue == EPI_STORE && plan.nbw == 4) launch_dma<EPI_STORE, 4>(s, A, Wp, C, M, N, K, plan.splits, nullptr, nullptr, 0.f, none);
-    else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 5>(s, A, Wp, C, M, N, K, plan.splits, nullptr, nullptr, 0.f, none);
-    else if (plan.nbw == 4) launch_dma<EPI_SWIGLU, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    if (epilogue == EPI_STORE && width == 4) launch_dma<EPI_STORE, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 5>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (width == 4) launch_dma<EPI_SWIGLU, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
     else launch_dma<EPI_SWIGLU, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
-    return plan.splits;
+    return sp;
   }
-  const int nchunks = K / 64, nw = plan.nw;
-  int splits = epilogue == EPI_SWIGLU ? 1 : std::max(1, std::min(plan.splits, nchunks));
+  if (plan.kind == GEMM_DECODE) {
+    auto go = [&](auto epi) {
+      constexpr int E = decltype(epi)::value;
+      if (width == 2) launch_decode_gemm<E, 2>(s, A, Wp, C, M, N, K, sp);
+      else if (width == 4) launch_decode_gemm<E, 4>(s, A, Wp, C, M, N, K, sp);
+      else if (width == 5) launch_decode_gemm<E, 5>(s, A, Wp, C, M, N, K, sp);
+      else launch_decode_gemm<E, 6>(s, A, Wp, C, M, N, K, sp);
+    };
+    if (epilogue == EPI_STORE) go(std::integral_constant<int, EPI_STORE>());
+    else go(std::integral_constant<int, EPI_SWIGLU>());
+    return sp;
+  }
+  const int nchunks = K / 64;
+  int splits = epilogue == EPI_SWIGLU ? 1 : std::max(1, std::min(sp, nchunks));
   const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
-  dim3 grid((N + 32 * nw - 1) / (32 * nw), (M + 127) / 128, splits);
+  dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
   // two chunks in flight: fewer registers, more resident workgroups (measured best at M = 128)
-  const int mb = M <= 32 ? 1 : M <= 64 ? 2 : 4;    // row blocks in use (one row tile when < 4)
-  if (nw == 2) {
-    if (mb == 1) gemm_launch<2, 2, 1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-    else if (mb == 2) gemm_launch<2, 2, 2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-    else gemm_launch<2, 2, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  } else {
-    if (mb == 1) gemm_launch<2, 4, 1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-    else if (mb == 2) gemm_launch<2, 4, 2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-    else gemm_launch<2, 4, 4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  }
+  if (M <= 32) gemm_launch<1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);      // row blocks in use (one row tile when < 4)
+  else if (M <= 64) gemm_launch<2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
+  else gemm_launch<4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
   return splits;
 }
 
@@ -681,7 +850,7 @@ __global__ __launch_bounds__(256) void lse_finish_kernel(const float2* __restric
 void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int V, int K,
                             const int32_t* tgt, float scale_c, float* part, float* zt, float* lp) {
   if (M <= 0) return;
-  if (plan_gemm(M, V, K, EPI_LSE, 0).nbw == 4) {
+  if (plan_gemm(M, V, K, EPI_LSE, 0).kind == GEMM_TILE256) {
     launch_dma<EPI_LSE, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
   } else {
     dim3 grid((V + 127) / 128, (M + 127) / 128, 1);

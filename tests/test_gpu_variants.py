@@ -111,3 +111,24 @@ def test_many_row_products(change, lens, sampled, kv8):
     assert np.abs(ra - rb).max() < tol
     assert np.array_equal(ra, a.recompute_logprobs(ids, 1.0))        # the same bits again
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("change", [dict(), dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=4128),
+                                    dict(hidden=4096, n_q_heads=4, n_kv_heads=4, intermediate=4096, vocab=4096)])
+@pytest.mark.parametrize("rows", [1, 15, 17, 32, 33, 64, 65, 128, 129])
+def test_decode_products_row_counts(change, rows):
+    # every row count at which the decode products change their tile, widths that end inside a tile of
+    # 32, 64, 80 or 96 columns, depths that are no whole number of 128-k stages, K-slices of unequal length
+    shape = SHAPES["small-d128"].replace(n_layers=1, **change)
+    blob = make_weight_blob(shape, seed=7, weight_std=0.02, gain_std=0.1)
+    kw = dict(max_context=32, max_trajectories=rows, kv_pool_pages=rows)
+    a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
+    rng = np.random.default_rng(rows)
+    ids = np.arange(rows, dtype=np.int32)
+    toks = rng.integers(0, shape.vocab, 3 * rows)
+    forced = rng.integers(0, shape.vocab, rows)
+    for e in (a, b):
+        e.append_observation(ids, toks, [3] * rows)
+    la, lb = (e.decode_step_forced(ids, 1.0, forced) for e in (a, b))
+    assert np.abs(la - lb).max() < 3e-2              # two bf16 paths over one layer, logits of deviation below 1.3
+    a.close(), b.close()
