@@ -1166,19 +1166,28 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
 #pragma unroll
   for (int cb = 0; cb < CB; cb++) {
     bool vis[8];
-    float mx = ATT_NEG;
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-      vis[i] = !MASKED || (pg + (i >> 2)) * RL_PAGE + 4 * g + (i & 3) <= mypos[cb];
-      mx = fmaxf(mx, vis[i] ? S[cb][i >> 2][i & 3] : ATT_NEG);
-    }
+    for (int i = 0; i < 8; i++) vis[i] = !MASKED || (pg + (i >> 2)) * RL_PAGE + 4 * g + (i & 3) <= mypos[cb];
     // m (in scaled units: score * scale2, scale2 > 0) is the reference point of the exponents, not
-    // necessarily the running maximum: it only moves, to the column's maximum so far, when some
-    // score of the wave lies more than kLazy above it.  Every term then stays below 2^kLazy, the
-    // ratio acc / l does not depend on m, and the common case needs neither the reduction over
-    // the column's four lanes nor a rescaling of the accumulators.
-    constexpr float kLazy = 8.0f;
-    if (__any(mx * scale2 > m[cb] + kLazy)) {
+    // necessarily the running maximum: it only moves, to the column's maximum so far, when some term of
+    // the wave exceeds it by about 2^kLazy.  The ratio acc / l does not depend on m, and the common
+    // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
+    // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
+    constexpr float kLazy = 256.0f;
+    float p[8];
+    auto terms = [&]() {
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[cb][i >> 2][i & 3], scale2, -m[cb]));
+        if (MASKED) p[i] = vis[i] ? p[i] : 0.f;
+      }
+      return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    };
+    float ps = terms();
+    if (__any(ps > kLazy)) {
+      float mx = ATT_NEG;
+#pragma unroll
+      for (int i = 0; i < 8; i++) mx = fmaxf(mx, vis[i] ? S[cb][i >> 2][i & 3] : ATT_NEG);
       mx = quad_max(mx);
       const float mn = fmaxf(m[cb], mx * scale2);
       const float alpha = exp2f(m[cb] - mn);
@@ -1188,15 +1197,9 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
 #pragma unroll
         for (int i = 0; i < 4; i++) acc[cb][j][i] *= alpha;
       m[cb] = mn;
+      ps = terms();
     }
-    const float mn = m[cb];
-    float p[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-      p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[cb][i >> 2][i & 3], scale2, -mn));
-      if (MASKED) p[i] = vis[i] ? p[i] : 0.f;
-    }
-    l[cb] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    l[cb] += ps;
     P[cb] = (bf16x8){(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3],
                      (__bf16)p[4], (__bf16)p[5], (__bf16)p[6], (__bf16)p[7]};
   }
@@ -1218,17 +1221,11 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
         acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
     }
   } else {
-    // the lane's 4 tokens of 16 output dims are 8 bytes in each page's block: two 8-byte reads
-    // make the 32-key operand without any register shuffling
-    uint2 v0[8], v1[8];
+    // the staging has put the lane's 4 tokens of a dim in the first page and in the second side by side:
+    // one 16-byte read is the 32-key operand
 #pragma unroll
     for (int jb = 0; jb < 8; jb++) {
-      v0[jb] = *(const uint2*)(vb + (jb >> 1) * 1024 + lane * 16 + (jb & 1) * 8);
-      v1[jb] = *(const uint2*)(vb + BLK + (jb >> 1) * 1024 + lane * 16 + (jb & 1) * 8);
-    }
-#pragma unroll
-    for (int jb = 0; jb < 8; jb++) {
-      const bf16x8 vo = __builtin_bit_cast(bf16x8, ((u32x4){v0[jb].x, v0[jb].y, v1[jb].x, v1[jb].y}));
+      const bf16x8 vo = __builtin_bit_cast(bf16x8, *(const u32x4*)(vb + jb * 1024 + lane * 16));
 #pragma unroll
       for (int cb = 0; cb < CB; cb++)
         acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
@@ -1240,7 +1237,9 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
 // 4 * CB * 16/G rows, kv head) as above, but a page's keys / values are fetched once per
 // workgroup (not once per wave) into a double-buffered LDS stage of NP pages, in the pool's
 // operand order, and the four waves read their operands from there (linear 16-byte reads, no bank
-// conflicts).  Pages are consumed in pairs (prefill_pair).  One barrier per stage: the loads of
+// conflicts), the bf16 values of a pair of pages interleaved so that a 32-key operand is one read (a
+// quarter of the vector instructions had been moves that put the operands together).  Pages are consumed
+// in pairs (prefill_pair).  One barrier per stage: the loads of
 // stage s + 1 are issued before the barrier of stage s and written to the other buffer after the
 // stage's arithmetic, which every wave can only reach once all waves have left stage s - 1.
 // Page indices past the item's last page are clamped to it (their keys are masked: they lie
@@ -1311,7 +1310,17 @@ void attention_prefill_lds_kernel(
   };
   auto stash = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < U; u++) *(u32x4*)(s_kv + b * STAGE + u * 4096 + tid * 16) = stg[u];
+    for (int u = 0; u < U; u++) {
+      char* dst = s_kv + b * STAGE + u * 4096 + tid * 16;
+      if (FP8 || u < NP) {
+        *(u32x4*)dst = stg[u];
+      } else {      // bf16 values, page u - NP: the slot's two operands go beside the other page's of the pair
+        const int p = u - NP;
+        char* v = s_kv + b * STAGE + (NP + (p & ~1)) * BLK + (tid >> 6) * 2048 + (tid & 63) * 16 + (p & 1) * 8;
+        *(uint2*)v = make_uint2(stg[u][0], stg[u][1]);
+        *(uint2*)(v + 1024) = make_uint2(stg[u][2], stg[u][3]);
+      }
+    }
   };
   if (nst > 0) {
     fetch(0);
