@@ -1145,16 +1145,19 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
                                              int g, int lane, float scale2) {
   constexpr int BLK = FP8 ? 2048 : 4096, NLD = BLK / 1024;
   f32x4 S[CB][2];
+  u32x4 raw[2][NLD];
 #pragma unroll
-  for (int pp = 0; pp < 2; pp++) {
-    u32x4 raw[NLD];
+  for (int c = 0; c < NLD; c++)
 #pragma unroll
-    for (int c = 0; c < NLD; c++) raw[c] = *(const u32x4*)(kb + pp * BLK + c * 1024 + lane * 16);
+    for (int pp = 0; pp < 2; pp++) raw[pp][c] = *(const u32x4*)(kb + pp * BLK + c * 1024 + lane * 16);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int cb = 0; cb < CB; cb++) S[cb][pp] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int cb = 0; cb < CB; cb++) S[cb][0] = S[cb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      const u32x4 kr = att_operand<FP8>(raw, c);
+  for (int c = 0; c < 4; c++) {
+#pragma unroll
+    for (int pp = 0; pp < 2; pp++) {
+      const u32x4 kr = att_operand<FP8>(raw[pp], c);
 #pragma unroll
       for (int cb = 0; cb < CB; cb++)
         S[cb][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr),
@@ -1162,6 +1165,12 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
                                                             S[cb][pp], 0, 0, 0);
     }
   }
+  // the values' reads travel while the softmax is computed
+  u32x4 vr[FP8 ? 2 * NLD : 8];
+#pragma unroll
+  for (int i = 0; i < (FP8 ? 2 * NLD : 8); i++)
+    vr[i] = *(const u32x4*)(vb + (FP8 ? (i & 1) * BLK + (i >> 1) * 1024 : i * 1024) + lane * 16);
+  __builtin_amdgcn_sched_barrier(0);
   bf16x8 P[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; cb++) {
@@ -1203,33 +1212,22 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
     P[cb] = (bf16x8){(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3],
                      (__bf16)p[4], (__bf16)p[5], (__bf16)p[6], (__bf16)p[7]};
   }
-  if constexpr (FP8) {
-    u32x4 raw0[NLD], raw1[NLD];
 #pragma unroll
-    for (int c = 0; c < NLD; c++) {
-      raw0[c] = *(const u32x4*)(vb + c * 1024 + lane * 16);
-      raw1[c] = *(const u32x4*)(vb + BLK + c * 1024 + lane * 16);
-    }
-#pragma unroll
-    for (int jb = 0; jb < 8; jb++) {
+  for (int jb = 0; jb < 8; jb++) {
+    bf16x8 vo;
+    if constexpr (FP8) {
       uint32_t a0, b0, a1, b1;
-      e4m3x4_to_bf16(raw0[jb >> 2][jb & 3], &a0, &b0);
-      e4m3x4_to_bf16(raw1[jb >> 2][jb & 3], &a1, &b1);
-      const bf16x8 vo = __builtin_bit_cast(bf16x8, ((u32x4){a0, b0, a1, b1}));
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++)
-        acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
+      e4m3x4_to_bf16(vr[2 * (jb >> 2)][jb & 3], &a0, &b0);
+      e4m3x4_to_bf16(vr[2 * (jb >> 2) + 1][jb & 3], &a1, &b1);
+      vo = __builtin_bit_cast(bf16x8, ((u32x4){a0, b0, a1, b1}));
+    } else {
+      // the staging has put the lane's 4 tokens of a dim in the first page and in the second side by
+      // side: one 16-byte read is the 32-key operand
+      vo = __builtin_bit_cast(bf16x8, vr[jb]);
     }
-  } else {
-    // the staging has put the lane's 4 tokens of a dim in the first page and in the second side by side:
-    // one 16-byte read is the 32-key operand
 #pragma unroll
-    for (int jb = 0; jb < 8; jb++) {
-      const bf16x8 vo = __builtin_bit_cast(bf16x8, *(const u32x4*)(vb + jb * 1024 + lane * 16));
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++)
-        acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
-    }
+    for (int cb = 0; cb < CB; cb++)
+      acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
   }
 }
 
