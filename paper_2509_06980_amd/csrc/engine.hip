@@ -43,6 +43,7 @@ struct Traj {
   std::vector<float> logp;
   std::vector<int32_t> pages;
   int shared_lead = 0;  // leading pages that were shared with another trajectory by a fork
+  uint64_t seen = 0;    // last call that listed it (duplicate check)
 };
 
 struct LayerW {
@@ -81,14 +82,21 @@ struct rl_model {
   void *xa = nullptr, *xo = nullptr, *xm = nullptr, *qb = nullptr;
   int32_t *d_meta = nullptr, *h_meta = nullptr;  // device / pinned staging for per-call integers
   size_t meta_ints = 0;
+  // page-table entries (slot, index, page) taken by the running call and not yet on the device: they
+  // travel with the metadata of the call's first pass (upload_meta), or by themselves at its end
+  std::vector<int32_t> page_upd;
+  char** d_pools = nullptr;      // [2][n_layers]: every layer's key pool, then every layer's value pool
+  uint64_t calls = 0;
   SamplerScratch ss{};
-  int32_t *d_ids = nullptr, *h_ids = nullptr;
+  int32_t* h_ids = nullptr;
   // several decode steps in one call: per-step ids / log-probs on the device and pinned, and one
   // event per staging region (the host runs that many steps ahead of the GPU)
   int32_t *d_ids_hist = nullptr, *h_ids_hist = nullptr;
   float *d_lp_hist = nullptr, *h_lp_hist = nullptr;
   std::vector<hipEvent_t> ev_region;
   float *d_lp = nullptr, *h_lp = nullptr;
+  int32_t* hd_ids = nullptr;   // device addresses of h_ids and h_lp
+  float* hd_lp = nullptr;
   float* d_stripmax = nullptr;   // [Rl, V / 32] maxima of 32-logit strips from the lm-head epilogue
   float *d_zt = nullptr, *d_lp_rows = nullptr, *h_lp_rows = nullptr;   // masked log-prob pass: Mcap rows
   uint8_t* d_mask = nullptr;
@@ -311,6 +319,7 @@ struct DevMeta {
 };
 
 int check_pass(rl_model* m, const Staging& st, int slots_used);
+int flush_page_updates(rl_model* m);
 
 // at: offset (in ints) of the region of the staging buffers this pass uses (0 unless several
 // passes are staged ahead of the GPU)
@@ -324,6 +333,13 @@ int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
   }
   static_assert(sizeof(AttnItem) == 32 && sizeof(AttnMerge) == 32, "metadata records are 8 ints");
   size_t need = 6 * M + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size();
+  const size_t n_upd = m->page_upd.size();
+  if (n_upd > 0 && (at > 0 || need + n_upd > m->meta_ints)) {
+    int frc = flush_page_updates(m);
+    if (frc) return frc;
+  }
+  const size_t upd_at = need;
+  need += m->page_upd.size();
   if (at + need > m->meta_ints) return fail(RL_E_ARG, "internal: metadata staging too small");
   int32_t* h = m->h_meta + at;
   int32_t* d = m->d_meta + at;
@@ -336,7 +352,12 @@ int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
   if (!st.merges.empty())
     memcpy(h + 6 * M + 8 * st.items.size(), st.merges.data(), st.merges.size() * sizeof(AttnMerge));
   put(st.rowlist, 6 * M + 8 * st.items.size() + 8 * st.merges.size());
+  put(m->page_upd, upd_at);
   HIPCHECK(hipMemcpyAsync(d, h, need * 4, hipMemcpyHostToDevice, m->stream));
+  if (!m->page_upd.empty()) {
+    launch_page_table_update(m->stream, m->page_table, d + upd_at, (int)(m->page_upd.size() / 3), m->md.max_pages_per_traj);
+    m->page_upd.clear();
+  }
   dm->tok = d; dm->pos = d + M; dm->slot = d + 2 * M;
   dm->traj = d + 3 * M; dm->newpos = d + 4 * M; dm->forced = d + 5 * M;
   dm->items = (AttnItem*)(d + 6 * M);
@@ -347,18 +368,19 @@ int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
   return RL_OK;
 }
 
-// page-table updates (slot, index, page) -> device, in batches through the staging buffer
-int push_page_updates(rl_model* m, const std::vector<int32_t>& upd) {
-  size_t n = upd.size() / 3, done = 0;
+// the page-table entries that no pass has taken along -> device, in batches through the staging buffer
+int flush_page_updates(rl_model* m) {
+  size_t n = m->page_upd.size() / 3, done = 0;
   size_t cap = m->meta_ints / 3;
   while (done < n) {
     size_t k = std::min(cap, n - done);
-    memcpy(m->h_meta, upd.data() + 3 * done, k * 12);
+    memcpy(m->h_meta, m->page_upd.data() + 3 * done, k * 12);
     HIPCHECK(hipMemcpyAsync(m->d_meta, m->h_meta, k * 12, hipMemcpyHostToDevice, m->stream));
     launch_page_table_update(m->stream, m->page_table, m->d_meta, (int)k, m->md.max_pages_per_traj);
     HIPCHECK(hipStreamSynchronize(m->stream));
     done += k;
   }
+  m->page_upd.clear();
   return RL_OK;
 }
 
@@ -383,6 +405,24 @@ int check_ids(const int32_t* ids, int32_t n) {
     if (ids[i] < 0) return fail(RL_E_ARG, "negative trajectory id");
   for (int i = 0; i < n; i++)
     if (!seen.insert(ids[i]).second) return fail(RL_E_DUP_ID, "duplicate trajectory id");
+  return RL_OK;
+}
+
+// The listed trajectories, each looked up once.  Unknown or repeated ids take the full check, which
+// decides the error code.
+int find_trajs(rl_model* m, const int32_t* ids, int32_t n, std::vector<Traj*>* out) {
+  if (n < 0 || (n > 0 && !ids)) return fail(RL_E_ARG, "null ids or negative count");
+  const uint64_t call = ++m->calls;
+  out->resize(n);
+  for (int i = 0; i < n; i++) {
+    auto it = ids[i] < 0 ? m->traj.end() : m->traj.find(ids[i]);
+    if (it == m->traj.end() || it->second.seen == call) {
+      int rc = check_ids(ids, n);
+      return rc ? rc : RL_E_BAD_TRAJ;
+    }
+    it->second.seen = call;
+    (*out)[i] = &it->second;
+  }
   return RL_OK;
 }
 
@@ -587,17 +627,12 @@ int prefill(rl_model* m, const std::vector<std::pair<Traj*, int>>& work) {
 int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, uint64_t seed,
                 const int32_t* forced, int32_t* ids_out, float* lp_out,
                 const std::vector<std::pair<Traj*, int>>* extra, bool* extra_done) {
-  int rc = check_ids(ids, n);
-  if (rc) return rc;
+  std::vector<Traj*> ts;
+  int rc = find_trajs(m, ids, n, &ts);
+  if (rc && rc != RL_E_BAD_TRAJ) return rc;
   if (!(temperature >= 0.0f)) return fail(RL_E_ARG, "negative temperature");
   if (n > 0 && !lp_out) return fail(RL_E_ARG, "null output");
-  if (n > m->rt.max_trajectories) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
-  std::vector<Traj*> ts(n);
-  for (int i = 0; i < n; i++) {
-    auto it = m->traj.find(ids[i]);
-    if (it == m->traj.end()) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
-    ts[i] = &it->second;
-  }
+  if (n > m->rt.max_trajectories || rc) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
   for (Traj* t : ts)
     if (t->tokens.empty()) return fail(RL_E_EMPTY, "trajectory has no context");
   if (forced)
@@ -622,14 +657,12 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
     extra_rows = 0;
   }
   // commit page reservations (call order), then compute
-  std::vector<int32_t> upd;
   for (Traj* t : ts)
     if (t->tokens.size() % RL_PAGE == 0) {
       int p = take_page(m);
-      upd.insert(upd.end(), {t->slot, (int32_t)t->pages.size(), p});
+      m->page_upd.insert(m->page_upd.end(), {t->slot, (int32_t)t->pages.size(), p});
       t->pages.push_back(p);
     }
-  if (!upd.empty()) { rc = push_page_updates(m, upd); if (rc) return rc; }
   Staging st;
   int max_pos = 0;
   double kvb = 0.0;
@@ -687,12 +720,10 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
   lm_head_rows(m, M, 0, n, false, n, stripmax);
   float c = (float)(1.4426950408889634 / (greedy ? 1.0 : (double)temperature));
   launch_sampler(m->stream, m->logits, (size_t)m->md.V, n, m->md.V, c, greedy ? 1 : 0, nullptr, seed,
-                 dm.traj, dm.newpos, forced ? dm.forced : nullptr, nullptr, m->ss, m->d_ids, m->d_lp,
-                 stripmax, m->md.V / 32);
+                 dm.traj, dm.newpos, forced ? dm.forced : nullptr, nullptr, m->ss, m->hd_ids, m->hd_lp,
+                 stripmax, m->md.V / 32);       // ids and log-probs go straight to the pinned host buffers
   HIPCHECK(hipGetLastError());
   if (timed) (void)hipEventRecord(m->ev_step[1], m->stream);
-  HIPCHECK(hipMemcpyAsync(m->h_ids, m->d_ids, n * 4, hipMemcpyDeviceToHost, m->stream));
-  HIPCHECK(hipMemcpyAsync(m->h_lp, m->d_lp, n * 4, hipMemcpyDeviceToHost, m->stream));
   if (m->timing_every > 0 && extra_rows == 0) {
     // byte accounting of pure decode steps, done while the GPU works: keys + values per trajectory,
     // and of the distinct pages (pages shared by forked trajectories count once)
@@ -751,18 +782,13 @@ const int kMaxStepsPerChunk = 1024;
 
 int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, float temperature,
                  uint64_t seed, int32_t* ids_out, float* lp_out) {
-  int rc = check_ids(ids, n);
-  if (rc) return rc;
+  std::vector<Traj*> ts;
+  int rc = find_trajs(m, ids, n, &ts);
+  if (rc && rc != RL_E_BAD_TRAJ) return rc;
   if (n_steps < 0) return fail(RL_E_ARG, "negative step count");
   if (!(temperature >= 0.0f)) return fail(RL_E_ARG, "negative temperature");
   if (n > 0 && n_steps > 0 && (!ids_out || !lp_out)) return fail(RL_E_ARG, "null output");
-  if (n > m->rt.max_trajectories) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
-  std::vector<Traj*> ts(n);
-  for (int i = 0; i < n; i++) {
-    auto it = m->traj.find(ids[i]);
-    if (it == m->traj.end()) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
-    ts[i] = &it->second;
-  }
+  if (n > m->rt.max_trajectories || rc) return fail(RL_E_BAD_TRAJ, "unknown trajectory id");
   for (Traj* t : ts)
     if (t->tokens.empty()) return fail(RL_E_EMPTY, "trajectory has no context");
   int64_t need = 0;
@@ -774,7 +800,6 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
   if (need > m->n_free) return fail(RL_E_NOPAGES, "page pool exhausted");
   if (n == 0 || n_steps == 0) return RL_OK;
   {
-    std::vector<int32_t> upd;
     std::vector<size_t> len0(n);
     for (int i = 0; i < n; i++) len0[i] = ts[i]->tokens.size();
     for (int sidx = 0; sidx < n_steps; sidx++)
@@ -782,10 +807,11 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
         if ((len0[i] + sidx) % RL_PAGE == 0) {
           Traj* t = ts[i];
           int p = take_page(m);
-          upd.insert(upd.end(), {t->slot, (int32_t)t->pages.size(), p});
+          m->page_upd.insert(m->page_upd.end(), {t->slot, (int32_t)t->pages.size(), p});
           t->pages.push_back(p);
         }
-    if (!upd.empty()) { rc = push_page_updates(m, upd); if (rc) return rc; }
+    rc = flush_page_updates(m);     // on their own: the passes below are staged in regions of fixed size
+    if (rc) return rc;
   }
   // one staging region per step; the host may run as many steps ahead as there are regions
   const size_t region_ints = 7 * (size_t)n + 8 * (size_t)(2 * n + m->attn_slots + 8);
@@ -905,6 +931,11 @@ int decode_common(rl_model* m, const int32_t* ids, int32_t n, float temperature,
     std::string msg = g_err;
     int prc = prefill(m, *extra);
     if (rc == RL_OK) rc = prc; else g_err = msg;
+  }
+  if (!m->page_upd.empty()) {
+    std::string msg = g_err;
+    int urc = flush_page_updates(m);
+    if (rc == RL_OK) rc = urc; else g_err = msg;
   }
   return rc;
 }
@@ -1087,7 +1118,6 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   TRY(m->dalloc((void**)&m->d_lp_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_ids_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_lp_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
-  TRY(m->dalloc((void**)&m->d_ids, (size_t)m->Rl * 4));
   TRY(m->dalloc((void**)&m->d_lp, (size_t)m->Rl * 4));
   TRY(m->dalloc((void**)&m->d_mask, Mc));
   TRY(m->dalloc((void**)&m->d_zt, Mc * 4));
@@ -1106,6 +1136,15 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   HIPTRY(hipHostMalloc((void**)&m->h_ids, (size_t)m->Rl * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_lp, (size_t)m->Rl * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_lp_rows, Mc * 4));
+  HIPTRY(hipHostGetDevicePointer((void**)&m->hd_ids, m->h_ids, 0));
+  HIPTRY(hipHostGetDevicePointer((void**)&m->hd_lp, m->h_lp, 0));
+  {
+    std::vector<char*> base;
+    for (int l = 0; l < c.n_layers; l++) base.push_back((char*)m->pools[l].k);
+    for (int l = 0; l < c.n_layers; l++) base.push_back((char*)m->pools[l].v);
+    TRY(m->dalloc((void**)&m->d_pools, base.size() * sizeof(char*)));
+    HIPTRY(hipMemcpy(m->d_pools, base.data(), base.size() * sizeof(char*), hipMemcpyHostToDevice));
+  }
   m->ev.resize(2 * c.n_layers);
   for (auto& e : m->ev) HIPTRY(hipEventCreate(&e));
   HIPTRY(hipEventCreate(&m->ev_step[0]));
@@ -1170,7 +1209,6 @@ static int append_host(rl_model* m, const int32_t* traj_ids, int32_t n, const in
     return fail(RL_E_TOO_MANY, "too many trajectories");
   if (need > m->n_free) return fail(RL_E_NOPAGES, "page pool exhausted");
   // commit
-  std::vector<int32_t> upd;
   std::vector<std::pair<Traj*, int>> work;
   int64_t off = 0;
   for (int i = 0; i < n; i++) {
@@ -1182,7 +1220,7 @@ static int append_host(rl_model* m, const int32_t* traj_ids, int32_t n, const in
     size_t after = t.tokens.size() + lens[i];
     while (t.pages.size() * RL_PAGE < after) {
       int p = take_page(m);
-      upd.insert(upd.end(), {t.slot, (int32_t)t.pages.size(), p});
+      m->page_upd.insert(m->page_upd.end(), {t.slot, (int32_t)t.pages.size(), p});
       t.pages.push_back(p);
     }
     t.tokens.insert(t.tokens.end(), tokens + off, tokens + off + lens[i]);
@@ -1194,7 +1232,6 @@ static int append_host(rl_model* m, const int32_t* traj_ids, int32_t n, const in
     Traj& t = m->traj[traj_ids[i]];
     if (!t.tokens.empty()) work.push_back({&t, (int)t.tokens.size() - 1});
   }
-  if (!upd.empty()) { rc = push_page_updates(m, upd); if (rc) return rc; }
   *work_out = std::move(work);
   return RL_OK;
 }
@@ -1204,7 +1241,9 @@ extern "C" int rl_append_observation(rl_model* m, const int32_t* traj_ids, int32
   std::vector<std::pair<Traj*, int>> work;
   int rc = append_host(m, traj_ids, n, tokens, lens, &work);
   if (rc) return rc;
-  return prefill(m, work);
+  rc = prefill(m, work);
+  const int urc = flush_page_updates(m);      // nothing left unless no token needed a pass
+  return rc ? rc : urc;
 }
 
 extern "C" int rl_decode_step_with_appends(rl_model* m, const int32_t* app_ids, int32_t n_app,
@@ -1281,7 +1320,8 @@ extern "C" int rl_fork(rl_model* m, int32_t src, const int32_t* dst_ids, int32_t
   int n_own = (int)sit->second.pages.size() - n_shared;
   if ((int64_t)m->traj.size() + n > m->rt.max_trajectories) return fail(RL_E_TOO_MANY, "too many trajectories");
   if ((int64_t)n_own * n > m->n_free) return fail(RL_E_NOPAGES, "page pool exhausted");
-  std::vector<int32_t> upd, pairs;
+  std::vector<int32_t>& upd = m->page_upd;
+  std::vector<int32_t> pairs;
   m->traj.reserve(m->traj.size() + n);
   for (int i = 0; i < n; i++) {
     Traj t = m->traj.find(src)->second;   // copy of tokens / mask / logp / n_cached
@@ -1302,16 +1342,25 @@ extern "C" int rl_fork(rl_model* m, int32_t src, const int32_t* dst_ids, int32_t
     Traj& st = m->traj.find(src)->second;
     st.shared_lead = std::max(st.shared_lead, n_shared);
   }
-  if (!upd.empty()) { rc = push_page_updates(m, upd); if (rc) return rc; }
-  size_t np = pairs.size() / 2, done = 0, cap = m->meta_ints / 2;
-  while (done < np) {
-    size_t k = std::min(cap, np - done);
-    memcpy(m->h_meta, pairs.data() + 2 * done, k * 8);
-    HIPCHECK(hipMemcpyAsync(m->d_meta, m->h_meta, k * 8, hipMemcpyHostToDevice, m->stream));
-    for (int l = 0; l < m->md.L; l++) launch_copy_pages(m->stream, m->pools[l], m->d_meta, (int)k, m->page_bytes);
+  // page-table entries and page copies travel in one transfer, all layers' copies in one launch
+  size_t nu = upd.size() / 3, np = pairs.size() / 2;
+  if (3 * nu + 2 * np > m->meta_ints) {
+    rc = flush_page_updates(m);
+    if (rc) return rc;
+    nu = 0;
+  }
+  for (size_t done = 0; nu > 0 || done < np;) {
+    const size_t k = std::min((m->meta_ints - 3 * nu) / 2, np - done);
+    if (nu) memcpy(m->h_meta, upd.data(), nu * 12);
+    if (k) memcpy(m->h_meta + 3 * nu, pairs.data() + 2 * done, k * 8);
+    HIPCHECK(hipMemcpyAsync(m->d_meta, m->h_meta, nu * 12 + k * 8, hipMemcpyHostToDevice, m->stream));
+    launch_page_table_update(m->stream, m->page_table, m->d_meta, (int)nu, m->md.max_pages_per_traj);
+    launch_copy_pages(m->stream, m->d_pools, m->md.L, m->d_meta + 3 * nu, (int)k, m->page_bytes);
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipStreamSynchronize(m->stream));
     done += k;
+    nu = 0;
+    upd.clear();
   }
   return RL_OK;
 }

@@ -183,8 +183,9 @@ void launch_grpo_terms(hipStream_t s, const float* lp, const float* old_lp, cons
                        double clip_eps, double beta, double* acc);
 void launch_grpo_finish(hipStream_t s, const double* acc, int n, double* out);
 
-// copy one page (all kv heads) within a layer pool: dst page <- src page; n pairs
-void launch_copy_pages(hipStream_t s, KvPool pool, const int32_t* src_dst_pairs, int n_pairs,
+// copy one page (all kv heads) within every layer's key and value pool (pools: 2 n_layers base
+// addresses): dst page <- src page; n pairs
+void launch_copy_pages(hipStream_t s, char* const* pools, int n_layers, const int32_t* src_dst_pairs, int n_pairs,
                        size_t page_bytes);
 // page_table[upd[3i] * stride + upd[3i+1]] = upd[3i+2]
 void launch_page_table_update(hipStream_t s, int32_t* page_table, const int32_t* upd, int n,

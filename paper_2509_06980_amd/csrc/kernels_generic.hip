@@ -427,11 +427,11 @@ __global__ void swiglu_kernel(const float* __restrict__ gu, TA* __restrict__ m, 
   else stf(m + (size_t)row * I + j, y);
 }
 
-__global__ void copy_pages_kernel(char* __restrict__ k, char* __restrict__ v,
-                                  const int32_t* __restrict__ pairs, size_t page_bytes) {
+// grid (pairs, 2 n_layers): one page of one pool
+__global__ void copy_pages_kernel(char* const* __restrict__ pools, const int32_t* __restrict__ pairs, size_t page_bytes) {
   int p = blockIdx.x;
   size_t src = (size_t)pairs[2 * p] * page_bytes, dst = (size_t)pairs[2 * p + 1] * page_bytes;
-  char* base = blockIdx.y ? v : k;
+  char* base = pools[blockIdx.y];
   const uint4* s4 = (const uint4*)(base + src);
   uint4* d4 = (uint4*)(base + dst);
   for (size_t i = threadIdx.x; i < page_bytes / 16; i += blockDim.x) d4[i] = s4[i];
@@ -645,10 +645,10 @@ void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool ati
 template void launch_swiglu<float>(hipStream_t, const float*, float*, int, int, bool);
 template void launch_swiglu<bf16_t>(hipStream_t, const float*, bf16_t*, int, int, bool);
 
-void launch_copy_pages(hipStream_t s, KvPool pool, const int32_t* pairs, int n_pairs,
+void launch_copy_pages(hipStream_t s, char* const* pools, int n_layers, const int32_t* pairs, int n_pairs,
                        size_t page_bytes) {
   if (n_pairs <= 0) return;
-  copy_pages_kernel<<<dim3(n_pairs, 2), 256, 0, s>>>((char*)pool.k, (char*)pool.v, pairs, page_bytes);
+  copy_pages_kernel<<<dim3(n_pairs, 2 * n_layers), 256, 0, s>>>(pools, pairs, page_bytes);
 }
 void launch_page_table_update(hipStream_t s, int32_t* page_table, const int32_t* upd, int n,
                               int stride) {
