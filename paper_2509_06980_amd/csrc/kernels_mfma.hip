@@ -311,80 +311,126 @@ __device__ __forceinline__ void xcd_tile256(int id, int tiles_m, int tiles_n, in
   *tn = within / gm;
 }
 
-// QK-norm, RoPE and the writes of one head (EPI_QKV) for batch row `row`: val(b, i) is dim
-// 32 b + (i / 4) * 8 + (lane / 32) * 4 + i % 4 of the head.  The same arithmetic as qkrope128_kernel;
-// only the order of the sum of squares differs.
+// QK-norm, RoPE and the writes of one head (EPI_QKV) for a wave's four blocks of 32 batch rows:
+// val(a, b, i) is dim 32 b + (i / 4) * 8 + (lane / 32) * 4 + i % 4 of the head for row row0 + 32 a + lane % 32.
+// The same arithmetic as qkrope128_kernel; only the order of the sum of squares differs.  With one wave
+// per SIMD nothing else hides a memory round trip: positions, pages and gains are read once, and the
+// RoPE table pieces of half a row block are requested before the half ahead of it is computed.
 template <bool FP8, typename F>
-__device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row, int M, int hd, int lane) {
+__device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row0, int M, int hd, int lane) {
   const int h4 = (lane >> 5) * 4;
-  float ss = 0.f;
-#pragma unroll
-  for (int b = 0; b < 4; b++)
-#pragma unroll
-    for (int i = 0; i < 16; i++) ss += val(b, i) * val(b, i);
-  ss += __shfl_xor(ss, 32, 64);
-  if (row >= M) return;
-  const int pos = q.row_pos[row], tok = pos & (RL_PAGE - 1);
   const bool is_q = hd < q.nq, is_v = hd >= q.nq + q.nkv;
-  size_t blk = 0;
-  if (!is_q) {
-    const int page = q.page_table[(size_t)q.row_slot[row] * q.pt_stride + (pos >> 4)];
-    blk = ((size_t)page * q.nkv + (is_v ? hd - q.nq - q.nkv : hd - q.nq)) * (RL_PAGE * 128);
+  int pos[4];
+  size_t blk[4];
+#pragma unroll
+  for (int a = 0; a < 4; a++) pos[a] = q.row_pos[min(row0 + 32 * a + (lane & 31), M - 1)];
+#pragma unroll
+  for (int a = 0; a < 4; a++) {
+    blk[a] = 0;
+    if (!is_q) {
+      const int slot = q.row_slot[min(row0 + 32 * a + (lane & 31), M - 1)];
+      const int page = q.page_table[(size_t)slot * q.pt_stride + (pos[a] >> 4)];
+      blk[a] = ((size_t)page * q.nkv + (is_v ? hd - q.nq - q.nkv : hd - q.nq)) * (RL_PAGE * 128);
+    }
   }
   if (is_v) {
 #pragma unroll
-    for (int b = 0; b < 4; b++)
+    for (int a = 0; a < 4; a++) {
+      if (row0 + 32 * a + (lane & 31) >= M) continue;
+      const int tok = pos[a] & (RL_PAGE - 1);
 #pragma unroll
-      for (int i = 0; i < 16; i++) {
-        const int d = 32 * b + (i >> 2) * 8 + h4 + (i & 3);
-        if (FP8) ((uint8_t*)q.vpool)[blk + vswz8_off(tok, d)] = f2e4m3(val(b, i));
-        else ((bf16_t*)q.vpool)[blk + vswz_off(tok, d)] = f2bf(val(b, i));
-      }
+      for (int b = 0; b < 4; b++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          const int d = 32 * b + (i >> 2) * 8 + h4 + (i & 3);
+          if (FP8) ((uint8_t*)q.vpool)[blk[a] + vswz8_off(tok, d)] = f2e4m3(val(a, b, i));
+          else ((bf16_t*)q.vpool)[blk[a] + vswz_off(tok, d)] = f2bf(val(a, b, i));
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     return;
   }
   const bf16_t* g = is_q ? q.gq : q.gk;
-  const float inv = q.qk_norm ? 1.0f / sqrtf(ss / 128.0f + q.eps) : 1.0f;
+  uint2 gl[8], gh[8];      // gains of dims 32 b + 8 c + h4 .. + 3 and of their partners, piece x = 4 b + c
 #pragma unroll
-  for (int b = 0; b < 2; b++)
+  for (int x = 0; x < 8; x++) {
+    const int d = 32 * (x >> 2) + (x & 3) * 8 + h4;
+    gl[x] = gh[x] = make_uint2(0u, 0u);
+    if (q.qk_norm) {
+      gl[x] = *(const uint2*)(g + d);
+      gh[x] = *(const uint2*)(g + d + 64);
+    }
+  }
+  float4 cs[2][8];         // (cos, sin) of four pieces: half a row block, y = 2 a + b
+  auto fetch = [&](int y) {
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-      const int d = 32 * b + c * 8 + h4;                 // dims d .. d + 3 and their partners d + 64 ..
-      const float4 cs0 = *(const float4*)(q.rope_cs + ((size_t)pos * 64 + d) * 2);
-      const float4 cs1 = *(const float4*)(q.rope_cs + ((size_t)pos * 64 + d) * 2 + 4);
-      const float co[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sn[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
-      float gl[4] = {1.f, 1.f, 1.f, 1.f}, gh[4] = {1.f, 1.f, 1.f, 1.f};
-      if (q.qk_norm) {
-        ld4(g + d, gl[0], gl[1], gl[2], gl[3]);
-        ld4(g + d + 64, gh[0], gh[1], gh[2], gh[3]);
-      }
-      float y1[4], y2[4];
+      const float* t = q.rope_cs + ((size_t)pos[y >> 1] * 64 + 32 * (y & 1) + c * 8 + h4) * 2;
+      cs[y & 1][2 * c] = *(const float4*)t;
+      cs[y & 1][2 * c + 1] = *(const float4*)(t + 4);
+    }
+  };
+  fetch(0);
+  float inv = 1.0f;
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
-        float x1 = val(b, 4 * c + e), x2 = val(b + 2, 4 * c + e);
-        if (q.qk_norm) { x1 = x1 * inv * gl[e]; x2 = x2 * inv * gh[e]; }
-        y1[e] = x1 * co[e] - x2 * sn[e];
-        y2[e] = x2 * co[e] + x1 * sn[e];
-      }
-      if (FP8 && !is_q) {
-        uint8_t* k8 = (uint8_t*)q.kpool + blk;
-        *(uint32_t*)(k8 + kswz8_off(tok, d)) = f2e4m3x4(y1[0], y1[1], y1[2], y1[3]);
-        *(uint32_t*)(k8 + kswz8_off(tok, d + 64)) = f2e4m3x4(y2[0], y2[1], y2[2], y2[3]);
-        continue;
-      }
-      const uint2 w1 = make_uint2((uint32_t)f2bf(y1[0]) | ((uint32_t)f2bf(y1[1]) << 16),
-                                  (uint32_t)f2bf(y1[2]) | ((uint32_t)f2bf(y1[3]) << 16));
-      const uint2 w2 = make_uint2((uint32_t)f2bf(y2[0]) | ((uint32_t)f2bf(y2[1]) << 16),
-                                  (uint32_t)f2bf(y2[2]) | ((uint32_t)f2bf(y2[3]) << 16));
-      if (is_q) {
-        bf16_t* dst = q.qout + ((size_t)row * q.nq + hd) * 128 + d;
-        *(uint2*)dst = w1;
-        *(uint2*)(dst + 64) = w2;
-      } else {
-        bf16_t* kb = (bf16_t*)q.kpool + blk;
-        *(uint2*)(kb + kswz_off(tok, d)) = w1;
-        *(uint2*)(kb + kswz_off(tok, d + 64)) = w2;
+  for (int y = 0; y < 8; y++) {
+    const int a = y >> 1, b = y & 1;
+    if (y < 7) fetch(y + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (b == 0) {
+      float ss = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; v++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          const float x = val(a, v, i);
+          ss += x * x;
+        }
+      ss += __shfl_xor(ss, 32, 64);
+      inv = 1.0f / sqrtf(ss / 128.0f + q.eps);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int row = row0 + 32 * a + (lane & 31), tok = pos[a] & (RL_PAGE - 1);
+    if (row < M) {
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        const int x = 4 * b + c, d = 32 * b + c * 8 + h4;
+        const float4 c0 = cs[y & 1][2 * c], c1 = cs[y & 1][2 * c + 1];
+        const float co[4] = {c0.x, c0.z, c1.x, c1.z}, sn[4] = {c0.y, c0.w, c1.y, c1.w};
+        float y1[4], y2[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          float x1 = val(a, b, 4 * c + e), x2 = val(a, b + 2, 4 * c + e);
+          if (q.qk_norm) {
+            x1 = x1 * inv * bf2f((bf16_t)((e & 2 ? gl[x].y : gl[x].x) >> (e & 1 ? 16 : 0)));
+            x2 = x2 * inv * bf2f((bf16_t)((e & 2 ? gh[x].y : gh[x].x) >> (e & 1 ? 16 : 0)));
+          }
+          y1[e] = x1 * co[e] - x2 * sn[e];
+          y2[e] = x2 * co[e] + x1 * sn[e];
+        }
+        if (FP8 && !is_q) {
+          uint8_t* k8 = (uint8_t*)q.kpool + blk[a];
+          *(uint32_t*)(k8 + kswz8_off(tok, d)) = f2e4m3x4(y1[0], y1[1], y1[2], y1[3]);
+          *(uint32_t*)(k8 + kswz8_off(tok, d + 64)) = f2e4m3x4(y2[0], y2[1], y2[2], y2[3]);
+          continue;
+        }
+        const uint2 w1 = make_uint2((uint32_t)f2bf(y1[0]) | ((uint32_t)f2bf(y1[1]) << 16),
+                                    (uint32_t)f2bf(y1[2]) | ((uint32_t)f2bf(y1[3]) << 16));
+        const uint2 w2 = make_uint2((uint32_t)f2bf(y2[0]) | ((uint32_t)f2bf(y2[1]) << 16),
+                                    (uint32_t)f2bf(y2[2]) | ((uint32_t)f2bf(y2[3]) << 16));
+        if (is_q) {
+          bf16_t* dst = q.qout + ((size_t)row * q.nq + hd) * 128 + d;
+          *(uint2*)dst = w1;
+          *(uint2*)(dst + 64) = w2;
+        } else {
+          bf16_t* kb = (bf16_t*)q.kpool + blk[a];
+          *(uint2*)(kb + kswz_off(tok, d)) = w1;
+          *(uint2*)(kb + kswz_off(tok, d + 64)) = w2;
+        }
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // Buffer descriptor of `bytes` bytes at p in scalar registers (p and bytes are the same in every lane).
@@ -511,16 +557,24 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
   // all loads into LDS are done; the last assembly MFMAs' results may be read
   asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15"
                : "+v"(acc5[0]), "+v"(acc5[1]), "+v"(acc5[2]), "+v"(acc5[3])::"memory");
+  const int mtile = wm == 0 ? mt0 : mt0 + 1;
+  if (mtile >= mtiles128) return;
+  if constexpr (EPI == EPI_QKV || EPI == EPI_QKV8) {
+    // every use reads its own element: the compiler otherwise keeps copies of whole 16-register
+    // accumulators in vector registers and spills
+    auto val = [&](int a, int b, int i) {
+      float x;
+      asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[a][b][i]));
+      return x;
+    };
+    if (strip0 + wn * 4 < NB) qkv_head<EPI == EPI_QKV8>(val, qkv, mtile * 128, M, (strip0 >> 2) + wn, lane);
+    return;
+  }
   float* Cp = (float*)Cv + (size_t)blockIdx.z * M * N;
 #pragma unroll
   for (int a = 0; a < 4; a++) {
-    const int mtile = wm == 0 ? mt0 : mt0 + 1;
-    if (mtile >= mtiles128) continue;
     const int row0 = mtile * 128 + a * 32, row = row0 + (lane & 31);
-    if constexpr (EPI == EPI_QKV || EPI == EPI_QKV8) {
-      if (strip0 + wn * 4 < NB)
-        qkv_head<EPI == EPI_QKV8>([&](int b, int i) { return acc[a][b][i]; }, qkv, row, M, (strip0 >> 2) + wn, lane);
-    } else {
+    {
 #pragma unroll
       for (int b = 0; b < NBW; b++) {
         const int nb = strip0 + wn * NBW + b;
