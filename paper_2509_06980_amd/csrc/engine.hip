@@ -225,7 +225,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
   // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
   const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
-  const bool fused_qkv = pf.kind == GEMM_TILE256 && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
+  const bool fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
@@ -234,7 +234,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
                        (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,
                        md.max_pages_per_traj, md.eps};
-      launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, qa);
+      launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, pf, qa);
     } else {
       int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, pq);
       launch_qkrope<bf16_t, bf16_t, bf16_t, true>(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq,

@@ -88,7 +88,8 @@ enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 
 // Kernel and K-slices of one product (see plan_gemm's definition).  width: GEMM_TILE256: 64-column groups
 // of the tile (4 or 5); GEMM_DECODE: 16-column blocks of the tile (2, 4, 5 or 6).  cost: estimate in us,
 // comparable between plans of as many rows.
-enum GemmKind { GEMM_TILE128 = 0, GEMM_TILE256 = 1, GEMM_DECODE = 2 };
+// GEMM_WIDE128: 128 x 256 tiles of the same kernel.
+enum GemmKind { GEMM_TILE128 = 0, GEMM_TILE256 = 1, GEMM_DECODE = 2, GEMM_WIDE128 = 3 };
 struct GemmPlan { int kind, width, splits; double cost; };
 const int kMaxSplits = 8;
 // part_rows: rows the partial-sum buffer holds (every K-slice takes M of them)
@@ -111,7 +112,7 @@ struct QkvArgs {
   float eps;
 };
 void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int N, int K, bool kv_fp8,
-                     const QkvArgs& q);
+                     const GemmPlan& plan, const QkvArgs& q);
 // lm-head fused with the log-softmax of the masked log-prob pass: for each of the M rows of A
 // (bf16 A-tile layout) lp[row] = log softmax(z / T)[tgt[row]] with z = A[row] . Wp^T (V logits, never
 // stored) and scale_c = log2(e) / T.  part: scratch of M * (V / 32) float pairs; zt: M floats.

@@ -271,16 +271,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 }
 
 // =============================================================================================
-// GEMM for many rows (chunked prefill, teacher-forced passes, mixed steps): tile 256 x 64*NBW, 4 waves
-// as 2 x 2, wave tile 128 x 32*NBW (NBW = 4: 256 columns, 16 accumulators of 32x32; NBW = 5: 320 columns,
-// 20 of them).  Per 16-k step a wave reads 4 row and NBW column operands from LDS for 4*NBW MFMAs.
+// GEMM for many rows (chunked prefill, teacher-forced passes, mixed steps): tile 64*MB x 64*NBW, 4 waves
+// as 2 x 2, wave tile 32*MB x 32*NBW (MB = 4: 256 rows; NBW = 4: 256 columns, 16 accumulators of 32x32;
+// NBW = 5: 320 columns, 20 of them; MB = 2: 128 rows for passes of a few hundred rows, whose last
+// 256-row tile would be mostly empty).  Per 16-k step a wave reads MB row and NBW column operands from
+// LDS for MB*NBW MFMAs.
 // Both operands go from memory straight into LDS (16-byte buffer loads with the LDS destination; no
 // staging registers, no LDS stores in the instruction stream) as chunks of 32 k in a ring of four
-// stages, three and a half chunks ahead.  The loop is one steady stream: every group of NBW MFMAs
-// carries one such load, and the next step's operands are read in the first three of four groups, so
-// that the wait in front of the barrier (group 4 of a chunk's 8: the next chunk is complete, this one
-// is read out) finds them there.  The loads return in order, so "at most 2 chunks outstanding" means
-// that the next chunk has landed; before the epilogue all are drained.
+// stages (MB = 2: three), three and a half (two and a half) chunks ahead.  The loop is one steady
+// stream: every group of NBW MFMAs carries its share of these loads, and the next step's operands are
+// read ahead of its last group, so that the wait in front of the barrier (half way through a chunk: the
+// next chunk is complete, this one is read out) finds them there.  The loads return in order, so "at
+// most the chunks behind it outstanding" means that the next chunk has landed; before the epilogue all
+// are drained.
 // The fifth accumulator column lives in vector registers: 320 accumulator registers exceed the 256
 // accumulation registers, and the builtin, which takes all of its kind from one file, then copies.
 // blockIdx.z selects a K-slice (EPI_STORE only); each slice stores its own partial sum.
@@ -292,7 +295,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 // Measured at 8192 rows in the pass (us; before: register staging, 256-column tiles or 128 x 128):
 // gate-up N = 19456 K = 2560 with SwiGLU 880 -> 690, down N = 2560 K = 9728 443 -> 308 (1.41 PFLOP/s
 // alone), O N = 2560 K = 4096 192 -> 138, QKV N = 6144 K = 2560 with norm, RoPE and cache write
-// 244 + 80 -> 271, lm-head with log-softmax at 1536 rows (N = 151936) 1709 -> 1034.
+// 244 + 80 -> 268, lm-head with log-softmax at 1536 rows (N = 151936) 1709 -> 1034.  128-row tiles at
+// 587 rows (before: 128 x 128): QKV 30.5 -> 25.0 in two slices, O 23.6 -> 19.1, down 45.0 -> 38.9 in five.
 // XCD-aware tile numbering (xcd_tile256).  K % 64 == 0, N % 32 == 0.
 // =============================================================================================
 // Tile of a workgroup: the hardware hands workgroups to the 8 XCDs round-robin by linear index
@@ -311,21 +315,21 @@ __device__ __forceinline__ void xcd_tile256(int id, int tiles_m, int tiles_n, in
   *tn = within / gm;
 }
 
-// QK-norm, RoPE and the writes of one head (EPI_QKV) for a wave's four blocks of 32 batch rows:
+// QK-norm, RoPE and the writes of one head (EPI_QKV) for a wave's MB blocks of 32 batch rows:
 // val(a, b, i) is dim 32 b + (i / 4) * 8 + (lane / 32) * 4 + i % 4 of the head for row row0 + 32 a + lane % 32.
 // The same arithmetic as qkrope128_kernel; only the order of the sum of squares differs.  With one wave
 // per SIMD nothing else hides a memory round trip: positions, pages and gains are read once, and the
 // RoPE table pieces of half a row block are requested before the half ahead of it is computed.
-template <bool FP8, typename F>
+template <bool FP8, int MB, typename F>
 __device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row0, int M, int hd, int lane) {
   const int h4 = (lane >> 5) * 4;
   const bool is_q = hd < q.nq, is_v = hd >= q.nq + q.nkv;
-  int pos[4];
-  size_t blk[4];
+  int pos[MB];
+  size_t blk[MB];
 #pragma unroll
-  for (int a = 0; a < 4; a++) pos[a] = q.row_pos[min(row0 + 32 * a + (lane & 31), M - 1)];
+  for (int a = 0; a < MB; a++) pos[a] = q.row_pos[min(row0 + 32 * a + (lane & 31), M - 1)];
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
+  for (int a = 0; a < MB; a++) {
     blk[a] = 0;
     if (!is_q) {
       const int slot = q.row_slot[min(row0 + 32 * a + (lane & 31), M - 1)];
@@ -335,7 +339,7 @@ __device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row0, int 
   }
   if (is_v) {
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
+    for (int a = 0; a < MB; a++) {
       if (row0 + 32 * a + (lane & 31) >= M) continue;
       const int tok = pos[a] & (RL_PAGE - 1);
 #pragma unroll
@@ -373,9 +377,9 @@ __device__ __forceinline__ void qkv_head(F val, const QkvArgs& q, int row0, int 
   fetch(0);
   float inv = 1.0f;
 #pragma unroll
-  for (int y = 0; y < 8; y++) {
+  for (int y = 0; y < 2 * MB; y++) {
     const int a = y >> 1, b = y & 1;
-    if (y < 7) fetch(y + 1);
+    if (y < 2 * MB - 1) fetch(y + 1);
     __builtin_amdgcn_sched_barrier(0);
     if (b == 0) {
       float ss = 0.f;
@@ -453,16 +457,19 @@ __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, 
                : "memory");
 }
 
-template <int EPI, int NBW>
-__global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
+template <int EPI, int MB, int NBW>
+__global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K,
                                                        int chunks_per_split, const int32_t* __restrict__ tgt,
                                                        float* __restrict__ zt, float scale_c, QkvArgs qkv) {
   constexpr bool TR = EPI != EPI_STORE;       // weights as the row operand
   constexpr int NS = 2 * NBW;                 // strips of the tile
-  constexpr int PW = 4 + NBW;                 // 1 KB pieces per wave and chunk
-  constexpr int BUF = (16 + 4 * NBW) * 1024;  // bytes of a stage: 16 row pieces, then [strip][kb]
-  extern __shared__ u32x4 smem[];             // 4 stages
+  constexpr int NA = 4 * MB;                  // row pieces of a stage: [128-row tile][kb][32-row block]
+  constexpr int PW = MB + NBW;                // 1 KB pieces per wave and chunk
+  constexpr int BUF = (NA + 4 * NBW) * 1024;  // bytes of a stage: the row pieces, then [strip][kb]
+  constexpr int R = MB == 4 ? 4 : 3;          // stages
+  constexpr int F = PW / 2;                   // pieces of a chunk that are asked for half a chunk ahead of the others
+  extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
   const int NB = N >> 5, nch = K >> 5;
@@ -470,7 +477,8 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
   const int c0 = blockIdx.z * chunks_per_split, c1 = min(c0 + chunks_per_split, nch);
   int bx, by;
   xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
-  const int mt0 = by * 2, mt1 = min(mt0 + 1, mtiles128 - 1);   // second half clamped (results dropped)
+  // MB = 4: second half clamped (results dropped)
+  const int mt0 = by * (MB / 2), mt1 = MB == 4 ? min(mt0 + 1, mtiles128 - 1) : mt0;
   const int strip0 = bx * NS;
   const u32x4 ra = buffer_rsrc(A + (size_t)mt0 * K * 128, (unsigned)(mt1 - mt0 + 1) * (unsigned)K * 256u);
   const u32x4 rb = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
@@ -480,66 +488,71 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
   // piece j of this wave of chunk c (past the end of the slice: its last chunk again, never read)
   auto dma = [&](int c, int j) {
     const int cl = min(c, c1 - 1);
-    const unsigned dst = lds0 + (unsigned)(c & 3) * BUF + (unsigned)(j * 4 + wave) * 1024u;
+    const unsigned dst = lds0 + (unsigned)(R == 4 ? c & 3 : c % R) * BUF + (unsigned)(j * 4 + wave) * 1024u;
     unsigned so;
-    if (j < 4) {
+    if (j < MB) {
       so = ((j >> 1) ? a_rt1 : 0u) + (unsigned)((2 * cl + (j & 1)) * 4 + wave) * 1024u;
     } else {     // strips past the end (N not a multiple of the tile): the last one again, results dropped
-      const int st = min(strip0 + 2 * (j - 4) + (wave >> 1), NB - 1);
+      const int st = min(strip0 + 2 * (j - MB) + (wave >> 1), NB - 1);
       so = ((unsigned)(cl >> 1) * NB + st) * 4096u + (cl & 1) * 2048u + (wave & 1) * 1024u;
     }
-    load_to_lds(dst, voff, j < 4 ? ra : rb, so);
+    load_to_lds(dst, voff, j < MB ? ra : rb, so);
   };
-  f32x16 acc[4][4], acc5[4];
+  f32x16 acc[MB][4], acc5[MB];
 #pragma unroll
-  for (int a = 0; a < 4; a++)
+  for (int a = 0; a < MB; a++)
 #pragma unroll
     for (int e = 0; e < 16; e++) {
       acc5[a][e] = 0.f;
 #pragma unroll
       for (int b = 0; b < 4; b++) acc[a][b][e] = 0.f;
     }
-  u32x4 av[2][4], bv[2][NBW];
-  const u32x4* As = smem + (wm * 8) * 64 + lane;               // [kb][32-row block]
-  const u32x4* Bs = smem + (16 + wn * NBW * 2) * 64 + lane;    // [strip][kb]
+  u32x4 av[2][MB], bv[2][NBW];
+  const u32x4* As = smem + (MB == 4 ? wm * 8 : wm * 2) * 64 + lane;   // [kb][32-row block]
+  const u32x4* Bs = smem + (NA + wn * NBW * 2) * 64 + lane;           // [strip][kb]
 #pragma unroll
-  for (int c = 0; c < 3; c++)
+  for (int c = 0; c < R - 1; c++)
 #pragma unroll
     for (int j = 0; j < PW; j++) dma(c0 + c, j);
 #pragma unroll
-  for (int j = 0; j < 4; j++) dma(c0 + 3, j);
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PW + 4) : "memory");
+  for (int j = 0; j < F; j++) dma(c0 + R - 1, j);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 2) * PW + F) : "memory");
   __builtin_amdgcn_s_barrier();
   {
-    const int base = (c0 & 3) * (BUF / 16);
+    const int base = (R == 4 ? c0 & 3 : c0 % R) * (BUF / 16);
 #pragma unroll
-    for (int x = 0; x < 4; x++) av[0][x] = As[base + x * 64];
+    for (int x = 0; x < MB; x++) av[0][x] = As[base + x * 64];
 #pragma unroll
     for (int x = 0; x < NBW; x++) bv[0][x] = Bs[base + x * 128];
   }
   for (int c = c0; c < c1; c++) {
-    const int cur = (c & 3) * (BUF / 16), nxt = ((c + 1) & 3) * (BUF / 16);
+    const int cur = (R == 4 ? c & 3 : c % R) * (BUF / 16), nxt = (R == 4 ? (c + 1) & 3 : (c + 1) % R) * (BUF / 16);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < 8; g++) {
-      const int a = g & 3, st = g >> 2;
-      if (g == 4) {      // chunk c + 1 has landed for every wave, chunk c is read out by every wave
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * PW) : "memory");
+    for (int g = 0; g < 2 * MB; g++) {
+      const int a = g % MB, st = g / MB;
+      if (g == MB) {     // chunk c + 1 has landed for every wave, chunk c is read out by every wave
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((R - 2) * PW) : "memory");
         __builtin_amdgcn_s_barrier();
       }
       const int base = st == 0 ? cur : nxt, kb = st == 0 ? 1 : 0;
       auto rd = [&](int q) {      // operand q of the next 16-k step
-        if (q < 4) av[1 - st][q] = As[base + (kb * 4 + q) * 64];
-        else bv[1 - st][q - 4] = Bs[base + ((q - 4) * 2 + kb) * 64];
+        if (q < MB) av[1 - st][q] = As[base + (kb * 4 + q) * 64];
+        else bv[1 - st][q - MB] = Bs[base + ((q - MB) * 2 + kb) * 64];
       };
-      if (a == 0) { rd(4); rd(0); rd(5); }
-      if (a == 1) { rd(6); rd(7); rd(1); }
-      if (a == 2) { rd(2); rd(3); if (NBW == 5) rd(8); }
-      if (st == 0) {
-        dma(c + 3, 4 + a);
-        if (NBW == 5 && a == 3) dma(c + 3, 8);
-      } else {
-        dma(c + 4, a);
+      if (MB == 4) {
+        if (a == 0) { rd(4); rd(0); rd(5); }
+        if (a == 1) { rd(6); rd(7); rd(1); }
+        if (a == 2) { rd(2); rd(3); if (NBW == 5) rd(8); }
+      } else if (a == 0) {
+#pragma unroll
+        for (int q = 0; q < MB + NBW; q++) rd(q);
+      }
+      // this step's share of the loads: the rest of chunk c + R - 1, then the first F pieces of chunk c + R
+#pragma unroll
+      for (int j = 0; j < PW; j++) {
+        if (st == 0 && j >= F && (j - F) * MB / (PW - F) == a) dma(c + R - 1, j);
+        if (st == 1 && j < F && j * MB / F == a) dma(c + R, j);
       }
 #pragma unroll
       for (int b = 0; b < 4; b++)
@@ -555,10 +568,14 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
     }
   }
   // all loads into LDS are done; the last assembly MFMAs' results may be read
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15"
-               : "+v"(acc5[0]), "+v"(acc5[1]), "+v"(acc5[2]), "+v"(acc5[3])::"memory");
-  const int mtile = wm == 0 ? mt0 : mt0 + 1;
+  if constexpr (NBW == 5)
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15"
+                 : "+v"(acc5[0]), "+v"(acc5[1]), "+v"(acc5[2]), "+v"(acc5[3])::"memory");
+  else
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+  const int mtile = MB == 4 ? mt0 + wm : mt0;
   if (mtile >= mtiles128) return;
+  const int wrow0 = mtile * 128 + (MB == 4 ? 0 : wm * 64);
   if constexpr (EPI == EPI_QKV || EPI == EPI_QKV8) {
     // every use reads its own element: the compiler otherwise keeps copies of whole 16-register
     // accumulators in vector registers and spills
@@ -567,30 +584,28 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const bf16_t* __restrict_
       asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[a][b][i]));
       return x;
     };
-    if (strip0 + wn * 4 < NB) qkv_head<EPI == EPI_QKV8>(val, qkv, mtile * 128, M, (strip0 >> 2) + wn, lane);
+    if (strip0 + wn * 4 < NB) qkv_head<EPI == EPI_QKV8, MB>(val, qkv, wrow0, M, (strip0 >> 2) + wn, lane);
     return;
   }
   float* Cp = (float*)Cv + (size_t)blockIdx.z * M * N;
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
-    const int row0 = mtile * 128 + a * 32, row = row0 + (lane & 31);
-    {
+  for (int a = 0; a < MB; a++) {
+    const int row0 = wrow0 + a * 32, row = row0 + (lane & 31);
 #pragma unroll
-      for (int b = 0; b < NBW; b++) {
-        const int nb = strip0 + wn * NBW + b;
-        if (nb >= NB) continue;
-        auto val = [&](int i) { return b < 4 ? acc[a][b & 3][i] : acc5[a][i]; };
-        if constexpr (EPI == EPI_SWIGLU) {
-          swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
-        } else if constexpr (EPI == EPI_LSE) {
-          lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
-        } else {
-          const int col = nb * 32 + (lane & 31);
+    for (int b = 0; b < NBW; b++) {
+      const int nb = strip0 + wn * NBW + b;
+      if (nb >= NB) continue;
+      auto val = [&](int i) { return b < 4 ? acc[a][b & 3][i] : acc5[a][i]; };
+      if constexpr (EPI == EPI_SWIGLU) {
+        swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
+      } else if constexpr (EPI == EPI_LSE) {
+        lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
+      } else {
+        const int col = nb * 32 + (lane & 31);
 #pragma unroll
-          for (int i = 0; i < 16; i++) {
-            const int r = row0 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-            if (r < M) __builtin_nontemporal_store(val(i), &Cp[(size_t)r * N + col]);
-          }
+        for (int i = 0; i < 16; i++) {
+          const int r = row0 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
+          if (r < M) __builtin_nontemporal_store(val(i), &Cp[(size_t)r * N + col]);
         }
       }
     }
@@ -608,15 +623,15 @@ static void set_lds_limit(std::atomic<uint64_t>& done, const void* kernel, int b
   done.fetch_or(bit, std::memory_order_release);
 }
 
-template <int EPI, int NBW>
+template <int EPI, int MB, int NBW>
 static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
                        const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
-  constexpr int lds = 4 * (16 + 4 * NBW) * 1024;
+  constexpr int lds = (MB == 4 ? 4 : 3) * (4 * MB + 4 * NBW) * 1024;
   static std::atomic<uint64_t> done{0};
-  set_lds_limit(done, (const void*)gemm_dma_kernel<EPI, NBW>, lds);
+  set_lds_limit(done, (const void*)gemm_dma_kernel<EPI, MB, NBW>, lds);
   const int cps = (K / 32 + splits - 1) / splits;
-  dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 255) / 256, splits);
-  gemm_dma_kernel<EPI, NBW><<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
+  dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 64 * MB - 1) / (64 * MB), splits);
+  gemm_dma_kernel<EPI, MB, NBW><<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
 }
 
 // =============================================================================================
@@ -766,7 +781,8 @@ static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t*
 // make whole rounds: 8B down at N = 4096 K = 12288, 12 rows 18.6 against 22.4 us with 64 columns).
 // More rows: a round is 256 workgroups, one per CU.  256-row tiles cost per 32-k chunk 0.43 us with most
 // CUs idle to 0.73 us with all of them busy (320 columns: 1.25 times that) and 4 to 16 us per round to
-// store a tile; 128 x 128 tiles cost 0.62 us per 64-k chunk and round, 0.59 us from the second round on
+// store a tile; 128 x 256 tiles 0.46 us per chunk and 5 us per round (two share a CU, at the speed of one
+// after the other); 128 x 128 tiles 0.62 us per 64-k chunk and round, 0.59 us from the second round on
 // (several to a CU).  Fitted on N = 2048 to 6144, K = 640 to 9728, 64 to 1280 tiles; e.g. 8192 x 2560 x
 // 9728: 320 columns make one full round of 256 tiles (289 us) where 256 columns make two (398 us).
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
@@ -812,6 +828,12 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
       offer(GEMM_TILE256, nbw, (K / 32 + cps - 1) / cps,
             3.0 + r * (cps * w * (0.43 + 0.30 * fill) + 4.0 + 10.0 * w * fill) + (sp - 1) * part);
     }
+  if (epilogue != EPI_LSE)
+    for (int sp = 1; sp <= most; sp++) {
+      const int t = ((N / 32 + 7) / 8) * ((M + 127) / 128) * sp, cps = (K / 32 + sp - 1) / sp;
+      const double r = t <= 512 ? (t + 255) / 256 : t / 256.0;
+      offer(GEMM_WIDE128, 4, (K / 32 + cps - 1) / cps, 3.0 + r * (cps * 0.46 + 5.0) + (sp - 1) * part);
+    }
   return best;
 }
 
@@ -819,12 +841,17 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
                      const GemmPlan& plan) {
   if (M <= 0) return 0;
   const int width = plan.width, sp = plan.splits;
+  const QkvArgs none{};
+  if (plan.kind == GEMM_WIDE128) {
+    if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 2, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else launch_dma<EPI_SWIGLU, 2, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    return sp;
+  }
   if (plan.kind == GEMM_TILE256) {
-    const QkvArgs none{};
-    if (epilogue == EPI_STORE && width == 4) launch_dma<EPI_STORE, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
-    else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 5>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
-    else if (width == 4) launch_dma<EPI_SWIGLU, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
-    else launch_dma<EPI_SWIGLU, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    if (epilogue == EPI_STORE && width == 4) launch_dma<EPI_STORE, 4, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 4, 5>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (width == 4) launch_dma<EPI_SWIGLU, 4, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    else launch_dma<EPI_SWIGLU, 4, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
     return sp;
   }
   if (plan.kind == GEMM_DECODE) {
@@ -852,10 +879,15 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
 }
 
 void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int N, int K, bool kv_fp8,
-                     const QkvArgs& q) {
+                     const GemmPlan& plan, const QkvArgs& q) {
   if (M <= 0) return;
-  if (kv_fp8) launch_dma<EPI_QKV8, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
-  else launch_dma<EPI_QKV, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+  if (plan.kind == GEMM_WIDE128) {
+    if (kv_fp8) launch_dma<EPI_QKV8, 2, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+    else launch_dma<EPI_QKV, 2, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+  } else {
+    if (kv_fp8) launch_dma<EPI_QKV8, 4, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+    else launch_dma<EPI_QKV, 4, 4>(s, A, Wp, nullptr, M, N, K, 1, nullptr, nullptr, 0.f, q);
+  }
 }
 
 // lm-head of a decode step: logits[M, V] (fp32, row-major) and stripmax[M, V / 32].
@@ -905,7 +937,7 @@ void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, in
                             const int32_t* tgt, float scale_c, float* part, float* zt, float* lp) {
   if (M <= 0) return;
   if (plan_gemm(M, V, K, EPI_LSE, 0).kind == GEMM_TILE256) {
-    launch_dma<EPI_LSE, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
+    launch_dma<EPI_LSE, 4, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
   } else {
     dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
     gemm_mfma_kernel<EPI_LSE, 2, 4, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);

@@ -83,7 +83,9 @@ def test_fp32_products_and_attention_at_the_edges(change, lens):
     (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [2048, 2049], 2),   # 4095 rows, last tile one row short
     (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [3713], 2),         # 30 row tiles of 128 (29 + 1 row)
     (dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=32768), [5, 3000], 130),    # 10 heads, 320-column tiles, odd strips
-    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [300, 288], 1),     # K-slices of 256-row tiles
+    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [300, 288], 1),     # K-slices of 128- and 256-row tiles
+    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [130, 3], 1),       # 132 rows: a second tile of 4
+    (dict(hidden=2560, n_q_heads=31, n_kv_heads=31, intermediate=9728, vocab=4096), [901], 1),         # an odd number of heads in 256 columns
 ])
 def test_many_row_products(change, lens, sampled, kv8):
     # the 256-row tiles (256 and 320 columns, K-slices, SwiGLU, QK-norm + RoPE + cache write and log-softmax
