@@ -226,6 +226,11 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
   const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
   const bool fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
+  // the residual add inside the products that leave one partial sum (the norm then reads one array instead
+  // of two and writes none back)
+  auto adds = [](const GemmPlan& p) { return p.splits == 1 && (p.kind == GEMM_TILE256 || p.kind == GEMM_WIDE128); };
+  const int eo = adds(po) ? EPI_ADD : EPI_STORE, ed = adds(pd) ? EPI_ADD : EPI_STORE;
+  float *const co = eo == EPI_ADD ? m->h : m->ph, *const cd = ed == EPI_ADD ? m->h : m->ph;
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
@@ -248,10 +253,10 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.pf_items, r.n_pf_items, nullptr, 0,
                             nullptr, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, true);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
-    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, m->ph, M, H, qw, EPI_STORE, po);
+    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, co, M, H, qw, eo, po);
     launch_add_rmsnorm(s, m->h, m->ph, so, (size_t)M * H, (const bf16_t*)w.g_post, (bf16_t*)m->xa, M, H, md.eps);
     launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, pg);
-    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, m->ph, M, H, I, EPI_STORE, pd);
+    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, cd, M, H, I, ed, pd);
   }
   m->pending_parts = pend;
 }

@@ -292,6 +292,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
 // formed transposed, which leaves a row's 128 dims of the head in two lanes, RoPE partners in the
 // same lane; the per-head norm (one swap), RoPE and the writes to q and the paged cache happen in
 // the epilogue, so the fp32 projection (201 MB at 8192 x 6144) is neither stored nor read back.
+// EPI_ADD: the product is added to the fp32 residual stream in place (O and down, one slice): 18 us more
+// than storing it at 8192 x 2560 (84 MB read by all workgroups at once), 30 us less in the norm behind it.
 // Measured at 8192 rows in the pass (us; before: register staging, 256-column tiles or 128 x 128):
 // gate-up N = 19456 K = 2560 with SwiGLU 880 -> 690, down N = 2560 K = 9728 443 -> 308 (1.41 PFLOP/s
 // alone), O N = 2560 K = 4096 192 -> 138, QKV N = 6144 K = 2560 with norm, RoPE and cache write
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
                                                        void* __restrict__ Cv, int M, int N, int K,
                                                        int chunks_per_split, const int32_t* __restrict__ tgt,
                                                        float* __restrict__ zt, float scale_c, QkvArgs qkv) {
-  constexpr bool TR = EPI != EPI_STORE;       // weights as the row operand
+  constexpr bool TR = EPI != EPI_STORE && EPI != EPI_ADD;   // weights as the row operand
   constexpr int NS = 2 * NBW;                 // strips of the tile
   constexpr int NA = 4 * MB;                  // row pieces of a stage: [128-row tile][kb][32-row block]
   constexpr int PW = MB + NBW;                // 1 KB pieces per wave and chunk
@@ -477,6 +479,8 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
   const int c0 = blockIdx.z * chunks_per_split, c1 = min(c0 + chunks_per_split, nch);
   int bx, by;
   xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
+  bx = __builtin_amdgcn_readfirstlane(bx);      // the division leaves them in vector registers
+  by = __builtin_amdgcn_readfirstlane(by);
   // MB = 4: second half clamped (results dropped)
   const int mt0 = by * (MB / 2), mt1 = MB == 4 ? min(mt0 + 1, mtiles128 - 1) : mt0;
   const int strip0 = bx * NS;
@@ -588,6 +592,36 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
     return;
   }
   float* Cp = (float*)Cv + (size_t)blockIdx.z * M * N;
+  if constexpr (EPI == EPI_ADD) {
+    // C += product, one 32 x 32 block after the other; the addends are requested two blocks ahead
+    if (wrow0 >= M) return;
+    float old[3][16];
+    const int last = M - 1 - wrow0, rsub = (lane >> 5) * 4;
+    const int first = strip0 + wn * NBW;
+    auto base = [&](int b) { return Cp + (size_t)wrow0 * N + min(first + b, NB - 1) * 32; };
+    auto off = [&](int a, int i) { return (unsigned)(min(a * 32 + (i >> 2) * 8 + rsub + (i & 3), last) * N + (lane & 31)); };
+    auto fetch = [&](int t) {
+#pragma unroll
+      for (int i = 0; i < 16; i++) old[t % 3][i] = base(t % NBW)[off(t / NBW, i)];
+    };
+    fetch(0);
+    fetch(1);
+#pragma unroll
+    for (int t = 0; t < MB * NBW; t++) {
+      const int a = t / NBW, b = t % NBW;
+      if (t + 2 < MB * NBW) fetch(t + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      if (first + b < NB) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+          const float v = old[t % 3][i] + (b < 4 ? acc[a][b & 3][i] : acc5[a][i]);
+          if (a * 32 + (i >> 2) * 8 + rsub + (i & 3) <= last) __builtin_nontemporal_store(v, &base(b)[off(a, i)]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return;
+  }
 #pragma unroll
   for (int a = 0; a < MB; a++) {
     const int row0 = wrow0 + a * 32, row = row0 + (lane & 31);
@@ -844,15 +878,18 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   const QkvArgs none{};
   if (plan.kind == GEMM_WIDE128) {
     if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 2, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_ADD) launch_dma<EPI_ADD, 2, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
     else launch_dma<EPI_SWIGLU, 2, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
-    return sp;
+    return epilogue == EPI_ADD ? 0 : sp;
   }
   if (plan.kind == GEMM_TILE256) {
     if (epilogue == EPI_STORE && width == 4) launch_dma<EPI_STORE, 4, 4>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
     else if (epilogue == EPI_STORE) launch_dma<EPI_STORE, 4, 5>(s, A, Wp, C, M, N, K, sp, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_ADD && width == 4) launch_dma<EPI_ADD, 4, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
+    else if (epilogue == EPI_ADD) launch_dma<EPI_ADD, 4, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
     else if (width == 4) launch_dma<EPI_SWIGLU, 4, 4>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
     else launch_dma<EPI_SWIGLU, 4, 5>(s, A, Wp, C, M, N, K, 1, nullptr, nullptr, 0.f, none);
-    return sp;
+    return epilogue == EPI_ADD ? 0 : sp;
   }
   if (plan.kind == GEMM_DECODE) {
     auto go = [&](auto epi) {

@@ -85,6 +85,7 @@ def test_fp32_products_and_attention_at_the_edges(change, lens):
     (dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=32768), [5, 3000], 130),    # 10 heads, 320-column tiles, odd strips
     (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [300, 288], 1),     # K-slices of 128- and 256-row tiles
     (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [130, 3], 1),       # 132 rows: a second tile of 4
+    (dict(hidden=2560, n_q_heads=4, n_kv_heads=1, intermediate=256, vocab=512), [3950, 3907], 0),      # 320 columns with the residual add, a last tile of 177 rows
     (dict(hidden=2560, n_q_heads=31, n_kv_heads=31, intermediate=9728, vocab=4096), [901], 1),         # an odd number of heads in 256 columns
 ])
 def test_many_row_products(change, lens, sampled, kv8):
@@ -92,7 +93,7 @@ def test_many_row_products(change, lens, sampled, kv8):
     # in the epilogue) at row counts and widths that end inside a tile, against the shape-generic kernels
     shape = SHAPES["small-d128"].replace(n_layers=1, **change)
     blob = make_weight_blob(shape, seed=6, weight_std=0.02, gain_std=0.1)
-    kw = dict(max_context=4096, max_trajectories=4, kv_pool_pages=400)
+    kw = dict(max_context=4096, max_trajectories=4, kv_pool_pages=520)
     a = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, **kw)
     b = rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
     rng = np.random.default_rng(sum(lens))
