@@ -218,7 +218,6 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   hipStream_t s = m->stream;
   const ModelDims& md = m->md;
   int H = md.H, qw = md.nq * md.d, kvw = md.nkv * md.d, I = md.I, QW = qw + 2 * kvw;
-  launch_embed<bf16_t>(s, (const bf16_t*)m->embed, r.tok, m->h, M, H);
   // the same for every layer
   const GemmPlan pq = plan_gemm(M, QW, H, EPI_STORE, m->part_rows), po = plan_gemm(M, H, qw, EPI_STORE, m->part_rows);
   const GemmPlan pg = plan_gemm(M, 2 * I, H, EPI_SWIGLU, m->part_rows), pd = plan_gemm(M, H, I, EPI_STORE, m->part_rows);
@@ -234,7 +233,8 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
-    launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
+    if (l == 0) launch_embed_rmsnorm(s, (const bf16_t*)m->embed, r.tok, m->h, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
+    else launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
     if (fused_qkv) {
       const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
                        (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,

@@ -73,6 +73,9 @@ void launch_qkrope(hipStream_t s, const float* qkv, int n_part, size_t part_stri
 void launch_add_rmsnorm(hipStream_t s, float* h, const float* parts, int n_part, size_t part_stride,
                         const bf16_t* g, bf16_t* out, int M, int H, float eps,
                         const int32_t* rows = nullptr);
+// h = embedding of tok, out = rmsnorm(h) * g in A-tile layout (what launch_embed and the call above leave)
+void launch_embed_rmsnorm(hipStream_t s, const bf16_t* embed, const int32_t* tok, float* h, const bf16_t* g,
+                          bf16_t* out, int M, int H, float eps);
 
 template <typename TA, typename TKV>
 void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int32_t* row_pos,

@@ -98,11 +98,13 @@ __global__ void add_rmsnorm_kernel(float* __restrict__ h, const float* __restric
 // of one XCD, whose L2 then writes whole lines: H = 2560, 8192 rows, one partial sum 72 -> 56 us (5.2 TB/s),
 // none 41 -> 25 us, 587 rows with five 12.9 -> 11.0 us.  Below 256 rows the launch is one latency chain
 // and rows stay in launch order (128 rows with two partial sums 5.4 against 6.0 us).
-template <int ITER, int NP>
+// EMB: the row is the embedding of token tok[row] instead, written to h on the way (first norm of a pass):
+// one launch and one reading of h less (8192 x 2560: 36 + 25 -> 43 us, 6 x 4096: 9.3 + 3.6 -> 4.7 us).
+template <int ITER, int NP, bool EMB>
 __global__ __launch_bounds__(256) void add_rmsnorm_reg_kernel(
     float* __restrict__ h, const float* __restrict__ parts, int n_part, size_t part_stride,
     const bf16_t* __restrict__ g, bf16_t* __restrict__ out, int H, float eps,
-    const int32_t* __restrict__ rows, int M) {
+    const int32_t* __restrict__ rows, int M, const bf16_t* __restrict__ embed, const int32_t* __restrict__ tok) {
   __shared__ float red[4];
   const int id = blockIdx.x;
   const int orow = M < 256 ? id : (id & ~63) + (id & 7) * 8 + (id >> 3 & 7);
@@ -110,14 +112,21 @@ __global__ __launch_bounds__(256) void add_rmsnorm_reg_kernel(
   const int row = rows ? rows[orow] : orow;
   float* x = h + (size_t)row * H;
   const float* pr = parts + (size_t)row * H;
+  const bf16_t* e = EMB ? embed + (size_t)tok[row] * H : nullptr;
   float4 v[ITER], u[ITER][NP];
   uint2 gw[ITER];
 #pragma unroll
   for (int it = 0; it < ITER; it++) {
     const int j = threadIdx.x * 4 + it * 1024;
     const bool ok = j < H;
-    v[it] = ok ? *(const float4*)(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
     gw[it] = ok ? *(const uint2*)(g + j) : make_uint2(0u, 0u);
+    if constexpr (EMB) {
+      const uint2 w = ok ? *(const uint2*)(e + j) : make_uint2(0u, 0u);
+      v[it] = make_float4(bf2f((bf16_t)(w.x & 0xffff)), bf2f((bf16_t)(w.x >> 16)),
+                          bf2f((bf16_t)(w.y & 0xffff)), bf2f((bf16_t)(w.y >> 16)));
+      continue;
+    }
+    v[it] = ok ? *(const float4*)(x + j) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int p = 0; p < NP; p++)
       u[it][p] = (ok && p < n_part) ? *(const float4*)(pr + (size_t)p * part_stride + j)
@@ -128,11 +137,11 @@ __global__ __launch_bounds__(256) void add_rmsnorm_reg_kernel(
   for (int it = 0; it < ITER; it++) {
 #pragma unroll
     for (int p = 0; p < NP; p++)
-      if (p < n_part) {   // ascending order, as the looping kernel adds them
+      if (!EMB && p < n_part) {   // ascending order, as the looping kernel adds them
         v[it].x += u[it][p].x; v[it].y += u[it][p].y; v[it].z += u[it][p].z; v[it].w += u[it][p].w;
       }
     const int j = threadIdx.x * 4 + it * 1024;
-    if (n_part > 0 && j < H) *(float4*)(x + j) = v[it];
+    if ((EMB || n_part > 0) && j < H) *(float4*)(x + j) = v[it];
     ss += v[it].x * v[it].x + v[it].y * v[it].y + v[it].z * v[it].z + v[it].w * v[it].w;
   }
   ss = wave_sum(ss);
@@ -155,14 +164,18 @@ __global__ __launch_bounds__(256) void add_rmsnorm_reg_kernel(
   }
 }
 
-template <int NP>
+template <int NP, bool EMB>
 static void launch_add_rmsnorm_reg(hipStream_t s, float* h, const float* parts, int n_part, size_t part_stride,
-                                   const bf16_t* g, bf16_t* out, int M, int H, float eps, const int32_t* rows) {
+                                   const bf16_t* g, bf16_t* out, int M, int H, float eps, const int32_t* rows,
+                                   const bf16_t* embed, const int32_t* tok) {
   const int grid = M < 256 ? M : (M + 63) / 64 * 64;
-  if (H <= 1024) add_rmsnorm_reg_kernel<1, NP><<<grid, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows, M);
-  else if (H <= 2048) add_rmsnorm_reg_kernel<2, NP><<<grid, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows, M);
-  else if (H <= 3072) add_rmsnorm_reg_kernel<3, NP><<<grid, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows, M);
-  else add_rmsnorm_reg_kernel<4, NP><<<grid, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows, M);
+  auto go = [&](auto kernel) {
+    kernel<<<grid, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows, M, embed, tok);
+  };
+  if (H <= 1024) go(add_rmsnorm_reg_kernel<1, NP, EMB>);
+  else if (H <= 2048) go(add_rmsnorm_reg_kernel<2, NP, EMB>);
+  else if (H <= 3072) go(add_rmsnorm_reg_kernel<3, NP, EMB>);
+  else go(add_rmsnorm_reg_kernel<4, NP, EMB>);
 }
 
 void launch_add_rmsnorm(hipStream_t s, float* h, const float* parts, int n_part, size_t part_stride,
@@ -170,11 +183,22 @@ void launch_add_rmsnorm(hipStream_t s, float* h, const float* parts, int n_part,
   if (M <= 0) return;
   if (n_part <= 8 && H % 4 == 0 && H <= 4096) {
     // registers for one partial sum only where there is no more: 8 blocks instead of 3 share a CU
-    if (n_part <= 1) launch_add_rmsnorm_reg<1>(s, h, parts, n_part, part_stride, g, out, M, H, eps, rows);
-    else launch_add_rmsnorm_reg<8>(s, h, parts, n_part, part_stride, g, out, M, H, eps, rows);
+    if (n_part <= 1) launch_add_rmsnorm_reg<1, false>(s, h, parts, n_part, part_stride, g, out, M, H, eps, rows, nullptr, nullptr);
+    else launch_add_rmsnorm_reg<8, false>(s, h, parts, n_part, part_stride, g, out, M, H, eps, rows, nullptr, nullptr);
     return;
   }
   add_rmsnorm_kernel<<<M, 256, 0, s>>>(h, parts, n_part, part_stride, g, out, H, eps, rows);
+}
+
+void launch_embed_rmsnorm(hipStream_t s, const bf16_t* embed, const int32_t* tok, float* h, const bf16_t* g,
+                          bf16_t* out, int M, int H, float eps) {
+  if (M <= 0) return;
+  if (H % 4 == 0 && H <= 4096) {
+    launch_add_rmsnorm_reg<1, true>(s, h, nullptr, 0, 0, g, out, M, H, eps, nullptr, embed, tok);
+    return;
+  }
+  launch_embed<bf16_t>(s, embed, tok, h, M, H);
+  launch_add_rmsnorm(s, h, nullptr, 0, 0, g, out, M, H, eps, nullptr);
 }
 
 template <typename TA, typename TW>

@@ -117,7 +117,8 @@ def test_many_row_products(change, lens, sampled, kv8):
 
 
 @pytest.mark.parametrize("change", [dict(), dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=4128),
-                                    dict(hidden=4096, n_q_heads=4, n_kv_heads=4, intermediate=4096, vocab=4096)])
+                                    dict(hidden=4096, n_q_heads=4, n_kv_heads=4, intermediate=4096, vocab=4096),
+                                    dict(hidden=4160, n_q_heads=4, n_kv_heads=4, intermediate=1024, vocab=4096)])   # the norms' looping form
 @pytest.mark.parametrize("rows", [1, 15, 17, 32, 33, 64, 65, 128, 129])
 def test_decode_products_row_counts(change, rows):
     # every row count at which the decode products change their tile, widths that end inside a tile of
