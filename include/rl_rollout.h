@@ -112,7 +112,9 @@ int rl_append_observation(rl_model* m, const int32_t* traj_ids, int32_t n,
  * inverse CDF at the 32-bit uniform rl_uniform_u32(rng_seed, traj_id, index of the new token);
  * temperature 0 selects the arg-max (lowest index on ties).  token_ids_out[i] and
  * logprobs_out[i] (log-prob under the temperature-scaled distribution; temperature 0 reports
- * it at temperature 1) are in call order.  The token is appended with mask 0.
+ * it at temperature 1) are in call order.  The token is appended with mask 0.  It lies in the
+ * vocabulary whatever the logits hold: NaN everywhere, or plus infinity in a row that is drawn, gives
+ * token 0 with a log-prob that is no number.
  * Errors: ARG, BAD_TRAJ, DUP_ID, EMPTY, CTX_OVERFLOW, NOPAGES, HIP.
  */
 int rl_decode_step(rl_model* m, const int32_t* active_traj_ids, int32_t n, float temperature,

@@ -153,8 +153,8 @@ struct SamplerScratch {
 };
 #define RL_SAMPLER_SEG 4096
 static inline int sampler_nseg(int V) { return (V + RL_SAMPLER_SEG - 1) / RL_SAMPLER_SEG; }
-
-// For each row of fp32 logits [rows, V] (row stride ldz): id and log-prob.
+// For each row of fp32 logits [rows, V] (row stride ldz): id and log-prob.  The id lies in [0, V) whatever the logits
+// hold: a row without any weight (NaN, or plus infinity in a sampled row) gives token 0 and a log-prob that is no number.
 //  scale_c = fl32(log2(e)/T) (T > 0) or fl32(log2(e)) with greedy = 1.
 //  u32 != null: use these draws; else draw from (seed, row_traj[r], row_newpos[r]).
 //  forced != null: id = forced[r] (no draw).  out_mask != null: logprob forced to 0 where

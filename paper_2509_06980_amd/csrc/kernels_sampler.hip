@@ -327,9 +327,10 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
       }
     }
     __syncthreads();
-    id = s_id;
-    // no weight at all (a row of infinities or NaN): id -1, the log-prob is not a number
-    zid = id >= 0 ? s_z : __builtin_nanf("");
+    // no weight at all (a row of NaN, or one with plus infinity): token 0 and no number as its log-prob.  The
+    // id has to lie in the vocabulary: a decode step embeds it
+    id = s_id < 0 ? 0 : s_id;
+    zid = s_id < 0 ? __builtin_nanf("") : s_z;
   }
   if (tid == 0) {
     float lp = 0.f;

@@ -31,6 +31,45 @@ def test_sampler_segment_layouts(V, rows, T):
         assert abs(lps[r] - lp) < 1e-5 * max(1.0, abs(lp))
 
 
+@pytest.mark.parametrize("V", [5, 4100, 4101])
+def test_sampler_rows_without_weight(V):
+    # no logit is a number, one is infinite, none is finite, one is no number: the id is a token all the same
+    nan, inf = np.float32("nan"), np.float32("inf")
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((4, V)).astype(np.float32)
+    z[0], z[2] = nan, -inf
+    z[1, V // 2] = inf
+    z[3, 1] = nan
+    u = rng.integers(0, 2**32, 4, dtype=np.uint64).astype(np.uint32)
+    others = z[3].copy()
+    others[1] = -1e30
+    drawn, lps = rl.sample_from_logits(z, 1.0, u)
+    assert drawn.tolist() == [0, 0, 0, sample_token(others, 1.0, int(u[3]))[0]] and np.isnan(lps).all()
+    best, lps = rl.sample_from_logits(z, 0.0, u)
+    assert best.tolist() == [0, V // 2, 0, int(others.argmax())] and np.isnan(lps).all()
+
+
+@pytest.mark.parametrize("name", ["small-d128", "tiny"])
+def test_decode_of_logits_that_are_no_numbers(name):
+    # the token that such a row yields is embedded by the next step, on the device within a call
+    shape = SHAPES[name].replace(tie_embeddings=1)
+    blob = make_weight_blob(shape, seed=8, weight_std=0.03)
+    kw = dict(max_context=64, max_trajectories=4, kv_pool_pages=16)
+    if shape.weight_dtype == 1:                                                        # the final norm's gains
+        blob.view(np.uint16)[-shape.hidden:] = 0x7FC0
+    else:
+        blob.view(np.uint32)[-shape.hidden:] = 0x7FC00000
+    g = rl.RolloutEngine(blob, **kw)
+    g.append_observation([0, 1], [3, 4, 5], [1, 2])
+    for T in (1.0, 0.0):
+        ids, lps = g.decode_steps([0, 1], 3, T, 1)
+        assert (ids == 0).all() and np.isnan(lps).all()
+        ids, lps = g.decode_step([0, 1], T, 2)
+        assert (ids == 0).all() and np.isnan(lps).all()
+    assert (g.traj_read(1)[0][2:] == 0).all() and np.isnan(g.debug_logits(0)).all()
+    g.close()
+
+
 @pytest.mark.parametrize("name", ["small-g1", "small-g2", "small-d128", "small-g8"])
 @pytest.mark.parametrize("lens", [[15], [256, 250], [127, 128, 129], [700], [1023, 900, 800], [40, 1000]])
 def test_decode_attention_cuts_and_merges(name, lens):
