@@ -723,7 +723,7 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
   // of a greedy step still takes that pass)
   float* stripmax = (m->mfma && !greedy) ? m->d_stripmax : nullptr;
   lm_head_rows(m, M, 0, n, false, n, stripmax);
-  float c = (float)(1.4426950408889634 / (greedy ? 1.0 : (double)temperature));
+  float c = sampler_scale(temperature);
   launch_sampler(m->stream, m->logits, (size_t)m->md.V, n, m->md.V, c, greedy ? 1 : 0, nullptr, seed,
                  dm.traj, dm.newpos, forced ? dm.forced : nullptr, nullptr, m->ss, m->hd_ids, m->hd_lp,
                  stripmax, m->md.V / 32);       // ids and log-probs go straight to the pinned host buffers
@@ -828,7 +828,7 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
     m->ev_region.push_back(e);
   }
   const bool greedy = temperature == 0.0f;
-  const float c = (float)(1.4426950408889634 / (greedy ? 1.0 : (double)temperature));
+  const float c = sampler_scale(temperature);
   float* stripmax = (m->mfma && !greedy) ? m->d_stripmax : nullptr;
   const double tokb = 2.0 * m->md.nkv * m->md.d * m->kv_el;
   Staging st;
@@ -1435,7 +1435,7 @@ struct ObjectiveCall {
 int teacher_forced_pass(rl_model* m, const int32_t* ids, int32_t n, float temperature, float* out,
                         const ObjectiveCall* obj) {
   int rc = RL_OK;
-  float c = (float)(1.4426950408889634 / (temperature == 0.0f ? 1.0 : (double)temperature));
+  float c = sampler_scale(temperature);
   // flat list of rows: (trajectory, position p) for p in [0, n_tokens - 1); row p predicts token p+1
   struct Seg { Traj* t; size_t out_off; };
   std::vector<Seg> segs;
@@ -1648,7 +1648,7 @@ extern "C" int rl_sample_from_logits(const float* logits, int32_t rows, int32_t 
   float* dlp = (float*)(dids + rows);
   int rc = RL_OK;
   bool greedy = temperature == 0.0f;
-  float c = (float)(1.4426950408889634 / (greedy ? 1.0 : (double)temperature));
+  float c = sampler_scale(temperature);
   hipError_t e = hipMemcpy(dz, logits, zb, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(du, u32, (size_t)rows * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess) {

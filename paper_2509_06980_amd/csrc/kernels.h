@@ -1,5 +1,6 @@
 // Host-side launchers of the rollout kernels.  All pointers are device pointers.
 #pragma once
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -153,9 +154,16 @@ struct SamplerScratch {
 };
 #define RL_SAMPLER_SEG 4096
 static inline int sampler_nseg(int V) { return (V + RL_SAMPLER_SEG - 1) / RL_SAMPLER_SEG; }
+// fl32(log2(e) / T), T = 0 (arg-max) counting as 1.  Below about 4.2e-39 the quotient leaves fp32: an infinite
+// factor times the 0 at the row's maximum would be no number, the largest finite one gives the maximum all weight.
+static inline float sampler_scale(float temperature) {
+  const double c = 1.4426950408889634 / (temperature == 0.0f ? 1.0 : (double)temperature);
+  return c < (double)FLT_MAX ? (float)c : FLT_MAX;
+}
+
 // For each row of fp32 logits [rows, V] (row stride ldz): id and log-prob.  The id lies in [0, V) whatever the logits
 // hold: a row without any weight (NaN, or plus infinity in a sampled row) gives token 0 and a log-prob that is no number.
-//  scale_c = fl32(log2(e)/T) (T > 0) or fl32(log2(e)) with greedy = 1.
+//  scale_c = sampler_scale(T).
 //  u32 != null: use these draws; else draw from (seed, row_traj[r], row_newpos[r]).
 //  forced != null: id = forced[r] (no draw).  out_mask != null: logprob forced to 0 where
 //  out_mask[r] != 0.

@@ -430,7 +430,7 @@ extern "C" int rl_sample_device_logits(const float* d_logits, int32_t rows, int3
   sc.segarg = (int32_t*)(sc.segmax + seg_n);
   sc.sege = (float*)(sc.segarg + seg_n);
   const bool greedy = temperature == 0.0f;
-  const float c = (float)(1.4426950408889634 / (greedy ? 1.0 : (double)temperature));
+  const float c = sampler_scale(temperature);
   launch_sampler((hipStream_t)stream, d_logits, (size_t)vocab, rows, vocab, c, greedy ? 1 : 0, d_u32, 0,
                  nullptr, nullptr, nullptr, nullptr, sc, d_ids_out, d_logprobs_out);
   e = hipGetLastError();

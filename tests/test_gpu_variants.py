@@ -49,12 +49,28 @@ def test_sampler_rows_without_weight(V):
     assert best.tolist() == [0, V // 2, 0, int(others.argmax())] and np.isnan(lps).all()
 
 
+@pytest.mark.parametrize("T", [1e-45, 1e-40, 4e-39, 1e-37])
+def test_sampler_temperatures_next_to_zero(T):
+    # log2(e) / T beyond fp32: the maximum has all the weight, two equal maxima half of it each
+    z = np.random.default_rng(5).standard_normal((3, 4100)).astype(np.float32)
+    z[1:, 7] = z[1:, 4099] = 9.0
+    ids, lps = rl.sample_from_logits(z, T, np.array([123, 2**31 - 1, 2**31], np.uint32))
+    assert ids.tolist() == [int(z[0].argmax()), 7, 4099]
+    assert np.abs(lps - [0.0, -np.log(2.0), -np.log(2.0)]).max() < 1e-6
+
+
 @pytest.mark.parametrize("name", ["small-d128", "tiny"])
 def test_decode_of_logits_that_are_no_numbers(name):
     # the token that such a row yields is embedded by the next step, on the device within a call
     shape = SHAPES[name].replace(tie_embeddings=1)
     blob = make_weight_blob(shape, seed=8, weight_std=0.03)
     kw = dict(max_context=64, max_trajectories=4, kv_pool_pages=16)
+    g = rl.RolloutEngine(blob, **kw)
+    g.append_observation([0], [3, 4, 5], [3])
+    z = g.debug_logits(0)
+    assert g.decode_steps([0], 2, 1e-40, 1)[0][0, 0] == z.argmax()                     # the temperature alone had done it
+    assert not np.isnan(g.recompute_logprobs([0], 1e-40)).any()
+    g.close()
     if shape.weight_dtype == 1:                                                        # the final norm's gains
         blob.view(np.uint16)[-shape.hidden:] = 0x7FC0
     else:
