@@ -47,11 +47,11 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 }
 
 // =============================================================================================
-// GEMM  C[M,N] = A[M,K] * W[N,K]^T for weight streaming.  Workgroup = NW waves (2 or 4), tile
-// 128 rows x 32*NW columns; wave w owns the 32-column strip NW*blockIdx.x + w for all 128 rows
+// GEMM  C[M,N] = A[M,K] * W[N,K]^T for weight streaming.  Workgroup = 4 waves, tile
+// 128 rows x 128 columns; wave w owns the 32-column strip 4*blockIdx.x + w for all 128 rows
 // (4 accumulators of 32x32).  Per 64-k chunk the A tile (16 KB, already in operand order in HBM)
 // is copied to LDS and shared by the waves; each wave streams its own weight cells straight from
-// HBM into registers, D chunks ahead.  blockIdx.z selects a K-slice (split-K); every slice
+// HBM into registers, two chunks ahead.  blockIdx.z selects a K-slice (split-K); every slice
 // stores its own fp32 partial sum, which the consumer kernel adds in a fixed order (no atomics:
 // results are bit-reproducible).
 // MB = number of 32-row blocks of the tile that can hold rows (1, 2 or 4; the launcher picks the
@@ -118,18 +118,17 @@ __device__ __forceinline__ void lse_block(F val, float2* __restrict__ P, float* 
   }
 }
 
-template <int EPI, int D, int NW, int MB>
-__global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
-                                                            const bf16_t* __restrict__ Wp,
-                                                            void* __restrict__ Cv, int M, int N,
-                                                            int K, int chunks_per_split,
-                                                            const int32_t* __restrict__ tgt,
-                                                            float* __restrict__ zt, float scale_c) {
-  constexpr int NT = 64 * NW;        // threads
-  constexpr int APT = 256 * MB / NT; // 16-byte pieces of the used part of an A chunk per thread
+template <int EPI, int MB>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
+                                                        const bf16_t* __restrict__ Wp,
+                                                        void* __restrict__ Cv, int M, int N,
+                                                        int K, int chunks_per_split,
+                                                        const int32_t* __restrict__ tgt,
+                                                        float* __restrict__ zt, float scale_c) {
+  // a thread stages MB 16-byte pieces of the used part of an A chunk
   __shared__ u32x4 As[2][1024];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int nb = blockIdx.x * NW + wave;
+  const int nb = blockIdx.x * 4 + wave;
   const bool active = nb * 32 < N;
   const int mt = blockIdx.y;
   const int nchunks = K >> 6;
@@ -146,35 +145,36 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
   for (int i = 0; i < MB; i++)
 #pragma unroll
     for (int j = 0; j < 16; j++) acc[i][j] = 0.f;
-  // D chunks of A (for the whole workgroup) and of this wave's weight strip are kept in flight.
+  // Two chunks of A (for the whole workgroup) and of this wave's weight strip are kept in flight
+  // (fewer registers and more resident workgroups than with four: measured best at M = 128).
   // Loads past the end of the K-slice are clamped to its last chunk (re-reads that hit in L2) so
   // that the pipeline has no conditional register definitions.  Stages are spelled out (no
   // arrays of stages) so that every buffer lives in registers.
   const int clast = c1 - 1;
-  u32x4 a0[APT], a1[APT], a2[APT], a3[APT], b0[4], b1[4], b2[4], b3[4];
+  u32x4 a0[MB], a1[MB], b0[4], b1[4];
 #define GEMM_LOAD(AR, BR, CHUNK)                                            \
   {                                                                         \
     const int cl_ = min((CHUNK), clast);                                    \
-    _Pragma("unroll") for (int i = 0; i < APT; i++)                         \
-      AR[i] = Ag[(size_t)cl_ * 1024 + a_piece(i * NT + tid)];               \
+    _Pragma("unroll") for (int i = 0; i < MB; i++)                          \
+      AR[i] = Ag[(size_t)cl_ * 1024 + a_piece(i * 256 + tid)];              \
     _Pragma("unroll") for (int i = 0; i < 4; i++)                           \
       BR[i] = Wg[((size_t)cl_ * NB * 4 + i) * 64 + lane];                   \
     /* keep the scheduler from sinking these loads towards their use */     \
     __builtin_amdgcn_sched_barrier(0);                                      \
   }
 #define GEMM_STAGE(S, AR, BR)                                               \
-  if ((S) < D) {                                                            \
+  {                                                                         \
     const int cc = c + (S);                                                 \
-    u32x4* buf = As[(S) & 1];                                               \
+    u32x4* buf = As[S];                                                     \
     /* past the end of the slice the weight operand is zeroed: the body stays branch free; \
        the masked copy also frees the staging registers before they are refilled */ \
     const unsigned keep = cc < c1 ? 0xffffffffu : 0u;                       \
     u32x4 bcur[4];                                                          \
-    _Pragma("unroll") for (int i = 0; i < APT; i++) buf[a_piece(i * NT + tid)] = AR[i]; \
+    _Pragma("unroll") for (int i = 0; i < MB; i++) buf[a_piece(i * 256 + tid)] = AR[i]; \
     _Pragma("unroll") for (int i = 0; i < 4; i++) bcur[i] = BR[i] & keep;   \
     __builtin_amdgcn_sched_barrier(0);                                      \
     __syncthreads();                                                        \
-    GEMM_LOAD(AR, BR, cc + D)                                               \
+    GEMM_LOAD(AR, BR, cc + 2)                                               \
     /* all 16 row operands of the chunk are requested from LDS before the first MFMA: with one \
        wave per SIMD nothing else hides the LDS latency */                  \
     u32x4 av[16];                                                           \
@@ -191,16 +191,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_mfma_kernel(const bf16_t* __rest
     }                                                                       \
   }
   GEMM_LOAD(a0, b0, c0)
-  if (D > 1) GEMM_LOAD(a1, b1, c0 + 1)
-  if (D > 2) GEMM_LOAD(a2, b2, c0 + 2)
-  if (D > 3) GEMM_LOAD(a3, b3, c0 + 3)
+  GEMM_LOAD(a1, b1, c0 + 1)
   // the barrier inside a stage also orders its LDS store after every wave's reads of the same
-  // buffer two chunks earlier (D is even, so stage parity equals chunk parity)
-  for (int c = c0; c < c1; c += D) {
+  // buffer two chunks earlier
+  for (int c = c0; c < c1; c += 2) {
     GEMM_STAGE(0, a0, b0)
     GEMM_STAGE(1, a1, b1)
-    GEMM_STAGE(2, a2, b2)
-    GEMM_STAGE(3, a3, b3)
   }
 #undef GEMM_LOAD
 #undef GEMM_STAGE
@@ -802,9 +798,9 @@ template <int MB>
 static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t* Wp, void* C, int M,
                         int N, int K, int epilogue, int cps) {
   if (epilogue == EPI_STORE)
-    gemm_mfma_kernel<EPI_STORE, 2, 4, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
+    gemm_mfma_kernel<EPI_STORE, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
   else
-    gemm_mfma_kernel<EPI_SWIGLU, 2, 4, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
+    gemm_mfma_kernel<EPI_SWIGLU, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
 }
 
 // Which kernel and how many K-slices: the cheapest by estimate (us), over at most kMaxSplits slices of
@@ -908,7 +904,6 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
   dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
-  // two chunks in flight: fewer registers, more resident workgroups (measured best at M = 128)
   if (M <= 32) gemm_launch<1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);      // row blocks in use (one row tile when < 4)
   else if (M <= 64) gemm_launch<2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
   else gemm_launch<4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
@@ -934,11 +929,11 @@ void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, flo
   dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
   const int cps = K / 64;
   if (M <= 32)
-    gemm_mfma_kernel<EPI_STORE_MAX, 2, 4, 1><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
+    gemm_mfma_kernel<EPI_STORE_MAX, 1><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
   else if (M <= 64)
-    gemm_mfma_kernel<EPI_STORE_MAX, 2, 4, 2><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
+    gemm_mfma_kernel<EPI_STORE_MAX, 2><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
   else
-    gemm_mfma_kernel<EPI_STORE_MAX, 2, 4, 4><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
+    gemm_mfma_kernel<EPI_STORE_MAX, 4><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
 }
 
 // One workgroup per row: combine the per-strip (max, sum) pairs in a fixed order and write
@@ -977,7 +972,7 @@ void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, in
     launch_dma<EPI_LSE, 4, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
   } else {
     dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
-    gemm_mfma_kernel<EPI_LSE, 2, 4, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
+    gemm_mfma_kernel<EPI_LSE, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
   }
   lse_finish_kernel<<<M, 256, 0, s>>>((const float2*)part, zt, V / 32, scale_c, lp);
 }
