@@ -196,18 +196,18 @@ void forward_generic(rl_model* m, int M, const RowMeta& r) {
   launch_embed<TW>(s, (const TW*)m->embed, r.tok, m->h, M, H);
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
-    launch_rmsnorm<TW, TA>(s, m->h, (const TW*)w.g_in, (TA*)m->xa, M, H, md.eps, false);
+    launch_rmsnorm<TW, TA>(s, m->h, (const TW*)w.g_in, (TA*)m->xa, M, H, md.eps);
     launch_gemm_generic<TA, TW>(s, (const TA*)m->xa, (const TW*)w.wqkv, m->qkv, M, qw + 2 * kvw, H, false);
-    launch_qkrope<TW, TA, TA, false>(s, m->qkv, 1, 0, (const TW*)w.gq, (const TW*)w.gk, m->rope_cs,
-                                     r.pos, r.slot, m->page_table, (TA*)m->qb, m->pools[l], md, M);
+    launch_qkrope<TW, TA, TA>(s, m->qkv, (const TW*)w.gq, (const TW*)w.gk, m->rope_cs, r.pos, r.slot,
+                              m->page_table, (TA*)m->qb, m->pools[l], md, M);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
     launch_attention_generic<TA, TA>(s, (const TA*)m->qb, m->pools[l], r.pos, r.slot, m->page_table,
                                      (TA*)m->xo, md, M);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
     launch_gemm_generic<TA, TW>(s, (const TA*)m->xo, (const TW*)w.wo, m->h, M, H, qw, true);
-    launch_rmsnorm<TW, TA>(s, m->h, (const TW*)w.g_post, (TA*)m->xa, M, H, md.eps, false);
+    launch_rmsnorm<TW, TA>(s, m->h, (const TW*)w.g_post, (TA*)m->xa, M, H, md.eps);
     launch_gemm_generic<TA, TW>(s, (const TA*)m->xa, (const TW*)w.wgu, m->gu, M, 2 * I, H, false);
-    launch_swiglu<TA>(s, m->gu, (TA*)m->xm, M, I, false);
+    launch_swiglu<TA>(s, m->gu, (TA*)m->xm, M, I);
     launch_gemm_generic<TA, TW>(s, (const TA*)m->xm, (const TW*)w.wdown, m->h, M, H, I, true);
   }
 }
@@ -242,9 +242,8 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, pf, qa);
     } else {
       int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, pq);
-      launch_qkrope<bf16_t, bf16_t, bf16_t, true>(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq,
-                                                  (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot,
-                                                  m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
+      launch_qkrope128(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs,
+                       r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
     }
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
     launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.items, r.n_items, r.merges, r.n_merges,
@@ -291,12 +290,12 @@ void lm_head_rows(rl_model* m, int M, int r0, int R, bool norm_done, int norm_ro
     }
   } else if (m->bf16) {
     if (!norm_done)
-      launch_rmsnorm<bf16_t, bf16_t>(s, m->h, (const bf16_t*)m->g_final, (bf16_t*)m->xa, norm_rows, md.H, md.eps, false);
+      launch_rmsnorm<bf16_t, bf16_t>(s, m->h, (const bf16_t*)m->g_final, (bf16_t*)m->xa, norm_rows, md.H, md.eps);
     launch_gemm_generic<bf16_t, bf16_t>(s, (const bf16_t*)m->xa + (size_t)r0 * md.H,
                                         (const bf16_t*)m->lm_head, m->logits, R, md.V, md.H, false);
   } else {
     if (!norm_done)
-      launch_rmsnorm<float, float>(s, m->h, (const float*)m->g_final, (float*)m->xa, norm_rows, md.H, md.eps, false);
+      launch_rmsnorm<float, float>(s, m->h, (const float*)m->g_final, (float*)m->xa, norm_rows, md.H, md.eps);
     launch_gemm_generic<float, float>(s, (const float*)m->xa + (size_t)r0 * md.H,
                                       (const float*)m->lm_head, m->logits, R, md.V, md.H, false);
   }

@@ -49,10 +49,9 @@ struct ModelDims {
 template <typename TW>
 void launch_embed(hipStream_t s, const TW* E, const int32_t* tok, float* h, int M, int H);
 
-// out = rmsnorm(h) * g.  ATILE: write `out` in A-tile layout (bf16 MFMA path).
+// out = rmsnorm(h) * g.
 template <typename TW, typename TA>
-void launch_rmsnorm(hipStream_t s, const float* h, const TW* g, TA* out, int M, int H, float eps,
-                    bool atile);
+void launch_rmsnorm(hipStream_t s, const float* h, const TW* g, TA* out, int M, int H, float eps);
 
 // C[M,N] (+)= A[M,K] * W[N,K]^T, fp32 accumulate, C row-major fp32.
 template <typename TA, typename TW>
@@ -60,13 +59,16 @@ void launch_gemm_generic(hipStream_t s, const TA* A, const TW* W, float* C, int 
                          bool accumulate);
 
 // q/k per-head RMSNorm (optional), rotate-half RoPE, q -> qout [M, nq*d] row-major, k and v into
-// the paged cache at (page_table[slot][pos/16], pos%16).  The projection arrives as n_part
-// split-K partial sums (qkv + p * part_stride), added here in ascending order.
-template <typename TW, typename TA, typename TKV, bool SWZ>
-void launch_qkrope(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const TW* gq,
-                   const TW* gk, const float* rope_cs, const int32_t* row_pos,
-                   const int32_t* row_slot, const int32_t* page_table, TA* qout, KvPool pool,
-                   const ModelDims& md, int M);
+// the paged cache at (page_table[slot][pos/16], pos%16).
+template <typename TW, typename TA, typename TKV>
+void launch_qkrope(hipStream_t s, const float* qkv, const TW* gq, const TW* gk, const float* rope_cs,
+                   const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table, TA* qout,
+                   KvPool pool, const ModelDims& md, int M);
+// The same for the MFMA path (head_dim 128, operand-order cache blocks).  The projection arrives as
+// n_part <= 8 split-K partial sums (qkv + p * part_stride), added here in ascending order.
+void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const bf16_t* gq,
+                      const bf16_t* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
+                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M);
 
 // h += sum of n_part split-K partial sums (ascending order), then out = rmsnorm(h) * g in A-tile
 // layout (bf16 MFMA path).  rows != null: gather: output row i is made from row rows[i] of h /
@@ -85,7 +87,7 @@ void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int
 
 // m = silu(gu[:, :I]) * gu[:, I:]
 template <typename TA>
-void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool atile);
+void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I);
 
 // ---- MFMA kernels (bf16, head_dim 128) -------------------------------------------------------
 enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4, EPI_QKV = 5, EPI_QKV8 = 6, EPI_ADD = 7 };

@@ -13,7 +13,7 @@ __global__ void embed_kernel(const TW* __restrict__ E, const int32_t* __restrict
   for (int j = threadIdx.x; j < H; j += blockDim.x) h[(size_t)row * H + j] = ldf(e + j);
 }
 
-template <typename TW, typename TA, bool ATILE>
+template <typename TW, typename TA>
 __global__ void rmsnorm_kernel(const float* __restrict__ h, const TW* __restrict__ g,
                                TA* __restrict__ out, int H, float eps) {
   __shared__ float red[4];
@@ -26,21 +26,7 @@ __global__ void rmsnorm_kernel(const float* __restrict__ h, const TW* __restrict
   __syncthreads();
   float tot = red[0] + red[1] + red[2] + red[3];
   float inv = 1.0f / sqrtf(tot / (float)H + eps);
-  if (ATILE) {
-    // 8 consecutive k share one 16-byte lane slot of the A-tile layout (H % 16 == 0)
-    for (int j = threadIdx.x * 8; j < H; j += 256 * 8) {
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        float y0 = x[j + 2 * e] * inv * ldf(g + j + 2 * e);
-        float y1 = x[j + 2 * e + 1] * inv * ldf(g + j + 2 * e + 1);
-        w[e] = (uint32_t)f2bf(y0) | ((uint32_t)f2bf(y1) << 16);
-      }
-      *(uint4*)((bf16_t*)out + atile_off(row, j, H)) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  } else {
-    for (int j = threadIdx.x; j < H; j += 256) stf(out + (size_t)row * H + j, x[j] * inv * ldf(g + j));
-  }
+  for (int j = threadIdx.x; j < H; j += 256) stf(out + (size_t)row * H + j, x[j] * inv * ldf(g + j));
 }
 
 // grid M, block 256: h[row] += sum_p parts[p][row]; out = rmsnorm(h[row]) * g, A-tile layout
@@ -314,9 +300,8 @@ __global__ __launch_bounds__(256) void gemm_mfma32_kernel(const TA* __restrict__
 }
 
 // grid (M, nq + 2 nkv), block 64
-template <typename TW, typename TA, typename TKV, bool SWZ>
-__global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t part_stride,
-                              const TW* __restrict__ gq,
+template <typename TW, typename TA, typename TKV>
+__global__ void qkrope_kernel(const float* __restrict__ qkv, const TW* __restrict__ gq,
                               const TW* __restrict__ gk, const float* __restrict__ rope_cs,
                               const int32_t* __restrict__ row_pos,
                               const int32_t* __restrict__ row_slot,
@@ -331,8 +316,7 @@ __global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t 
   float ss = 0.f;
   int cnt = 0;
   for (int i = threadIdx.x; i < half; i += 64, cnt++) {
-    float u = x[i], w = x[i + half];
-    for (int p = 1; p < n_part; p++) { u += x[p * part_stride + i]; w += x[p * part_stride + i + half]; }
+    const float u = x[i], w = x[i + half];
     x1[cnt] = u;
     x2[cnt] = w;
     ss += u * u + w * w;
@@ -351,8 +335,8 @@ __global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t 
   for (int i = threadIdx.x; i < half; i += 64, cnt++) {
     float a = x1[cnt], b = x2[cnt];
     if (is_v) {
-      stf(blk + vblk_off<SWZ>(tok, i, d), a);
-      stf(blk + vblk_off<SWZ>(tok, i + half, d), b);
+      stf(blk + tok * d + i, a);
+      stf(blk + tok * d + i + half, b);
       continue;
     }
     if (qk_norm) { a = a * inv * ldf(g + i); b = b * inv * ldf(g + i + half); }
@@ -362,8 +346,8 @@ __global__ void qkrope_kernel(const float* __restrict__ qkv, int n_part, size_t 
       stf(qout + (size_t)row * nq * d + (size_t)hd * d + i, y1);
       stf(qout + (size_t)row * nq * d + (size_t)hd * d + i + half, y2);
     } else {
-      stf(blk + kblk_off<SWZ>(tok, i, d), y1);
-      stf(blk + kblk_off<SWZ>(tok, i + half, d), y2);
+      stf(blk + tok * d + i, y1);
+      stf(blk + tok * d + i + half, y2);
     }
   }
 }
@@ -456,15 +440,14 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(
   }
 }
 
-template <typename TA, bool ATILE>
+template <typename TA>
 __global__ void swiglu_kernel(const float* __restrict__ gu, TA* __restrict__ m, int I) {
   int row = blockIdx.y;
   int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= I) return;
   float g = gu[(size_t)row * 2 * I + j], u = gu[(size_t)row * 2 * I + I + j];
   float y = g / (1.0f + expf(-g)) * u;
-  if (ATILE) stf(m + atile_off(row, j, I), y);
-  else stf(m + (size_t)row * I + j, y);
+  stf(m + (size_t)row * I + j, y);
 }
 
 // grid (pairs, 2 n_layers): one page of one pool
@@ -492,14 +475,11 @@ template void launch_embed<float>(hipStream_t, const float*, const int32_t*, flo
 template void launch_embed<bf16_t>(hipStream_t, const bf16_t*, const int32_t*, float*, int, int);
 
 template <typename TW, typename TA>
-void launch_rmsnorm(hipStream_t s, const float* h, const TW* g, TA* out, int M, int H, float eps,
-                    bool atile) {
-  if (M <= 0) return;
-  if (atile) rmsnorm_kernel<TW, TA, true><<<M, 256, 0, s>>>(h, g, out, H, eps);
-  else rmsnorm_kernel<TW, TA, false><<<M, 256, 0, s>>>(h, g, out, H, eps);
+void launch_rmsnorm(hipStream_t s, const float* h, const TW* g, TA* out, int M, int H, float eps) {
+  if (M > 0) rmsnorm_kernel<TW, TA><<<M, 256, 0, s>>>(h, g, out, H, eps);
 }
-template void launch_rmsnorm<float, float>(hipStream_t, const float*, const float*, float*, int, int, float, bool);
-template void launch_rmsnorm<bf16_t, bf16_t>(hipStream_t, const float*, const bf16_t*, bf16_t*, int, int, float, bool);
+template void launch_rmsnorm<float, float>(hipStream_t, const float*, const float*, float*, int, int, float);
+template void launch_rmsnorm<bf16_t, bf16_t>(hipStream_t, const float*, const bf16_t*, bf16_t*, int, int, float);
 
 template <typename TA, typename TW>
 void launch_gemm_generic(hipStream_t s, const TA* A, const TW* W, float* C, int M, int N, int K,
@@ -626,36 +606,32 @@ __global__ __launch_bounds__(256) void qkrope128_kernel(
   }
 }
 
-template <typename TW, typename TA, typename TKV, bool SWZ>
-void launch_qkrope(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const TW* gq,
-                   const TW* gk, const float* rope_cs, const int32_t* row_pos,
-                   const int32_t* row_slot, const int32_t* page_table, TA* qout, KvPool pool,
-                   const ModelDims& md, int M) {
+void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const bf16_t* gq,
+                      const bf16_t* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
+                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M) {
   if (M <= 0) return;
-  if constexpr (SWZ) {
-    if (md.d == 128 && n_part <= 8) {
-      dim3 grid128(M, (md.nq + 2 * md.nkv + 15) / 16);
-      if (md.kv_fp8)
-        qkrope128_kernel<true><<<grid128, 256, 0, s>>>(qkv, n_part, part_stride, gq, gk, rope_cs, row_pos,
-                                                       row_slot, page_table, qout, (bf16_t*)pool.k,
-                                                       (bf16_t*)pool.v, md.nq, md.nkv, md.eps, md.qk_norm,
-                                                       md.max_pages_per_traj);
-      else
-        qkrope128_kernel<false><<<grid128, 256, 0, s>>>(qkv, n_part, part_stride, gq, gk, rope_cs, row_pos,
-                                                        row_slot, page_table, qout, (bf16_t*)pool.k,
-                                                        (bf16_t*)pool.v, md.nq, md.nkv, md.eps, md.qk_norm,
-                                                        md.max_pages_per_traj);
-      return;
-    }
-  }
-  dim3 grid(M, md.nq + 2 * md.nkv);
-  qkrope_kernel<TW, TA, TKV, SWZ><<<grid, 64, 0, s>>>(
-      qkv, n_part, part_stride, gq, gk, rope_cs, row_pos, row_slot, page_table, qout, (TKV*)pool.k,
-      (TKV*)pool.v, md.nq, md.nkv, md.d, md.eps, md.qk_norm, md.max_pages_per_traj);
+  const dim3 grid(M, (md.nq + 2 * md.nkv + 15) / 16);
+  auto go = [&](auto kernel) {
+    kernel<<<grid, 256, 0, s>>>(qkv, n_part, part_stride, gq, gk, rope_cs, row_pos, row_slot, page_table, qout,
+                                (bf16_t*)pool.k, (bf16_t*)pool.v, md.nq, md.nkv, md.eps, md.qk_norm,
+                                md.max_pages_per_traj);
+  };
+  if (md.kv_fp8) go(qkrope128_kernel<true>);
+  else go(qkrope128_kernel<false>);
 }
-template void launch_qkrope<float, float, float, false>(hipStream_t, const float*, int, size_t, const float*, const float*, const float*, const int32_t*, const int32_t*, const int32_t*, float*, KvPool, const ModelDims&, int);
-template void launch_qkrope<bf16_t, bf16_t, bf16_t, false>(hipStream_t, const float*, int, size_t, const bf16_t*, const bf16_t*, const float*, const int32_t*, const int32_t*, const int32_t*, bf16_t*, KvPool, const ModelDims&, int);
-template void launch_qkrope<bf16_t, bf16_t, bf16_t, true>(hipStream_t, const float*, int, size_t, const bf16_t*, const bf16_t*, const float*, const int32_t*, const int32_t*, const int32_t*, bf16_t*, KvPool, const ModelDims&, int);
+
+template <typename TW, typename TA, typename TKV>
+void launch_qkrope(hipStream_t s, const float* qkv, const TW* gq, const TW* gk, const float* rope_cs,
+                   const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table, TA* qout,
+                   KvPool pool, const ModelDims& md, int M) {
+  if (M <= 0) return;
+  dim3 grid(M, md.nq + 2 * md.nkv);
+  qkrope_kernel<TW, TA, TKV><<<grid, 64, 0, s>>>(qkv, gq, gk, rope_cs, row_pos, row_slot, page_table, qout,
+                                                 (TKV*)pool.k, (TKV*)pool.v, md.nq, md.nkv, md.d, md.eps,
+                                                 md.qk_norm, md.max_pages_per_traj);
+}
+template void launch_qkrope<float, float, float>(hipStream_t, const float*, const float*, const float*, const float*, const int32_t*, const int32_t*, const int32_t*, float*, KvPool, const ModelDims&, int);
+template void launch_qkrope<bf16_t, bf16_t, bf16_t>(hipStream_t, const float*, const bf16_t*, const bf16_t*, const float*, const int32_t*, const int32_t*, const int32_t*, bf16_t*, KvPool, const ModelDims&, int);
 
 template <typename TA, typename TKV>
 void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int32_t* row_pos,
@@ -676,14 +652,11 @@ template void launch_attention_generic<float, float>(hipStream_t, const float*, 
 template void launch_attention_generic<bf16_t, bf16_t>(hipStream_t, const bf16_t*, KvPool, const int32_t*, const int32_t*, const int32_t*, bf16_t*, const ModelDims&, int);
 
 template <typename TA>
-void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I, bool atile) {
-  if (M <= 0) return;
-  dim3 grid((I + 255) / 256, M);
-  if (atile) swiglu_kernel<TA, true><<<grid, 256, 0, s>>>(gu, m, I);
-  else swiglu_kernel<TA, false><<<grid, 256, 0, s>>>(gu, m, I);
+void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I) {
+  if (M > 0) swiglu_kernel<TA><<<dim3((I + 255) / 256, M), 256, 0, s>>>(gu, m, I);
 }
-template void launch_swiglu<float>(hipStream_t, const float*, float*, int, int, bool);
-template void launch_swiglu<bf16_t>(hipStream_t, const float*, bf16_t*, int, int, bool);
+template void launch_swiglu<float>(hipStream_t, const float*, float*, int, int);
+template void launch_swiglu<bf16_t>(hipStream_t, const float*, bf16_t*, int, int);
 
 void launch_copy_pages(hipStream_t s, char* const* pools, int n_layers, const int32_t* pairs, int n_pairs,
                        size_t page_bytes) {

@@ -102,26 +102,6 @@ __device__ __forceinline__ void e4m3x4_to_bf16(uint32_t w, uint32_t* lo, uint32_
   *lo = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false));
   *hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true));
 }
-// Two raw 16-byte lane slots of an 8-bit block -> the four 16-byte operand registers that the
-// bf16 block of the same tokens would have delivered (same rule for keys and values).
-__device__ __forceinline__ void expand_e4m3_block(const u32x4 (&raw)[2], u32x4 (&out)[4]) {
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    uint32_t a, b, c, d;
-    e4m3x4_to_bf16(raw[i >> 1][2 * (i & 1)], &a, &b);
-    e4m3x4_to_bf16(raw[i >> 1][2 * (i & 1) + 1], &c, &d);
-    out[i] = (u32x4){a, b, c, d};
-  }
-}
-
-template <bool SWZ>
-__device__ __forceinline__ int kblk_off(int tok, int d, int D) {
-  return SWZ ? kswz_off(tok, d) : tok * D + d;
-}
-template <bool SWZ>
-__device__ __forceinline__ int vblk_off(int tok, int d, int D) {
-  return SWZ ? vswz_off(tok, d) : tok * D + d;
-}
 
 // Reductions over the four lanes {n, n + 16, n + 32, n + 48} (the four token groups of one MFMA
 // column) with the gfx950 row-swap instructions: swapping a register with itself puts lanes
