@@ -452,7 +452,7 @@ __device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
 __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
                "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
 
 template <int EPI, int MB, int NBW>
