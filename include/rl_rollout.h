@@ -249,6 +249,18 @@ int rl_sample_device_logits(const float* d_logits, int32_t rows, int32_t vocab, 
 uint32_t rl_uniform_u32(uint64_t seed, int32_t traj_id, int32_t position);
 
 /*
+ * Which kernel variant every matrix product of a forward pass over `rows` rows takes on the MFMA path of a model with
+ * configuration cfg, loaded for passes of up to max_rows rows (the larger of max_batch_rows and
+ * max_trajectories): host arithmetic only, for tests and profiles.  out: 6 records of 4 ints (kernel: 0 128 x 128
+ * tiles, 1 256-row tiles, 2 decode tiles of 64 or 128 rows, 3 128 x 256 tiles; its width: 64-column groups of a
+ * 256-row tile, 16-column blocks of a decode tile; K-slices; epilogue: 0 stored, 2 SwiGLU, 3 log-softmax, 5
+ * QK-norm + RoPE + cache write, 7 added to the residual stream) for QKV, O, gate-up, down, the lm-head of a
+ * log-prob pass over `rows` sampled tokens, and the lm-head that stores `rows` rows of logits outside a drawn step.
+ * Errors: ARG (also a shape that the MFMA kernels do not take).
+ */
+int rl_debug_pass_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);
+
+/*
  * Kernel timing for benchmarks: when enabled, every `every`-th decode step brackets its
  * decode-attention launches with HIP events on the engine's stream.  rl_timing_read returns
  * the accumulated duration, the number of timed launches and the bytes of keys / values

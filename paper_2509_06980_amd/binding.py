@@ -12,7 +12,7 @@ EXPORTED_SYMBOLS = [
     "rl_traj_read", "rl_free_pages", "rl_recompute_logprobs", "rl_debug_logits",
     "rl_decode_step_forced", "rl_sample_from_logits", "rl_sample_device_logits", "rl_uniform_u32", "rl_timing_enable",
     "rl_timing_read", "rl_timing_read_steps", "rl_timing_read_decode_bytes", "rl_measure_stream_read",
-    "rl_decode_step_with_appends", "rl_decode_step_forced_with_appends", "rl_grpo_objective",
+    "rl_decode_step_with_appends", "rl_decode_step_forced_with_appends", "rl_grpo_objective", "rl_debug_pass_plan",
 ]
 
 
@@ -79,6 +79,7 @@ def load_library():
                                       C.c_float, C.c_double, C.c_double, C.c_double, C.c_int32,
                                       C.POINTER(C.c_double), C.POINTER(C.c_double),
                                       C.POINTER(C.c_int64), C.POINTER(C.c_double)]
+    lib.rl_debug_pass_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
     lib.rl_debug_logits.argtypes = [C.c_void_p, C.c_int32, _F32P]
     lib.rl_sample_from_logits.argtypes = [_F32P, C.c_int32, C.c_int32, C.c_float, _U32P, _I32P, _F32P]
     lib.rl_sample_device_logits.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_float, C.c_void_p,
@@ -115,6 +116,17 @@ def measure_stream_read(nbytes=1 << 31, iters=10):
     out = C.c_double()
     _check(load_library().rl_measure_stream_read(C.c_size_t(int(nbytes)), int(iters), C.byref(out)))
     return out.value
+
+
+def debug_pass_plan(shape, rows, max_rows=8192):
+    """{product: (kernel, width, K-slices, epilogue)} of a forward pass over `rows` rows on the MFMA path; `shape`: an
+    object with the fields of the model configuration."""
+    cfg = _ModelConfig(*[getattr(shape, n) for n, _ in _ModelConfig._fields_])
+    out = (C.c_int32 * 24)()
+    _check(load_library().rl_debug_pass_plan(C.byref(cfg), int(rows), max(int(rows), int(max_rows)), out))
+    kernels, epilogues = ("tile128", "tile256", "decode", "wide128"), {0: "store", 2: "swiglu", 3: "logprob", 5: "qkv", 7: "add"}
+    return {name: (kernels[out[4 * i]], out[4 * i + 1], out[4 * i + 2], epilogues[out[4 * i + 3]])
+            for i, name in enumerate(("qkv", "o", "gate_up", "down", "score_head", "logits_head"))}
 
 
 def sample_from_logits(logits, temperature, u32):

@@ -212,36 +212,56 @@ void forward_generic(rl_model* m, int M, const RowMeta& r) {
   }
 }
 
+// Rows of the split-K partial-sum buffers: one pass of `cap` rows, and up to kMaxSplits slices of passes of up
+// to 1024 rows.  plan_gemm keeps slices times rows within them.
+size_t partial_rows(size_t cap) { return std::max<size_t>(cap, (size_t)kMaxSplits * std::min<size_t>(cap, 1024)); }
+
+// The products of one pass over M rows, the same for every layer.
+struct PassPlan {
+  GemmPlan q, o, g, d;      // QKV, O, gate-up, down
+  bool fused_qkv;           // QK-norm, RoPE and the cache write in the epilogue of QKV
+  int eo, ed;               // epilogues of O and down: EPI_ADD or EPI_STORE
+};
+PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
+  const int H = md.H, qw = md.nq * md.d, QW = qw + 2 * md.nkv * md.d, I = md.I;
+  PassPlan p;
+  p.q = plan_gemm(M, QW, H, EPI_STORE, part_rows);
+  p.o = plan_gemm(M, H, qw, EPI_STORE, part_rows);
+  p.g = plan_gemm(M, 2 * I, H, EPI_SWIGLU, part_rows);
+  p.d = plan_gemm(M, H, I, EPI_STORE, part_rows);
+  // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
+  // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
+  const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
+  p.fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) && pf.cost <= p.q.cost + 3.0 + 0.0098 * M;
+  if (p.fused_qkv) p.q = pf;
+  // the residual add inside the products that leave one partial sum (the norm then reads one array instead
+  // of two and writes none back)
+  auto adds = [](const GemmPlan& g) { return g.splits == 1 && (g.kind == GEMM_TILE256 || g.kind == GEMM_WIDE128); };
+  p.eo = adds(p.o) ? EPI_ADD : EPI_STORE;
+  p.ed = adds(p.d) ? EPI_ADD : EPI_STORE;
+  return p;
+}
+
 // Leaves the last down-projection as m->pending_parts partial sums in m->ph (added by the next
 // add_rmsnorm: the next layer's, or the final norm before the lm-head).
 void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   hipStream_t s = m->stream;
   const ModelDims& md = m->md;
   int H = md.H, qw = md.nq * md.d, kvw = md.nkv * md.d, I = md.I, QW = qw + 2 * kvw;
-  // the same for every layer
-  const GemmPlan pq = plan_gemm(M, QW, H, EPI_STORE, m->part_rows), po = plan_gemm(M, H, qw, EPI_STORE, m->part_rows);
-  const GemmPlan pg = plan_gemm(M, 2 * I, H, EPI_SWIGLU, m->part_rows), pd = plan_gemm(M, H, I, EPI_STORE, m->part_rows);
-  // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
-  // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
-  const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
-  const bool fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) && pf.cost <= pq.cost + 3.0 + 0.0098 * M;
-  // the residual add inside the products that leave one partial sum (the norm then reads one array instead
-  // of two and writes none back)
-  auto adds = [](const GemmPlan& p) { return p.splits == 1 && (p.kind == GEMM_TILE256 || p.kind == GEMM_WIDE128); };
-  const int eo = adds(po) ? EPI_ADD : EPI_STORE, ed = adds(pd) ? EPI_ADD : EPI_STORE;
-  float *const co = eo == EPI_ADD ? m->h : m->ph, *const cd = ed == EPI_ADD ? m->h : m->ph;
+  const PassPlan plan = plan_pass(md, M, m->part_rows);
+  float *const co = plan.eo == EPI_ADD ? m->h : m->ph, *const cd = plan.ed == EPI_ADD ? m->h : m->ph;
   int pend = 0;
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
     if (l == 0) launch_embed_rmsnorm(s, (const bf16_t*)m->embed, r.tok, m->h, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
     else launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
-    if (fused_qkv) {
+    if (plan.fused_qkv) {
       const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
                        (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,
                        md.max_pages_per_traj, md.eps};
-      launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, pf, qa);
+      launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, plan.q, qa);
     } else {
-      int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, pq);
+      int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, plan.q);
       launch_qkrope128(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs,
                        r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
     }
@@ -252,10 +272,10 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.pf_items, r.n_pf_items, nullptr, 0,
                             nullptr, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, true);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
-    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, co, M, H, qw, eo, po);
+    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, co, M, H, qw, plan.eo, plan.o);
     launch_add_rmsnorm(s, m->h, m->ph, so, (size_t)M * H, (const bf16_t*)w.g_post, (bf16_t*)m->xa, M, H, md.eps);
-    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, pg);
-    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, cd, M, H, I, ed, pd);
+    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, plan.g);
+    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, cd, M, H, I, plan.ed, plan.d);
   }
   m->pending_parts = pend;
 }
@@ -1095,9 +1115,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   size_t Mc = m->Mcap;
   size_t ael = m->bf16 ? 2 : 4;
   TRY(m->dalloc((void**)&m->h, Mc * H * 4, true));
-  // split-K partial sums: up to kMaxSplits slices of a decode-sized batch, or one prefill pass
-  // up to kMaxSplits slices for passes of up to 1024 rows (plan_gemm also clamps to this capacity)
-  size_t prow = m->mfma ? std::max<size_t>(Mc, (size_t)kMaxSplits * std::min<size_t>(Mc, 1024)) : Mc;
+  const size_t prow = m->mfma ? partial_rows(Mc) : Mc;
   m->part_rows = prow;
   TRY(m->dalloc((void**)&m->qkv, prow * (qw + 2 * kvw) * 4, true));
   if (m->mfma) TRY(m->dalloc((void**)&m->ph, prow * H * 4, true));
@@ -1661,6 +1679,26 @@ extern "C" int rl_sample_from_logits(const float* logits, int32_t rows, int32_t 
   if (e != hipSuccess) rc = fail(RL_E_HIP, hipGetErrorString(e));
   (void)hipFree(buf);
   return rc;
+}
+
+extern "C" int rl_debug_pass_plan(const rl_model_config* c, int32_t rows, int32_t max_rows, int32_t* out) {
+  if (!c || !out || rows <= 0 || max_rows < rows) return fail(RL_E_ARG, "bad argument");
+  if (c->n_layers <= 0 || c->hidden <= 0 || c->n_q_heads <= 0 || c->n_kv_heads <= 0 || c->intermediate <= 0 ||
+      c->vocab <= 0 || c->n_q_heads % c->n_kv_heads != 0 || !mfma_shape_ok(*c))
+    return fail(RL_E_ARG, "not a shape of the MFMA kernels");
+  const ModelDims md{c->n_layers, c->hidden, c->n_q_heads, c->n_kv_heads, c->head_dim, c->intermediate,
+                     c->vocab, c->rms_eps, c->qk_norm, 1, 0};
+  const PassPlan p = plan_pass(md, rows, partial_rows((size_t)round_up(max_rows, 128)));
+  auto put = [&](int at, const GemmPlan& g, int epilogue) {
+    out[4 * at] = g.kind; out[4 * at + 1] = g.width; out[4 * at + 2] = g.splits; out[4 * at + 3] = epilogue;
+  };
+  put(0, p.q, p.fused_qkv ? EPI_QKV : EPI_STORE);
+  put(1, p.o, p.eo);
+  put(2, p.g, EPI_SWIGLU);
+  put(3, p.d, p.ed);
+  put(4, plan_gemm(rows, md.V, md.H, EPI_LSE, 0), EPI_LSE);
+  put(5, plan_gemm(rows, md.V, md.H, EPI_STORE, 0), EPI_STORE);
+  return RL_OK;
 }
 
 extern "C" int rl_timing_enable(rl_model* m, int32_t every) {

@@ -1,0 +1,92 @@
+"""The choice of kernel and K-slices for the products of a pass (host arithmetic of the library)."""
+import os
+import random
+
+import pytest
+
+import paper_2509_06980_amd as rl
+from synthetic import SHAPES
+
+PRODUCTS = ("qkv", "o", "gate_up", "down", "score_head", "logits_head")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    if not os.path.exists(rl.LIB_PATH):
+        from paper_2509_06980_amd import build
+        build.build()
+    return rl.load_library()
+
+
+def _dims(s):
+    """product -> (N, K)"""
+    return dict(qkv=(s.q_width + 2 * s.kv_width, s.hidden), o=(s.hidden, s.q_width), gate_up=(2 * s.intermediate, s.hidden),
+                down=(s.hidden, s.intermediate), score_head=(s.vocab, s.hidden), logits_head=(s.vocab, s.hidden))
+
+
+def test_plans_stay_within_what_kernels_and_buffers_take():
+    rng = random.Random(5)
+    taken = set()
+    for _ in range(3000):
+        nkv = rng.choice([1, 2, 3, 4, 8, 16, 32])
+        s = SHAPES["small-d128"].replace(
+            hidden=64 * rng.randint(1, 96), n_kv_heads=nkv, n_q_heads=nkv * rng.choice([1, 2, 4, 8]),
+            intermediate=64 * rng.randint(1, 256), vocab=32 * rng.choice([1, 3, 128, 1000, 4748]))
+        rows = int(round(2 ** rng.uniform(0, 13)))
+        cap = max(rows, rng.choice([rows, 128, 1024, 8192]))
+        cap += -cap % 128
+        partial = max(cap, 8 * min(cap, 1024))            # rows of the partial-sum buffers
+        for name, (kernel, width, slices, epilogue) in rl.debug_pass_plan(s, rows, cap).items():
+            n, k = _dims(s)[name]
+            taken.add((kernel, width, min(slices, 2), epilogue))
+            assert 1 <= slices <= 8 and (slices == 1 or (epilogue == "store" and name != "logits_head"))
+            assert slices * rows <= max(partial, rows)
+            if epilogue in ("qkv", "add"):
+                assert kernel in ("tile256", "wide128") and rows > 128 and slices == 1
+                assert epilogue != "qkv" or width == 4                # a wave's 128 columns are a head
+            if kernel == "decode":
+                assert rows <= 128 and width in (2, 4, 5, 6)
+                depth = 128 if width == 5 else 64
+                assert k % depth == 0
+                per = -(-(k // depth) // slices)
+                assert (slices - 1) * per < k // depth                # no slice is empty
+            elif kernel in ("tile256", "wide128"):
+                assert rows > 128 and width in ((4, 5) if kernel == "tile256" else (4,))
+                per = -(-(k // 32) // slices)
+                assert (slices - 1) * per < k // 32
+            else:
+                assert kernel == "tile128"
+    # every variant that the library holds is some size's choice
+    for variant in [("decode", w, 1, e) for w in (2, 4, 5, 6) for e in ("store", "swiglu")] + \
+            [("tile256", w, 1, e) for w in (4, 5) for e in ("add", "swiglu")] + [("tile256", 4, 1, e) for e in ("qkv", "logprob", "store")] + \
+            [("wide128", 4, 1, e) for e in ("add", "swiglu", "qkv", "store")] + \
+            [("tile128", 0, 1, e) for e in ("store", "swiglu", "logprob")] + \
+            [(kernel, w, 2, "store") for kernel, w in (("decode", 2), ("decode", 4), ("tile256", 4), ("tile256", 5), ("wide128", 4), ("tile128", 0))]:
+        assert variant in taken, variant
+
+
+@pytest.mark.parametrize("rows", [1, 64, 128, 129, 600, 8192])
+def test_weights_beyond_a_buffer_descriptor_keep_64_bit_addresses(rows):
+    # N x K bf16 weights of 0x7fff0000 bytes and more: loads with the LDS destination have 31-bit offsets
+    base = SHAPES["qwen3-8b"]
+    for over, name, change in ((True, "score_head", dict(vocab=262144)), (False, "score_head", dict(vocab=262016)),
+                               (True, "gate_up", dict(intermediate=131072)), (False, "gate_up", dict(intermediate=131008)),
+                               (True, "down", dict(intermediate=262144)), (False, "down", dict(intermediate=262016))):
+        s = base.replace(**change)
+        n, k = _dims(s)[name]
+        assert (2 * n * k >= 0x7FFF0000) == over
+        plan = rl.debug_pass_plan(s, rows)
+        if over:
+            assert plan[name][0] == "tile128"
+            assert name != "score_head" or plan["logits_head"][0] == "tile128"
+        elif rows == 8192:                                        # the limit decides, not the estimate
+            assert plan[name][0] != "tile128"
+
+
+def test_pass_plan_refuses_what_the_matrix_kernels_do_not_take():
+    s = SHAPES["small-d128"]
+    for bad, rows in ((s.replace(head_dim=64), 1), (s.replace(weight_dtype=0), 1), (s.replace(hidden=96), 1),
+                      (s.replace(n_q_heads=6), 1), (s.replace(vocab=100), 1), (s, 0)):
+        with pytest.raises(rl.RolloutError) as ei:
+            rl.debug_pass_plan(bad, rows)
+        assert ei.value.code == -1
