@@ -229,10 +229,19 @@ PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   p.o = plan_gemm(M, H, qw, EPI_STORE, part_rows);
   p.g = plan_gemm(M, 2 * I, H, EPI_SWIGLU, part_rows);
   p.d = plan_gemm(M, H, I, EPI_STORE, part_rows);
-  // norm, RoPE and cache write inside the projection where 256-row tiles without K-slices pay: the
-  // separate kernel costs about 3 us + 9.8 ns a row (8192 rows: 80 us)
+  // Norm, RoPE and cache write inside the projection where that is expected to pay.  Per million values of the
+  // projection the separate kernel takes 1.6 us (a bit less with the 8-bit cache) and 0.5 us more for every further
+  // K-slice that it adds, the epilogue 0.55 us; 4.5 and 3 to 4.5 us come on top.  The remaining constants make up for
+  // what the estimates of the two products are off by (128 x 256 tiles: 0.45 us per million values).  Fitted on 8 shapes
+  // (1280 to 12288 columns, hidden 512 to 5120), 129 to 8192 rows and both caches: the slower way is taken
+  // in 8 of 124 cases, by more than 3 % in two (12288 columns, 1300 rows: 171 against 164 us); with a cost by rows
+  // alone it was in 12, by up to 15 % (12288 columns, 300 rows: 80.5 against 70.3 us; 6144 columns of hidden 4096,
+  // 3072 rows: 172.2 against 160.7 us).
   const GemmPlan pf = plan_gemm(M, QW, H, EPI_QKV, 0);
-  p.fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) && pf.cost <= p.q.cost + 3.0 + 0.0098 * M;
+  const double mval = 1e-6 * M * QW;
+  p.fused_qkv = (pf.kind == GEMM_TILE256 || pf.kind == GEMM_WIDE128) &&
+                pf.cost + (pf.kind == GEMM_WIDE128 ? 0.45 : 0.0) * mval <=
+                    p.q.cost + 2.0 + (1.0 + 0.65 * (p.q.splits - 1)) * mval;
   if (p.fused_qkv) p.q = pf;
   // the residual add inside the products that leave one partial sum (the norm then reads one array instead
   // of two and writes none back)

@@ -65,6 +65,17 @@ def test_plans_stay_within_what_kernels_and_buffers_take():
         assert variant in taken, variant
 
 
+@pytest.mark.parametrize("heads,hidden,rows,fused", [
+    ((32, 32), 4096, 300, True),                 # four K-slices of a wide projection: 80.5 us apart, 70.3 us in one
+    ((32, 8), 4096, 3072, False),                # 160.7 us apart, 172.2 us in one
+    ((32, 32), 4096, 1536, False),               # 168.6 / 173.0
+    ((32, 8), 2560, 8192, True), ((32, 8), 2560, 587, False), ((16, 8), 1024, 2048, True), ((32, 8), 4096, 8192, True),
+])
+def test_projection_epilogue_follows_the_width(heads, hidden, rows, fused):
+    s = SHAPES["small-d128"].replace(n_q_heads=heads[0], n_kv_heads=heads[1], hidden=hidden)
+    assert (rl.debug_pass_plan(s, rows)["qkv"][3] == "qkv") == fused
+
+
 @pytest.mark.parametrize("rows", [1, 64, 128, 129, 600, 8192])
 def test_weights_beyond_a_buffer_descriptor_keep_64_bit_addresses(rows):
     # N x K bf16 weights of 0x7fff0000 bytes and more: loads with the LDS destination have 31-bit offsets
