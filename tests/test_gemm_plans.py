@@ -5,6 +5,7 @@ import random
 import pytest
 
 import paper_2509_06980_amd as rl
+from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, small
 from synthetic import SHAPES
 
 PRODUCTS = ("qkv", "o", "gate_up", "down", "score_head", "logits_head")
@@ -101,3 +102,32 @@ def test_pass_plan_refuses_what_the_matrix_kernels_do_not_take():
         with pytest.raises(rl.RolloutError) as ei:
             rl.debug_pass_plan(bad, rows)
         assert ei.value.code == -1
+
+
+@pytest.mark.parametrize("change,lens,sampled,takes", MANY_ROWS + MANY_ROWS_ORACLE)
+def test_many_row_cases_reach_the_variants_that_they_are_there_for(change, lens, sampled, takes):
+    rows = dict(append=sum(n - 1 for n in lens), recompute=sum(n + sampled - 1 for n in lens), score=sampled * len(lens))
+    for part, products in takes.items():
+        assert rows[part] <= 8192                                  # one pass
+        plan = rl.debug_pass_plan(small(**change), rows[part])
+        assert {name: plan[name] for name in products} == products
+
+
+def test_decode_cases_reach_every_tile():
+    seen = set()
+    for change in DECODE:
+        s = small(**change)
+        for rows in DECODE_ROWS:
+            for name, (kernel, width, slices, epilogue) in rl.debug_pass_plan(s, rows).items():
+                if kernel != "decode" or name in ("score_head", "logits_head"):
+                    continue
+                n, k = _dims(s)[name]
+                stages = k // (128 if width == 5 else 64)
+                seen |= {(width, epilogue, rows > 64), (width, epilogue, rows > 64, "ends inside" if n % (16 * width) else "whole"),
+                         (width, epilogue, rows > 64, "unequal slices" if stages % slices else "equal slices")}
+    for more in (False, True):                                     # one and two 16-row blocks a wave
+        for width in (2, 4, 5, 6):
+            assert (width, "store", more) in seen and (width, "swiglu", more) in seen
+            assert (width, "store", more, "unequal slices") in seen
+        for width in (5, 6):                                       # every width is a multiple of 64
+            assert (width, "store", more, "ends inside") in seen and (width, "swiglu", more, "ends inside") in seen

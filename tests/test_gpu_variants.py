@@ -3,7 +3,10 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
+from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, small
 from oracle import OracleEngine
+from oracle.bf16_error_model import forward_bf16_model
+from oracle.decoder import forward_full
 from oracle.sampler import sample_token
 from synthetic import SHAPES, make_weight_blob
 
@@ -106,6 +109,9 @@ def test_decode_attention_cuts_and_merges(name, lens):
         assert np.abs(la - lb).max() < 3e-2          # two bf16 paths, the bound of the parity tests
     za, zb = a.debug_logits(ids[-1]), b.debug_logits(ids[-1])
     assert np.abs(za - zb).max() < 3e-2
+    o = OracleEngine(blob, **kw)                         # the last trajectory, as it stands now
+    o.append_observation(ids[-1:], a.traj_read(ids[-1])[0], [lens[-1] + 2])
+    assert np.abs(za - o.debug_logits(ids[-1])).max() < 3e-2
     a.close(), b.close()
 
 
@@ -134,19 +140,10 @@ def test_fp32_products_and_attention_at_the_edges(change, lens):
 
 
 @pytest.mark.parametrize("kv8", [False, True])
-@pytest.mark.parametrize("change,lens,sampled", [
-    (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [2048, 2049], 2),   # 4095 rows, last tile one row short
-    (dict(hidden=1024, n_q_heads=16, n_kv_heads=8, intermediate=3072, vocab=4096), [3713], 2),         # 30 row tiles of 128 (29 + 1 row)
-    (dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=32768), [5, 3000], 130),    # 10 heads, 320-column tiles, odd strips
-    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [300, 288], 1),     # K-slices of 128- and 256-row tiles
-    (dict(hidden=2560, n_q_heads=32, n_kv_heads=8, intermediate=9728, vocab=4096), [130, 3], 1),       # 132 rows: a second tile of 4
-    (dict(hidden=2560, n_q_heads=4, n_kv_heads=1, intermediate=256, vocab=512), [3950, 3907], 0),      # 320 columns with the residual add, a last tile of 177 rows
-    (dict(hidden=2560, n_q_heads=31, n_kv_heads=31, intermediate=9728, vocab=4096), [901], 1),         # an odd number of heads in 256 columns
-])
-def test_many_row_products(change, lens, sampled, kv8):
-    # the 256-row tiles (256 and 320 columns, K-slices, SwiGLU, QK-norm + RoPE + cache write and log-softmax
-    # in the epilogue) at row counts and widths that end inside a tile, against the shape-generic kernels
-    shape = SHAPES["small-d128"].replace(n_layers=1, **change)
+@pytest.mark.parametrize("change,lens,sampled,takes", MANY_ROWS)
+def test_many_row_products(change, lens, sampled, takes, kv8):
+    # long trajectories and real widths against the shape-generic kernels (the 8-bit cache coarsely: its own oracle is below)
+    shape = small(**change)
     blob = make_weight_blob(shape, seed=6, weight_std=0.02, gain_std=0.1)
     kw = dict(max_context=4096, max_trajectories=4, kv_pool_pages=520)
     a = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, **kw)
@@ -171,14 +168,45 @@ def test_many_row_products(change, lens, sampled, kv8):
     a.close(), b.close()
 
 
-@pytest.mark.parametrize("change", [dict(), dict(hidden=2560, n_q_heads=8, n_kv_heads=1, intermediate=1088, vocab=4128),
-                                    dict(hidden=4096, n_q_heads=4, n_kv_heads=4, intermediate=4096, vocab=4096),
-                                    dict(hidden=4160, n_q_heads=4, n_kv_heads=4, intermediate=1024, vocab=4096)])   # the norms' looping form
-@pytest.mark.parametrize("rows", [1, 15, 17, 32, 33, 64, 65, 128, 129])
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("change,lens,sampled,takes", MANY_ROWS_ORACLE)
+def test_many_row_products_against_the_oracle(change, lens, sampled, takes, kv8):
+    # every tile, K-slice and epilogue of the many-row products at widths that end inside a tile.  The bound of the 8-bit
+    # parity tests for both caches: eight times the rms that bf16 arithmetic costs on the trajectory under test (the largest
+    # of some thousand near-Gaussian differences lies at five to seven times it).  With short contexts a misplaced
+    # part of a head is 2 to 60 times the bound (8- or 4-dim pieces of one head's keys or values swapped in the oracle).
+    shape = small(**change)
+    blob = make_weight_blob(shape, seed=6, weight_std=0.02, gain_std=0.1)
+    kw = dict(max_context=max(lens) + sampled + 2, max_trajectories=len(lens), kv_pool_pages=sum((n + sampled + 16) // 16 for n in lens))
+    g = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, **kw)
+    o = OracleEngine(blob, kv_cache_dtype="fp8_e4m3" if kv8 else None, **kw)
+    rng = np.random.default_rng(sum(lens))
+    ids, ends = np.arange(len(lens)), np.cumsum(lens)
+    toks = [rng.integers(0, shape.vocab, n) for n in lens]
+    rows = np.cumsum([n - 1 for n in lens])
+    picked = sorted({int(np.searchsorted(rows, r, side="right")) for r in (0, 128, 256, rows[-1] // 2, rows[-1] - 1) if r < rows[-1]})
+    g.append_observation(ids, np.concatenate(toks), lens)
+    o.append_observation(picked, np.concatenate([toks[i] for i in picked]), [lens[i] for i in picked])
+    bound = 8.0 * max(float(np.sqrt(np.mean((forward_bf16_model(o.model, toks[i]) - forward_full(o.model, toks[i])) ** 2))) for i in picked)
+    for i in picked:
+        assert np.abs(g.debug_logits(i) - o.debug_logits(i)).max() < bound
+    for _ in range(sampled):
+        forced = rng.integers(0, shape.vocab, len(lens))
+        lg, lo = g.decode_step_forced(ids, 1.0, forced), o.decode_step_forced(picked, 1.0, forced[picked])
+        assert np.abs(lg[picked] - lo).max() < bound
+    rec, ref = g.recompute_logprobs(ids, 1.0), o.recompute_logprobs(picked, 1.0)
+    start = ends - lens + sampled * ids
+    assert np.abs(np.concatenate([rec[start[i]:start[i] + lens[i] + sampled] for i in picked]) - ref).max() < bound
+    assert np.array_equal(rec, g.recompute_logprobs(ids, 1.0))        # the same bits again
+    g.close()
+
+
+@pytest.mark.parametrize("change", DECODE)
+@pytest.mark.parametrize("rows", DECODE_ROWS)
 def test_decode_products_row_counts(change, rows):
-    # every row count at which the decode products change their tile, widths that end inside a tile of
-    # 32, 64, 80 or 96 columns, depths that are no whole number of 128-k stages, K-slices of unequal length
-    shape = SHAPES["small-d128"].replace(n_layers=1, **change)
+    # every row count at which the decode products change their tile, tiles of 32, 64, 80 and 96 columns, widths
+    # that end inside the last two, depths that are no whole number of 128-k stages, K-slices of unequal length
+    shape = small(**change)
     blob = make_weight_blob(shape, seed=7, weight_std=0.02, gain_std=0.1)
     kw = dict(max_context=32, max_trajectories=rows, kv_pool_pages=rows)
     a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
@@ -190,4 +218,7 @@ def test_decode_products_row_counts(change, rows):
         e.append_observation(ids, toks, [3] * rows)
     la, lb = (e.decode_step_forced(ids, 1.0, forced) for e in (a, b))
     assert np.abs(la - lb).max() < 3e-2              # two bf16 paths over one layer, logits of deviation below 1.3
+    o, picked = OracleEngine(blob, **kw), sorted({0, rows // 2, rows - 1})
+    o.append_observation(picked, toks.reshape(rows, 3)[picked].reshape(-1), [3] * len(picked))
+    assert np.abs(la[picked] - o.decode_step_forced(picked, 1.0, forced[picked])).max() < 3e-2
     a.close(), b.close()
