@@ -1296,8 +1296,8 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
 #pragma unroll
     for (int i = 0; i < 8; i++) vis[i] = !MASKED || (pg + (i >> 2)) * RL_PAGE + 4 * g + (i & 3) <= mypos[cb];
     // m (in scaled units: score * scale2, scale2 > 0) is the reference point of the exponents, not
-    // necessarily the running maximum: it only moves, to the column's maximum so far, when some term of
-    // the wave exceeds it by about 2^kLazy.  The ratio acc / l does not depend on m, and the common
+    // necessarily the running maximum: it only moves, to the column's maximum so far, when the eight terms
+    // of some lane of the wave sum to more than kLazy = 2^8.  The ratio acc / l does not depend on m, and the common
     // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
     // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
     constexpr float kLazy = 256.0f;
