@@ -91,10 +91,9 @@ void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I);
 
 // ---- MFMA kernels (bf16, head_dim 128) -------------------------------------------------------
 enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4, EPI_QKV = 5, EPI_QKV8 = 6, EPI_ADD = 7 };
-// Kernel and K-slices of one product (see plan_gemm's definition).  width: GEMM_TILE256: 64-column groups
-// of the tile (4 or 5); GEMM_DECODE: 16-column blocks of the tile (2, 4, 5 or 6).  cost: estimate in us,
-// comparable between plans of as many rows.
-// GEMM_WIDE128: 128 x 256 tiles of the same kernel.
+// Kernel and K-slices of one product (see plan_gemm's definition).  GEMM_TILE128: 128 x 128 tiles; GEMM_TILE256:
+// 256-row tiles of `width` 64-column groups (4 or 5); GEMM_WIDE128: 128 x 256 tiles of the same kernel; GEMM_DECODE:
+// tiles of `width` 16-column blocks (2, 4, 5 or 6).  cost: estimate in us, comparable between plans of as many rows.
 enum GemmKind { GEMM_TILE128 = 0, GEMM_TILE256 = 1, GEMM_DECODE = 2, GEMM_WIDE128 = 3 };
 struct GemmPlan { int kind, width, splits; double cost; };
 const int kMaxSplits = 8;
@@ -102,8 +101,9 @@ const int kMaxSplits = 8;
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows);
 // A: bf16 A-tile layout [ceil(M/128)*128, K]; Wp: repacked weights (see repack kernel).
 // EPI_STORE: K-slice z writes its fp32 partial sum to C + z * M * N (row-major [M, N]); the consumer
-// adds the partials.  EPI_ADD (one slice): C += product; returns 0.  EPI_SWIGLU (one slice): C is bf16 A-tile [.., N/2], gate and up interleaved in
-// groups of 8 rows.  K % 64 == 0, N % 32 == 0.  Returns the number of slices actually used.
+// adds the partials.  EPI_ADD (one slice): C += product.  EPI_SWIGLU (one slice): C is bf16 A-tile [.., N/2], gate
+// and up interleaved in groups of 8 rows.  K % 64 == 0, N % 32 == 0.  Returns the number of partial sums left in C
+// (EPI_ADD: 0).
 int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
                      const GemmPlan& plan);
 // QKV projection with QK-norm, RoPE and the cache write in its epilogue (head_dim 128): what the

@@ -58,7 +58,8 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // smallest that covers M when there is one row tile): only those blocks of the A chunk are
 // fetched, staged and multiplied.  At decode sizes a workgroup's time follows the bytes its CU
 // fetches, and the A chunk is half of them, so small batches gain most of what they leave out
-// (rows <= 32: gate-up 30.7 -> 23.6 us, down 18.3 -> 13.0 us); results per row are unchanged.
+// (N = 4096 K = 12288 in eight slices: 22.9 us with all four row blocks, 18.4 at 12 rows, 20.3 at 64; lm-head
+// 151936 x 2560 151 -> 137 us at 12 rows, 154 -> 145 at 48); results per row are unchanged.
 // EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.
 // EPI_LSE (lm-head of the masked log-prob pass): the product is formed transposed (weights as the
 // MFMA row operand; both operands have the same lane layout, so swapping them costs nothing), which
@@ -288,13 +289,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
 // formed transposed, which leaves a row's 128 dims of the head in two lanes, RoPE partners in the
 // same lane; the per-head norm (one swap), RoPE and the writes to q and the paged cache happen in
 // the epilogue, so the fp32 projection (201 MB at 8192 x 6144) is neither stored nor read back.
-// EPI_ADD: the product is added to the fp32 residual stream in place (O and down, one slice): 18 us more
+// EPI_ADD: the product is added to the fp32 residual stream in place (O and down, one slice): 13 to 19 us more
 // than storing it at 8192 x 2560 (84 MB read by all workgroups at once), 30 us less in the norm behind it.
-// Measured at 8192 rows in the pass (us; before: register staging, 256-column tiles or 128 x 128):
-// gate-up N = 19456 K = 2560 with SwiGLU 880 -> 690, down N = 2560 K = 9728 443 -> 308 (1.41 PFLOP/s
-// alone), O N = 2560 K = 4096 192 -> 138, QKV N = 6144 K = 2560 with norm, RoPE and cache write
-// 244 + 80 -> 268, lm-head with log-softmax at 1536 rows (N = 151936) 1709 -> 1034.  128-row tiles at
-// 587 rows (before: 128 x 128): QKV 30.5 -> 25.0 in two slices, O 23.6 -> 19.1, down 45.0 -> 38.9 in five.
+// Measured at 8192 rows (us alone / in the pass; before: register staging, 256-column tiles or 128 x 128, in the
+// pass): gate-up N = 19456 K = 2560 with SwiGLU 880 -> 646 / 655 (1.26 PFLOP/s), down N = 2560 K = 9728 443 -> 296
+// stored (1.38 PFLOP/s), 315 / 316 added, O N = 2560 K = 4096 192 -> 132 stored, 146 / 153 added, QKV N = 6144 K = 2560
+// with norm, RoPE and cache write 244 + 80 -> 247 / 264, lm-head with log-softmax at 1536 rows (N = 151936) 1709 ->
+// 1015 / 986.  128-row tiles at 587 rows (before: 128 x 128): QKV 30.5 -> 25 / 27 in two slices, O 23.6 -> 19 /
+// 20, down 45.0 -> 39 / 38 in five.
 // XCD-aware tile numbering (xcd_tile256).  K % 64 == 0, N % 32 == 0.
 // =============================================================================================
 // Tile of a workgroup: the hardware hands workgroups to the 8 XCDs round-robin by linear index
@@ -449,6 +451,8 @@ __device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
 // the builtin the compiler waits for all such loads before any LDS read.  Whoever uses it waits with an
 // explicit vmcnt (the loads return in order), puts a barrier before other waves read, and drains all of
 // them before the workgroup ends.  Pieces whose offset lies behind the buffer's end arrive as zeros.
+// The compiler counts no wait states for the instructions in here: the scalar operands come from scalar
+// arithmetic (one that a vector instruction wrote would have to be five wait states old).
 __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
                "s"(soff)
