@@ -2,7 +2,7 @@
 """Summarise rocprofv3 counter runs of bench.py for the decode-attention kernel.
 
 Usage (after the two counter runs named in the summary it writes):
-    python -m paper_2509_06980_amd.profile_summary FETCH.csv WRITE.csv [STATS.csv] > profiles/<name>.md
+    python -m paper_2509_06980_amd.profile_summary FETCH.csv WRITE.csv > profiles/<name>.md
 
 FETCH.csv / WRITE.csv are rocprofv3 `--pmc FETCH_SIZE` / `--pmc WRITE_SIZE` counter_collection
 files (KiB per dispatch).  Both counters are calibrated against the largest device-to-device
@@ -54,12 +54,30 @@ def trace_summary(path):
         print(f"| {g} | {n} | {t / n / 1e3:.2f} |")
 
 
+def decode_products():
+    """(kernel, threads of the launch) -> what it has to move, for the products of a decode step of 128
+    trajectories of the Qwen3-4B shape."""
+    from synthetic import SHAPES
+    from .binding import debug_pass_plan
+    s, rows = SHAPES["qwen3-4b"], 128
+    out = {("gemm_mfma_kernel<4, 4>", (s.vocab + 127) // 128 * 256):
+           f"lm-head: {s.vocab * s.hidden * 2 / 1e6:.1f} MB weights, {rows * s.vocab * 4 / 1e6:.1f} MB logits written"}
+    dims = dict(qkv=(s.q_width + 2 * s.kv_width, s.hidden), o=(s.hidden, s.q_width),
+                gate_up=(2 * s.intermediate, s.hidden), down=(s.hidden, s.intermediate))
+    for name, (kernel, width, slices, epilogue) in debug_pass_plan(s, rows).items():
+        if kernel != "decode" or name not in dims:
+            continue
+        n, k = dims[name]
+        ring = "128, 3" if width == 5 else "64, 4"
+        key = (f"gemm_decode_kernel<{2 if epilogue == 'swiglu' else 0}, 2, {width}, {ring}>", (n // 16 + width - 1) // width * slices * 256)
+        written = rows * n / 1e6 if epilogue == "swiglu" else rows * n * 4 / 1e6      # bf16 of half the columns
+        out[key] = f"{name}: {n * k * 2 / 1e6:.1f} MB weights, {slices} x {written:.1f} MB written"
+    return out
+
+
 def decode_step_table(fetch_path, write_path):
     """Per kernel and launch shape: mean HBM bytes fetched / written per dispatch (calibrated like
-    the attention summary), for every shape with at least 100 dispatches.  With the Qwen3-4B shape
-    and 128 trajectories the decode GEMM shapes are: QKV 240 workgroups (31.5 MB of weights), O and
-    down 160 workgroups each (21.0 and 49.8 MB; same launch shape, so they average to 35.4 MB),
-    gate-up 152 workgroups (99.6 MB), lm-head 1187 workgroups (777.9 MB)."""
+    the attention summary), for every shape with at least 100 dispatches."""
     fetch = read_counter(fetch_path, "FETCH_SIZE")
     write = read_counter(write_path, "WRITE_SIZE")
     copy_bytes = 151936 * 2560 * 2
@@ -69,10 +87,7 @@ def decode_step_table(fetch_path, write_path):
         return copy_bytes / (best * 1024.0) if best else float("nan")
 
     kf, kw = calib(fetch), calib(write)
-    expect = {("gemm_mfma_kernel<0, 2, 4, 4>", 240 * 256): "QKV: 31.5 MB weights + 5 x 3.1 MB partial sums written",
-              ("gemm_mfma_kernel<0, 2, 4, 4>", 160 * 256): "O / down mixed: 35.4 MB weights + 8 x 1.3 MB written",
-              ("gemm_mfma_kernel<2, 2, 4, 4>", 152 * 256): "gate-up: 99.6 MB weights, 2.5 MB written",
-              ("gemm_mfma_kernel<0, 2, 4, 4>", 1187 * 256): "lm-head: 777.9 MB weights, 77.8 MB logits written"}
+    expect = decode_products()
     print("# HBM traffic per dispatch of the decode-step kernels (Qwen3-4B shape, 128 trajectories)\n")
     print("Commands (MI355X box, repository root; one counter per run; the rollout is shortened, the "
           "decode launch shapes are those of the full workload):\n")
