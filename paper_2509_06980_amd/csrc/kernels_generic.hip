@@ -319,7 +319,7 @@ __global__ void qkrope_kernel(const float* __restrict__ qkv, const TW* __restric
     const float u = x[i], w = x[i + half];
     x1[cnt] = u;
     x2[cnt] = w;
-    ss += u * u + w * w;
+    ss += __builtin_fmaf(w, w, u * u);
   }
   ss = wave_sum(ss);
   float inv = (qk_norm && !is_v) ? 1.0f / sqrtf(ss / (float)d + eps) : 1.0f;
