@@ -50,6 +50,8 @@ def test_sampler_rows_without_weight(V):
     assert drawn.tolist() == [0, 0, 0, sample_token(others, 1.0, int(u[3]))[0]] and np.isnan(lps).all()
     best, lps = rl.sample_from_logits(z, 0.0, u)
     assert best.tolist() == [0, V // 2, 0, int(others.argmax())] and np.isnan(lps).all()
+    assert [sample_token(z[r], 1.0, int(u[r]))[0] for r in range(4)] == drawn.tolist()      # the oracle's rule
+    assert [sample_token(z[r], 0.0, 0)[0] for r in range(4)] == best.tolist()
 
 
 @pytest.mark.parametrize("T", [1e-45, 1e-40, 4e-39, 1e-37])

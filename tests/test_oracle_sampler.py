@@ -137,3 +137,30 @@ def test_chi_square_frequencies():
 def test_scale_constant():
     assert scale_constant(1.0) == np.float32(1.4426950408889634)
     assert scale_constant(0.5) == np.float32(2.8853900817779268)
+
+
+def test_rows_without_weight_and_logits_that_are_no_numbers():
+    nan, inf = np.float32("nan"), np.float32("inf")
+    z = np.random.default_rng(3).standard_normal(50).astype(np.float32)
+    for row in (np.full(50, nan), np.full(50, -inf), np.where(np.arange(50) == 20, inf, z)):
+        for u in (0, 2**31, 2**32 - 1):
+            tok, lp = sample_token(row, 1.0, u)
+            assert tok == 0 and math.isnan(lp)
+    assert [sample_token(row, 0.0, 0)[0] for row in (np.full(50, nan), np.full(50, -inf), np.where(np.arange(50) == 20, inf, z))] == [0, 0, 20]
+    # a logit that is no number weighs nothing, like one far below the others; the log-prob is no number
+    holes, low = z.copy(), z.copy()
+    holes[5], low[5] = nan, -1e30
+    for T in (1.0, 0.4, 0.0):
+        for u in (0, 123456789, 2**31, 2**32 - 1):
+            tok, lp = sample_token(holes, T, u)
+            assert tok == sample_token(low, T, u)[0] and math.isnan(lp)
+
+
+def test_temperatures_whose_scale_leaves_float32():
+    z = np.random.default_rng(4).standard_normal(300).astype(np.float32)
+    z[7] = z[299] = 9.0
+    assert scale_constant(4.3e-39) < np.finfo(np.float32).max == scale_constant(4.2e-39)
+    for T in (1e-45, 1e-40, 4e-39, 1e-37):
+        for u, tok in ((2**31 - 1, 7), (2**31, 299)):
+            got, lp = sample_token(z, T, u)
+            assert got == tok and abs(lp + math.log(2.0)) < 1e-6
