@@ -141,6 +141,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
   auto a_piece = [](int p) { return MB == 4 ? p : (p / (64 * MB)) * 256 + (p % (64 * MB)); };
   const int NB = N >> 5;
   const u32x4* Wg = (const u32x4*)Wp + (size_t)(active ? nb : 0) * 256;   // cell (chunk 0, strip nb)
+  // At most 64 rows (one row tile, every weight read once, the stream from HBM is all that counts): past the caches.
+  // lm-head of 151936 x 4096 at 6 rows 212 -> 190 us (6.5 TB/s), x 2560 at 37 rows 144 -> 135, x 1024 at one row 54 ->
+  // 51.5; N = 4096 K = 12288 in eight slices at 6 rows 19.1 -> 17.8.  At 128 rows the kernel is not held by the stream
+  // and plain loads are the better ones (164 against 166 us).
+  auto weight = [](const u32x4* p) {
+    if constexpr (MB < 4) return __builtin_nontemporal_load(p);
+    else return *p;
+  };
   f32x16 acc[MB];
 #pragma unroll
   for (int i = 0; i < MB; i++)
@@ -159,7 +167,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
     _Pragma("unroll") for (int i = 0; i < MB; i++)                          \
       AR[i] = Ag[(size_t)cl_ * 1024 + a_piece(i * 256 + tid)];              \
     _Pragma("unroll") for (int i = 0; i < 4; i++)                           \
-      BR[i] = Wg[((size_t)cl_ * NB * 4 + i) * 64 + lane];                   \
+      BR[i] = weight(Wg + ((size_t)cl_ * NB * 4 + i) * 64 + lane);          \
     /* keep the scheduler from sinking these loads towards their use */     \
     __builtin_amdgcn_sched_barrier(0);                                      \
   }
