@@ -705,15 +705,30 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
   constexpr int BUF = (NA + NW) * 1024;
   extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int tile = blockIdx.x / splits, split = blockIdx.x - tile * splits;
+  // Slices of a tile are neighbours, except four long ones: dealt round-robin to the 8 XCDs they would put every other
+  // tile of a slice on an XCD (N = 4096 K = 4096 at 16 rows, 64 columns: 9.4 us; K = 12288 21.0).  There an XCD takes a
+  // contiguous range of tiles of one slice (7.9, 17.9; N = 6144 K = 4096 10.4 -> 10.2).  Other counts and slices under
+  // 512 k are better off, or no worse, the plain way (N = 4096 K = 1024: 3.7 against 4.3).
+  int tile, split;
+  if (splits == 4 && stages_per_split * SK >= 512) {
+    const int tiles = gridDim.x / 4, base = gridDim.x >> 3, rem = gridDim.x & 7, x = blockIdx.x & 7;
+    const int v = x * base + min(x, rem) + (blockIdx.x >> 3);
+    split = __builtin_amdgcn_readfirstlane(v / tiles);
+    tile = __builtin_amdgcn_readfirstlane(v - split * tiles);
+  } else {
+    tile = blockIdx.x / splits;
+    split = blockIdx.x - tile * splits;
+  }
   const int NB = N >> 5, N16 = N >> 4, nst = K / SK;
   const int s0 = split * stages_per_split, s1 = min(s0 + stages_per_split, nst);
+  const int r16 = (M + 15) >> 4;      // 16-row blocks in use: the others are not fetched
   const u32x4 ra = buffer_rsrc(A, (unsigned)K * 256u), rw = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
   const int lp = ((lane & 15) + (((lane >> 4) & 1) << 5)) << 4;
   const int lw = ((lane >> 5) << 10) + lp, la = ((lane >> 5) << 12) + lp;
   // piece j of this wave of stage s: block id j * 4 + wave, weight blocks first; stages behind the slice
-  // are asked for behind the buffer's end: no memory traffic, and the count of loads stays the same
+  // and row blocks without rows are asked for behind the buffer's end: no memory traffic (gate-up of the 4B shape at 1 to
+  // 48 rows 18.8 -> 18.1 us, 80 rows 25.5 -> 24.5; 8B QKV at 80 rows 13.4 -> 12.1), and the count of loads stays the same
   auto dma = [&](int s, int j) {
     const int sl = min(s, s1 - 1), id = j * 4 + wave;
     const unsigned dst = lds0 + (unsigned)((s - s0) % NST) * BUF + (unsigned)id * 1024u;
@@ -723,7 +738,7 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
                   ((unsigned)(t >> 1) * NB + (c16 >> 1)) * 4096u + (t & 1) * 2048u + (c16 & 1) * 256u);
     } else {
       const int x = id - NW, r = x % (4 * RB), t = sl * KB + x / (4 * RB);
-      load_to_lds(dst, s < s1 ? la : 0x7fff0000, ra, (unsigned)t * 8192u + (r >> 1) * 1024u + (r & 1) * 256u);
+      load_to_lds(dst, s < s1 && r < r16 ? la : 0x7fff0000, ra, (unsigned)t * 8192u + (r >> 1) * 1024u + (r & 1) * 256u);
     }
   };
   f32x4 acc[CB][RB];
@@ -817,10 +832,13 @@ static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t*
 
 // Which kernel and how many K-slices: the cheapest by estimate (us), over at most kMaxSplits slices of
 // at least 256 k.  Further partial sums cost their stores and their reading at 5 TB/s.
-// At most 128 rows: per round of 256 workgroups the time of a workgroup's weight bytes at 27 GB/s and of
-// its activation bytes at 125 GB/s, plus 2.2 us (decode kernel) or 3.2 us (128-column kernel, which
-// fetches only the 32-row blocks in use; it stays the better one where its 128 columns times slices
-// make whole rounds: 8B down at N = 4096 K = 12288, 12 rows 18.6 against 22.4 us with 64 columns).
+// At most 128 rows: per round of 256 workgroups the time of a workgroup's weight bytes and of its activation bytes,
+// plus the launch.  Up to 64 rows: decode kernel 27 and 113 GB/s (the 16-row blocks in use), 2.2 us, and with 32 columns
+// no less than 0.25 us per 64 k (the ring then holds too few bytes to cover the latency); 128-column kernel 29 and 103
+// GB/s, 2.7 us.  Above: 27 and 125 GB/s (128 rows) for both, 2.2 and 3.2 us.  The 128-column kernel fetches the 32-row
+// blocks in use and stays the better one where its 128 columns times slices make whole rounds (8B down at N = 4096
+// K = 12288, 48 rows: 18.7 against 19.5 us with 96 columns).  Fitted on 20 products of hidden 1024 to 4096 at 1 to 128
+// rows: with the reading of its partial sums the plan's product is 0.9 % above the best plan's on average, 10 % at most.
 // More rows: a round is 256 workgroups, one per CU.  256-row tiles cost per 32-k chunk 0.43 us with most
 // CUs idle to 0.73 us with all of them busy (320 columns: 1.25 times that) and 4 to 16 us per round to
 // store a tile; 128 x 256 tiles 0.46 us per chunk and 5 us per round (two share a CU, at the speed of one
@@ -839,16 +857,19 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
     if (cost < best.cost) best = GemmPlan{kind, width, splits, cost};
   };
   if (M <= 128) {
-    const double arow = (M <= 32 ? 32 : M <= 64 ? 64 : 128) * 2.0, adec = (M <= 64 ? 64 : 128) * 2.0;
+    const double arow = (M <= 32 ? 32 : M <= 64 ? 64 : 128) * 2.0, adec = M <= 64 ? (M + 15) / 16 * 32.0 : 256.0;
+    const bool few = M <= 64;
     for (int sp = 1; sp <= most; sp++) {
       const int cps = (nch + sp - 1) / sp, r = (tiles * sp + 255) / 256;
-      offer(GEMM_TILE128, 0, sp, 3.2 + r * cps * 64 * (256 / 27.0e3 + arow / 125.0e3) + (2 * sp - 1) * part);
+      offer(GEMM_TILE128, 0, sp, (few ? 2.7 : 3.2) + r * cps * 64 * (256 / (few ? 29.0e3 : 27.0e3) + arow / (few ? 103.0e3 : 125.0e3)) +
+                                     (2 * sp - 1) * part);
       if (wide || (epilogue != EPI_STORE && epilogue != EPI_SWIGLU)) continue;
       for (int cb : {2, 4, 5, 6}) {
         const int sk = cb == 5 ? 128 : 64;
         if (K % sk != 0) continue;
         const int k = (K / sk + sp - 1) / sp * sk, rd = ((N / 16 + cb - 1) / cb * sp + 255) / 256;
-        offer(GEMM_DECODE, cb, sp, 2.2 + rd * k * (32 * cb / 27.0e3 + adec / 125.0e3) + (2 * sp - 1) * part);
+        const double t = std::max(k * (32 * cb / 27.0e3 + adec / (few ? 113.0e3 : 125.0e3)), cb == 2 && few ? k / 64 * 0.25 : 0.0);
+        offer(GEMM_DECODE, cb, sp, 2.2 + rd * t + (2 * sp - 1) * part);
       }
     }
     if (best.kind == GEMM_DECODE) {     // no empty slices
