@@ -119,7 +119,12 @@ __device__ __forceinline__ void lse_block(F val, float2* __restrict__ P, float* 
   }
 }
 
-template <int EPI, int MB>
+// Weights that are read once a pass and are too large to stay in the 256 MB last-level cache until the next one go past
+// the caches.  The line: products of 31 MB and more gain 3 to 7 % from it at 64 rows and fewer (see the kernels), one of
+// 21 MB nothing, and those of a model that the cache holds (4 MB, 64 of them in turn) lose up to 30 % (3.0 -> 3.9 us).
+static bool streams_weights(int N, int K) { return (size_t)N * K * 2 >= ((size_t)24 << 20); }
+
+template <int EPI, int MB, bool NT>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
                                                         const bf16_t* __restrict__ Wp,
                                                         void* __restrict__ Cv, int M, int N,
@@ -141,12 +146,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
   auto a_piece = [](int p) { return MB == 4 ? p : (p / (64 * MB)) * 256 + (p % (64 * MB)); };
   const int NB = N >> 5;
   const u32x4* Wg = (const u32x4*)Wp + (size_t)(active ? nb : 0) * 256;   // cell (chunk 0, strip nb)
-  // At most 64 rows (one row tile, every weight read once, the stream from HBM is all that counts): past the caches.
+  // NT (at most 64 rows: one row tile, every weight read once, the stream from HBM is all that counts): past the caches.
   // lm-head of 151936 x 4096 at 6 rows 212 -> 190 us (6.5 TB/s), x 2560 at 37 rows 144 -> 135, x 1024 at one row 54 ->
   // 51.5; N = 4096 K = 12288 in eight slices at 6 rows 19.1 -> 17.8.  At 128 rows the kernel is not held by the stream
   // and plain loads are the better ones (164 against 166 us).
   auto weight = [](const u32x4* p) {
-    if constexpr (MB < 4) return __builtin_nontemporal_load(p);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
   };
   f32x16 acc[MB];
@@ -461,8 +466,14 @@ __device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
 // them before the workgroup ends.  Pieces whose offset lies behind the buffer's end arrive as zeros.
 // The compiler counts no wait states for the instructions in here: the scalar operands come from scalar
 // arithmetic (one that a vector instruction wrote would have to be five wait states old).
+template <bool NT = false>     // past the caches
 __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, unsigned soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rsrc),
+               "s"(soff)
+               : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc),
                "s"(soff)
                : "memory", "m0");
 }
@@ -690,10 +701,12 @@ static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C
 // us at 128 / 64 rows, the 128-column kernel -> this: gate-up N = 19456 K = 2560 28.8 -> 26.0 / 23.4 -> 19.0,
 // down N = 2560 K = 9728 17.9 -> 15.9 / 14.1 -> 11.9, O N = 2560 K = 4096 9.9 -> 8.5 / 7.9 -> 6.7, QKV
 // N = 6144 K = 2560 11.7 -> 10.7 / 8.6 -> 8.4; 0.6B shape: gate-up 11.3 -> 7.2 / 7.5 -> 5.7, down 7.0 -> 4.4 /
-// 4.8 -> 3.6.  Deeper rings gain nothing; leaving out the loads behind the slice with a branch costs
+// 4.8 -> 3.6.  NT (up to 64 rows, weights of 24 MB and more): weights past the caches, at 16 rows 8B gate-up N = 24576
+// K = 4096 34.3 -> 32.2 us (6.3 TB/s), down N = 4096 K = 12288 17.8 -> 17.1, O 8.0 -> 7.6, 4B QKV 7.5 -> 7.2, gate-up 18.3 ->
+// 17.9; at 96 rows 0 to 2 %.  Deeper rings gain nothing; leaving out the loads behind the slice with a branch costs
 // 10 % (the loop falls apart into blocks).
 // =============================================================================================
-template <int EPI, int RB, int CB, int SK, int NST>
+template <int EPI, int RB, int CB, int SK, int NST, bool NT>
 __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K, int splits,
                                                        int stages_per_split) {
@@ -734,7 +747,7 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
     const unsigned dst = lds0 + (unsigned)((s - s0) % NST) * BUF + (unsigned)id * 1024u;
     if (id < NW) {
       const int t = sl * KB + id / CB, c16 = min(tile * CB + id % CB, N16 - 1);   // columns past the end: dropped
-      load_to_lds(dst, s < s1 ? lw : 0x7fff0000, rw,
+      load_to_lds<NT>(dst, s < s1 ? lw : 0x7fff0000, rw,
                   ((unsigned)(t >> 1) * NB + (c16 >> 1)) * 4096u + (t & 1) * 2048u + (c16 & 1) * 256u);
     } else {
       const int x = id - NW, r = x % (4 * RB), t = sl * KB + x / (4 * RB);
@@ -811,23 +824,29 @@ template <int EPI, int CB>
 static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits) {
   constexpr int SK = CB == 5 ? 128 : 64, NST = CB == 5 ? 3 : 4;   // CB = 5: whole rounds of 4 waves need 128 k
   const int rb = M <= 64 ? 1 : 2, lds = NST * (4 * rb + CB) * (SK / 32) * 1024;
-  static std::atomic<uint64_t> done[2];
+  const bool nt = rb == 1 && streams_weights(N, K);
+  static std::atomic<uint64_t> done[3];
   auto go = [&](auto kernel) {
-    set_lds_limit(done[rb - 1], (const void*)kernel, lds);
+    set_lds_limit(done[nt ? 2 : rb - 1], (const void*)kernel, lds);
     const int sps = (K / SK + splits - 1) / splits;
     kernel<<<(N / 16 + CB - 1) / CB * splits, 256, lds, s>>>(A, Wp, C, M, N, K, splits, sps);
   };
-  if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST>);
-  else go(gemm_decode_kernel<EPI, 2, CB, SK, NST>);
+  if (nt) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, true>);
+  else if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, false>);
+  else go(gemm_decode_kernel<EPI, 2, CB, SK, NST, false>);
 }
 
-template <int MB>
-static void gemm_launch(hipStream_t s, dim3 grid, const bf16_t* A, const bf16_t* Wp, void* C, int M,
-                        int N, int K, int epilogue, int cps) {
-  if (epilogue == EPI_STORE)
-    gemm_mfma_kernel<EPI_STORE, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
-  else
-    gemm_mfma_kernel<EPI_SWIGLU, MB><<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, nullptr, 0.f);
+template <int EPI>
+static void gemm_launch(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits, int cps,
+                        float* zt) {
+  const dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
+  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, zt, 0.f); };
+  const bool nt = streams_weights(N, K);
+  if (M <= 32 && nt) go(gemm_mfma_kernel<EPI, 1, true>);      // row blocks in use (one row tile when < 4)
+  else if (M <= 32) go(gemm_mfma_kernel<EPI, 1, false>);
+  else if (M <= 64 && nt) go(gemm_mfma_kernel<EPI, 2, true>);
+  else if (M <= 64) go(gemm_mfma_kernel<EPI, 2, false>);
+  else go(gemm_mfma_kernel<EPI, 4, false>);
 }
 
 // Which kernel and how many K-slices: the cheapest by estimate (us), over at most kMaxSplits slices of
@@ -936,10 +955,8 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   int splits = epilogue == EPI_SWIGLU ? 1 : std::max(1, std::min(sp, nchunks));
   const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
-  dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
-  if (M <= 32) gemm_launch<1>(s, grid, A, Wp, C, M, N, K, epilogue, cps);      // row blocks in use (one row tile when < 4)
-  else if (M <= 64) gemm_launch<2>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
-  else gemm_launch<4>(s, grid, A, Wp, C, M, N, K, epilogue, cps);
+  if (epilogue == EPI_STORE) gemm_launch<EPI_STORE>(s, A, Wp, C, M, N, K, splits, cps, nullptr);
+  else gemm_launch<EPI_SWIGLU>(s, A, Wp, C, M, N, K, splits, cps, nullptr);
   return splits;
 }
 
@@ -959,14 +976,7 @@ void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, in
 void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* logits, int M,
                            int V, int K, float* stripmax) {
   if (M <= 0) return;
-  dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
-  const int cps = K / 64;
-  if (M <= 32)
-    gemm_mfma_kernel<EPI_STORE_MAX, 1><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
-  else if (M <= 64)
-    gemm_mfma_kernel<EPI_STORE_MAX, 2><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
-  else
-    gemm_mfma_kernel<EPI_STORE_MAX, 4><<<grid, 256, 0, s>>>(A, Wp, logits, M, V, K, cps, nullptr, stripmax, 0.f);
+  gemm_launch<EPI_STORE_MAX>(s, A, Wp, logits, M, V, K, 1, K / 64, stripmax);
 }
 
 // One workgroup per row: combine the per-strip (max, sum) pairs in a fixed order and write
@@ -1005,7 +1015,7 @@ void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, in
     launch_dma<EPI_LSE, 4, 4>(s, A, Wp, part, M, V, K, 1, tgt, zt, scale_c, QkvArgs{});
   } else {
     dim3 grid((V + 127) / 128, (M + 127) / 128, 1);
-    gemm_mfma_kernel<EPI_LSE, 4><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
+    gemm_mfma_kernel<EPI_LSE, 4, false><<<grid, 256, 0, s>>>(A, Wp, part, M, V, K, K / 64, tgt, zt, scale_c);
   }
   lse_finish_kernel<<<M, 256, 0, s>>>((const float2*)part, zt, V / 32, scale_c, lp);
 }
