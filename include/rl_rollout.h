@@ -259,6 +259,12 @@ uint32_t rl_uniform_u32(uint64_t seed, int32_t traj_id, int32_t position);
  * Errors: ARG (also a shape that the MFMA kernels do not take).
  */
 int rl_debug_pass_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);
+/*
+ * Tiles of O and down where they carry the residual add and the norm behind them (up to 512 rows) instead of the plan
+ * that rl_debug_pass_plan gives for the product alone.  out: {16-row blocks, 16-column blocks} of O, then of down; 0, 0
+ * where the plan holds.  Errors: ARG.
+ */
+int rl_debug_residual_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);
 
 /*
  * Kernel timing for benchmarks: when enabled, every `every`-th decode step brackets its

@@ -13,6 +13,7 @@ EXPORTED_SYMBOLS = [
     "rl_decode_step_forced", "rl_sample_from_logits", "rl_sample_device_logits", "rl_uniform_u32", "rl_timing_enable",
     "rl_timing_read", "rl_timing_read_steps", "rl_timing_read_decode_bytes", "rl_measure_stream_read",
     "rl_decode_step_with_appends", "rl_decode_step_forced_with_appends", "rl_grpo_objective", "rl_debug_pass_plan",
+    "rl_debug_residual_plan",
 ]
 
 
@@ -80,6 +81,7 @@ def load_library():
                                       C.POINTER(C.c_double), C.POINTER(C.c_double),
                                       C.POINTER(C.c_int64), C.POINTER(C.c_double)]
     lib.rl_debug_pass_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
+    lib.rl_debug_residual_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
     lib.rl_debug_logits.argtypes = [C.c_void_p, C.c_int32, _F32P]
     lib.rl_sample_from_logits.argtypes = [_F32P, C.c_int32, C.c_int32, C.c_float, _U32P, _I32P, _F32P]
     lib.rl_sample_device_logits.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_float, C.c_void_p,
@@ -127,6 +129,15 @@ def debug_pass_plan(shape, rows, max_rows=8192):
     kernels, epilogues = ("tile128", "tile256", "decode", "wide128"), {0: "store", 2: "swiglu", 3: "logprob", 5: "qkv", 7: "add"}
     return {name: (kernels[out[4 * i]], out[4 * i + 1], out[4 * i + 2], epilogues[out[4 * i + 3]])
             for i, name in enumerate(("qkv", "o", "gate_up", "down", "score_head", "logits_head"))}
+
+
+def debug_residual_plan(shape, rows, max_rows=8192):
+    """{product: (16-row blocks, 16-column blocks)} of the tiles of O and down that carry the residual add and the norm
+    behind them in a pass over `rows` rows; products that do not are left out."""
+    cfg = _ModelConfig(*[getattr(shape, n) for n, _ in _ModelConfig._fields_])
+    out = (C.c_int32 * 4)()
+    _check(load_library().rl_debug_residual_plan(C.byref(cfg), int(rows), max(int(rows), int(max_rows)), out))
+    return {name: (out[2 * i], out[2 * i + 1]) for i, name in enumerate(("o", "down")) if out[2 * i]}
 
 
 def sample_from_logits(logits, temperature, u32):

@@ -78,6 +78,7 @@ struct rl_model {
   int attn_slots = 0;      // scratch slots for partial attention results
   bool cascade = false;    // shared-prefix decode attention
   float *h = nullptr, *qkv = nullptr, *ph = nullptr, *gu = nullptr, *logits = nullptr, *attn_scratch = nullptr;
+  float* ssq = nullptr;    // sums of squares of the residual stream's rows, [H / 16][up to kResidualRows]
   int pending_parts = 0;   // split-K partial sums of the last down-projection still to be added to h
   void *xa = nullptr, *xo = nullptr, *xm = nullptr, *qb = nullptr;
   int32_t *d_meta = nullptr, *h_meta = nullptr;  // device / pinned staging for per-call integers
@@ -221,6 +222,7 @@ struct PassPlan {
   GemmPlan q, o, g, d;      // QKV, O, gate-up, down
   bool fused_qkv;           // QK-norm, RoPE and the cache write in the epilogue of QKV
   int eo, ed;               // epilogues of O and down: EPI_ADD or EPI_STORE
+  ResidualPlan ro, rd;      // rb > 0: O / down with the residual add and the next norm instead
 };
 PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   const int H = md.H, qw = md.nq * md.d, QW = qw + 2 * md.nkv * md.d, I = md.I;
@@ -248,6 +250,14 @@ PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   auto adds = [](const GemmPlan& g) { return g.splits == 1 && (g.kind == GEMM_TILE256 || g.kind == GEMM_WIDE128); };
   p.eo = adds(p.o) ? EPI_ADD : EPI_STORE;
   p.ed = adds(p.d) ? EPI_ADD : EPI_STORE;
+  // With the residual add and the norm inside where that is expected to be faster than the product and the norm's launch
+  // (3.6 us and 0.45 us per 1024 columns; the product's estimate holds the partial sums that the norm reads).
+  auto residual = [&](const GemmPlan& g, int K) {
+    const ResidualPlan r = plan_residual(M, H, K);
+    return r.rb > 0 && r.cost < g.cost + 3.6 + 4.5e-4 * H ? r : ResidualPlan{0, 0, 0.0};
+  };
+  p.ro = gate_up_takes_scale(p.g, M, H) ? residual(p.o, qw) : ResidualPlan{0, 0, 0.0};
+  p.rd = p.fused_qkv ? ResidualPlan{0, 0, 0.0} : residual(p.d, I);
   return p;
 }
 
@@ -260,10 +270,12 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   const PassPlan plan = plan_pass(md, M, m->part_rows);
   float *const co = plan.eo == EPI_ADD ? m->h : m->ph, *const cd = plan.ed == EPI_ADD ? m->h : m->ph;
   int pend = 0;
+  const float *so_q = nullptr, *so_g;       // sums of squares, where the norm's division is left to the consumer
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
+    const bf16_t* g_next = (const bf16_t*)(l + 1 < md.L ? m->layers[l + 1].g_in : m->g_final);
     if (l == 0) launch_embed_rmsnorm(s, (const bf16_t*)m->embed, r.tok, m->h, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
-    else launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
+    else if (!so_q) launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
     if (plan.fused_qkv) {
       const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
                        (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,
@@ -272,7 +284,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
     } else {
       int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, plan.q);
       launch_qkrope128(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs,
-                       r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
+                       r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M, so_q);
     }
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
     launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.items, r.n_items, r.merges, r.n_merges,
@@ -281,10 +293,22 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.pf_items, r.n_pf_items, nullptr, 0,
                             nullptr, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, true);
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
-    int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, co, M, H, qw, plan.eo, plan.o);
-    launch_add_rmsnorm(s, m->h, m->ph, so, (size_t)M * H, (const bf16_t*)w.g_post, (bf16_t*)m->xa, M, H, md.eps);
-    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, plan.g);
-    pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, cd, M, H, I, plan.ed, plan.d);
+    if (plan.ro.rb > 0) {
+      launch_gemm_residual(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, m->h, (const bf16_t*)w.g_post, (bf16_t*)m->xa, m->ssq, M, H, qw, plan.ro);
+      so_g = m->ssq;
+    } else {
+      int so = launch_gemm_mfma(s, (const bf16_t*)m->xo, (const bf16_t*)w.wo, co, M, H, qw, plan.eo, plan.o);
+      launch_add_rmsnorm(s, m->h, m->ph, so, (size_t)M * H, (const bf16_t*)w.g_post, (bf16_t*)m->xa, M, H, md.eps);
+      so_g = nullptr;
+    }
+    launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wgu, m->xm, M, 2 * I, H, EPI_SWIGLU, plan.g, so_g, md.eps);
+    if (plan.rd.rb > 0) {
+      launch_gemm_residual(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, m->h, g_next, (bf16_t*)m->xa, m->ssq, M, H, I, plan.rd);
+      so_q = m->ssq;
+      pend = 0;
+    } else {
+      pend = launch_gemm_mfma(s, (const bf16_t*)m->xm, (const bf16_t*)w.wdown, cd, M, H, I, plan.ed, plan.d);
+    }
   }
   m->pending_parts = pend;
 }
@@ -1128,6 +1152,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   m->part_rows = prow;
   TRY(m->dalloc((void**)&m->qkv, prow * (qw + 2 * kvw) * 4, true));
   if (m->mfma) TRY(m->dalloc((void**)&m->ph, prow * H * 4, true));
+  if (m->mfma) TRY(m->dalloc((void**)&m->ssq, (size_t)kResidualRows * (H / 16) * 4));
   TRY(m->dalloc(&m->xa, Mc * H * ael, true));
   TRY(m->dalloc(&m->xo, Mc * qw * ael, true));
   TRY(m->dalloc(&m->xm, Mc * I * ael, true));
@@ -1690,14 +1715,33 @@ extern "C" int rl_sample_from_logits(const float* logits, int32_t rows, int32_t 
   return rc;
 }
 
-extern "C" int rl_debug_pass_plan(const rl_model_config* c, int32_t rows, int32_t max_rows, int32_t* out) {
+namespace {
+int debug_plan(const rl_model_config* c, int32_t rows, int32_t max_rows, const int32_t* out, ModelDims* md, PassPlan* p) {
   if (!c || !out || rows <= 0 || max_rows < rows) return fail(RL_E_ARG, "bad argument");
   if (c->n_layers <= 0 || c->hidden <= 0 || c->n_q_heads <= 0 || c->n_kv_heads <= 0 || c->intermediate <= 0 ||
       c->vocab <= 0 || c->n_q_heads % c->n_kv_heads != 0 || !mfma_shape_ok(*c))
     return fail(RL_E_ARG, "not a shape of the MFMA kernels");
-  const ModelDims md{c->n_layers, c->hidden, c->n_q_heads, c->n_kv_heads, c->head_dim, c->intermediate,
-                     c->vocab, c->rms_eps, c->qk_norm, 1, 0};
-  const PassPlan p = plan_pass(md, rows, partial_rows((size_t)round_up(max_rows, 128)));
+  *md = ModelDims{c->n_layers, c->hidden, c->n_q_heads, c->n_kv_heads, c->head_dim, c->intermediate,
+                  c->vocab, c->rms_eps, c->qk_norm, 1, 0};
+  *p = plan_pass(*md, rows, partial_rows((size_t)round_up(max_rows, 128)));
+  return RL_OK;
+}
+}  // namespace
+
+extern "C" int rl_debug_residual_plan(const rl_model_config* c, int32_t rows, int32_t max_rows, int32_t* out) {
+  ModelDims md;
+  PassPlan p;
+  const int rc = debug_plan(c, rows, max_rows, out, &md, &p);
+  if (rc) return rc;
+  out[0] = p.ro.rb; out[1] = p.ro.cb; out[2] = p.rd.rb; out[3] = p.rd.cb;
+  return RL_OK;
+}
+
+extern "C" int rl_debug_pass_plan(const rl_model_config* c, int32_t rows, int32_t max_rows, int32_t* out) {
+  ModelDims md;
+  PassPlan p;
+  const int rc = debug_plan(c, rows, max_rows, out, &md, &p);
+  if (rc) return rc;
   auto put = [&](int at, const GemmPlan& g, int epilogue) {
     out[4 * at] = g.kind; out[4 * at + 1] = g.width; out[4 * at + 2] = g.splits; out[4 * at + 3] = epilogue;
   };

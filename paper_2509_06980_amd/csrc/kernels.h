@@ -65,10 +65,12 @@ void launch_qkrope(hipStream_t s, const float* qkv, const TW* gq, const TW* gk, 
                    const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table, TA* qout,
                    KvPool pool, const ModelDims& md, int M);
 // The same for the MFMA path (head_dim 128, operand-order cache blocks).  The projection arrives as
-// n_part <= 8 split-K partial sums (qkv + p * part_stride), added here in ascending order.
+// n_part <= 8 split-K partial sums (qkv + p * part_stride), added here in ascending order.  ssq: the input rows of the
+// projection came from launch_gemm_residual; its rows are divided by their rms here.
 void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const bf16_t* gq,
                       const bf16_t* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
-                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M);
+                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M,
+                      const float* ssq = nullptr);
 
 // h += sum of n_part split-K partial sums (ascending order), then out = rmsnorm(h) * g in A-tile
 // layout (bf16 MFMA path).  rows != null: gather: output row i is made from row rows[i] of h /
@@ -103,9 +105,18 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows);
 // EPI_STORE: K-slice z writes its fp32 partial sum to C + z * M * N (row-major [M, N]); the consumer
 // adds the partials.  EPI_ADD (one slice): C += product.  EPI_SWIGLU (one slice): C is bf16 A-tile [.., N/2], gate
 // and up interleaved in groups of 8 rows.  K % 64 == 0, N % 32 == 0.  Returns the number of partial sums left in C
-// (EPI_ADD: 0).
+// (EPI_ADD: 0).  ssq (EPI_SWIGLU, where gate_up_takes_scale): A is what launch_gemm_residual has left, and its rows
+// are divided by their rms here.
 int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
-                     const GemmPlan& plan);
+                     const GemmPlan& plan, const float* ssq = nullptr, float eps = 0.f);
+// O or down of at most kResidualRows rows with the residual add and the norm behind it: h [M, N] += A * W^T; out = bf16(h * g) in
+// A-tile layout, its rows not yet divided by their rms; ssq[N / 16][M rounded up to 16]: sums of squares of 16 columns.
+const int kResidualRows = 512;
+struct ResidualPlan { int rb, cb; double cost; };      // tile of 16 rb rows x 16 cb columns; rb = 0: none
+ResidualPlan plan_residual(int M, int N, int K);
+bool gate_up_takes_scale(const GemmPlan& plan, int M, int K);
+void launch_gemm_residual(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* h, const bf16_t* g, bf16_t* out, float* ssq,
+                          int M, int N, int K, const ResidualPlan& plan);
 // QKV projection with QK-norm, RoPE and the cache write in its epilogue (head_dim 128): what the
 // projection followed by launch_qkrope leaves, without the fp32 projection in memory.
 struct QkvArgs {

@@ -60,7 +60,8 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // fetches, and the A chunk is half of them, so small batches gain most of what they leave out
 // (N = 4096 K = 12288 in eight slices: 22.9 us with all four row blocks, 18.4 at 12 rows, 20.3 at 64; lm-head
 // 151936 x 2560 151 -> 137 us at 12 rows, 154 -> 145 at 48); results per row are unchanged.
-// EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.
+// EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.  EPI_SWIGLU with zt: the rows of A are still to be
+// divided by their rms, zt holds their sums of squares and scale_c is epsilon (see gemm_residual_kernel).
 // EPI_LSE (lm-head of the masked log-prob pass): the product is formed transposed (weights as the
 // MFMA row operand; both operands have the same lane layout, so swapping them costs nothing), which
 // puts 16 vocabulary entries of one batch row into the registers of a lane.  The epilogue reduces
@@ -71,6 +72,20 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // step), written to zt[row * (N / 32) + strip]: the sampler gets the row maximum it needs before
 // any weight can be formed from V / 32 numbers per row instead of a pass over the logits.
 // =============================================================================================
+// Sum of p[x * stride] over x = first, first + step, ... below n, in ascending order, eight reads in flight (a loop with
+// one read at a time is a chain of latencies: 64 of them 2.4 us).
+__device__ __forceinline__ float strided_sum(const float* __restrict__ p, int first, int step, int n, int stride) {
+  float t = 0.f;
+  for (int x = first; x < n; x += 8 * step) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) v[u] = p[min(x + u * step, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; u++) t += x + u * step < n ? v[u] : 0.f;
+  }
+  return t;
+}
+
 // SwiGLU of one transposed 32x32 block (EPI_SWIGLU forms the product with the weights as the row
 // operand): lane l holds, for batch row l % 32, weight rows (i / 4) * 8 + (l / 32) * 4 + i % 4, and the
 // repack puts 8 gate rows before the 8 up rows of the same units: gate and up of a unit are in the same
@@ -220,7 +235,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
 #pragma unroll
     for (int mb = 0; mb < MB; mb++) {
       const int row = mt * 128 + mb * 32 + (lane & 31);
-      auto val = [&](int i) { return acc[mb][i]; };
+      float inv = 1.0f;
+      if (EPI == EPI_SWIGLU && zt) {      // added up in the order of gemm_decode_kernel
+        const float* p = zt + min(row, M - 1);
+        const int r16 = (M + 15) >> 4 << 4, q = (lane >> 5) * 2;
+        float t = strided_sum(p, q, 4, K >> 4, r16) + strided_sum(p, q + 1, 4, K >> 4, r16);
+        t += __shfl_xor(t, 32, 64);
+        inv = 1.0f / sqrtf(t / (float)K + scale_c);
+      }
+      auto val = [&](int i) { return EPI == EPI_SWIGLU ? acc[mb][i] * inv : acc[mb][i]; };
       if (EPI == EPI_SWIGLU) swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
       else lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
     }
@@ -666,6 +689,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
   }
 }
 
+constexpr int kLdsBytes = 160 * 1024;     // of a CU
 // More than 64 KB of dynamic LDS need an opt-in, once per kernel and device.
 static void set_lds_limit(std::atomic<uint64_t>& done, const void* kernel, int bytes) {
   int dev = 0;
@@ -709,7 +733,7 @@ static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C
 template <int EPI, int RB, int CB, int SK, int NST, bool NT>
 __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K, int splits,
-                                                       int stages_per_split) {
+                                                       int stages_per_split, const float* __restrict__ ssq, float eps) {
   constexpr int KB = SK / 32;                    // 32-k steps of a stage
   constexpr int NA = 4 * RB * KB, NW = CB * KB;  // blocks
   constexpr int PW = (NA + NW) / 4;
@@ -759,6 +783,12 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
   for (int c = 0; c < CB; c++)
 #pragma unroll
     for (int r = 0; r < RB; r++) acc[c][r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // the sums of squares behind the ring; the ring's loads are younger, so its first wait covers these
+  const int ss_bytes = EPI == EPI_SWIGLU && ssq ? r16 * (K >> 4) * 64 : 0;
+  if (EPI == EPI_SWIGLU) {
+    const u32x4 rs = buffer_rsrc(ssq, (unsigned)ss_bytes);
+    for (int p = wave; p * 1024 < ss_bytes; p += 4) load_to_lds(lds0 + NST * BUF + p * 1024, lane * 16, rs, (unsigned)p * 1024u);
+  }
 #pragma unroll
   for (int p = 0; p < NST - 1; p++)
 #pragma unroll
@@ -796,12 +826,21 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
 #pragma unroll
   for (int r = 0; r < RB; r++) {
     const int row = (wave * RB + r) * 16 + (lane & 15);
+    float inv = 1.0f;
+    if (ss_bytes) {       // the row's norm: every lane group of 16 sums every fourth partial sum
+      const float* sq = (const float*)(smem + NST * (BUF / 16)) + min(row, r16 * 16 - 1);
+      float t = strided_sum(sq, lane >> 4, 4, K >> 4, r16 * 16);
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      inv = 1.0f / sqrtf(t / (float)K + eps);
+    }
 #pragma unroll
     for (int c = 0; c < CB; c++) {
       const int c16 = tile * CB + c;
       if (c16 >= N16) continue;
       f32x4 v = acc[c][r];
       if (EPI == EPI_SWIGLU) {
+        v *= inv;
         f32x4 up;
 #pragma unroll
         for (int i = 0; i < 4; i++) up[i] = __shfl_xor(v[i], 32, 64);
@@ -820,27 +859,180 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
   }
 }
 
+// LDS of a workgroup: the ring and, with the rows' sums of squares, those of `scaled` rows
+static int decode_gemm_lds(int M, int K, int cb, bool scaled) {
+  const int rb = M <= 64 ? 1 : 2, sk = cb == 5 ? 128 : 64, nst = cb == 5 ? 3 : 4;
+  return nst * (4 * rb + cb) * (sk / 32) * 1024 + (scaled ? ((M + 15) / 16 * (K / 16) * 64 + 1023) / 1024 * 1024 : 0);
+}
 template <int EPI, int CB>
-static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits) {
+static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
+                               const float* ssq, float eps) {
   constexpr int SK = CB == 5 ? 128 : 64, NST = CB == 5 ? 3 : 4;   // CB = 5: whole rounds of 4 waves need 128 k
-  const int rb = M <= 64 ? 1 : 2, lds = NST * (4 * rb + CB) * (SK / 32) * 1024;
+  const int rb = M <= 64 ? 1 : 2, lds = decode_gemm_lds(M, K, CB, ssq != nullptr);
   const bool nt = rb == 1 && streams_weights(N, K);
   static std::atomic<uint64_t> done[3];
   auto go = [&](auto kernel) {
-    set_lds_limit(done[nt ? 2 : rb - 1], (const void*)kernel, lds);
+    set_lds_limit(done[nt ? 2 : rb - 1], (const void*)kernel, kLdsBytes);
     const int sps = (K / SK + splits - 1) / splits;
-    kernel<<<(N / 16 + CB - 1) / CB * splits, 256, lds, s>>>(A, Wp, C, M, N, K, splits, sps);
+    kernel<<<(N / 16 + CB - 1) / CB * splits, 256, lds, s>>>(A, Wp, C, M, N, K, splits, sps, ssq, eps);
   };
   if (nt) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, true>);
   else if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, false>);
   else go(gemm_decode_kernel<EPI, 2, CB, SK, NST, false>);
 }
 
+// =============================================================================================
+// O and down of few rows, with the residual add and the norm behind them: h += A * W^T, out = bf16(h * g) in A-tile
+// layout, not yet divided by the row's rms, and per 16 columns the row's sum of squares, ssq[N / 16][rows in
+// use rounded up to 16].  The consumer (QKV's norm / RoPE kernel, gate-up's epilogue) divides: a row's factor commutes with the
+// product, and bf16 rounds h g and h g / rms alike.  The separate norm (4 to 6 us: a launch and a chain of memory
+// round trips for a few KB per row) and the fp32 partial sums between the two are gone.
+// Tile 16 RB rows x 16 CB columns, as narrow as gives most CUs a workgroup without slicing K over workgroups; the
+// workgroup's four waves take every fourth 32-k step, operands straight to registers, U steps in flight, and one wave per
+// 16 x 16 block adds the four sums in ascending order: a row's bits depend on neither the tile nor the row count.  (Eight waves:
+// 0 to 1 us slower.)  Bound by the weights' stream (16 rows) and by what a CU fetches (about
+// 50 GB/s of both operands): more rows re-read the weights in every row tile, so it is taken where its estimate beats
+// the sliced product and the norm (plan_residual).
+// us, sliced product + norm -> this: N = 1024 K = 2048 at 1 / 64 rows 6.8 -> 4.4 / 7.7 -> 4.0, K = 3072 at 64 8.2 -> 5.1;
+// N = 2560 K = 4096 at 16 / 64 11.9 -> 7.2 / 12.5 -> 10.9, K = 9728 at 16 15.7 -> 14.0; N = 4096 K = 4096 at 16 / 64
+// 13.4 -> 8.3 / 14.8 -> 11.6, K = 12288 at 16 24.0 -> 18.9.
+// =============================================================================================
+template <int RB, int CB, int U, bool NT>
+__global__ __launch_bounds__(256) void gemm_residual_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp, float* __restrict__ h, const bf16_t* __restrict__ g,
+    bf16_t* __restrict__ out, float* __restrict__ ssq, int M, int N, int K, int row_tiles) {
+  constexpr int NW = 4, NBLK = RB * CB, OWN = (NBLK + NW - 1) / NW;      // 16 x 16 blocks, and those that a wave finishes
+  __shared__ f32x4 red[NW][NBLK][64];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int NB = N >> 5, N16 = N >> 4, steps = K >> 5, r16 = (M + 15) >> 4;
+  // the row tiles of a column tile follow each other on one XCD, whose L2 then has the weights
+  int ct = blockIdx.x, rt = 0;
+  if (row_tiles > 1) {
+    const int y = blockIdx.x >> 3;
+    rt = y % row_tiles;
+    ct = y / row_tiles * 8 + (blockIdx.x & 7);
+  }
+  if (ct * CB >= N16) return;
+  const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, ((M + 127) >> 7) * K * 256, 0x00027000);
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)Wp, 0, (int)((unsigned)N * (unsigned)K * 2u), 0x00027000);
+  const int lp = ((lane & 15) + (((lane >> 4) & 1) << 5)) << 4;
+  const int lw = ((lane >> 5) << 10) + lp, la = ((lane >> 5) << 12) + lp;
+  f32x4 acc[CB][RB];
+#pragma unroll
+  for (int c = 0; c < CB; c++)
+#pragma unroll
+    for (int r = 0; r < RB; r++) acc[c][r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  u32x4 w[U][CB], a[U][RB];
+  auto fetch = [&](int u, int t) {      // steps behind the end and row blocks without rows: behind the buffer, zeros
+    const bool in = t < steps;
+#pragma unroll
+    for (int c = 0; c < CB; c++) {
+      const int c16 = ct * CB + c;
+      const int so = ((t >> 1) * NB + (c16 >> 1)) * 4096 + (t & 1) * 2048 + (c16 & 1) * 256;
+      w[u][c] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              rw, in && c16 < N16 ? lw : 0x7fff0000, in && c16 < N16 ? so : 0, NT ? 2 : 0));
+    }
+#pragma unroll
+    for (int r = 0; r < RB; r++) {
+      const int x = rt * RB + r;
+      const int so = (x >> 3) * K * 256 + t * 8192 + (x >> 1 & 3) * 1024 + (x & 1) * 256;
+      a[u][r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                              ra, in && x < r16 ? la : 0x7fff0000, in && x < r16 ? so : 0, 0));
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < U; u++) fetch(u, wave + u * NW);
+  f32x4 old[OWN];
+  uint2 gw[OWN];
+#pragma unroll
+  for (int k = 0; k < OWN; k++) {
+    const int b = k * NW + wave, row = (rt * RB + b % RB) * 16 + (lane & 15), col = (ct * CB + b / RB) * 16 + 4 * (lane >> 4);
+    old[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    gw[k] = make_uint2(0u, 0u);
+    if (b < NBLK && row < M && col < N) {
+      old[k] = *(const f32x4*)(h + (size_t)row * N + col);
+      gw[k] = *(const uint2*)(g + col);
+    }
+  }
+  for (int t = wave; t < steps; t += NW * U) {
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+#pragma unroll
+      for (int c = 0; c < CB; c++)
+#pragma unroll
+        for (int r = 0; r < RB; r++)
+          acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[u][c]),
+                                                              __builtin_bit_cast(bf16x8, a[u][r]), acc[c][r], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(u, t + (u + U) * NW);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CB; c++)
+#pragma unroll
+    for (int r = 0; r < RB; r++) red[wave][c * RB + r][lane] = acc[c][r];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < OWN; k++) {
+    const int b = k * NW + wave;
+    if (b >= NBLK) break;
+    const int row = (rt * RB + b % RB) * 16 + (lane & 15), c16 = ct * CB + b / RB, col = c16 * 16 + 4 * (lane >> 4);
+    f32x4 v = red[0][b][lane];
+#pragma unroll
+    for (int x = 1; x < NW; x++) v += red[x][b][lane];
+    v += old[k];
+    float ss = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (row >= M || c16 >= N16) continue;
+    *(f32x4*)(h + (size_t)row * N + col) = v;
+    const uint32_t y0 = f2bf(v[0] * bf2f((bf16_t)(gw[k].x & 0xffff))), y1 = f2bf(v[1] * bf2f((bf16_t)(gw[k].x >> 16)));
+    const uint32_t y2 = f2bf(v[2] * bf2f((bf16_t)(gw[k].y & 0xffff))), y3 = f2bf(v[3] * bf2f((bf16_t)(gw[k].y >> 16)));
+    *(uint2*)(out + atile_off(row, col, N)) = make_uint2(y0 | (y1 << 16), y2 | (y3 << 16));
+    if (lane < 16) ssq[(size_t)c16 * (r16 * 16) + row] = ss;
+  }
+}
+
+// Tile of the product with residual add and norm, and its estimate in us: per round of 256 workgroups 1.28, 1.75 or
+// 2.1 us per 1000 k for 16 x 16, 16 x 32 and 32 x 32 (what the workgroup's operands take), plus the launch and what the
+// consumer takes to add up the sums of squares.  Fitted on six products of hidden 1024 to 4096 at 1 to 128 rows.
+// rb = 0: not for this size.
+ResidualPlan plan_residual(int M, int N, int K) {
+  ResidualPlan best{0, 0, 1e30};
+  if (M > kResidualRows || (size_t)N * K * 2 >= 0x7fff0000ull) return best;
+  const struct { int rb, cb; double launch, per_k; } tiles[] = {{1, 1, 3.0, 1.28e-3}, {1, 2, 3.0, 1.75e-3}, {2, 2, 3.1, 2.1e-3}};
+  for (const auto& t : tiles) {
+    const int wgs = (M + 16 * t.rb - 1) / (16 * t.rb) * ((N / 16 + t.cb - 1) / t.cb);
+    const double cost = t.launch + (wgs + 255) / 256 * (K * t.per_k);
+    if (cost < best.cost) best = ResidualPlan{t.rb, t.cb, cost};
+  }
+  return best;
+}
+bool gate_up_takes_scale(const GemmPlan& plan, int M, int K) {
+  return plan.kind == GEMM_TILE128 || (plan.kind == GEMM_DECODE && decode_gemm_lds(M, K, plan.width, true) <= kLdsBytes);
+}
+
+void launch_gemm_residual(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* h, const bf16_t* g, bf16_t* out, float* ssq,
+                          int M, int N, int K, const ResidualPlan& plan) {
+  if (M <= 0) return;
+  const int rt = (M + 16 * plan.rb - 1) / (16 * plan.rb), ct = (N / 16 + plan.cb - 1) / plan.cb;
+  const int grid = rt == 1 ? ct : (ct + 7) / 8 * 8 * rt;
+  const bool nt = rt == 1 && streams_weights(N, K);
+  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(A, Wp, h, g, out, ssq, M, N, K, rt); };
+  if (plan.cb == 1 && nt) go(gemm_residual_kernel<1, 1, 8, true>);
+  else if (plan.cb == 1) go(gemm_residual_kernel<1, 1, 8, false>);
+  else if (plan.rb == 1 && nt) go(gemm_residual_kernel<1, 2, 6, true>);
+  else if (plan.rb == 1) go(gemm_residual_kernel<1, 2, 6, false>);
+  else if (nt) go(gemm_residual_kernel<2, 2, 4, true>);
+  else go(gemm_residual_kernel<2, 2, 4, false>);
+}
+
 template <int EPI>
 static void gemm_launch(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits, int cps,
-                        float* zt) {
+                        float* zt, float scale_c) {
   const dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
-  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, zt, 0.f); };
+  auto go = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, zt, scale_c); };
   const bool nt = streams_weights(N, K);
   if (M <= 32 && nt) go(gemm_mfma_kernel<EPI, 1, true>);      // row blocks in use (one row tile when < 4)
   else if (M <= 32) go(gemm_mfma_kernel<EPI, 1, false>);
@@ -920,7 +1112,7 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
 }
 
 int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
-                     const GemmPlan& plan) {
+                     const GemmPlan& plan, const float* ssq, float eps) {
   if (M <= 0) return 0;
   const int width = plan.width, sp = plan.splits;
   const QkvArgs none{};
@@ -942,10 +1134,10 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   if (plan.kind == GEMM_DECODE) {
     auto go = [&](auto epi) {
       constexpr int E = decltype(epi)::value;
-      if (width == 2) launch_decode_gemm<E, 2>(s, A, Wp, C, M, N, K, sp);
-      else if (width == 4) launch_decode_gemm<E, 4>(s, A, Wp, C, M, N, K, sp);
-      else if (width == 5) launch_decode_gemm<E, 5>(s, A, Wp, C, M, N, K, sp);
-      else launch_decode_gemm<E, 6>(s, A, Wp, C, M, N, K, sp);
+      if (width == 2) launch_decode_gemm<E, 2>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else if (width == 4) launch_decode_gemm<E, 4>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else if (width == 5) launch_decode_gemm<E, 5>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else launch_decode_gemm<E, 6>(s, A, Wp, C, M, N, K, sp, ssq, eps);
     };
     if (epilogue == EPI_STORE) go(std::integral_constant<int, EPI_STORE>());
     else go(std::integral_constant<int, EPI_SWIGLU>());
@@ -955,8 +1147,8 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   int splits = epilogue == EPI_SWIGLU ? 1 : std::max(1, std::min(sp, nchunks));
   const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
-  if (epilogue == EPI_STORE) gemm_launch<EPI_STORE>(s, A, Wp, C, M, N, K, splits, cps, nullptr);
-  else gemm_launch<EPI_SWIGLU>(s, A, Wp, C, M, N, K, splits, cps, nullptr);
+  if (epilogue == EPI_STORE) gemm_launch<EPI_STORE>(s, A, Wp, C, M, N, K, splits, cps, nullptr, 0.f);
+  else gemm_launch<EPI_SWIGLU>(s, A, Wp, C, M, N, K, splits, cps, const_cast<float*>(ssq), eps);
   return splits;
 }
 
@@ -976,7 +1168,7 @@ void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, in
 void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* logits, int M,
                            int V, int K, float* stripmax) {
   if (M <= 0) return;
-  gemm_launch<EPI_STORE_MAX>(s, A, Wp, logits, M, V, K, 1, K / 64, stripmax);
+  gemm_launch<EPI_STORE_MAX>(s, A, Wp, logits, M, V, K, 1, K / 64, stripmax, 0.f);
 }
 
 // One workgroup per row: combine the per-strip (max, sum) pairs in a fixed order and write

@@ -75,4 +75,17 @@ DECODE = [
     _dims(3392, 24, 3, 448),        # 96-column tiles with slices of unequal length
     _dims(1536, 8, 8, 384),
     _dims(3392, 16, 2, 256),
+    _dims(2816, 10, 5, 192),        # QKV: 80 columns, slices of unequal length, at most 64 rows
+    _dims(1536, 14, 7, 256),        # QKV ends inside a tile of 96 columns, at most 64 rows
+]
+
+# O and down with the residual add and the norm inside, two layers so that every consumer of the undivided rows runs
+RESIDUAL_ROWS = [1, 16, 17, 33, 64, 65, 128, 129, 300, 512]
+RESIDUAL = [
+    _dims(64, 1, 1, 64),            # K of two 32-k steps: waves without any
+    _dims(320, 3, 3, 448),          # K = 384 and 448: the waves' shares differ
+    _dims(1024, 16, 8, 3072),
+    _dims(2560, 32, 8, 1088),
+    _dims(4096, 2, 2, 4096),        # 256 column blocks
+    _dims(4160, 4, 4, 1024),        # 260: two rounds of the narrowest tile
 ]

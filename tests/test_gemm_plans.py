@@ -5,7 +5,7 @@ import random
 import pytest
 
 import paper_2509_06980_amd as rl
-from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, small
+from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from synthetic import SHAPES
 
 PRODUCTS = ("qkv", "o", "gate_up", "down", "score_head", "logits_head")
@@ -131,3 +131,53 @@ def test_decode_cases_reach_every_tile():
             assert (width, "store", more, "unequal slices") in seen
         for width in (5, 6):                                       # every width is a multiple of 64
             assert (width, "store", more, "ends inside") in seen and (width, "swiglu", more, "ends inside") in seen
+
+
+def test_decode_cases_reach_every_tile_beside_the_residual_products():
+    # O and down leave the plan where they carry the residual add: the sliced tiles are reached without them
+    seen = set()
+    for change in DECODE:
+        s = small(**change)
+        for rows in DECODE_ROWS:
+            inside = rl.debug_residual_plan(s, rows)
+            for name, (kernel, width, slices, epilogue) in rl.debug_pass_plan(s, rows).items():
+                if kernel == "decode" and name not in inside:
+                    n, k = _dims(s)[name]
+                    stages = k // (128 if width == 5 else 64)
+                    seen |= {(width, epilogue, rows > 64, n % (16 * width) != 0), (width, epilogue, rows > 64, "unequal", stages % slices != 0)}
+    for more in (False, True):
+        for width in (2, 4, 5, 6):
+            assert (width, "store", more, "unequal", True) in seen
+        for width in (5, 6):
+            assert (width, "store", more, True) in seen and (width, "swiglu", more, True) in seen
+
+
+def test_residual_products_tiles_and_bounds():
+    reached = {}
+    for change in RESIDUAL:
+        s = small(**change)
+        for rows in RESIDUAL_ROWS:
+            for name, tile in rl.debug_residual_plan(s, rows).items():
+                reached.setdefault((name, tile), set()).add(rows)
+    for name in ("o", "down"):
+        for tile in ((1, 1), (1, 2), (2, 2)):
+            assert (name, tile) in reached, (name, tile)
+        assert {1, 16} <= reached[name, (1, 1)] and {17, 33} & reached[name, (1, 2)] and 64 in reached[name, (2, 2)]
+    rng = random.Random(6)
+    for _ in range(2000):
+        nkv = rng.choice([1, 2, 4, 8])
+        s = SHAPES["small-d128"].replace(hidden=64 * rng.randint(1, 96), n_kv_heads=nkv, n_q_heads=nkv * rng.choice([1, 2, 4]),
+                                         intermediate=64 * rng.randint(1, 256))
+        rows = int(round(2 ** rng.uniform(0, 9)))
+        plan, inside = rl.debug_pass_plan(s, rows), rl.debug_residual_plan(s, rows)
+        assert not inside or rows <= 512
+        assert "down" not in inside or plan["qkv"][3] == "store"      # the norm / RoPE kernel divides the rows
+        if "o" in inside:             # gate-up divides them: the 128-column kernel, or the decode kernel where its ring
+            kernel, width = plan["gate_up"][:2]                       # and 4 bytes per row and 16 columns fit 160 KB
+            assert kernel in ("decode", "tile128")
+            if kernel == "tile128":
+                continue
+            ring = (3 if width == 5 else 4) * (4 * (1 if rows <= 64 else 2) + width) * (4 if width == 5 else 2) * 1024
+            assert ring + -(-rows // 16) * 16 * (s.hidden // 16) * 4 <= 160 * 1024
+    for rows in (1, 16, 512):
+        assert "down" not in rl.debug_residual_plan(SHAPES["qwen3-8b"].replace(intermediate=262144), rows)      # 31-bit offsets

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
-from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, small
+from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from oracle import OracleEngine
 from oracle.bf16_error_model import forward_bf16_model
 from oracle.decoder import forward_full
@@ -223,4 +223,32 @@ def test_decode_products_row_counts(change, rows):
     o, picked = OracleEngine(blob, **kw), sorted({0, rows // 2, rows - 1})
     o.append_observation(picked, toks.reshape(rows, 3)[picked].reshape(-1), [3] * len(picked))
     assert np.abs(la[picked] - o.decode_step_forced(picked, 1.0, forced[picked])).max() < 3e-2
+    a.close(), b.close()
+
+
+@pytest.mark.parametrize("change", RESIDUAL)
+@pytest.mark.parametrize("rows", RESIDUAL_ROWS)
+def test_residual_add_and_norm_inside_the_products(change, rows):
+    # two layers: gate-up and the next layer's QKV divide the rows by their rms, the last norm reads the stream itself;
+    # the same trajectory twice in the batch has the same bits wherever its row lies
+    shape = small(**change).replace(n_layers=2)
+    blob = make_weight_blob(shape, seed=8, weight_std=0.02, gain_std=0.1)
+    kw = dict(max_context=32, max_trajectories=rows, kv_pool_pages=rows)
+    a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
+    rng = np.random.default_rng(rows)
+    ids = np.arange(rows, dtype=np.int32)
+    toks, forced = rng.integers(0, shape.vocab, (rows, 3)), rng.integers(0, shape.vocab, (2, rows))
+    toks[-1], forced[:, -1] = toks[0], forced[:, 0]
+    for e in (a, b):
+        e.append_observation(ids, toks.reshape(-1), [3] * rows)
+    o, picked = OracleEngine(blob, **kw), sorted({0, rows // 2, rows - 1})
+    o.append_observation(picked, toks[picked].reshape(-1), [3] * len(picked))
+    # logits of deviation below 1.3, as in the one-layer cases and their 3e-2: the layers' roundings are independent,
+    # their energies add, and two layers have at most twice that of one and the head
+    bound = 3e-2 * 2 ** 0.5
+    for step in forced:
+        la, lb = (e.decode_step_forced(ids, 1.0, step) for e in (a, b))
+        assert la[0] == la[-1]
+        assert np.abs(la - lb).max() < bound
+        assert np.abs(la[picked] - o.decode_step_forced(picked, 1.0, step[picked])).max() < bound
     a.close(), b.close()
