@@ -744,10 +744,14 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // Slices of a tile are neighbours, except four long ones: dealt round-robin to the 8 XCDs they would put every other
   // tile of a slice on an XCD (N = 4096 K = 4096 at 16 rows, 64 columns: 9.4 us; K = 12288 21.0).  There an XCD takes a
-  // contiguous range of tiles of one slice (7.9, 17.9; N = 6144 K = 4096 10.4 -> 10.2).  Other counts and slices under
-  // 512 k are better off, or no worse, the plain way (N = 4096 K = 1024: 3.7 against 4.3).
+  // contiguous range of tiles of one slice (7.9, 17.9; N = 6144 K = 4096 10.4 -> 10.2).  Other counts, slices under
+  // 512 k and more than 64 rows are better off, or no worse, the plain way (N = 4096 K = 1024: 3.7 against 4.3; N = 6144
+  // K = 2560 at 128 rows 10.7 against 11.0).
   int tile, split;
-  if (splits == 4 && stages_per_split * SK >= 512) {
+  if constexpr (EPI == EPI_SWIGLU) {      // one slice
+    tile = blockIdx.x;
+    split = 0;
+  } else if (RB == 1 && splits == 4 && stages_per_split * SK >= 512) {
     const int tiles = gridDim.x / 4, base = gridDim.x >> 3, rem = gridDim.x & 7, x = blockIdx.x & 7;
     const int v = x * base + min(x, rem) + (blockIdx.x >> 3);
     split = __builtin_amdgcn_readfirstlane(v / tiles);
@@ -757,7 +761,7 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
     split = blockIdx.x - tile * splits;
   }
   const int NB = N >> 5, N16 = N >> 4, nst = K / SK;
-  const int s0 = split * stages_per_split, s1 = min(s0 + stages_per_split, nst);
+  const int s0 = split * stages_per_split, s1 = EPI == EPI_SWIGLU ? nst : min(s0 + stages_per_split, nst);
   const int r16 = (M + 15) >> 4;      // 16-row blocks in use: the others are not fetched
   const u32x4 ra = buffer_rsrc(A, (unsigned)K * 256u), rw = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
