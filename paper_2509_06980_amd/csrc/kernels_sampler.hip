@@ -343,6 +343,114 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
   }
 }
 
+// Where the line lies: rl_sample on 1 / 256 rows of 4096 logits 12.8 / 14.8 -> 5.3 / 6.1 us, 8192 13.4 / 15.5 -> 6.1 / 7.2,
+// 16384 13.3 / 17.9 -> 9.1 / 10.6.  A thread holds no more than 16, and rows that cannot be read in 16-byte pieces lose from
+// 8192 on (16001, greedy: 11.3 -> 13.5).
+constexpr int kRowLogits = 16384, kRowLogitsScalar = 4096;
+// Rows of up to 16 T logits: maximum, weights, sums and search in one workgroup of T threads, 16 consecutive logits a
+// thread, all in registers.  The three launches above are three latency chains (4 rows of 4096: 3.5 + 4.4 + 3.4 us and the gaps
+// between them); a row that fits one workgroup needs none of their hand-over through memory.
+template <int T, bool VEC>
+__global__ __launch_bounds__(T) void sample_row_kernel(
+    const float* __restrict__ z, size_t ldz, int V, float c, int greedy, const uint32_t* __restrict__ u32, uint64_t seed,
+    const int32_t* __restrict__ row_traj, const int32_t* __restrict__ row_newpos, const int32_t* __restrict__ forced,
+    const uint8_t* __restrict__ out_mask, int32_t* __restrict__ ids_out, float* __restrict__ logp_out) {
+  constexpr int NW = T / 64, PER = 16;
+  __shared__ float sm[NW], se[NW], s_z;
+  __shared__ int sa[NW], s_id;
+  __shared__ uint64_t sw[NW];
+  const int row = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, base = tid * PER;
+  const float* zr = z + (size_t)row * ldz;
+  float v[PER];
+  if (VEC) {
+#pragma unroll
+    for (int j = 0; j < PER; j += 4) {
+      const float4 q = *(const float4*)(zr + (base + j < V ? base + j : 0));
+      v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < PER; j++) v[j] = zr[base + j < V ? base + j : 0];
+  }
+  const int want = forced ? forced[row] : -1;
+  float m = -INFINITY;
+  int arg = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < PER; j++)
+    if (base + j < V && (v[j] > m || (v[j] == m && base + j < arg))) { m = v[j]; arg = base + j; }
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(m, o, 64);
+    const int oa = __shfl_xor(arg, o, 64);
+    if (ov > m || (ov == m && oa < arg)) { m = ov; arg = oa; }
+  }
+  if (lane == 0) { sm[wave] = m; sa[wave] = arg; }
+  if (tid == 0) { s_id = -1; s_z = 0.f; }
+  __syncthreads();
+  m = sm[0];
+  arg = sa[0];
+  for (int k = 1; k < NW; k++)
+    if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
+  uint64_t wl[PER], mine = 0;
+  float e = 0.f;
+#pragma unroll
+  for (int j = 0; j < PER; j++) {
+    float x;
+    uint32_t w;
+    exp2_weight(v[j], m, c, x, w);
+    const bool in = base + j < V;
+    wl[j] = in ? (uint64_t)w + (x >= kTwo32 ? kTop : 0u) : 0;
+    mine += wl[j];
+    e = __fadd_rn(e, in ? x : 0.f);
+  }
+  uint64_t incl = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += y;
+  }
+  for (int o = 32; o > 0; o >>= 1) e = __fadd_rn(e, __shfl_xor(e, o, 64));
+  if (lane == 63) sw[wave] = incl;
+  if (lane == 0) se[wave] = e;
+  __syncthreads();
+  uint64_t before = incl - mine, W = 0;
+  float E = 0.f;
+  for (int k = 0; k < NW; k++) {
+    if (k < wave) before += sw[k];
+    W += sw[k];
+    E = __fadd_rn(E, se[k]);
+  }
+  E *= 0x1p-32f;
+  if (forced || greedy) {
+    const int id = forced ? want : (arg == 0x7fffffff ? 0 : arg);      // a row without any number: token 0
+#pragma unroll
+    for (int j = 0; j < PER; j++)
+      if (base + j == id && id < V) s_z = v[j];
+    if (tid == 0) s_id = id;
+  } else {
+    const uint32_t u = u32 ? u32[row] : splitmix_u32(seed, row_traj[row], row_newpos[row]);
+    const uint64_t hi = __umul64hi(W, (uint64_t)u), lo = W * (uint64_t)u;
+    const uint64_t r = (hi << 32) | (lo >> 32);          // floor(u * W / 2^32) < W
+    if (before <= r && r < before + mine) {
+      uint64_t acc = before;
+      bool found = false;
+#pragma unroll
+      for (int j = 0; j < PER; j++) {
+        acc += wl[j];
+        if (!found && acc > r) { found = true; s_id = base + j; s_z = v[j]; }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const bool drawn = !(forced || greedy);
+    const int id = drawn && s_id < 0 ? 0 : s_id;         // no weight at all: token 0 and no number as its log-prob
+    const float zid = drawn && s_id < 0 ? __builtin_nanf("") : s_z;
+    float lp = 0.f;
+    if (!(out_mask && out_mask[row])) lp = __fmul_rn(__fsub_rn(zid, m), c) * 0.6931471805599453f - logf(E);
+    if (ids_out) ids_out[row] = id;
+    logp_out[row] = lp;
+  }
+}
+
 void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, int V, float scale_c,
                     int greedy, const uint32_t* u32, uint64_t seed, const int32_t* row_traj,
                     const int32_t* row_newpos, const int32_t* forced, const uint8_t* out_mask,
@@ -352,6 +460,15 @@ void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, in
   const int nseg = sampler_nseg(V);
   const dim3 grid(nseg, rows);
   const bool vec = V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+  if (V <= (vec ? kRowLogits : kRowLogitsScalar)) {
+    auto go = [&](auto kernel, int threads) {
+      kernel<<<rows, threads, 0, s>>>(logits, ldz, V, scale_c, greedy, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out, logp_out);
+    };
+    if (V <= 4096) vec ? go(sample_row_kernel<256, true>, 256) : go(sample_row_kernel<256, false>, 256);
+    else if (V <= 8192) vec ? go(sample_row_kernel<512, true>, 512) : go(sample_row_kernel<512, false>, 512);
+    else vec ? go(sample_row_kernel<1024, true>, 1024) : go(sample_row_kernel<1024, false>, 1024);
+    return;
+  }
   if (greedy || nstrips <= 0) stripmax = nullptr;   // the arg-max needs the pass over the logits
   if (!stripmax) {
     if (vec) seg_max_kernel<true><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
