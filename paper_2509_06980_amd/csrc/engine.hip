@@ -213,6 +213,37 @@ void forward_generic(rl_model* m, int M, const RowMeta& r) {
   }
 }
 
+// fp32: the norms, the activation and, for few rows and small heads, QK-norm + RoPE + cache write inside the products.
+// False where the blob's layout does not give the products whole 16-byte pieces (forward_generic takes those).
+bool forward_fp32(rl_model* m, int M, const RowMeta& r) {
+  hipStream_t s = m->stream;
+  const ModelDims& md = m->md;
+  const int H = md.H, qw = md.nq * md.d, QW = qw + 2 * md.nkv * md.d, I = md.I;
+  for (const LayerW& w : m->layers)
+    if (!norm_gemm32_takes(m->h, w.g_in, w.wqkv, H) || !norm_gemm32_takes(m->h, w.g_post, w.wgu, H)) return false;
+  if (((uintptr_t)m->embed & 15) != 0) return false;
+  const bool qkv = norm_qkv32_takes(md, M);
+  for (int l = 0; l < md.L; l++) {
+    const LayerW& w = m->layers[l];
+    const int32_t* tok = l == 0 ? r.tok : nullptr;
+    if (qkv) {
+      launch_norm_qkv32(s, m->h, (const float*)m->embed, tok, (const float*)w.g_in, (const float*)w.wqkv, (const float*)w.gq,
+                        (const float*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table, (float*)m->qb, m->pools[l], md, M);
+    } else {
+      launch_norm_gemm32(s, m->h, (const float*)m->embed, tok, (const float*)w.g_in, (const float*)w.wqkv, m->qkv, M, QW, H, md.eps, false);
+      launch_qkrope<float, float, float>(s, m->qkv, (const float*)w.gq, (const float*)w.gk, m->rope_cs, r.pos, r.slot,
+                                         m->page_table, (float*)m->qb, m->pools[l], md, M);
+    }
+    if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
+    launch_attention_generic<float, float>(s, (const float*)m->qb, m->pools[l], r.pos, r.slot, m->page_table, (float*)m->xo, md, M);
+    if (r.time_attn) (void)hipEventRecord(m->ev[2 * l + 1], s);
+    launch_gemm_generic<float, float>(s, (const float*)m->xo, (const float*)w.wo, m->h, M, H, qw, true);
+    launch_norm_gemm32(s, m->h, nullptr, nullptr, (const float*)w.g_post, (const float*)w.wgu, (float*)m->xm, M, I, H, md.eps, true);
+    launch_gemm_generic<float, float>(s, (const float*)m->xm, (const float*)w.wdown, m->h, M, H, I, true);
+  }
+  return true;
+}
+
 // Rows of the split-K partial-sum buffers: one pass of `cap` rows, and up to kMaxSplits slices of passes of up
 // to 1024 rows.  plan_gemm keeps slices times rows within them.
 size_t partial_rows(size_t cap) { return std::max<size_t>(cap, (size_t)kMaxSplits * std::min<size_t>(cap, 1024)); }
@@ -316,7 +347,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
 void forward_rows(rl_model* m, int M, const RowMeta& r) {
   if (m->mfma) forward_mfma(m, M, r);
   else if (m->bf16) forward_generic<bf16_t, bf16_t>(m, M, r);
-  else forward_generic<float, float>(m, M, r);
+  else if (!forward_fp32(m, M, r)) forward_generic<float, float>(m, M, r);
 }
 
 // final norm + lm-head for rows [r0, r0 + R) of m->h -> m->logits[0 .. R)
@@ -346,6 +377,8 @@ void lm_head_rows(rl_model* m, int M, int r0, int R, bool norm_done, int norm_ro
       launch_rmsnorm<bf16_t, bf16_t>(s, m->h, (const bf16_t*)m->g_final, (bf16_t*)m->xa, norm_rows, md.H, md.eps);
     launch_gemm_generic<bf16_t, bf16_t>(s, (const bf16_t*)m->xa + (size_t)r0 * md.H,
                                         (const bf16_t*)m->lm_head, m->logits, R, md.V, md.H, false);
+  } else if (!norm_done && r0 == 0 && R == norm_rows && norm_gemm32_takes(m->h, m->g_final, m->lm_head, md.H)) {
+    launch_norm_gemm32(s, m->h, nullptr, nullptr, (const float*)m->g_final, (const float*)m->lm_head, m->logits, R, md.V, md.H, md.eps, false);
   } else {
     if (!norm_done)
       launch_rmsnorm<float, float>(s, m->h, (const float*)m->g_final, (float*)m->xa, norm_rows, md.H, md.eps);

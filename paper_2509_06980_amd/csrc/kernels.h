@@ -91,6 +91,17 @@ void launch_attention_generic(hipStream_t s, const TA* q, KvPool pool, const int
 template <typename TA>
 void launch_swiglu(hipStream_t s, const float* gu, TA* m, int M, int I);
 
+// fp32 models.  C = (rmsnorm(h) * g) * W^T, or with swiglu silu of the first N columns times the second N (W: 2N rows).
+// tok != null (not with swiglu): h is first filled with the embeddings of tok.  Needs norm_gemm32_takes.
+bool norm_gemm32_takes(const void* h, const void* g, const void* W, int K);
+void launch_norm_gemm32(hipStream_t s, float* h, const float* E, const int32_t* tok, const float* g, const float* W, float* C,
+                        int M, int N, int K, float eps, bool swiglu);
+// The same norm, then QKV and what launch_qkrope does, in one launch, where norm_qkv32_takes as well.
+bool norm_qkv32_takes(const ModelDims& md, int M);
+void launch_norm_qkv32(hipStream_t s, float* h, const float* E, const int32_t* tok, const float* g, const float* W,
+                       const float* gq, const float* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
+                       const int32_t* page_table, float* qout, KvPool pool, const ModelDims& md, int M);
+
 // ---- MFMA kernels (bf16, head_dim 128) -------------------------------------------------------
 enum GemmEpilogue { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_LSE = 3, EPI_STORE_MAX = 4, EPI_QKV = 5, EPI_QKV8 = 6, EPI_ADD = 7 };
 // Kernel and K-slices of one product (see plan_gemm's definition).  GEMM_TILE128: 128 x 128 tiles; GEMM_TILE256:

@@ -233,17 +233,19 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const TA* __restrict_
 // The same product on the fp32 matrix instruction (16x16x4: exact fp32 products, fp32 accumulation), for
 // rows of whole 4-element pieces.  A wave forms 16 R rows x 16 columns with no LDS in its loop: lane
 // (i = lane % 16, g = lane / 16) reads four consecutive k of row (column) i at k0 + 4 g and feeds
-// component c of both operands to MFMA c, whose k index is then k0 + 4 g + c on either side.  The four
-// waves of a workgroup take every fourth 16-k step, several steps in flight, and wave r adds the four
-// sums of row block r in ascending order.  At the few rows of a decode step a launch is
-// a chain of memory round trips, not arithmetic: K / 128 of them here, against K / 16 with two barriers
+// component c of both operands to MFMA c, whose k index is then k0 + 4 g + c on either side.  The eight
+// waves of a workgroup take every eighth 16-k step, several steps in flight, and the eight sums are added in ascending
+// order, a row of each group of four per wave.  At the few rows of a decode step a launch is
+// a chain of memory round trips, not arithmetic: K / 768 of them here, against K / 16 with two barriers
 // each in the tile kernel above, which keeps the shapes whose rows are not whole pieces (4 rows: K = 256
-// 30 -> 3.3 us, K = 688 85 -> 5.1 us; 51 200 rows at hidden 1024, fp32: a two-layer prefill 138 -> 95 ms).
+// 30 -> 2.7 us, K = 688 85 -> 4.5 us, 5.6 with four waves; 51 200 rows at hidden 1024, fp32: a two-layer prefill 138 -> 95 ms
+// with four waves, 82 ms with eight and the norm inside).
+constexpr int kWaves32 = 8;
 template <typename TA, typename TW, int R>
-__global__ __launch_bounds__(256) void gemm_mfma32_kernel(const TA* __restrict__ A, const TW* __restrict__ W,
+__global__ __launch_bounds__(64 * kWaves32) void gemm_mfma32_kernel(const TA* __restrict__ A, const TW* __restrict__ W,
                                                           float* __restrict__ C, int M, int N, int K,
                                                           int accumulate) {
-  __shared__ f32x4 red[R][4][64];
+  __shared__ f32x4 red[R][kWaves32][64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * R);
   const TW* w = W + (size_t)min(n0 + i, N - 1) * K;      // rows and columns past the end: repeated, not stored
@@ -253,12 +255,12 @@ __global__ __launch_bounds__(256) void gemm_mfma32_kernel(const TA* __restrict__
   f32x4 acc[R];
 #pragma unroll
   for (int r = 0; r < R; r++) acc[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  constexpr int U = R == 1 ? 4 : 2;                      // 16-k steps in flight
-  for (int k0 = wave * 16; k0 < K; k0 += 64 * U) {
+  constexpr int U = R == 1 ? 6 : 2, STEP = 16 * kWaves32;   // 16-k steps in flight
+  for (int k0 = wave * 16; k0 < K; k0 += STEP * U) {
     float wv[U][4], av[U][R][4];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const int k = k0 + 64 * u + 4 * g;
+      const int k = k0 + STEP * u + 4 * g;
       const bool in = k < K;                             // K % 4 == 0: a piece is inside or outside as a whole
 #pragma unroll
       for (int e = 0; e < 4; e++) wv[u][e] = 0.f;
@@ -281,21 +283,232 @@ __global__ __launch_bounds__(256) void gemm_mfma32_kernel(const TA* __restrict__
 #pragma unroll
   for (int r = 0; r < R; r++) red[r][wave][lane] = acc[r];
   __syncthreads();
+  const int n = n0 + i;
+  if (n >= N) return;
+#pragma unroll
+  for (int x = 0; x < 4 * R; x += kWaves32) {      // one row of every four-row group of a block per wave
+    const int y = x + wave, r = y >> 2, e = y & 3;
+    if (y >= 4 * R) break;
+    // the same order for every row: a row's bits do not depend on where it lies in the batch
+    float v = red[r][0][lane][e];
+#pragma unroll
+    for (int q = 1; q < kWaves32; q++) v += red[r][q][lane][e];
+    const int row = m0 + 16 * r + 4 * g + e;
+    if (row < M) {
+      float* c = C + (size_t)row * N + n;
+      *c = accumulate ? *c + v : v;
+    }
+  }
+}
+
+// fp32 models: rmsnorm and the product behind it in one launch, C[M, N] = (rmsnorm(h) g) W^T, and with SWIGLU also the
+// activation: W holds N gate rows, then N up rows, C = silu(gate) * up.  The loop of gemm_mfma32_kernel; the rows of h pass
+// through every workgroup anyway, so each sums their squares on the way and divides its 16 columns at the end (the factor
+// of a row commutes with the product).  A pass of a few rows is a chain of launches of 2 to 5 us; this takes out the norms (2.0 us
+// each and the gap) and the activation (2.3 us): gate-up at 4 rows, K = 256, N = 688 2.0 + 3.3 + 2.3 -> 4.7 us.  EMB: the rows are the embeddings of tok, written to h by the first
+// column of workgroups.
+template <int R, bool SWIGLU, bool EMB>
+__global__ __launch_bounds__(64 * kWaves32) void norm_gemm32_kernel(float* h, const float* __restrict__ E,
+                                                          const int32_t* __restrict__ tok, const float* __restrict__ gain,
+                                                          const float* __restrict__ W, float* __restrict__ C, int M, int N,
+                                                          int K, float eps) {
+  constexpr int S = SWIGLU ? 2 : 1;
+  __shared__ f32x4 red[S][R][kWaves32][64];
+  __shared__ float sq[R][kWaves32][16];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * R), n = n0 + i;
+  const float* w[S];
+#pragma unroll
+  for (int s = 0; s < S; s++) w[s] = W + ((size_t)s * N + min(n, N - 1)) * K;    // rows and columns past the end: repeated, not stored
+  const float* a[R];
 #pragma unroll
   for (int r = 0; r < R; r++) {
-    if (wave != (r & 3)) continue;
-    // the same order for every row: a row's bits do not depend on where it lies in the batch
-    const f32x4 v = ((red[r][0][lane] + red[r][1][lane]) + red[r][2][lane]) + red[r][3][lane];
-    const int n = n0 + i;
-    if (n >= N) continue;
+    const int row = min(m0 + 16 * r + i, M - 1);
+    a[r] = EMB ? E + (size_t)tok[row] * K : h + (size_t)row * K;
+  }
+  f32x4 acc[S][R];
+  float ss[R];
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int row = m0 + 16 * r + 4 * g + e;
-      if (row < M) {
-        float* c = C + (size_t)row * N + n;
-        *c = accumulate ? *c + v[e] : v[e];
+  for (int r = 0; r < R; r++) {
+    ss[r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < S; s++) acc[s][r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  constexpr int U = R == 1 ? 4 : 2, STEP = 16 * kWaves32;
+  for (int k0 = wave * 16; k0 < K; k0 += STEP * U) {
+    float wv[U][S][4], av[U][R][4], gv[U][4];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int k = k0 + STEP * u + 4 * g;
+      const bool in = k < K;                             // K % 4 == 0: a piece is inside or outside as a whole
+      const float zero = 0.f;
+      auto get = [&](const float* p, float (&x)[4]) {
+        x[0] = x[1] = x[2] = x[3] = zero;
+        if (in) ld4(p + k, x[0], x[1], x[2], x[3]);
+      };
+      get(gain, gv[u]);
+#pragma unroll
+      for (int s = 0; s < S; s++) get(w[s], wv[u][s]);
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+        get(a[r], av[u][r]);
+        if (EMB && in && blockIdx.x == 0 && m0 + 16 * r + i < M)
+          *(f32x4*)(h + (size_t)(m0 + 16 * r + i) * K + k) = (f32x4){av[u][r][0], av[u][r][1], av[u][r][2], av[u][r][3]};
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          ss[r] = __builtin_fmaf(av[u][r][e], av[u][r][e], ss[r]);
+          const float x = av[u][r][e] * gv[u][e];
+#pragma unroll
+          for (int s = 0; s < S; s++) acc[s][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv[u][s][e], acc[s][r], 0, 0, 0);
+        }
+  }
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+#pragma unroll
+    for (int s = 0; s < S; s++) red[s][r][wave][lane] = acc[s][r];
+    ss[r] += __shfl_xor(ss[r], 16, 64);
+    ss[r] += __shfl_xor(ss[r], 32, 64);
+    if (lane < 16) sq[r][wave][lane] = ss[r];
+  }
+  __syncthreads();
+  if (n >= N) return;
+#pragma unroll
+  for (int x = 0; x < 4 * R; x += kWaves32) {      // one row of every four-row group of a block per wave
+    const int y = x + wave, r = y >> 2, e = y & 3, m = 4 * g + e, row = m0 + 16 * r + m;
+    if (y >= 4 * R) break;
+    // the same order for every row: a row's bits do not depend on where it lies in the batch
+    float v[S], t = sq[r][0][m];
+#pragma unroll
+    for (int s = 0; s < S; s++) v[s] = red[s][r][0][lane][e];
+#pragma unroll
+    for (int q = 1; q < kWaves32; q++) {
+      t += sq[r][q][m];
+#pragma unroll
+      for (int s = 0; s < S; s++) v[s] += red[s][r][q][lane][e];
+    }
+    if (row >= M) continue;
+    const float inv = 1.0f / sqrtf(t / (float)K + eps);
+    float z = v[0] * inv;
+    if (SWIGLU) z = z / (1.0f + expf(-z)) * (v[S - 1] * inv);
+    C[(size_t)row * N + n] = z;
+  }
+}
+
+// fp32 models, few rows: rmsnorm, one head's QKV projection, QK-norm, RoPE and the cache write in one launch (grid: heads x blocks
+// of 16 rows).  D: head_dim, 64 or 128.  The four waves share K as above; the head's 16 x D block is put together in LDS,
+// where 16 lanes then own a row's head.  Against the product and the norm / RoPE kernel: two launches and the fp32 projection
+// less (4 rows, 8 heads of 64, K = 256: 2.0 + 3.4 + 3.2 -> 6.0 us and two gaps); but a head is one workgroup's, which
+// reads D K weights alone, so it is for small K (see the launcher).
+template <int D, bool EMB>
+__global__ __launch_bounds__(64 * kWaves32) void norm_qkv32_kernel(float* h, const float* __restrict__ E, const int32_t* __restrict__ tok,
+                                                         const float* __restrict__ gain, const float* __restrict__ W,
+                                                         const float* __restrict__ gq, const float* __restrict__ gk,
+                                                         const float* __restrict__ rope_cs, const int32_t* __restrict__ row_pos,
+                                                         const int32_t* __restrict__ row_slot,
+                                                         const int32_t* __restrict__ page_table, float* __restrict__ qout,
+                                                         float* __restrict__ kpool, float* __restrict__ vpool, int nq, int nkv,
+                                                         int M, int K, float eps, int qk_norm, int pt_stride) {
+  constexpr int CB = D / 16, U = 2, HALF = D / 2, LPR = 4 * kWaves32, PP = HALF / LPR, STEP = 16 * kWaves32;
+  __shared__ f32x4 red[kWaves32][CB][64];
+  __shared__ float xs[16][D + 1], sq[kWaves32][16];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
+  const int hd = blockIdx.x, m0 = blockIdx.y * 16;
+  const float* w = W + ((size_t)hd * D + i) * K;
+  const int arow = min(m0 + i, M - 1);
+  const float* a = EMB ? E + (size_t)tok[arow] * K : h + (size_t)arow * K;
+  // what the end needs, asked for first: LPR lanes own a row's head, each PP pairs of dims
+  const int x = tid / LPR, sub = tid % LPR, row = m0 + x, prow = min(row, M - 1);
+  const bool is_q = hd < nq, is_v = hd >= nq + nkv;
+  const int pos = row_pos[prow], page = page_table[(size_t)row_slot[prow] * pt_stride + (pos >> 4)];
+  float cs[PP], sn[PP], g1[PP], g2[PP];
+#pragma unroll
+  for (int j = 0; j < PP; j++) {
+    const int d = sub + LPR * j;
+    cs[j] = rope_cs[((size_t)pos * HALF + d) * 2];
+    sn[j] = rope_cs[((size_t)pos * HALF + d) * 2 + 1];
+    g1[j] = (is_q ? gq : gk)[d];
+    g2[j] = (is_q ? gq : gk)[d + HALF];
+  }
+  f32x4 acc[CB];
+#pragma unroll
+  for (int c = 0; c < CB; c++) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  float ss = 0.f;
+  for (int k0 = wave * 16; k0 < K; k0 += STEP * U) {
+    float wv[U][CB][4], av[U][4], gv[U][4];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int k = k0 + STEP * u + 4 * g;
+      const bool in = k < K;
+      auto get = [&](const float* p, float (&x)[4]) {
+        x[0] = x[1] = x[2] = x[3] = 0.f;
+        if (in) ld4(p + k, x[0], x[1], x[2], x[3]);
+      };
+      get(a, av[u]);
+      get(gain, gv[u]);
+#pragma unroll
+      for (int c = 0; c < CB; c++) get(w + (size_t)c * 16 * K, wv[u][c]);
+      if (EMB && in && hd == 0 && m0 + i < M)
+        *(f32x4*)(h + (size_t)(m0 + i) * K + k) = (f32x4){av[u][0], av[u][1], av[u][2], av[u][3]};
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        ss = __builtin_fmaf(av[u][e], av[u][e], ss);
+        const float x = av[u][e] * gv[u][e];
+#pragma unroll
+        for (int c = 0; c < CB; c++) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv[u][c][e], acc[c], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int c = 0; c < CB; c++) red[wave][c][lane] = acc[c];
+  ss += __shfl_xor(ss, 16, 64);
+  ss += __shfl_xor(ss, 32, 64);
+  if (lane < 16) sq[wave][lane] = ss;
+  __syncthreads();
+  if (wave < CB) {
+    f32x4 v = red[0][wave][lane];
+#pragma unroll
+    for (int q = 1; q < kWaves32; q++) v += red[q][wave][lane];
+#pragma unroll
+    for (int e = 0; e < 4; e++) xs[4 * g + e][16 * wave + i] = v[e];
+  }
+  __syncthreads();
+  if (row >= M) return;          // whole groups of LPR lanes; no barrier below
+  float t = sq[0][x];
+#pragma unroll
+  for (int q = 1; q < kWaves32; q++) t += sq[q][x];
+  const float inv_row = 1.0f / sqrtf(t / (float)K + eps);
+  float lo[PP], hi[PP], s2 = 0.f;
+#pragma unroll
+  for (int j = 0; j < PP; j++) {
+    lo[j] = xs[x][sub + LPR * j] * inv_row;
+    hi[j] = xs[x][sub + LPR * j + HALF] * inv_row;
+    s2 = __builtin_fmaf(hi[j], hi[j], __builtin_fmaf(lo[j], lo[j], s2));
+  }
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, LPR);
+  const float inv = (qk_norm && !is_v) ? 1.0f / sqrtf(s2 / (float)D + eps) : 1.0f;
+  float* dst = is_q ? qout + ((size_t)row * nq + hd) * D
+                    : (is_v ? vpool : kpool) + (((size_t)page * nkv + (is_v ? hd - nq - nkv : hd - nq)) * RL_PAGE + (pos & (RL_PAGE - 1))) * D;
+#pragma unroll
+  for (int j = 0; j < PP; j++) {
+    const int d = sub + LPR * j;
+    float u = lo[j], v = hi[j];
+    if (!is_v) {
+      if (qk_norm) { u = u * inv * g1[j]; v = v * inv * g2[j]; }
+      const float y = u * cs[j] - v * sn[j];
+      v = v * cs[j] + u * sn[j];
+      u = y;
+    }
+    dst[d] = u;
+    dst[d + HALF] = v;
   }
 }
 
@@ -488,9 +701,9 @@ void launch_gemm_generic(hipStream_t s, const TA* A, const TW* W, float* C, int 
   const bool vec = K % 4 == 0 && ((uintptr_t)A % (4 * sizeof(TA))) == 0 && ((uintptr_t)W % (4 * sizeof(TW))) == 0;
   if (vec) {
     if (M <= 16)
-      gemm_mfma32_kernel<TA, TW, 1><<<dim3((N + 15) / 16, 1), 256, 0, s>>>(A, W, C, M, N, K, accumulate ? 1 : 0);
+      gemm_mfma32_kernel<TA, TW, 1><<<dim3((N + 15) / 16, 1), 64 * kWaves32, 0, s>>>(A, W, C, M, N, K, accumulate ? 1 : 0);
     else
-      gemm_mfma32_kernel<TA, TW, 4><<<dim3((N + 15) / 16, (M + 63) / 64), 256, 0, s>>>(A, W, C, M, N, K,
+      gemm_mfma32_kernel<TA, TW, 4><<<dim3((N + 15) / 16, (M + 63) / 64), 64 * kWaves32, 0, s>>>(A, W, C, M, N, K,
                                                                                        accumulate ? 1 : 0);
     return;
   }
@@ -499,6 +712,41 @@ void launch_gemm_generic(hipStream_t s, const TA* A, const TW* W, float* C, int 
 }
 template void launch_gemm_generic<float, float>(hipStream_t, const float*, const float*, float*, int, int, int, bool);
 template void launch_gemm_generic<bf16_t, bf16_t>(hipStream_t, const bf16_t*, const bf16_t*, float*, int, int, int, bool);
+
+bool norm_gemm32_takes(const void* h, const void* g, const void* W, int K) {
+  return K % 4 == 0 && (((uintptr_t)h | (uintptr_t)g | (uintptr_t)W) & 15) == 0;
+}
+void launch_norm_gemm32(hipStream_t s, float* h, const float* E, const int32_t* tok, const float* g, const float* W, float* C,
+                        int M, int N, int K, float eps, bool swiglu) {
+  if (M <= 0) return;
+  auto go = [&](auto kernel, int rows) {
+    kernel<<<dim3((N + 15) / 16, (M + rows - 1) / rows), 64 * kWaves32, 0, s>>>(h, E, tok, g, W, C, M, N, K, eps);
+  };
+  if (M <= 16) {
+    if (swiglu) go(norm_gemm32_kernel<1, true, false>, 16);
+    else if (tok) go(norm_gemm32_kernel<1, false, true>, 16);
+    else go(norm_gemm32_kernel<1, false, false>, 16);
+  } else {
+    if (swiglu) go(norm_gemm32_kernel<4, true, false>, 64);
+    else if (tok) go(norm_gemm32_kernel<4, false, true>, 64);
+    else go(norm_gemm32_kernel<4, false, false>, 64);
+  }
+}
+// A head's weights are at most 128 KB (a workgroup reads them at about 50 GB/s) and no more than four blocks of 16 rows
+// read them again.
+bool norm_qkv32_takes(const ModelDims& md, int M) { return (md.d == 64 || md.d == 128) && md.d * md.H <= 32768 && M <= 64; }
+void launch_norm_qkv32(hipStream_t s, float* h, const float* E, const int32_t* tok, const float* g, const float* W,
+                       const float* gq, const float* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
+                       const int32_t* page_table, float* qout, KvPool pool, const ModelDims& md, int M) {
+  if (M <= 0) return;
+  auto go = [&](auto kernel) {
+    kernel<<<dim3(md.nq + 2 * md.nkv, (M + 15) / 16), 64 * kWaves32, 0, s>>>(h, E, tok, g, W, gq, gk, rope_cs, row_pos, row_slot, page_table,
+                                                                 qout, (float*)pool.k, (float*)pool.v, md.nq, md.nkv, M, md.H,
+                                                                 md.eps, md.qk_norm, md.max_pages_per_traj);
+  };
+  if (md.d == 64) tok ? go(norm_qkv32_kernel<64, true>) : go(norm_qkv32_kernel<64, false>);
+  else tok ? go(norm_qkv32_kernel<128, true>) : go(norm_qkv32_kernel<128, false>);
+}
 
 // head_dim 128, bf16, MFMA cache layout: grid (M, ceil(heads / 16)), block 256.  Sixteen lanes
 // own one head: lane `sub` holds dims 4 sub .. 4 sub + 3 and their rotate-half partners 64 + ...,

@@ -252,3 +252,30 @@ def test_residual_add_and_norm_inside_the_products(change, rows):
         assert np.abs(la - lb).max() < bound
         assert np.abs(la[picked] - o.decode_step_forced(picked, 1.0, step[picked])).max() < bound
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("hidden,head_dim,heads,intermediate", [
+    (256, 64, (4, 2), 688), (256, 128, (2, 1), 324),     # norm, QKV, RoPE and cache write in one launch up to 64 rows
+    (20, 64, (1, 1), 20),                                # one piece of four, waves without a step
+    (516, 64, (3, 3), 260),                              # too wide for it: the norm inside the product, RoPE apart
+    (256, 48, (4, 2), 100), (254, 64, (4, 2), 256)])     # another head_dim; rows that are no whole pieces: apart
+@pytest.mark.parametrize("rows", [1, 16, 17, 64, 65])
+def test_fp32_products_with_the_norm_inside(hidden, head_dim, heads, intermediate, rows):
+    shape = SHAPES["tiny"].replace(hidden=hidden, head_dim=head_dim, n_q_heads=heads[0], n_kv_heads=heads[1],
+                                   intermediate=intermediate, vocab=516)
+    blob = make_weight_blob(shape, seed=9, weight_std=0.03, gain_std=0.1)
+    kw = dict(max_context=32, max_trajectories=rows, kv_pool_pages=2 * rows)
+    o, g = OracleEngine(blob, **kw), rl.RolloutEngine(blob, **kw)
+    rng = np.random.default_rng(rows)
+    ids, lens = np.arange(rows, dtype=np.int32), rng.integers(1, 9, rows)
+    toks = rng.integers(0, shape.vocab, int(lens.sum()))
+    for e in (o, g):
+        e.append_observation(ids, toks, lens)
+    for step in range(2):
+        forced = rng.integers(0, shape.vocab, rows)
+        a, b = (e.decode_step_forced(ids, 1.0, forced) for e in (o, g))
+        assert np.abs(a - b).max() < 1e-4            # the fp32 bound of the whole suite
+    k = rows // 2
+    assert np.abs(o.debug_logits(k) - g.debug_logits(k)).max() < 1e-4
+    assert np.abs(np.asarray(o.recompute_logprobs([k], 1.0)) - g.recompute_logprobs([k], 1.0)).max() < 1e-4
+    g.close()
