@@ -401,8 +401,8 @@ __global__ __launch_bounds__(64 * kWaves32) void norm_gemm32_kernel(float* h, co
 }
 
 // fp32 models, few rows: rmsnorm, one head's QKV projection, QK-norm, RoPE and the cache write in one launch (grid: heads x blocks
-// of 16 rows).  D: head_dim, 64 or 128.  The four waves share K as above; the head's 16 x D block is put together in LDS,
-// where 16 lanes then own a row's head.  Against the product and the norm / RoPE kernel: two launches and the fp32 projection
+// of 16 rows).  D: head_dim, 64 or 128.  The waves share K as above; the head's 16 x D block is put together in LDS,
+// where 32 lanes then own a row's head.  Against the product and the norm / RoPE kernel: two launches and the fp32 projection
 // less (4 rows, 8 heads of 64, K = 256: 2.0 + 3.4 + 3.2 -> 6.0 us and two gaps); but a head is one workgroup's, which
 // reads D K weights alone, so it is for small K (see the launcher).
 template <int D, bool EMB>

@@ -1004,7 +1004,8 @@ __global__ __launch_bounds__(256) void gemm_residual_kernel(
 // rb = 0: not for this size.
 ResidualPlan plan_residual(int M, int N, int K) {
   ResidualPlan best{0, 0, 1e30};
-  if (M > kResidualRows || (size_t)N * K * 2 >= 0x7fff0000ull) return best;
+  // 31-bit offsets into the weights and into the row tiles
+  if (M > kResidualRows || (size_t)N * K * 2 >= 0x7fff0000ull || (size_t)((M + 127) / 128) * K * 256 >= 0x7fff0000ull) return best;
   const struct { int rb, cb; double launch, per_k; } tiles[] = {{1, 1, 3.0, 1.28e-3}, {1, 2, 3.0, 1.75e-3}, {2, 2, 3.1, 2.1e-3}};
   for (const auto& t : tiles) {
     const int wgs = (M + 16 * t.rb - 1) / (16 * t.rb) * ((N / 16 + t.cb - 1) / t.cb);
