@@ -752,8 +752,11 @@ void launch_norm_qkv32(hipStream_t s, float* h, const float* E, const int32_t* t
 // own one head: lane `sub` holds dims 4 sub .. 4 sub + 3 and their rotate-half partners 64 + ...,
 // so partial sums arrive as 16-byte loads (all issued before the first add) and q, k leave as
 // 8-byte stores.  FP8: keys and values go from fp32 straight to E4M3 codes (8-bit cache layout).
-template <bool FP8>
-__global__ __launch_bounds__(256) void qkrope128_kernel(
+// UNDIV: the row is still to be divided by the rms of the projection's input, ssq holds that input's sums of squares.  A
+// choice at compile time: tested at run time the plain form with the 8-bit cache took 101 registers instead of 84, 4 waves
+// a SIMD instead of 5.  The bound holds the dividing forms at five (93 registers; 101 without it).
+template <bool FP8, bool UNDIV>
+__global__ __launch_bounds__(256, 5) void qkrope128_kernel(
     const float* __restrict__ qkv, int n_part, size_t part_stride, const bf16_t* __restrict__ gq,
     const bf16_t* __restrict__ gk, const float* __restrict__ rope_cs,
     const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_slot,
@@ -772,7 +775,7 @@ __global__ __launch_bounds__(256) void qkrope128_kernel(
     hi[p] = p < n_part ? *(const float4*)(x + (size_t)p * part_stride + 64) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   float sq = 0.f;            // the row's sum of squares where its norm is still to be applied: n16 partial sums
-  if (ssq)
+  if (UNDIV)
     for (int x = sub; x < n16; x += 16 * 8) {      // eight reads in flight: one at a time cost 2.6 us (160 sums) to 4 us
       float v[8];
 #pragma unroll
@@ -792,7 +795,7 @@ __global__ __launch_bounds__(256) void qkrope128_kernel(
       a[0] += lo[p].x; a[1] += lo[p].y; a[2] += lo[p].z; a[3] += lo[p].w;
       b[0] += hi[p].x; b[1] += hi[p].y; b[2] += hi[p].z; b[3] += hi[p].w;
     }
-  if (ssq) {
+  if (UNDIV) {
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 16);
     const float inv = 1.0f / sqrtf(sq / (float)hidden + eps);
@@ -881,8 +884,8 @@ void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_s
                                 (bf16_t*)pool.k, (bf16_t*)pool.v, md.nq, md.nkv, md.eps, md.qk_norm,
                                 md.max_pages_per_traj, ssq, md.H / 16, (M + 15) / 16 * 16, md.H);
   };
-  if (md.kv_fp8) go(qkrope128_kernel<true>);
-  else go(qkrope128_kernel<false>);
+  if (md.kv_fp8) ssq ? go(qkrope128_kernel<true, true>) : go(qkrope128_kernel<true, false>);
+  else ssq ? go(qkrope128_kernel<false, true>) : go(qkrope128_kernel<false, false>);
 }
 
 template <typename TW, typename TA, typename TKV>

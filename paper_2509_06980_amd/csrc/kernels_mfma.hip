@@ -60,8 +60,9 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // fetches, and the A chunk is half of them, so small batches gain most of what they leave out
 // (N = 4096 K = 12288 in eight slices: 22.9 us with all four row blocks, 18.4 at 12 rows, 20.3 at 64; lm-head
 // 151936 x 2560 151 -> 137 us at 12 rows, 154 -> 145 at 48); results per row are unchanged.
-// EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.  EPI_SWIGLU with zt: the rows of A are still to be
-// divided by their rms, zt holds their sums of squares and scale_c is epsilon (see gemm_residual_kernel).
+// EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.  UNDIV (EPI_SWIGLU): the rows of A are still to be
+// divided by their rms, zt holds their sums of squares and scale_c is epsilon (see gemm_residual_kernel).  A choice at compile
+// time: tested at run time the division had grown the plain form from 7.4 to 13.3 KB of code with four row blocks.
 // EPI_LSE (lm-head of the masked log-prob pass): the product is formed transposed (weights as the
 // MFMA row operand; both operands have the same lane layout, so swapping them costs nothing), which
 // puts 16 vocabulary entries of one batch row into the registers of a lane.  The epilogue reduces
@@ -139,7 +140,7 @@ __device__ __forceinline__ void lse_block(F val, float2* __restrict__ P, float* 
 // 21 MB nothing, and those of a model that the cache holds (4 MB, 64 of them in turn) lose up to 30 % (3.0 -> 3.9 us).
 static bool streams_weights(int N, int K) { return (size_t)N * K * 2 >= ((size_t)24 << 20); }
 
-template <int EPI, int MB, bool NT>
+template <int EPI, int MB, bool NT, bool UNDIV = false>
 __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
                                                         const bf16_t* __restrict__ Wp,
                                                         void* __restrict__ Cv, int M, int N,
@@ -236,14 +237,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
     for (int mb = 0; mb < MB; mb++) {
       const int row = mt * 128 + mb * 32 + (lane & 31);
       float inv = 1.0f;
-      if (EPI == EPI_SWIGLU && zt) {      // added up in the order of gemm_decode_kernel
+      if (UNDIV) {      // added up in the order of gemm_decode_kernel
         const float* p = zt + min(row, M - 1);
         const int r16 = (M + 15) >> 4 << 4, q = (lane >> 5) * 2;
         float t = strided_sum(p, q, 4, K >> 4, r16) + strided_sum(p, q + 1, 4, K >> 4, r16);
         t += __shfl_xor(t, 32, 64);
         inv = 1.0f / sqrtf(t / (float)K + scale_c);
       }
-      auto val = [&](int i) { return EPI == EPI_SWIGLU ? acc[mb][i] * inv : acc[mb][i]; };
+      auto val = [&](int i) { return UNDIV ? acc[mb][i] * inv : acc[mb][i]; };
       if (EPI == EPI_SWIGLU) swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
       else lse_block(val, (float2*)Cv, zt, tgt, row, M, nb, NB, lane, scale_c);
     }
@@ -730,7 +731,9 @@ static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C
 // 17.9; at 96 rows 0 to 2 %.  Deeper rings gain nothing; leaving out the loads behind the slice with a branch costs
 // 10 % (the loop falls apart into blocks).
 // =============================================================================================
-template <int EPI, int RB, int CB, int SK, int NST, bool NT>
+// UNDIV (SwiGLU): the rows of A are still to be divided by their rms, ssq holds their sums of squares.  A choice at compile time:
+// tested at run time the division had grown the plain form from 12.5 to 15 KB of code.
+template <int EPI, int RB, int CB, int SK, int NST, bool NT, bool UNDIV>
 __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K, int splits,
                                                        int stages_per_split, const float* __restrict__ ssq, float eps) {
@@ -788,8 +791,8 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
 #pragma unroll
     for (int r = 0; r < RB; r++) acc[c][r] = (f32x4){0.f, 0.f, 0.f, 0.f};
   // the sums of squares behind the ring; the ring's loads are younger, so its first wait covers these
-  const int ss_bytes = EPI == EPI_SWIGLU && ssq ? r16 * (K >> 4) * 64 : 0;
-  if (EPI == EPI_SWIGLU) {
+  if (UNDIV) {
+    const int ss_bytes = r16 * (K >> 4) * 64;
     const u32x4 rs = buffer_rsrc(ssq, (unsigned)ss_bytes);
     for (int p = wave; p * 1024 < ss_bytes; p += 4) load_to_lds(lds0 + NST * BUF + p * 1024, lane * 16, rs, (unsigned)p * 1024u);
   }
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
   for (int r = 0; r < RB; r++) {
     const int row = (wave * RB + r) * 16 + (lane & 15);
     float inv = 1.0f;
-    if (ss_bytes) {       // the row's norm: every lane group of 16 sums every fourth partial sum
+    if (UNDIV) {       // the row's norm: every lane group of 16 sums every fourth partial sum
       const float* sq = (const float*)(smem + NST * (BUF / 16)) + min(row, r16 * 16 - 1);
       float t = strided_sum(sq, lane >> 4, 4, K >> 4, r16 * 16);
       t += __shfl_xor(t, 16, 64);
@@ -844,7 +847,7 @@ __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restri
       if (c16 >= N16) continue;
       f32x4 v = acc[c][r];
       if (EPI == EPI_SWIGLU) {
-        v *= inv;
+        if (UNDIV) v *= inv;
         f32x4 up;
 #pragma unroll
         for (int i = 0; i < 4; i++) up[i] = __shfl_xor(v[i], 32, 64);
@@ -868,11 +871,11 @@ static int decode_gemm_lds(int M, int K, int cb, bool scaled) {
   const int rb = M <= 64 ? 1 : 2, sk = cb == 5 ? 128 : 64, nst = cb == 5 ? 3 : 4;
   return nst * (4 * rb + cb) * (sk / 32) * 1024 + (scaled ? ((M + 15) / 16 * (K / 16) * 64 + 1023) / 1024 * 1024 : 0);
 }
-template <int EPI, int CB>
+template <int EPI, int CB, bool UNDIV>
 static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
                                const float* ssq, float eps) {
   constexpr int SK = CB == 5 ? 128 : 64, NST = CB == 5 ? 3 : 4;   // CB = 5: whole rounds of 4 waves need 128 k
-  const int rb = M <= 64 ? 1 : 2, lds = decode_gemm_lds(M, K, CB, ssq != nullptr);
+  const int rb = M <= 64 ? 1 : 2, lds = decode_gemm_lds(M, K, CB, UNDIV);
   const bool nt = rb == 1 && streams_weights(N, K);
   static std::atomic<uint64_t> done[3];
   auto go = [&](auto kernel) {
@@ -880,9 +883,9 @@ static void launch_decode_gemm(hipStream_t s, const bf16_t* A, const bf16_t* Wp,
     const int sps = (K / SK + splits - 1) / splits;
     kernel<<<(N / 16 + CB - 1) / CB * splits, 256, lds, s>>>(A, Wp, C, M, N, K, splits, sps, ssq, eps);
   };
-  if (nt) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, true>);
-  else if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, false>);
-  else go(gemm_decode_kernel<EPI, 2, CB, SK, NST, false>);
+  if (nt) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, true, UNDIV>);
+  else if (rb == 1) go(gemm_decode_kernel<EPI, 1, CB, SK, NST, false, UNDIV>);
+  else go(gemm_decode_kernel<EPI, 2, CB, SK, NST, false, UNDIV>);
 }
 
 // =============================================================================================
@@ -1033,17 +1036,17 @@ void launch_gemm_residual(hipStream_t s, const bf16_t* A, const bf16_t* Wp, floa
   else go(gemm_residual_kernel<2, 2, 4, false>);
 }
 
-template <int EPI>
+template <int EPI, bool UNDIV = false>
 static void gemm_launch(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits, int cps,
                         float* zt, float scale_c) {
   const dim3 grid((N + 127) / 128, (M + 127) / 128, splits);
   auto go = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(A, Wp, C, M, N, K, cps, nullptr, zt, scale_c); };
   const bool nt = streams_weights(N, K);
-  if (M <= 32 && nt) go(gemm_mfma_kernel<EPI, 1, true>);      // row blocks in use (one row tile when < 4)
-  else if (M <= 32) go(gemm_mfma_kernel<EPI, 1, false>);
-  else if (M <= 64 && nt) go(gemm_mfma_kernel<EPI, 2, true>);
-  else if (M <= 64) go(gemm_mfma_kernel<EPI, 2, false>);
-  else go(gemm_mfma_kernel<EPI, 4, false>);
+  if (M <= 32 && nt) go(gemm_mfma_kernel<EPI, 1, true, UNDIV>);      // row blocks in use (one row tile when < 4)
+  else if (M <= 32) go(gemm_mfma_kernel<EPI, 1, false, UNDIV>);
+  else if (M <= 64 && nt) go(gemm_mfma_kernel<EPI, 2, true, UNDIV>);
+  else if (M <= 64) go(gemm_mfma_kernel<EPI, 2, false, UNDIV>);
+  else go(gemm_mfma_kernel<EPI, 4, false, UNDIV>);
 }
 
 // Which kernel and how many K-slices: the cheapest by estimate (us), over at most kMaxSplits slices of
@@ -1137,15 +1140,17 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
     return epilogue == EPI_ADD ? 0 : sp;
   }
   if (plan.kind == GEMM_DECODE) {
-    auto go = [&](auto epi) {
+    auto go = [&](auto epi, auto undiv) {
       constexpr int E = decltype(epi)::value;
-      if (width == 2) launch_decode_gemm<E, 2>(s, A, Wp, C, M, N, K, sp, ssq, eps);
-      else if (width == 4) launch_decode_gemm<E, 4>(s, A, Wp, C, M, N, K, sp, ssq, eps);
-      else if (width == 5) launch_decode_gemm<E, 5>(s, A, Wp, C, M, N, K, sp, ssq, eps);
-      else launch_decode_gemm<E, 6>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      constexpr bool U = decltype(undiv)::value;
+      if (width == 2) launch_decode_gemm<E, 2, U>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else if (width == 4) launch_decode_gemm<E, 4, U>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else if (width == 5) launch_decode_gemm<E, 5, U>(s, A, Wp, C, M, N, K, sp, ssq, eps);
+      else launch_decode_gemm<E, 6, U>(s, A, Wp, C, M, N, K, sp, ssq, eps);
     };
-    if (epilogue == EPI_STORE) go(std::integral_constant<int, EPI_STORE>());
-    else go(std::integral_constant<int, EPI_SWIGLU>());
+    if (epilogue == EPI_STORE) go(std::integral_constant<int, EPI_STORE>(), std::false_type());
+    else if (!ssq) go(std::integral_constant<int, EPI_SWIGLU>(), std::false_type());
+    else go(std::integral_constant<int, EPI_SWIGLU>(), std::true_type());
     return sp;
   }
   const int nchunks = K / 64;
@@ -1153,7 +1158,8 @@ int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, 
   const int cps = (nchunks + splits - 1) / splits;
   splits = (nchunks + cps - 1) / cps;
   if (epilogue == EPI_STORE) gemm_launch<EPI_STORE>(s, A, Wp, C, M, N, K, splits, cps, nullptr, 0.f);
-  else gemm_launch<EPI_SWIGLU>(s, A, Wp, C, M, N, K, splits, cps, const_cast<float*>(ssq), eps);
+  else if (!ssq) gemm_launch<EPI_SWIGLU>(s, A, Wp, C, M, N, K, splits, cps, nullptr, 0.f);
+  else gemm_launch<EPI_SWIGLU, true>(s, A, Wp, C, M, N, K, splits, cps, const_cast<float*>(ssq), eps);
   return splits;
 }
 
