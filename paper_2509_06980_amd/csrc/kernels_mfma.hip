@@ -149,6 +149,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
                                                         float* __restrict__ zt, float scale_c) {
   // a thread stages MB 16-byte pieces of the used part of an A chunk
   __shared__ u32x4 As[2][1024];
+  __shared__ float sq[UNDIV ? 256 : 1];      // [half of the partial sums][row]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int nb = blockIdx.x * 4 + wave;
   const bool active = nb * 32 < N;
@@ -222,6 +223,30 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
   }
   GEMM_LOAD(a0, b0, c0)
   GEMM_LOAD(a1, b1, c0 + 1)
+  if (UNDIV) {
+    // A thread sums two of a row's four interleaved shares of partial sums, in the order of gemm_decode_kernel, while the
+    // first chunks arrive; the epilogue reads both halves from LDS, behind the loop's barriers.  Summed in the epilogue,
+    // by every wave for itself and one row block after the other, they cost 4 to 6 us (gate-up of hidden 1024 at 131 rows,
+    // undivided rows or not: 20.3 and 13.8 us, now 15.5; of hidden 512 at 300 rows 13.0 and 8.8, now 9.8).
+    const int q = (tid >> 7) * 2, n = K >> 4, r16 = (M + 15) >> 4 << 4;
+    const float* p = zt + min(mt * 128 + (tid & 127), M - 1);
+    float t0 = 0.f, t1 = 0.f;
+    for (int x = q; x < n; x += 32) {      // n is a multiple of 4
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const float* px = p + (size_t)min(x + 4 * u, n - 4 + q) * r16;
+        v[2 * u] = px[0];
+        v[2 * u + 1] = px[r16];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        t0 += x + 4 * u < n ? v[2 * u] : 0.f;
+        t1 += x + 4 * u < n ? v[2 * u + 1] : 0.f;
+      }
+    }
+    sq[tid] = t0 + t1;
+  }
   // the barrier inside a stage also orders its LDS store after every wave's reads of the same
   // buffer two chunks earlier
   for (int c = c0; c < c1; c += 2) {
@@ -237,12 +262,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
     for (int mb = 0; mb < MB; mb++) {
       const int row = mt * 128 + mb * 32 + (lane & 31);
       float inv = 1.0f;
-      if (UNDIV) {      // added up in the order of gemm_decode_kernel
-        const float* p = zt + min(row, M - 1);
-        const int r16 = (M + 15) >> 4 << 4, q = (lane >> 5) * 2;
-        float t = strided_sum(p, q, 4, K >> 4, r16) + strided_sum(p, q + 1, 4, K >> 4, r16);
-        t += __shfl_xor(t, 32, 64);
-        inv = 1.0f / sqrtf(t / (float)K + scale_c);
+      if (UNDIV) {
+        const float* t = sq + mb * 32 + (lane & 31);
+        inv = 1.0f / sqrtf((t[0] + t[128]) / (float)K + scale_c);
       }
       auto val = [&](int i) { return UNDIV ? acc[mb][i] * inv : acc[mb][i]; };
       if (EPI == EPI_SWIGLU) swiglu_block(val, (bf16_t*)Cv, row, M, nb, lane, N >> 1);
