@@ -397,16 +397,18 @@ __global__ __launch_bounds__(T) void sample_row_kernel(
   arg = sa[0];
   for (int k = 1; k < NW; k++)
     if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
-  uint64_t wl[PER], mine = 0;
+  uint32_t wl[PER];          // saturated at 2^32 - 1, which no float below 2^32 converts to: that one stands for 2^32
+  auto weight = [&](int j) { return (uint64_t)wl[j] + (wl[j] == 0xffffffffu ? kTop : 0u); };
+  uint64_t mine = 0;
   float e = 0.f;
 #pragma unroll
   for (int j = 0; j < PER; j++) {
     float x;
-    uint32_t w;
-    exp2_weight(v[j], m, c, x, w);
+    exp2_weight(v[j], m, c, x, wl[j]);
     const bool in = base + j < V;
-    wl[j] = in ? (uint64_t)w + (x >= kTwo32 ? kTop : 0u) : 0;
-    mine += wl[j];
+    if (!in) wl[j] = 0;
+    mine += weight(j);
+    asm volatile("" : "+v"(wl[j]));      // the search forms the 64-bit weights again rather than keep 32 registers for them
     e = __fadd_rn(e, in ? x : 0.f);
   }
   uint64_t incl = mine;
@@ -441,7 +443,7 @@ __global__ __launch_bounds__(T) void sample_row_kernel(
       bool found = false;
 #pragma unroll
       for (int j = 0; j < PER; j++) {
-        acc += wl[j];
+        acc += weight(j);
         if (!found && acc > r) { found = true; s_id = base + j; s_z = v[j]; }
       }
     }

@@ -80,3 +80,8 @@ def test_forms_that_divide_no_rows_hold_no_code_for_it(kernels):
         assert divides["code"] - plain["code"] > 500
         for k in (plain, divides):                             # 512 registers a SIMD lane in steps of 8: five waves
             assert k[".vgpr_count"] <= 96
+
+
+def test_no_kernel_keeps_registers_in_scratch_memory(kernels):
+    spills = {(key, k[".private_segment_fixed_size"]) for key, ks in kernels.items() for k in ks if k[".private_segment_fixed_size"]}
+    assert not spills
