@@ -473,9 +473,10 @@ void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, in
     auto go = [&](auto kernel, int threads) {
       kernel<<<rows, threads, 0, s>>>(logits, ldz, V, scale_c, greedy, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out, logp_out);
     };
-    if (V <= 4096) vec ? go(sample_row_kernel<256, true>, 256) : go(sample_row_kernel<256, false>, 256);
-    else if (V <= 8192) vec ? go(sample_row_kernel<512, true>, 512) : go(sample_row_kernel<512, false>, 512);
-    else vec ? go(sample_row_kernel<1024, true>, 1024) : go(sample_row_kernel<1024, false>, 1024);
+    static_assert(kRowLogitsScalar <= 16 * 256, "the scalar form has 256 threads");
+    if (V <= 16 * 256) vec ? go(sample_row_kernel<256, true>, 256) : go(sample_row_kernel<256, false>, 256);
+    else if (V <= 8192) go(sample_row_kernel<512, true>, 512);
+    else go(sample_row_kernel<1024, true>, 1024);
     return;
   }
   if (greedy || nstrips <= 0) stripmax = nullptr;   // the arg-max needs the pass over the logits

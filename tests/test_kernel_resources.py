@@ -85,3 +85,8 @@ def test_forms_that_divide_no_rows_hold_no_code_for_it(kernels):
 def test_no_kernel_keeps_registers_in_scratch_memory(kernels):
     spills = {(key, k[".private_segment_fixed_size"]) for key, ks in kernels.items() for k in ks if k[".private_segment_fixed_size"]}
     assert not spills
+
+
+def test_rows_in_one_workgroup_of_the_sampler_come_in_the_forms_that_are_launched(kernels):
+    # (threads, 16-byte reads): rows that cannot be read in 16-byte pieces stop at the 4096 logits of 256 threads
+    assert {args for name, args in kernels if name == "sample_row_kernel"} == {(256, 0), (256, 1), (512, 1), (1024, 1)}
