@@ -350,11 +350,17 @@ void forward_rows(rl_model* m, int M, const RowMeta& r) {
   else if (!forward_fp32(m, M, r)) forward_generic<float, float>(m, M, r);
 }
 
+// Where a step that draws leaves the maxima of its logits' strips; null where the sampler would not read them.
+float* drawn_maxima(const rl_model* m, bool drawn) {
+  return m->mfma && drawn && sampler_reads_maxima(m->logits, (size_t)m->md.V, m->md.V, false) ? m->d_stripmax : nullptr;
+}
+
 // final norm + lm-head for rows [r0, r0 + R) of m->h -> m->logits[0 .. R)
 // M: rows of the forward pass (stride of its partial sums); norm_rows <= M: leading rows to normalise
-// stripmax (MFMA path only): also leave the per-strip maxima of the logits there
+// drawn: a token is drawn from every row (on the MFMA path the kernel is then the same for every row count, and the
+// logits' per-strip maxima are left in m->d_stripmax where the sampler reads them)
 void lm_head_rows(rl_model* m, int M, int r0, int R, bool norm_done, int norm_rows = -1,
-                  float* stripmax = nullptr) {
+                  bool drawn = false) {
   hipStream_t s = m->stream;
   const ModelDims& md = m->md;
   if (norm_rows < 0) norm_rows = M;
@@ -365,9 +371,9 @@ void lm_head_rows(rl_model* m, int M, int r0, int R, bool norm_done, int norm_ro
       m->pending_parts = 0;
     }
     // r0 is a multiple of 128: skip whole A tiles
-    if (stripmax) {
+    if (drawn) {
       launch_lm_head_logits(s, (const bf16_t*)m->xa + (size_t)r0 * md.H, (const bf16_t*)m->lm_head,
-                            m->logits, R, md.V, md.H, stripmax);
+                            m->logits, R, md.V, md.H, drawn_maxima(m, true));
     } else {
       launch_gemm_mfma(s, (const bf16_t*)m->xa + (size_t)r0 * md.H, (const bf16_t*)m->lm_head, m->logits,
                        R, md.V, md.H, EPI_STORE, plan_gemm(R, md.V, md.H, EPI_STORE, 0));
@@ -806,12 +812,11 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
   // sampling needs the row maximum before any weight can be formed: the lm-head epilogue leaves the
   // maximum of every 32-logit strip, so no separate pass over the logits looks for it (the arg-max
   // of a greedy step still takes that pass)
-  float* stripmax = (m->mfma && !greedy) ? m->d_stripmax : nullptr;
-  lm_head_rows(m, M, 0, n, false, n, stripmax);
+  lm_head_rows(m, M, 0, n, false, n, !greedy);
   float c = sampler_scale(temperature);
   launch_sampler(m->stream, m->logits, (size_t)m->md.V, n, m->md.V, c, greedy ? 1 : 0, nullptr, seed,
                  dm.traj, dm.newpos, forced ? dm.forced : nullptr, nullptr, m->ss, m->hd_ids, m->hd_lp,
-                 stripmax, m->md.V / 32);       // ids and log-probs go straight to the pinned host buffers
+                 drawn_maxima(m, !greedy), m->md.V / 32);       // ids and log-probs go straight to the pinned host buffers
   HIPCHECK(hipGetLastError());
   if (timed) (void)hipEventRecord(m->ev_step[1], m->stream);
   if (m->timing_every > 0 && extra_rows == 0) {
@@ -914,7 +919,6 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
   }
   const bool greedy = temperature == 0.0f;
   const float c = sampler_scale(temperature);
-  float* stripmax = (m->mfma && !greedy) ? m->d_stripmax : nullptr;
   const double tokb = 2.0 * m->md.nkv * m->md.d * m->kv_el;
   Staging st;
   for (int s0 = 0; s0 < n_steps; s0 += kMaxStepsPerChunk) {
@@ -950,10 +954,10 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
                 dm.rowlist, nullptr, 0, false, kvb, timed};
       if (timed) (void)hipEventRecord(m->ev_step[0], m->stream);
       forward_rows(m, n, r);
-      lm_head_rows(m, n, 0, n, false, n, stripmax);
+      lm_head_rows(m, n, 0, n, false, n, !greedy);
       launch_sampler(m->stream, m->logits, (size_t)m->md.V, n, m->md.V, c, greedy ? 1 : 0, nullptr, seed,
                      dm.traj, dm.newpos, nullptr, nullptr, m->ss, m->d_ids_hist + (size_t)sc * n,
-                     m->d_lp_hist + (size_t)sc * n, stripmax, m->md.V / 32);
+                     m->d_lp_hist + (size_t)sc * n, drawn_maxima(m, !greedy), m->md.V / 32);
       HIPCHECK(hipGetLastError());
       if (timed) (void)hipEventRecord(m->ev_step[1], m->stream);
       HIPCHECK(hipEventRecord(m->ev_region[region], m->stream));

@@ -146,9 +146,9 @@ void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, in
 // stored) and scale_c = log2(e) / T.  part: scratch of M * (V / 32) float pairs; zt: M floats.
 void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, int V, int K,
                             const int32_t* tgt, float scale_c, float* part, float* zt, float* lp);
-// lm-head of a decode step (final norm -> lm-head -> sampler): logits[M, V] fp32 row-major and, from
+// lm-head of a decode step (final norm -> lm-head -> sampler): logits[M, V] fp32 row-major and, unless null, from
 // the same epilogue, stripmax[M, V / 32]: the maximum of every 32 consecutive logits of a row, from
-// which the sampler takes the row maximum without a pass over the logits.  V % 32 == 0.
+// which the sampler takes the row maximum without a pass over the logits (where sampler_reads_maxima).  V % 32 == 0.
 void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* logits, int M,
                            int V, int K, float* stripmax);
 // W[N,K] row-major -> operand strips.  interleave8: rows come from two matrices Wg, Wu
@@ -193,6 +193,8 @@ static inline float sampler_scale(float temperature) {
 //  out_mask[r] != 0.
 //  stripmax != null (not with greedy): [rows, nstrips] maxima that together cover each row (from
 //  the lm-head epilogue); the pass over the logits that finds the row maximum is then left out.
+//  sampler_reads_maxima: false where they would not be read (arg-max, rows that one workgroup takes whole).
+bool sampler_reads_maxima(const float* logits, size_t ldz, int V, bool greedy);
 void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, int V, float scale_c,
                     int greedy, const uint32_t* u32, uint64_t seed, const int32_t* row_traj,
                     const int32_t* row_newpos, const int32_t* forced, const uint8_t* out_mask,

@@ -1197,11 +1197,13 @@ void launch_gemm_qkv(hipStream_t s, const bf16_t* A, const bf16_t* Wp, int M, in
   }
 }
 
-// lm-head of a decode step: logits[M, V] (fp32, row-major) and stripmax[M, V / 32].
+// lm-head of a decode step: logits[M, V] (fp32, row-major) and, unless null, stripmax[M, V / 32]; the logits are the same
+// bits either way.
 void launch_lm_head_logits(hipStream_t s, const bf16_t* A, const bf16_t* Wp, float* logits, int M,
                            int V, int K, float* stripmax) {
   if (M <= 0) return;
-  gemm_launch<EPI_STORE_MAX>(s, A, Wp, logits, M, V, K, 1, K / 64, stripmax, 0.f);
+  if (stripmax) gemm_launch<EPI_STORE_MAX>(s, A, Wp, logits, M, V, K, 1, K / 64, stripmax, 0.f);
+  else gemm_launch<EPI_STORE>(s, A, Wp, logits, M, V, K, 1, K / 64, nullptr, 0.f);
 }
 
 // One workgroup per row: combine the per-strip (max, sum) pairs in a fixed order and write

@@ -460,6 +460,13 @@ __global__ __launch_bounds__(T) void sample_row_kernel(
   }
 }
 
+static bool whole_pieces(const float* logits, size_t ldz, int V) {
+  return V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+}
+static bool row_in_one_workgroup(bool vec, int V) { return V <= (vec ? kRowLogits : kRowLogitsScalar); }
+bool sampler_reads_maxima(const float* logits, size_t ldz, int V, bool greedy) {
+  return !greedy && !row_in_one_workgroup(whole_pieces(logits, ldz, V), V);
+}
 void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, int V, float scale_c,
                     int greedy, const uint32_t* u32, uint64_t seed, const int32_t* row_traj,
                     const int32_t* row_newpos, const int32_t* forced, const uint8_t* out_mask,
@@ -468,8 +475,8 @@ void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, in
   if (rows <= 0) return;
   const int nseg = sampler_nseg(V);
   const dim3 grid(nseg, rows);
-  const bool vec = V % 4 == 0 && ldz % 4 == 0 && ((uintptr_t)logits & 15) == 0;
-  if (V <= (vec ? kRowLogits : kRowLogitsScalar)) {
+  const bool vec = whole_pieces(logits, ldz, V);
+  if (row_in_one_workgroup(vec, V)) {
     auto go = [&](auto kernel, int threads) {
       kernel<<<rows, threads, 0, s>>>(logits, ldz, V, scale_c, greedy, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out, logp_out);
     };
