@@ -282,7 +282,9 @@ PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   p.eo = adds(p.o) ? EPI_ADD : EPI_STORE;
   p.ed = adds(p.d) ? EPI_ADD : EPI_STORE;
   // With the residual add and the norm inside where that is expected to be faster than the product and the norm's launch
-  // (3.6 us and 0.45 us per 1024 columns; the product's estimate holds the partial sums that the norm reads).
+  // (3.6 us and 0.45 us per 1024 columns; the product's estimate holds the partial sums that the norm reads).  Of the last
+  // layer's down the launch stays, without partial sums to read: there the two ways are about equal (hidden 1024 at 64 rows
+  // 5.2 + 3.1 against 4.8 + 4.4 us), and one plan serves all layers.
   auto residual = [&](const GemmPlan& g, int K) {
     const ResidualPlan r = plan_residual(M, H, K);
     return r.rb > 0 && r.cost < g.cost + 3.6 + 4.5e-4 * H ? r : ResidualPlan{0, 0, 0.0};
@@ -304,6 +306,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   const float *so_q = nullptr, *so_g;       // sums of squares, where the norm's division is left to the consumer
   for (int l = 0; l < md.L; l++) {
     const LayerW& w = m->layers[l];
+    // (the last layer's rows with the final gains are read by nobody: the lm-head's own norm gathers the rows it needs from h)
     const bf16_t* g_next = (const bf16_t*)(l + 1 < md.L ? m->layers[l + 1].g_in : m->g_final);
     if (l == 0) launch_embed_rmsnorm(s, (const bf16_t*)m->embed, r.tok, m->h, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
     else if (!so_q) launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
