@@ -77,6 +77,8 @@ DECODE = [
     _dims(3392, 16, 2, 256),
     _dims(2816, 10, 5, 192),        # QKV: 80 columns, slices of unequal length, at most 64 rows
     _dims(1536, 14, 7, 256),        # QKV ends inside a tile of 96 columns, at most 64 rows
+    _dims(2048, 11, 11, 256),       # QKV: 53 tiles in four slices, numbered by XCD with a remainder
+    _dims(2112, 22, 11, 256),       # 59 tiles
 ]
 
 # O and down with the residual add and the norm inside, two layers so that every consumer of the undivided rows runs
@@ -88,4 +90,5 @@ RESIDUAL = [
     _dims(2560, 32, 8, 1088),
     _dims(4096, 2, 2, 4096),        # 256 column blocks
     _dims(4160, 4, 4, 1024),        # 260: two rounds of the narrowest tile
+    _dims(4160, 1, 1, 3072),        # down: 24 MB of weights, which one row tile reads past the caches
 ]

@@ -118,47 +118,36 @@ def test_decode_cases_reach_every_tile():
     for change in DECODE:
         s = small(**change)
         for rows in DECODE_ROWS:
+            inside = rl.debug_residual_plan(s, rows)               # O and down leave the plan there
             for name, (kernel, width, slices, epilogue) in rl.debug_pass_plan(s, rows).items():
-                if kernel != "decode" or name in ("score_head", "logits_head"):
+                if kernel != "decode" or name in inside or name in ("score_head", "logits_head"):
                     continue
                 n, k = _dims(s)[name]
-                stages = k // (128 if width == 5 else 64)
+                stages, tiles = k // (128 if width == 5 else 64), -(-n // (16 * width))
                 seen |= {(width, epilogue, rows > 64), (width, epilogue, rows > 64, "ends inside" if n % (16 * width) else "whole"),
                          (width, epilogue, rows > 64, "unequal slices" if stages % slices else "equal slices")}
+                if rows <= 64 and slices == 4 and -(-stages // 4) * (k // stages) >= 512:      # numbered by XCD
+                    seen.add(("by XCD", width, "remainder" if tiles % 2 else "none"))
     for more in (False, True):                                     # one and two 16-row blocks a wave
         for width in (2, 4, 5, 6):
             assert (width, "store", more) in seen and (width, "swiglu", more) in seen
             assert (width, "store", more, "unequal slices") in seen
         for width in (5, 6):                                       # every width is a multiple of 64
             assert (width, "store", more, "ends inside") in seen and (width, "swiglu", more, "ends inside") in seen
-
-
-def test_decode_cases_reach_every_tile_beside_the_residual_products():
-    # O and down leave the plan where they carry the residual add: the sliced tiles are reached without them
-    seen = set()
-    for change in DECODE:
-        s = small(**change)
-        for rows in DECODE_ROWS:
-            inside = rl.debug_residual_plan(s, rows)
-            for name, (kernel, width, slices, epilogue) in rl.debug_pass_plan(s, rows).items():
-                if kernel == "decode" and name not in inside:
-                    n, k = _dims(s)[name]
-                    stages = k // (128 if width == 5 else 64)
-                    seen |= {(width, epilogue, rows > 64, n % (16 * width) != 0), (width, epilogue, rows > 64, "unequal", stages % slices != 0)}
-    for more in (False, True):
-        for width in (2, 4, 5, 6):
-            assert (width, "store", more, "unequal", True) in seen
-        for width in (5, 6):
-            assert (width, "store", more, True) in seen and (width, "swiglu", more, True) in seen
+    assert {("by XCD", 4, "none"), ("by XCD", 5, "remainder"), ("by XCD", 6, "remainder")} <= seen
 
 
 def test_residual_products_tiles_and_bounds():
-    reached = {}
+    reached, past_caches = {}, set()
     for change in RESIDUAL:
         s = small(**change)
         for rows in RESIDUAL_ROWS:
             for name, tile in rl.debug_residual_plan(s, rows).items():
                 reached.setdefault((name, tile), set()).add(rows)
+                n, k = _dims(s)[name]
+                if rows <= 16 * tile[0] and 2 * n * k >= 24 << 20:
+                    past_caches.add(tile)
+    assert past_caches == {(1, 1), (1, 2), (2, 2)}
     for name in ("o", "down"):
         for tile in ((1, 1), (1, 2), (2, 2)):
             assert (name, tile) in reached, (name, tile)
