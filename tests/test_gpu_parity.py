@@ -63,12 +63,15 @@ def test_sampler_draws_match_oracle_stream():
 
 
 @pytest.mark.parametrize("n_rows", [3, 40, 70, 131])
-def test_mfma_decode_step_sampler_with_strip_maxima_is_bit_exact(n_rows):
-    # bf16 MFMA path: the lm-head epilogue hands the sampler per-strip maxima instead of a pass over
-    # the logits.  Given the logits the step produced (rl_debug_logits: the same kernels on the same
-    # rows, one row at a time) and the step's draws, the ids must be the oracle sampler's, bit for
-    # bit, for every instance of the lm-head kernel (1, 2, 4 row blocks; two row tiles).
-    shape = SHAPES["small-d128"]
+@pytest.mark.parametrize("vocab", [8192, 20512, 24608])
+def test_mfma_decode_step_sampler_with_strip_maxima_is_bit_exact(n_rows, vocab):
+    # bf16 MFMA path: above 16384 logits the lm-head epilogue hands the sampler per-strip maxima instead of a pass
+    # over the logits (8192: a row in one workgroup, which takes its maximum itself; 24608: 24 MB of weights, which
+    # up to 64 rows go past the caches).  Given the step's draws and its logits (rl_debug_logits: one row at a time; its
+    # product may add up in another order, which moves the boundaries of a draw by some 1e-7 of the total weight), the
+    # ids must be the oracle sampler's, for every instance of the lm-head kernel (1, 2, 4 row blocks; two row tiles).
+    shape = SHAPES["small-d128"].replace(vocab=vocab)
+    assert vocab * shape.hidden * 2 >= 24 << 20 or vocab != 24608
     blob = make_weight_blob(shape, seed=5, weight_std=0.05, gain_std=0.1)
     g = rl.RolloutEngine(blob, max_context=64, max_trajectories=n_rows, kv_pool_pages=n_rows * 4)
     rng = np.random.default_rng(n_rows)

@@ -227,7 +227,7 @@ def test_decode_batch_of_260_rows_three_row_tiles():
     # more active trajectories than two 128-row tiles hold (cfg5 runs 256 at once when memory
     # allows): every GEMM of the decode step, the lm-head with its strip maxima and the sampler
     # walk three row tiles, the last one ragged
-    shape = SHAPES["small-d128"]
+    shape = SHAPES["small-d128"].replace(vocab=20512)      # above 16384: drawn from the strip maxima
     blob = make_weight_blob(shape, seed=51, weight_std=0.03, gain_std=0.1)
     n = 260
     kw = dict(max_context=128, max_trajectories=n, kv_pool_pages=n * 6)

@@ -13,11 +13,14 @@ from synthetic import SHAPES, make_weight_blob
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V,rows,T", [(1, 2, 1.0), (5, 3, 1.0), (4095, 2, 0.7), (4096, 1, 1.0), (4100, 300, 1.0), (4101, 3, 1.0),
-                                      (12292, 400, 1.0), (12292, 3, 0.0), (1100000, 2, 1.0), (1100001, 1, 0.0)])
+@pytest.mark.parametrize("V,rows,T", [(1, 2, 1.0), (5, 3, 1.0), (4095, 2, 0.7), (4096, 1, 1.0), (4097, 3, 1.0), (4100, 300, 1.0), (4101, 3, 1.0),
+                                      (8192, 4, 1.0), (8196, 4, 1.0), (12292, 400, 1.0), (12292, 3, 0.0), (16384, 5, 1.0), (16384, 3, 0.0),
+                                      (16388, 5, 1.0), (20483, 300, 1.0), (20484, 300, 1.0), (20484, 300, 0.0), (40964, 260, 0.7),
+                                      (1100000, 2, 1.0), (1100001, 1, 0.0)])
 def test_sampler_segment_layouts(V, rows, T):
-    # rows of whole 16-byte pieces and others, one to many segments per workgroup, more than 256 segments
-    # in a row, masked logits (minus infinity and the lowest float: weight 0, as -1e30 for the oracle)
+    # rows of whole 16-byte pieces (in one workgroup of 256, 512 or 1024 threads up to 4096, 8192, 16384 logits) and others (up
+    # to 4096); in segments beyond: one or several segments (two of 6, three of 11) per workgroup, a last one with few logits,
+    # more than 256 in a row; masked logits (minus infinity and the lowest float: weight 0, as -1e30 for the oracle)
     rng = np.random.default_rng(V + rows)
     z = (rng.standard_normal((rows, V)) * 2).astype(np.float32)
     ref = z.copy()
@@ -34,7 +37,7 @@ def test_sampler_segment_layouts(V, rows, T):
         assert abs(lps[r] - lp) < 1e-5 * max(1.0, abs(lp))
 
 
-@pytest.mark.parametrize("V", [5, 4100, 4101])
+@pytest.mark.parametrize("V", [5, 4100, 4101, 16384, 16388])
 def test_sampler_rows_without_weight(V):
     # no logit is a number, one is infinite, none is finite, one is no number: the id is a token all the same
     nan, inf = np.float32("nan"), np.float32("inf")
@@ -54,13 +57,14 @@ def test_sampler_rows_without_weight(V):
     assert [sample_token(z[r], 0.0, 0)[0] for r in range(4)] == best.tolist()
 
 
+@pytest.mark.parametrize("V", [4100, 16388])         # a row in one workgroup, and in segments
 @pytest.mark.parametrize("T", [1e-45, 1e-40, 4e-39, 1e-37])
-def test_sampler_temperatures_next_to_zero(T):
+def test_sampler_temperatures_next_to_zero(T, V):
     # log2(e) / T beyond fp32: the maximum has all the weight, two equal maxima half of it each
-    z = np.random.default_rng(5).standard_normal((3, 4100)).astype(np.float32)
-    z[1:, 7] = z[1:, 4099] = 9.0
+    z = np.random.default_rng(5).standard_normal((3, V)).astype(np.float32)
+    z[1:, 7] = z[1:, V - 1] = 9.0
     ids, lps = rl.sample_from_logits(z, T, np.array([123, 2**31 - 1, 2**31], np.uint32))
-    assert ids.tolist() == [int(z[0].argmax()), 7, 4099]
+    assert ids.tolist() == [int(z[0].argmax()), 7, V - 1]
     assert np.abs(lps - [0.0, -np.log(2.0), -np.log(2.0)]).max() < 1e-6
 
 

@@ -63,9 +63,10 @@ def _run_device(z, u, T):
 
 
 def test_no_alloc_sampler_matches_allocating_entry_point_twice_second_call_smaller():
-    # two calls in a row share the library's scratch array; the second is smaller in rows and in
-    # vocabulary, so stale entries of the first call lie behind and between its own
-    for rows, V, T, seed in [(100, 151936, 1.0, 1), (24, 5000, 0.7, 2), (7, 4096, 0.0, 3)]:
+    # calls in a row share the library's scratch array; the later ones are smaller in rows and in
+    # vocabulary, so stale entries of the first call lie behind and between their own (the last two rows fit a
+    # workgroup each and use none of it)
+    for rows, V, T, seed in [(100, 151936, 1.0, 1), (24, 20000, 0.7, 2), (7, 17000, 0.0, 4), (24, 5000, 0.7, 2), (7, 4096, 0.0, 3)]:
         z, u, T = _case(rows, V, T, seed)
         want_ids, want_lps = rl.sample_from_logits(z, T, u)
         ids, lps = _run_device(z, u, T)
