@@ -285,12 +285,22 @@ PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   // (3.6 us and 0.45 us per 1024 columns; the product's estimate holds the partial sums that the norm reads).  Of the last
   // layer's down the launch stays, without partial sums to read: there the two ways are about equal (hidden 1024 at 64 rows
   // 5.2 + 3.1 against 4.8 + 4.4 us), and one plan serves all layers.
-  auto residual = [&](const GemmPlan& g, int K) {
+  // Above 128 rows every part on its own, `consumer` the division in gate-up or in the norm / RoPE kernel: the product's
+  // estimate is 3 us too high there (its own kernels are told apart by differences), the norm takes its launch and the
+  // traffic of its partial sums, its looping form for more than 4096 columns 5 us more.  With the rule of few rows 300 to 512
+  // rows of hidden 2048 and more had lost up to 12 us a layer (hidden 4096, intermediate 1024, 448 rows: 97 -> 109 us).
+  // Fitted on 18 shapes of hidden 512 to 5120, 131 to 512 rows: of the 193 products that took the inside way by the old rule
+  // two still do and are slower (by 1.5 and 2 us), six no longer do and would be faster (by at most 1 us).
+  auto residual = [&](const GemmPlan& g, int K, double consumer) {
     const ResidualPlan r = plan_residual(M, H, K);
-    return r.rb > 0 && r.cost < g.cost + 3.6 + 4.5e-4 * H ? r : ResidualPlan{0, 0, 0.0};
+    const double mh = 1e-6 * M * H;
+    const bool pays = M <= 128 ? r.cost < g.cost + 3.6 + 4.5e-4 * H
+                               : r.cost + consumer + 0.5 < 0.95 * g.cost + 0.4 + 5.2e-4 * H + (0.74 + 0.5 * g.splits) * mh + (H > 4096 ? 5.0 : 0.0);
+    return r.rb > 0 && pays ? r : ResidualPlan{0, 0, 0.0};
   };
-  p.ro = gate_up_takes_scale(p.g, M, H) ? residual(p.o, qw) : ResidualPlan{0, 0, 0.0};
-  p.rd = p.fused_qkv ? ResidualPlan{0, 0, 0.0} : residual(p.d, I);
+  const double mh = 1e-6 * M * H;
+  p.ro = gate_up_takes_scale(p.g, M, H) ? residual(p.o, qw, 0.75 + 9.1e-4 * H + 0.18 * mh) : ResidualPlan{0, 0, 0.0};
+  p.rd = p.fused_qkv ? ResidualPlan{0, 0, 0.0} : residual(p.d, I, 0.88 + 1.3e-4 * H + 0.7 * mh);
   return p;
 }
 

@@ -1026,6 +1026,8 @@ __global__ __launch_bounds__(256) void gemm_residual_kernel(
 // Tile of the product with residual add and norm, and its estimate in us: per round of 256 workgroups 1.28, 1.75 or
 // 2.1 us per 1000 k for 16 x 16, 16 x 32 and 32 x 32 (what the workgroup's operands take), plus the launch and what the
 // consumer takes to add up the sums of squares.  Fitted on six products of hidden 1024 to 4096 at 1 to 128 rows.
+// More rows: the same tile, its time (without the consumer) by rounds, by what the row tiles re-read of the weights and by the
+// residual stream's traffic; fitted to 0.65 us on 18 shapes of hidden 512 to 5120 at 131 to 512 rows (see plan_pass).
 // rb = 0: not for this size.
 ResidualPlan plan_residual(int M, int N, int K) {
   ResidualPlan best{0, 0, 1e30};
@@ -1036,6 +1038,10 @@ ResidualPlan plan_residual(int M, int N, int K) {
     const int wgs = (M + 16 * t.rb - 1) / (16 * t.rb) * ((N / 16 + t.cb - 1) / t.cb);
     const double cost = t.launch + (wgs + 255) / 256 * (K * t.per_k);
     if (cost < best.cost) best = ResidualPlan{t.rb, t.cb, cost};
+  }
+  if (M > 128) {
+    const int wgs = (M + 16 * best.rb - 1) / (16 * best.rb) * ((N / 16 + best.cb - 1) / best.cb);
+    best.cost = 2.5 + K * ((best.rb == 2 ? 0.8e-3 : 0.45e-3) * ((wgs + 255) / 256) + 0.68e-3 * wgs / 256) + 3.7e-6 * M * N;
   }
   return best;
 }

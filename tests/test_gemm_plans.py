@@ -170,3 +170,15 @@ def test_residual_products_tiles_and_bounds():
             assert ring + -(-rows // 16) * 16 * (s.hidden // 16) * 4 <= 160 * 1024
     for rows in (1, 16, 512):
         assert "down" not in rl.debug_residual_plan(SHAPES["qwen3-8b"].replace(intermediate=262144), rows)      # 31-bit offsets
+
+
+@pytest.mark.parametrize("shape,rows,inside", [
+    ((4096, 8, 2, 1024), 448, set()), ((4096, 8, 2, 1024), 131, {"o", "down"}),      # a layer 97 us apart, 109 inside
+    ((2048, 16, 8, 1536), 512, set()), ((2048, 16, 8, 1536), 192, {"o", "down"}),    # 79, 85
+    ((2560, 8, 8, 1088), 512, set()), ((2560, 8, 8, 1088), 192, {"o", "down"}),      # 86, 93
+    ((2560, 32, 8, 2048), 192, {"down"}),                                            # O of 4096: 46.2 with gate-up, 47.6
+    ((1024, 16, 8, 3072), 512, {"o", "down"}), ((512, 8, 2, 1024), 512, {"o", "down"}),
+])
+def test_residual_products_of_more_than_128_rows_where_they_are_faster(shape, rows, inside):
+    s = SHAPES["small-d128"].replace(**dict(zip(("hidden", "n_q_heads", "n_kv_heads", "intermediate"), shape)))
+    assert set(rl.debug_residual_plan(s, rows)) == inside
