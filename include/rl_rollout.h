@@ -256,6 +256,7 @@ uint32_t rl_uniform_u32(uint64_t seed, int32_t traj_id, int32_t position);
  * 256-row tile, 16-column blocks of a decode tile; K-slices; epilogue: 0 stored, 2 SwiGLU, 3 log-softmax, 5
  * QK-norm + RoPE + cache write, 7 added to the residual stream) for QKV, O, gate-up, down, the lm-head of a
  * log-prob pass over `rows` sampled tokens, and the lm-head that stores `rows` rows of logits outside a drawn step.
+ * O and down take what rl_debug_residual_plan says instead where that names a tile.
  * Errors: ARG (also a shape that the MFMA kernels do not take).
  */
 int rl_debug_pass_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);

@@ -288,7 +288,7 @@ PassPlan plan_pass(const ModelDims& md, int M, size_t part_rows) {
   // Above 128 rows every part on its own, `consumer` the division in gate-up or in the norm / RoPE kernel: the product's
   // estimate is 3 us too high there (its own kernels are told apart by differences), the norm takes its launch and the
   // traffic of its partial sums, its looping form for more than 4096 columns 5 us more.  With the rule of few rows 300 to 512
-  // rows of hidden 2048 and more had lost up to 12 us a layer (hidden 4096, intermediate 1024, 448 rows: 97 -> 109 us).
+  // rows of hidden 2048 and more had lost up to 8.5 us a layer (hidden 4096, intermediate 1024, 448 rows: 97 -> 105 us).
   // Fitted on 18 shapes of hidden 512 to 5120, 131 to 512 rows: of the 193 products that took the inside way by the old rule
   // two still do and are slower (by 1.5 and 2 us), six no longer do and would be faster (by at most 1 us).
   auto residual = [&](const GemmPlan& g, int K, double consumer) {

@@ -59,7 +59,8 @@ void launch_repack_weight(hipStream_t s, const bf16_t* W, const bf16_t* Wu, bf16
 // fetched, staged and multiplied.  At decode sizes a workgroup's time follows the bytes its CU
 // fetches, and the A chunk is half of them, so small batches gain most of what they leave out
 // (N = 4096 K = 12288 in eight slices: 22.9 us with all four row blocks, 18.4 at 12 rows, 20.3 at 64; lm-head
-// 151936 x 2560 151 -> 137 us at 12 rows, 154 -> 145 at 48); results per row are unchanged.
+// 151936 x 2560 151 -> 137 us at 12 rows, 154 -> 145 at 48, plain loads; past the caches 127 at 12); results per row are
+// unchanged.
 // EPI_SWIGLU and EPI_LSE form the product transposed; see swiglu_block.  UNDIV (EPI_SWIGLU): the rows of A are still to be
 // divided by their rms, zt holds their sums of squares and scale_c is epsilon (see gemm_residual_kernel).  A choice at compile
 // time: tested at run time the division had grown the plain form from 7.4 to 13.3 KB of code with four row blocks.
@@ -753,8 +754,10 @@ static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C
 // 17.9; at 96 rows 0 to 2 %.  Deeper rings gain nothing; leaving out the loads behind the slice with a branch costs
 // 10 % (the loop falls apart into blocks).
 // =============================================================================================
-// UNDIV (SwiGLU): the rows of A are still to be divided by their rms, ssq holds their sums of squares.  A choice at compile time:
-// tested at run time the division had grown the plain form from 12.5 to 15 KB of code.
+// UNDIV (SwiGLU): the rows of A are still to be divided by their rms, ssq holds their sums of squares.  The epilogue adds up K / 64
+// of them per lane, 0.6 to 1 us (8B gate-up in a pass of 6 / 16 rows 33.5 / 34.8 us, 6.0 / 5.8 TB/s; 4B at 37 rows 18.8 ->
+// 19.8, hidden 1024 at 64 rows 6.2 -> 6.8).  A choice at compile time: tested at run time it had grown the plain form from
+// 12.5 to 15 KB of code.
 template <int EPI, int RB, int CB, int SK, int NST, bool NT, bool UNDIV>
 __global__ __launch_bounds__(256) void gemm_decode_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K, int splits,
