@@ -16,6 +16,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -398,18 +399,28 @@ __global__ __launch_bounds__(T) void sample_row_kernel(
   arg = sa[0];
   for (int k = 1; k < NW; k++)
     if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
-  uint32_t wl[PER];          // saturated at 2^32 - 1, which no float below 2^32 converts to: that one stands for 2^32
-  auto weight = [&](int j) { return (uint64_t)wl[j] + (wl[j] == 0xffffffffu ? kTop : 0u); };
+  // 1024 threads have 128 registers each, which sixteen 64-bit weights leave no room in (12 bytes of scratch a lane): they hold the
+  // conversion saturated at 2^32 - 1, to which no float below 2^32 converts, and the search forms the weights again (64 rows
+  // of 16384 logits 10.3 -> 9.9 us; with 256 and 512 threads, which have the room, the drawn rows took 0.2 to 0.3 us more).
+  constexpr bool SAT = T == 1024;
+  std::conditional_t<SAT, uint32_t, uint64_t> wl[PER];
+  auto weight = [&](int j) { return SAT ? (uint64_t)wl[j] + (wl[j] == 0xffffffffu ? kTop : 0u) : (uint64_t)wl[j]; };
   uint64_t mine = 0;
   float e = 0.f;
 #pragma unroll
   for (int j = 0; j < PER; j++) {
     float x;
-    exp2_weight(v[j], m, c, x, wl[j]);
+    uint32_t w;
+    exp2_weight(v[j], m, c, x, w);
     const bool in = base + j < V;
-    if (!in) wl[j] = 0;
-    mine += weight(j);
-    asm volatile("" : "+v"(wl[j]));      // the search forms the 64-bit weights again rather than keep 32 registers for them
+    if constexpr (SAT) {
+      wl[j] = in ? w : 0u;
+      mine += weight(j);
+      asm volatile("" : "+v"(wl[j]));      // or the 64-bit weights would be kept after all
+    } else {
+      wl[j] = in ? (uint64_t)w + (x >= kTwo32 ? kTop : 0u) : 0;
+      mine += wl[j];
+    }
     e = __fadd_rn(e, in ? x : 0.f);
   }
   uint64_t incl = mine;
