@@ -330,20 +330,28 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
 // =============================================================================================
 // GEMM for many rows (chunked prefill, teacher-forced passes, mixed steps): tile 64*MB x 64*NBW, 4 waves
 // as 2 x 2, wave tile 32*MB x 32*NBW (MB = 4: 256 rows; NBW = 4: 256 columns, 16 accumulators of 32x32;
-// NBW = 5: 320 columns, 20 of them; MB = 2: 128 rows for passes of a few hundred rows, whose last
+// NBW = 5: 320 columns, 20 of them; MB = 2, NBW = 4: 128 x 256, for passes of a few hundred rows, whose last
 // 256-row tile would be mostly empty).  Per 16-k step a wave reads MB row and NBW column operands from
 // LDS for MB*NBW MFMAs.
 // Both operands go from memory straight into LDS (16-byte buffer loads with the LDS destination; no
-// staging registers, no LDS stores in the instruction stream) as chunks of 32 k in a ring of four
-// stages (MB = 2: three), three and a half (two and a half) chunks ahead.  The loop is one steady
-// stream: every group of NBW MFMAs carries its share of these loads, and the next step's operands are
-// read ahead of its last group, so that the wait in front of the barrier (half way through a chunk: the
-// next chunk is complete, this one is read out) finds them there.  The loads return in order, so "at
-// most the chunks behind it outstanding" means that the next chunk has landed; before the epilogue all
-// are drained.
+// staging registers, no LDS stores in the instruction stream) as chunks of 32 k in a ring of R stages.  The
+// loads return in order, so "at most the chunks behind it outstanding" means that the next chunk has landed;
+// before the epilogue all are drained.  Chunks behind the slice and 32-row blocks without rows are asked for behind the
+// buffer's end: zeros, no memory traffic.
+// MB = 4: four stages, three and a half chunks ahead, operands one 16-k step ahead.  Every group of NBW MFMAs carries its share of
+// the loads, and the next step's operands are read ahead of its last group, so that the wait in front of the barrier
+// (half way through a chunk: the next chunk is complete, this one is read out) finds them there.
+// What bounds it at thousands of rows is power: on operands of zeros the same instructions take 213 us instead of 295
+// (8192 x 2560 x 9728: 1.92 and 1.38 PFLOP/s), and MFMAs alone, on registers, reach 2.4 and 1.87.  (16x16x32 MFMAs
+// draw less, 2.13 PFLOP/s alone with two waves a SIMD, but one wave a SIMD cannot issue them back to back: 312 us.)
+// MB = 2: bound by what the CUs fetch from L2 (without the loads 587 x 2560 x 9728 in five slices takes 27 us of 35) and by the
+// latencies of one wave a SIMD: the operands of a whole chunk are read one chunk ahead, one read behind an MFMA, and the
+// next chunk's loads between them (587 x 2560 x 4096 undivided, 50 workgroups: 51 us with operands half a chunk ahead, reads and
+// loads in front of each group of four MFMAs; 43.5 a chunk ahead; 41.4 one by one).  Three stages let two workgroups share a CU;
+// where there is only one to a CU anyway four hide more of the weights' stream (300 x 19456 x 2560 42.6 -> 39.7 us).
 // The fifth accumulator column lives in vector registers: 320 accumulator registers exceed the 256
 // accumulation registers, and the builtin, which takes all of its kind from one file, then copies.
-// blockIdx.z selects a K-slice (EPI_STORE only); each slice stores its own partial sum.
+// A K-slice (EPI_STORE only) stores its own partial sum.
 // The k order per output element is that of the 128 x 128 kernel: with one slice the bits are the same.
 // EPI_QKV / EPI_QKV8 (bf16 / 8-bit cache; NBW = 4: a wave's 128 columns are one head): the product is
 // formed transposed, which leaves a row's 128 dims of the head in two lanes, RoPE partners in the
@@ -355,24 +363,26 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
 // pass): gate-up N = 19456 K = 2560 with SwiGLU 880 -> 646 / 655 (1.26 PFLOP/s), down N = 2560 K = 9728 443 -> 296
 // stored (1.38 PFLOP/s), 315 / 316 added, O N = 2560 K = 4096 192 -> 132 stored, 146 / 153 added, QKV N = 6144 K = 2560
 // with norm, RoPE and cache write 244 + 80 -> 247 / 264, lm-head with log-softmax at 1536 rows (N = 151936) 1709 ->
-// 1015 / 986.  128-row tiles at 587 rows (before: 128 x 128): QKV 30.5 -> 25 / 27 in two slices, O 23.6 -> 19 /
-// 20, down 45.0 -> 39 / 38 in five.
-// XCD-aware tile numbering (xcd_tile256).  K % 64 == 0, N % 32 == 0.
+// 1015 / 986.
+// XCD-aware tile numbering (xcd_tile).  K % 64 == 0, N % 32 == 0.
 // =============================================================================================
-// Tile of a workgroup: the hardware hands workgroups to the 8 XCDs round-robin by linear index
-// and each XCD has its own L2.  XCD x works through a contiguous range of a sequence that walks
-// groups of 4 row tiles column by column, so the 32 workgroups resident on an XCD cover a
-// compact block of 4 x 8 tiles (12 distinct operand tiles per chunk instead of ~22).  A
-// bijection for any tile counts.
-__device__ __forceinline__ void xcd_tile256(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-  constexpr int GM = 4;
-  const int total = tiles_m * tiles_n;
+// Tile and K-slice of a workgroup: the hardware hands workgroups to the 8 XCDs round-robin by linear index
+// and each XCD has its own L2.  XCD x works through a contiguous range of a sequence that takes one slice after the
+// other and in it groups of gm_most row tiles column by column, so the 32 workgroups resident on an XCD cover a
+// compact block of tiles of one slice (256-row tiles: 4 x 8, 12 distinct operand tiles per chunk instead of ~22).  With
+// the slices dealt over all XCDs an XCD had met a few tiles of every slice (128 x 256 tiles, 587 x 2560 x 9728 in five
+// slices 36.7 -> 35.2 us, 300 rows in eight 25.7 -> 23.8).  A bijection for any tile counts.
+__device__ __forceinline__ void xcd_tile(int gm_most, int* tm, int* tn, int* slice) {
+  const int tiles_n = gridDim.x, tiles_m = gridDim.y, tiles = tiles_m * tiles_n, total = tiles * gridDim.z;
+  const int id = (blockIdx.z * tiles_m + blockIdx.y) * tiles_n + blockIdx.x;
   const int base = total >> 3, rem = total & 7, x = id & 7;
-  const int vid = x * base + min(x, rem) + (id >> 3);
-  const int per_group = GM * tiles_n, grp = vid / per_group, first = grp * GM;
-  const int gm = min(GM, tiles_m - first), within = vid - grp * per_group;
-  *tm = first + within % gm;
-  *tn = within / gm;
+  const int vid = x * base + min(x, rem) + (id >> 3), z = vid / tiles, v = vid - z * tiles;
+  const int per_group = gm_most * tiles_n, grp = v / per_group, first = grp * gm_most;
+  const int gm = min(gm_most, tiles_m - first), within = v - grp * per_group;
+  // the divisions leave them in vector registers
+  *tm = __builtin_amdgcn_readfirstlane(first + within % gm);
+  *tn = __builtin_amdgcn_readfirstlane(within / gm);
+  *slice = __builtin_amdgcn_readfirstlane(z);
 }
 
 // QK-norm, RoPE and the writes of one head (EPI_QKV) for a wave's MB blocks of 32 batch rows:
@@ -525,8 +535,8 @@ __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, 
                : "memory", "m0");
 }
 
-template <int EPI, int MB, int NBW>
-__global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
+template <int EPI, int MB, int NBW, int R>
+__global__ __launch_bounds__(256, MB == 2 && R == 3 ? 2 : 1) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K,
                                                        int chunks_per_split, const int32_t* __restrict__ tgt,
                                                        float* __restrict__ zt, float scale_c, QkvArgs qkv) {
@@ -535,39 +545,39 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
   constexpr int NA = 4 * MB;                  // row pieces of a stage: [128-row tile][kb][32-row block]
   constexpr int PW = MB + NBW;                // 1 KB pieces per wave and chunk
   constexpr int BUF = (NA + 4 * NBW) * 1024;  // bytes of a stage: the row pieces, then [strip][kb]
-  constexpr int R = MB == 4 ? 4 : 3;          // stages
-  constexpr int F = PW / 2;                   // pieces of a chunk that are asked for half a chunk ahead of the others
+  constexpr int F = PW / 2;                   // MB = 4: pieces of a chunk that are asked for half a chunk ahead of the others
+  constexpr int kFar = 0x7fff0000;            // behind every buffer's end: zeros, no memory traffic
   extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
-  const int NB = N >> 5, nch = K >> 5;
-  const int mtiles128 = (M + 127) >> 7;
-  const int c0 = blockIdx.z * chunks_per_split, c1 = min(c0 + chunks_per_split, nch);
-  int bx, by;
-  xcd_tile256(blockIdx.y * gridDim.x + blockIdx.x, gridDim.y, gridDim.x, &by, &bx);
-  bx = __builtin_amdgcn_readfirstlane(bx);      // the division leaves them in vector registers
-  by = __builtin_amdgcn_readfirstlane(by);
-  // MB = 4: second half clamped (results dropped)
-  const int mt0 = by * (MB / 2), mt1 = MB == 4 ? min(mt0 + 1, mtiles128 - 1) : mt0;
-  const int strip0 = bx * NS;
-  const u32x4 ra = buffer_rsrc(A + (size_t)mt0 * K * 128, (unsigned)(mt1 - mt0 + 1) * (unsigned)K * 256u);
+  const int NB = N >> 5, nch = K >> 5, r32 = (M + 31) >> 5;
+  int bx, by, slice;
+  xcd_tile(MB == 4 ? 4 : 8, &by, &bx, &slice);
+  const int c0 = slice * chunks_per_split, c1 = min(c0 + chunks_per_split, nch);
+  const int blk0 = by * 2 * MB, strip0 = bx * NS;           // first 32-row block and strip of the tile
+  const int mt0 = blk0 >> 2, mts = min((r32 + 3) / 4 - mt0, MB == 4 ? 2 : 1);      // its 128-row tiles of A
+  const u32x4 ra = buffer_rsrc(A + (size_t)mt0 * K * 128, (unsigned)mts * (unsigned)K * 256u);
   const u32x4 rb = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
   const int voff = lane * 16;
-  const unsigned a_rt1 = (unsigned)(mt1 - mt0) * (unsigned)K * 256u;
-  // piece j of this wave of chunk c (past the end of the slice: its last chunk again, never read)
-  auto dma = [&](int c, int j) {
-    const int cl = min(c, c1 - 1);
-    const unsigned dst = lds0 + (unsigned)(R == 4 ? c & 3 : c % R) * BUF + (unsigned)(j * 4 + wave) * 1024u;
-    unsigned so;
+  int avoff[2];                               // MB = 4: of this wave's row block in either 128-row tile
+#pragma unroll
+  for (int t = 0; t < 2; t++) avoff[t] = blk0 + 4 * t + wave < r32 ? voff : kFar;
+  // piece j of this wave of chunk c into stage buf; far: 0, or kFar for chunks behind the slice (MB = 4: the last chunk again, never
+  // read, as the registers that the choice takes would spill)
+  auto dma = [&](int chunk, int j, int buf, int far) {
+    const int c = MB == 4 ? min(chunk, c1 - 1) : chunk;
+    const unsigned dst = lds0 + (unsigned)buf * BUF + (unsigned)(j * 4 + wave) * 1024u;
     if (j < MB) {
-      so = ((j >> 1) ? a_rt1 : 0u) + (unsigned)((2 * cl + (j & 1)) * 4 + wave) * 1024u;
+      const int tile = j >> 1, kb = j & 1;
+      load_to_lds(dst, MB == 4 ? avoff[tile] : voff | (blk0 + wave < r32 ? far : kFar), ra,
+                  (unsigned)tile * (unsigned)K * 256u + (unsigned)((2 * c + kb) * 4 + wave) * 1024u);
     } else {     // strips past the end (N not a multiple of the tile): the last one again, results dropped
       const int st = min(strip0 + 2 * (j - MB) + (wave >> 1), NB - 1);
-      so = ((unsigned)(cl >> 1) * NB + st) * 4096u + (cl & 1) * 2048u + (wave & 1) * 1024u;
+      load_to_lds(dst, voff | far, rb, ((unsigned)(c >> 1) * NB + st) * 4096u + (c & 1) * 2048u + (wave & 1) * 1024u);
     }
-    load_to_lds(dst, voff, j < MB ? ra : rb, so);
   };
+  auto behind = [&](int c) { return MB == 4 || c < c1 ? 0 : kFar; };
   f32x16 acc[MB][4], acc5[MB];
 #pragma unroll
   for (int a = 0; a < MB; a++)
@@ -577,64 +587,107 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
 #pragma unroll
       for (int b = 0; b < 4; b++) acc[a][b][e] = 0.f;
     }
-  u32x4 av[2][MB], bv[2][NBW];
+  auto mfma = [&](const u32x4& row, const u32x4& col, f32x16& c) {
+    c = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, col), __builtin_bit_cast(bf16x8, row), c, 0, 0, 0)
+           : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row), __builtin_bit_cast(bf16x8, col), c, 0, 0, 0);
+  };
   const u32x4* As = smem + (MB == 4 ? wm * 8 : wm * 2) * 64 + lane;   // [kb][32-row block]
   const u32x4* Bs = smem + (NA + wn * NBW * 2) * 64 + lane;           // [strip][kb]
 #pragma unroll
   for (int c = 0; c < R - 1; c++)
 #pragma unroll
-    for (int j = 0; j < PW; j++) dma(c0 + c, j);
+    for (int j = 0; j < PW; j++) dma(c0 + c, j, c, behind(c0 + c));
+  if constexpr (MB == 4) {
+    u32x4 av[2][MB], bv[2][NBW];
 #pragma unroll
-  for (int j = 0; j < F; j++) dma(c0 + R - 1, j);
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 2) * PW + F) : "memory");
-  __builtin_amdgcn_s_barrier();
-  {
-    const int base = (R == 4 ? c0 & 3 : c0 % R) * (BUF / 16);
+    for (int j = 0; j < F; j++) dma(c0 + R - 1, j, R - 1, behind(c0 + R - 1));
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 2) * PW + F) : "memory");
+    __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int x = 0; x < MB; x++) av[0][x] = As[base + x * 64];
+    for (int x = 0; x < MB; x++) av[0][x] = As[x * 64];
 #pragma unroll
-    for (int x = 0; x < NBW; x++) bv[0][x] = Bs[base + x * 128];
-  }
-  for (int c = c0; c < c1; c++) {
-    const int cur = (R == 4 ? c & 3 : c % R) * (BUF / 16), nxt = (R == 4 ? (c + 1) & 3 : (c + 1) % R) * (BUF / 16);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int x = 0; x < NBW; x++) bv[0][x] = Bs[x * 128];
+    for (int c = c0; c < c1; c++) {
+      const int sc = (c - c0) & (R - 1), sn = (sc + 1) & (R - 1), sl = (sc - 1) & (R - 1);      // stages of chunks c, c + 1, c + R - 1
+      const int f0 = behind(c + R - 1), f1 = behind(c + R);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < 2 * MB; g++) {
-      const int a = g % MB, st = g / MB;
-      if (g == MB) {     // chunk c + 1 has landed for every wave, chunk c is read out by every wave
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((R - 2) * PW) : "memory");
-        __builtin_amdgcn_s_barrier();
-      }
-      const int base = st == 0 ? cur : nxt, kb = st == 0 ? 1 : 0;
-      auto rd = [&](int q) {      // operand q of the next 16-k step
-        if (q < MB) av[1 - st][q] = As[base + (kb * 4 + q) * 64];
-        else bv[1 - st][q - MB] = Bs[base + ((q - MB) * 2 + kb) * 64];
-      };
-      if (MB == 4) {
+      for (int g = 0; g < 2 * MB; g++) {
+        const int a = g % MB, st = g / MB;
+        if (g == MB) {     // chunk c + 1 has landed for every wave, chunk c is read out by every wave
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((R - 2) * PW) : "memory");
+          __builtin_amdgcn_s_barrier();
+        }
+        const int base = (st == 0 ? sc : sn) * (BUF / 16), kb = st == 0 ? 1 : 0;
+        auto rd = [&](int q) {      // operand q of the next 16-k step
+          if (q < MB) av[1 - st][q] = As[base + (kb * 4 + q) * 64];
+          else bv[1 - st][q - MB] = Bs[base + ((q - MB) * 2 + kb) * 64];
+        };
         if (a == 0) { rd(4); rd(0); rd(5); }
         if (a == 1) { rd(6); rd(7); rd(1); }
         if (a == 2) { rd(2); rd(3); if (NBW == 5) rd(8); }
-      } else if (a == 0) {
+        // this step's share of the loads: the rest of chunk c + R - 1, then the first F pieces of chunk c + R
 #pragma unroll
-        for (int q = 0; q < MB + NBW; q++) rd(q);
-      }
-      // this step's share of the loads: the rest of chunk c + R - 1, then the first F pieces of chunk c + R
+        for (int j = 0; j < PW; j++) {
+          if (st == 0 && j >= F && (j - F) * MB / (PW - F) == a) dma(c + R - 1, j, sl, f0);
+          if (st == 1 && j < F && j * MB / F == a) dma(c + R, j, sc, f1);
+        }
 #pragma unroll
-      for (int j = 0; j < PW; j++) {
-        if (st == 0 && j >= F && (j - F) * MB / (PW - F) == a) dma(c + R - 1, j);
-        if (st == 1 && j < F && j * MB / F == a) dma(c + R, j);
+        for (int b = 0; b < 4; b++) mfma(av[st][a], bv[st][b], acc[a][b]);
+        if (NBW == 5) {
+          if (TR) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(bv[st][NBW - 1]), "v"(av[st][a]));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(av[st][a]), "v"(bv[st][NBW - 1]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
+  } else {
+    u32x4 av[2][2][MB], bv[2][2][4];      // [chunk parity][kb]
+    constexpr int NM = 8 * MB, T = 2 * (MB + 4);      // MFMAs and operand reads of a chunk
 #pragma unroll
-      for (int b = 0; b < 4; b++)
-        acc[a][b] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bv[st][b]),
-                                                                 __builtin_bit_cast(bf16x8, av[st][a]), acc[a][b], 0, 0, 0)
-                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[st][a]),
-                                                                 __builtin_bit_cast(bf16x8, bv[st][b]), acc[a][b], 0, 0, 0);
-      if (NBW == 5) {
-        if (TR) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(bv[st][NBW - 1]), "v"(av[st][a]));
-        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc5[a]) : "v"(av[st][a]), "v"(bv[st][NBW - 1]));
-      }
+    for (int j = 0; j < PW; j++) dma(c0 + R - 1, j, R - 1, behind(c0 + R - 1));
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 1) * PW) : "memory");
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++) {
+#pragma unroll
+      for (int x = 0; x < MB; x++) av[0][kb][x] = As[(kb * 4 + x) * 64];
+#pragma unroll
+      for (int x = 0; x < 4; x++) bv[0][kb][x] = Bs[(x * 2 + kb) * 64];
+    }
+    int sc = 0;                           // stage of chunk c
+    auto chunk = [&](int c, auto parity) {
+      constexpr int p = decltype(parity)::value;
+      const int sn = sc + 1 == R ? 0 : sc + 1, base = sn * (BUF / 16), far = behind(c + R);
       __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < NM; m++) {
+        const int kb = m / (4 * MB), a = m / 4 % MB, b = m % 4;
+        if (m == 1) {      // chunk c + 1 has landed for every wave, chunk c is read out by every wave
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((R - 2) * PW) : "memory");
+          __builtin_amdgcn_s_barrier();
+        }
+        mfma(av[p][kb][a], bv[p][kb][b], acc[a][b]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m > 0) {
+#pragma unroll
+          for (int q = 0; q < T; q++)
+            if (1 + q * (NM - 4) / T == m) {
+              const int k = q / (MB + 4), r = q % (MB + 4);
+              if (r < 4) bv[1 - p][k][r] = Bs[base + (r * 2 + k) * 64];
+              else av[1 - p][k][r - 4] = As[base + (k * 4 + r - 4) * 64];
+            }
+#pragma unroll
+          for (int j = 0; j < PW; j++)
+            if (2 + j * (NM - 2) / PW == m) dma(c + R, j, sc, far);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      sc = sn;
+    };
+    for (int c = c0; c < c1; c += 2) {
+      chunk(c, std::integral_constant<int, 0>());
+      if (c + 1 < c1) chunk(c + 1, std::integral_constant<int, 1>());
     }
   }
   // all loads into LDS are done; the last assembly MFMAs' results may be read
@@ -643,13 +696,13 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
                  : "+v"(acc5[0]), "+v"(acc5[1]), "+v"(acc5[2]), "+v"(acc5[3])::"memory");
   else
     asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  const int mtile = MB == 4 ? mt0 + wm : mt0;
-  if (mtile >= mtiles128) return;
-  const int wrow0 = mtile * 128 + (MB == 4 ? 0 : wm * 64);
+  const int wrow0 = (blk0 + wm * MB) * 32;
+  if ((wrow0 >> 7) >= (M + 127) >> 7) return;
   if constexpr (EPI == EPI_QKV || EPI == EPI_QKV8) {
     // every use reads its own element: the compiler otherwise keeps copies of whole 16-register
     // accumulators in vector registers and spills
     auto val = [&](int a, int b, int i) {
+      if (MB == 2) return acc[a][b][i];
       float x;
       asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[a][b][i]));
       return x;
@@ -657,7 +710,7 @@ __global__ __launch_bounds__(256, MB == 4 ? 1 : 2) void gemm_dma_kernel(const bf
     if (strip0 + wn * 4 < NB) qkv_head<EPI == EPI_QKV8, MB>(val, qkv, wrow0, M, (strip0 >> 2) + wn, lane);
     return;
   }
-  float* Cp = (float*)Cv + (size_t)blockIdx.z * M * N;
+  float* Cp = (float*)Cv + (size_t)slice * M * N;
   if constexpr (EPI == EPI_ADD) {
     // C += product, one 32 x 32 block after the other; the addends are requested two blocks ahead
     if (wrow0 >= M) return;
@@ -727,12 +780,22 @@ static void set_lds_limit(std::atomic<uint64_t>& done, const void* kernel, int b
 template <int EPI, int MB, int NBW>
 static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
                        const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
-  constexpr int lds = (MB == 4 ? 4 : 3) * (4 * MB + 4 * NBW) * 1024;
-  static std::atomic<uint64_t> done{0};
-  set_lds_limit(done, (const void*)gemm_dma_kernel<EPI, MB, NBW>, lds);
   const int cps = (K / 32 + splits - 1) / splits;
-  dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 64 * MB - 1) / (64 * MB), splits);
-  gemm_dma_kernel<EPI, MB, NBW><<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
+  const dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 64 * MB - 1) / (64 * MB), splits);
+  static std::atomic<uint64_t> done[2];
+  auto go = [&](auto kernel, int stages) {
+    const int lds = stages * (4 * MB + 4 * NBW) * 1024;
+    set_lds_limit(done[stages - 3], (const void*)kernel, lds);
+    kernel<<<grid, 256, lds, s>>>(A, Wp, C, M, N, K, cps, tgt, zt, scale_c, q);
+  };
+  if constexpr (MB == 4) {
+    go(gemm_dma_kernel<EPI, 4, NBW, 4>, 4);
+  } else {
+    if constexpr (EPI != EPI_QKV && EPI != EPI_QKV8) {
+      if (grid.x * grid.y * grid.z <= 256 && cps >= 48) return go(gemm_dma_kernel<EPI, 2, 4, 4>, 4);
+    }
+    go(gemm_dma_kernel<EPI, 2, 4, 3>, 3);
+  }
 }
 
 // =============================================================================================
@@ -1095,6 +1158,8 @@ static void gemm_launch(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* 
 // after the other); 128 x 128 tiles 0.62 us per 64-k chunk and round, 0.59 us from the second round on
 // (several to a CU).  Fitted on N = 2048 to 6144, K = 640 to 9728, 64 to 1280 tiles; e.g. 8192 x 2560 x
 // 9728: 320 columns make one full round of 256 tiles (289 us) where 256 columns make two (398 us).
+// The 128 x 256 tiles' loop has become faster since (0.40 us per chunk); with the old constants the plan's product is still 1.1 %
+// above the best plan's on average (209 products of hidden 512 to 4096 at 131 to 4096 rows, refitted 0.6 %).
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows) {
   const bool can_split = epilogue == EPI_STORE;
   int most = can_split ? (int)std::min<size_t>(kMaxSplits, std::max<size_t>(1, part_rows / (size_t)std::max(M, 1))) : 1;
