@@ -1594,231 +1594,198 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   }
 }
 
-// Two consecutive pages (32 keys) of the LDS-staged prefill kernel for the CB column blocks of a
-// wave.  kb / vb point at the first page's key / value block in LDS, the second page's blocks lie
-// BLK bytes behind them.  Scores: 4 x mfma 16x16x32 per page and column block.  The two pages
-// share one softmax update, and P (32 keys x 16 columns) meets the two pages' values in one
-// 16x16x32 MFMA per 16 output dims: operand slot 8 g + i of lane group g is key 4 g + i of the
-// first page for i < 4 and key 4 g + i - 4 of the second page otherwise, on both operands.
-template <int CB, bool FP8, bool MASKED>
-__device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int pg,
-                                             const u32x4 (&qreg)[CB][4], f32x4 (&acc)[CB][8],
-                                             float (&m)[CB], float (&l)[CB], const int (&mypos)[CB],
-                                             int g, int lane, float scale2) {
-  constexpr int BLK = FP8 ? 2048 : 4096, NLD = BLK / 1024;
-  f32x4 S[CB][2];
-  u32x4 raw[2][NLD];
-#pragma unroll
-  for (int c = 0; c < NLD; c++)
-#pragma unroll
-    for (int pp = 0; pp < 2; pp++) raw[pp][c] = *(const u32x4*)(kb + pp * BLK + c * 1024 + lane * 16);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int cb = 0; cb < CB; cb++) S[cb][0] = S[cb][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < 4; c++) {
-#pragma unroll
-    for (int pp = 0; pp < 2; pp++) {
-      const u32x4 kr = att_operand<FP8>(raw[pp], c);
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++)
-        S[cb][pp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr),
-                                                            __builtin_bit_cast(bf16x8, qreg[cb][c]),
-                                                            S[cb][pp], 0, 0, 0);
-    }
-  }
-  // the values' reads travel while the softmax is computed
-  u32x4 vr[FP8 ? 2 * NLD : 8];
-#pragma unroll
-  for (int i = 0; i < (FP8 ? 2 * NLD : 8); i++)
-    vr[i] = *(const u32x4*)(vb + (FP8 ? (i & 1) * BLK + (i >> 1) * 1024 : i * 1024) + lane * 16);
-  __builtin_amdgcn_sched_barrier(0);
-  bf16x8 P[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; cb++) {
-    bool vis[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) vis[i] = !MASKED || (pg + (i >> 2)) * RL_PAGE + 4 * g + (i & 3) <= mypos[cb];
-    // m (in scaled units: score * scale2, scale2 > 0) is the reference point of the exponents, not
-    // necessarily the running maximum: it only moves, to the column's maximum so far, when the eight terms
-    // of some lane of the wave sum to more than kLazy = 2^8.  The ratio acc / l does not depend on m, and the common
-    // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
-    // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
-    constexpr float kLazy = 256.0f;
-    float p[8];
-    auto terms = [&]() {
-#pragma unroll
-      for (int i = 0; i < 8; i++) {
-        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[cb][i >> 2][i & 3], scale2, -m[cb]));
-        if (MASKED) p[i] = vis[i] ? p[i] : 0.f;
-      }
-      return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    };
-    float ps = terms();
-    if (__any(ps > kLazy)) {
-      float mx = ATT_NEG;
-#pragma unroll
-      for (int i = 0; i < 8; i++) mx = fmaxf(mx, vis[i] ? S[cb][i >> 2][i & 3] : ATT_NEG);
-      mx = quad_max(mx);
-      const float mn = fmaxf(m[cb], mx * scale2);
-      const float alpha = exp2f(m[cb] - mn);
-      l[cb] *= alpha;
-#pragma unroll
-      for (int j = 0; j < 8; j++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) acc[cb][j][i] *= alpha;
-      m[cb] = mn;
-      ps = terms();
-    }
-    l[cb] += ps;
-    P[cb] = (bf16x8){(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3],
-                     (__bf16)p[4], (__bf16)p[5], (__bf16)p[6], (__bf16)p[7]};
-  }
-#pragma unroll
-  for (int jb = 0; jb < 8; jb++) {
-    bf16x8 vo;
-    if constexpr (FP8) {
-      uint32_t a0, b0, a1, b1;
-      e4m3x4_to_bf16(vr[2 * (jb >> 2)][jb & 3], &a0, &b0);
-      e4m3x4_to_bf16(vr[2 * (jb >> 2) + 1][jb & 3], &a1, &b1);
-      vo = __builtin_bit_cast(bf16x8, ((u32x4){a0, b0, a1, b1}));
-    } else {
-      // the staging has put the lane's 4 tokens of a dim in the first page and in the second side by
-      // side: one 16-byte read is the 32-key operand
-      vo = __builtin_bit_cast(bf16x8, vr[jb]);
-    }
-#pragma unroll
-    for (int cb = 0; cb < CB; cb++)
-      acc[cb][jb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vo, P[cb], acc[cb][jb], 0, 0, 0);
-  }
-}
-
-// Chunked prefill with the pages staged through LDS: one workgroup per (item of up to
-// 4 * CB * 16/G rows, kv head) as above, but a page's keys / values are fetched once per
-// workgroup (not once per wave) into a double-buffered LDS stage of NP pages, in the pool's
-// operand order, and the four waves read their operands from there (linear 16-byte reads, no bank
-// conflicts), the bf16 values of a pair of pages interleaved so that a 32-key operand is one read (a
-// quarter of the vector instructions had been moves that put the operands together).  Pages are consumed
-// in pairs (prefill_pair).  One barrier per stage: the loads of
-// stage s + 1 are issued before the barrier of stage s and written to the other buffer after the
-// stage's arithmetic, which every wave can only reach once all waves have left stage s - 1.
+// Chunked prefill: one workgroup per (item of up to 4 * 32/G rows, kv head), a wave = 32 columns
+// (query row, head of the group), 32x32x16 MFMAs.  A pair of pages (32 keys) is a stage of 16 KB in LDS (8-bit cache: 8 KB), loaded
+// there directly in the pool's operand order (no registers, no LDS stores), two pairs ahead in a ring of three:
+//   S^T[32 keys, 32 columns] = K . Q^T, 8 steps of 16 dims: lane (key, half) reads its 8 dims of a step as 16 bytes (8-bit cache:
+//   of two steps), 16 keys of a page being 256 contiguous bytes;
+//   O^T[32 dims, 32 columns] += V^T . P^T per page and block of 32 dims: lane l of the scores holds, for column l % 32, keys
+//   8 j + 4 (l / 32) + 0 .. 3 (j = 0 .. 3), so operand slot 4 x + e of a page is key 8 x + 4 (l / 32) + e on both sides, and the values
+//   are two 8-byte reads 512 bytes apart, 64 lanes covering 512 contiguous bytes.
+// Nothing is moved between registers to put an operand together.  One barrier per pair: behind it the pair is complete for
+// every wave and the stage of the pair before is free for the pair after the next.
+// What bounds it: a wave's matrix and vector work take turns (32 keys x 32 columns: 512 cycles of MFMA, 60 vector instructions
+// of which 16 exponentials), so other waves of the SIMD have to fill the pipes, and three fit the registers (149); then power: on
+// operands of zeros 12 x 610 rows over 3000 keys take 329 us, on random ones 395 (1.0 PFLOP/s).  Before, with 16x16x32 MFMAs,
+// two waves a SIMD, keys and values through registers and the pages' addresses formed by every lane: 430; 16 x 512 rows over
+// none 77 -> 69 us, 24 x 340 over 2000 with two heads a group 204 -> 169.
+// Items are taken from the last to the first: a trajectory's later rows see more keys, and short items fill the end of the launch
+// better (8 x 1024 rows over none 105 -> 99 us).
 // Page indices past the item's last page are clamped to it (their keys are masked: they lie
 // behind every row of the item); the pool is cleared at load, so such blocks hold finite values.
-template <int CB, bool FP8>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attention_prefill_lds_kernel(
+template <bool FP8, bool MASKED>
+__device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int key0, const u32x4 (&q)[8], f32x16 (&acc)[4],
+                                             float& m, float& l, int mypos, float scale2) {
+  f32x16 S;
+#pragma unroll
+  for (int i = 0; i < 16; i++) S[i] = 0.f;
+  auto score = [&](const u32x4& k, int ks) {
+    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, q[ks]), S, 0, 0, 0);
+  };
+  if constexpr (FP8) {
+#pragma unroll
+    for (int x = 0; x < 4; x++) {      // a slot holds the lane's dims of steps ks and ks + 2
+      const u32x4 raw[1] = {*(const u32x4*)(kb + (x >> 1) * 1024 + (x & 1) * 512)};
+      score(att_operand<true>(raw, 0), 4 * (x >> 1) + (x & 1));
+      score(att_operand<true>(raw, 1), 4 * (x >> 1) + (x & 1) + 2);
+    }
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 8; ks++) score(*(const u32x4*)(kb + ks * 512), ks);
+  }
+  // m (in scaled units: score * scale2, scale2 > 0) is the reference point of the exponents, not
+  // necessarily the running maximum: it only moves, to the column's maximum so far, when the sixteen terms
+  // of some lane of the wave sum to more than kLazy = 2^8.  The ratio acc / l does not depend on m, and the common
+  // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
+  // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
+  constexpr float kLazy = 256.0f;
+  float p[16];
+  auto vis = [&](int i) { return !MASKED || key0 + (i >> 2) * 8 + (i & 3) <= mypos; };
+  auto terms = [&]() {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], scale2, -m));
+      if (MASKED) p[i] = vis(i) ? p[i] : 0.f;
+    }
+    return (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
+           (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
+  };
+  float ps = terms();
+  if (__any(ps > kLazy)) {
+    float mx = ATT_NEG;
+#pragma unroll
+    for (int i = 0; i < 16; i++) mx = fmaxf(mx, vis(i) ? S[i] : ATT_NEG);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m, mx * scale2);
+    const float alpha = exp2f(m - mn);
+    l *= alpha;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) acc[j][i] *= alpha;
+    m = mn;
+    ps = terms();
+  }
+  l += ps;
+  bf16x8 P[2];
+#pragma unroll
+  for (int i = 0; i < 16; i++) P[i >> 3][i & 7] = (__bf16)p[i];
+#pragma unroll
+  for (int pp = 0; pp < 2; pp++)
+#pragma unroll
+    for (int db = 0; db < 4; db++) {
+      u32x4 v;
+      if constexpr (FP8) {
+        const char* x = vb + pp * 2048 + (db >> 1) * 1024 + (db & 1) * 8;
+        uint32_t a, b, c, d;
+        e4m3x4_to_bf16(*(const uint32_t*)x, &a, &b);
+        e4m3x4_to_bf16(*(const uint32_t*)(x + 512), &c, &d);
+        v = (u32x4){a, b, c, d};
+      } else {
+        const char* x = vb + pp * 4096 + db * 1024;
+        const uint2 lo = *(const uint2*)x, hi = *(const uint2*)(x + 512);
+        v = (u32x4){lo.x, lo.y, hi.x, hi.y};
+      }
+      acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), P[pp], acc[db], 0, 0, 0);
+    }
+}
+
+template <bool FP8>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attention_prefill_kernel(
     const bf16_t* __restrict__ q, const char* __restrict__ kpool, const char* __restrict__ vpool,
     const AttnItem* __restrict__ items, const int32_t* __restrict__ page_table,
     bf16_t* __restrict__ o, int nq, int nkv, int gshift, int pt_stride, float scale2) {
-  constexpr int NP = 4;
-  constexpr int BLK = FP8 ? 2048 : 4096;
-  constexpr int STAGE = 2 * NP * BLK;            // NP key blocks, then NP value blocks
-  constexpr int U = STAGE / 4096;                // 16-byte loads per thread and stage
-  __shared__ __align__(16) char s_kv[2 * STAGE];
-  const int item_idx = blockIdx.x / nkv;
-  const AttnItem it = items[item_idx];
-  const int kvh = blockIdx.x - item_idx * nkv;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = lane >> 4, n = lane & 15, hq = n & ((1 << gshift) - 1);
-  const int rpb = 16 >> gshift;                       // rows per column block
-  const int wrow0 = wave * CB * rpb;                  // first row of this wave within the item
-  const int wave_rows = min(it.nrows - wrow0, CB * rpb);
+  constexpr int BLK = FP8 ? 2048 : 4096, R = 3, STAGE = 4 * BLK;         // key blocks of the two pages, then value blocks
+  constexpr int NL = BLK / 1024;                                         // loads of a wave and stage
+  __shared__ __align__(16) char s_kv[R * STAGE];
+  const int back = blockIdx.x / nkv, kvh = blockIdx.x - back * nkv;
+  const AttnItem it = items[gridDim.x / nkv - 1 - back];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n = lane & 31, half = lane >> 5, head = (kvh << gshift) + (n & ((1 << gshift) - 1));
+  const int rpw = 32 >> gshift;                       // rows of a wave
+  const int wrow0 = wave * rpw, wave_rows = min(it.nrows - wrow0, rpw);
   const int pg1 = wave_rows > 0 ? (it.pos0 + wrow0 + wave_rows - 1) / RL_PAGE + 1 : 0;
-  const int item_pg1 = (it.pos0 + it.nrows - 1) / RL_PAGE + 1;
-  const int pglast = item_pg1 - 1;
-  const int nst = (item_pg1 + NP - 1) / NP;
-  const int32_t* pt = page_table + (size_t)it.slot * pt_stride;
-  u32x4 qreg[CB][4];
-  f32x4 acc[CB][8];
-  float m[CB], l[CB];
-  int mypos[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; cb++) {
-    const int r = wrow0 + cb * rpb + (n >> gshift);
-    // columns past the item's rows get position -1: every key of a masked pair is masked for them
-    mypos[cb] = r < it.nrows ? it.pos0 + r : -1;
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-      qreg[cb][c] = (u32x4){0u, 0u, 0u, 0u};
-      if (r < it.nrows)
-        qreg[cb][c] = *(const u32x4*)(q + ((size_t)(it.row0 + r) * nq + ((kvh << gshift) + hq)) * 128 + c * 32 + g * 8);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; j++) acc[cb][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    m[cb] = ATT_NEG;
-    l[cb] = 0.f;
-  }
+  const int pglast = (it.pos0 + it.nrows - 1) / RL_PAGE;
+  const int nst = (pglast + 2) / 2;
   // pages that end at or before the wave's first row are visible to all of its rows: no masking
   const int full_pages = wave_rows > 0 ? (it.pos0 + wrow0 + 1) / RL_PAGE : 0;
-  u32x4 stg[U];
-  auto fetch = [&](int s) {
-    int id[NP];
-#pragma unroll
-    for (int p = 0; p < NP; p++) id[p] = pt[min(s * NP + p, pglast)];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int byte = u * 4096 + tid * 16;
-      const int blk = byte / BLK, off = byte % BLK;
-      const bool isv = blk >= NP;
-      const int p = isv ? blk - NP : blk;
-      int pid = id[0];
-#pragma unroll
-      for (int x = 1; x < NP; x++) pid = p == x ? id[x] : pid;
-      const char* src = (isv ? vpool : kpool) + ((size_t)pid * nkv + kvh) * BLK + off;
-      stg[u] = *(const u32x4*)src;
+  const int32_t* pt = page_table + (size_t)it.slot * pt_stride;
+  const int r = wrow0 + (n >> gshift);
+  // columns past the item's rows get position -1: every key of a masked pair is masked for them
+  const int mypos = r < it.nrows ? it.pos0 + r : -1;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)s_kv;
+  // (a pool holds less than 2^32 (page, kv head) blocks)
+  auto block = [&](int pg) { return (size_t)((unsigned)pt[min(pg, pglast)] * (unsigned)nkv + (unsigned)kvh) * BLK; };
+  // this wave's share of a stage: a quarter of each of its four blocks, or with the 8-bit cache half of one page's two
+  auto load = [&](int buf, size_t b0, size_t b1) {
+    const unsigned dst = lds0 + (unsigned)buf * STAGE, part = (unsigned)(FP8 ? wave & 1 : wave) * 1024u;
+    if constexpr (FP8) {
+      const size_t b = wave < 2 ? b0 : b1;
+      const unsigned at = dst + (wave < 2 ? 0u : 2048u) + part;
+      load_to_lds(at, lane * 16, buffer_rsrc(kpool + b, BLK), part);
+      load_to_lds(at + 4096u, lane * 16, buffer_rsrc(vpool + b, BLK), part);
+    } else {
+      load_to_lds(dst + part, lane * 16, buffer_rsrc(kpool + b0, BLK), part);
+      load_to_lds(dst + 4096u + part, lane * 16, buffer_rsrc(kpool + b1, BLK), part);
+      load_to_lds(dst + 8192u + part, lane * 16, buffer_rsrc(vpool + b0, BLK), part);
+      load_to_lds(dst + 12288u + part, lane * 16, buffer_rsrc(vpool + b1, BLK), part);
     }
   };
-  auto stash = [&](int b) {
+  u32x4 qr[8];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      char* dst = s_kv + b * STAGE + u * 4096 + tid * 16;
-      if (FP8 || u < NP) {
-        *(u32x4*)dst = stg[u];
-      } else {      // bf16 values, page u - NP: the slot's two operands go beside the other page's of the pair
-        const int p = u - NP;
-        char* v = s_kv + b * STAGE + (NP + (p & ~1)) * BLK + (tid >> 6) * 2048 + (tid & 63) * 16 + (p & 1) * 8;
-        *(uint2*)v = make_uint2(stg[u][0], stg[u][1]);
-        *(uint2*)(v + 1024) = make_uint2(stg[u][2], stg[u][3]);
-      }
-    }
+  for (int ks = 0; ks < 8; ks++) {
+    qr[ks] = (u32x4){0u, 0u, 0u, 0u};
+    if (r < it.nrows) qr[ks] = *(const u32x4*)(q + ((size_t)(it.row0 + r) * nq + head) * 128 + ks * 16 + half * 8);
+  }
+#pragma unroll
+  for (int ks = 0; ks < 8; ks++) asm volatile("" : "+v"(qr[ks]));      // they have arrived before the loads that the loop counts
+  f32x16 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++)
+#pragma unroll
+    for (int i = 0; i < 16; i++) acc[j][i] = 0.f;
+  float m = ATT_NEG, l = 0.f;
+  load(0, block(0), block(1));
+  load(1, block(2), block(3));
+  size_t n0 = block(4), n1 = block(5);
+  const char* kl = s_kv + (n >> 4) * BLK + (n & 15) * 16 + half * 256;
+  const char* vl = s_kv + 2 * BLK + (n & 15) * 16 + (n >> 4) * (FP8 ? 4 : 8) + half * 256;
+  int buf = 0;
+  // pair s is there for every wave, and pair s - 1 is read out by every wave: pair s + 2 takes its stage
+  auto advance = [&](int s) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NL) : "memory");
+    __builtin_amdgcn_s_barrier();
+    load(buf == 0 ? 2 : buf - 1, n0, n1);
+    n0 = block(2 * s + 6);
+    n1 = block(2 * s + 7);
   };
-  if (nst > 0) {
-    fetch(0);
-    stash(0);
+  // (two loops: with the choice inside one the accumulators are copied between the two forms)
+  const int nfull = full_pages >> 1;
+  for (int s = 0; s < nfull; s++) {
+    advance(s);
+    prefill_pair<FP8, false>(kl + buf * STAGE, vl + buf * STAGE, 0, qr, acc, m, l, mypos, scale2);
+    buf = buf == 2 ? 0 : buf + 1;
   }
-  for (int s = 0; s < nst; s++) {
-    if (s + 1 < nst) fetch(s + 1);
-    __syncthreads();
-    const char* buf = s_kv + (s & 1) * STAGE;
+  for (int s = nfull; s < nst; s++) {
+    advance(s);
+    if (2 * s < pg1)
+      prefill_pair<FP8, true>(kl + buf * STAGE, vl + buf * STAGE, 2 * s * RL_PAGE + 4 * half, qr, acc, m, l, mypos, scale2);
+    buf = buf == 2 ? 0 : buf + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  l += __shfl_xor(l, 32, 64);
+  if (r >= it.nrows) return;
+  // acc[db][i] is O[row r][head][d = 32 db + (i / 4) * 8 + 4 half + i % 4]: four consecutive dims = one 8-byte store
+  const float inv = 1.0f / l;
 #pragma unroll
-    for (int j = 0; j < NP / 2; j++) {
-      const int pg = s * NP + 2 * j;
-      const char* kb = buf + 2 * j * BLK;
-      const char* vb = buf + (NP + 2 * j) * BLK;
-      if (pg + 1 < full_pages)
-        prefill_pair<CB, FP8, false>(kb, vb, pg, qreg, acc, m, l, mypos, g, lane, scale2);
-      else if (pg < pg1)
-        prefill_pair<CB, FP8, true>(kb, vb, pg, qreg, acc, m, l, mypos, g, lane, scale2);
+  for (int db = 0; db < 4; db++)
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      uint2 w;
+      w.x = (uint32_t)f2bf(acc[db][4 * j] * inv) | ((uint32_t)f2bf(acc[db][4 * j + 1] * inv) << 16);
+      w.y = (uint32_t)f2bf(acc[db][4 * j + 2] * inv) | ((uint32_t)f2bf(acc[db][4 * j + 3] * inv) << 16);
+      *(uint2*)(o + atile_off(it.row0 + r, head * 128 + 32 * db + 8 * j + 4 * half, nq * 128)) = w;
     }
-    if (s + 1 < nst) stash((s + 1) & 1);
-  }
-#pragma unroll
-  for (int cb = 0; cb < CB; cb++) {
-    const float lt = quad_sum(l[cb]);
-    const int r = wrow0 + cb * rpb + (n >> gshift);
-    if (r < it.nrows) {
-      // acc[jb][i] is O[row r][head hq][d = 16 jb + 4 g + i]: four consecutive dims = one 8-byte store
-      const float inv = 1.0f / lt;
-      const size_t base = atile_off(it.row0 + r, ((kvh << gshift) + hq) * 128 + 4 * g, nq * 128);
-#pragma unroll
-      for (int jb = 0; jb < 8; jb++) {
-        uint2 w;
-        w.x = (uint32_t)f2bf(acc[cb][jb][0] * inv) | ((uint32_t)f2bf(acc[cb][jb][1] * inv) << 16);
-        w.y = (uint32_t)f2bf(acc[cb][jb][2] * inv) | ((uint32_t)f2bf(acc[cb][jb][3] * inv) << 16);
-        *(uint2*)(o + base + (size_t)jb * (4 * 64 * 8)) = w;
-      }
-    }
-  }
 }
 
 // grid (n_merges, nkv), block 256: merge the parts of one (row, kv head): the shared-prefix parts (the
@@ -1922,11 +1889,9 @@ void launch_attention_mfma(hipStream_t s, const bf16_t* q, KvPool pool, const At
   const dim3 grid(n_items * md.nkv);
   if (prefill) {
     if (md.kv_fp8)
-      attention_prefill_lds_kernel<RL_PREFILL_CB, true><<<grid, 256, 0, s>>>(
-          q, kp, vp, items, page_table, o, md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
+      attention_prefill_kernel<true><<<grid, 256, 0, s>>>(q, kp, vp, items, page_table, o, md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
     else
-      attention_prefill_lds_kernel<RL_PREFILL_CB, false><<<grid, 256, 0, s>>>(
-          q, kp, vp, items, page_table, o, md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
+      attention_prefill_kernel<false><<<grid, 256, 0, s>>>(q, kp, vp, items, page_table, o, md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
     return;
   }
   if (md.kv_fp8)

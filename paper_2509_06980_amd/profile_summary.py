@@ -180,7 +180,7 @@ def rollout_summary(trace_path, stats_path, bench_log):
           "trajectory x kv head) by launch shape, from the kernel trace:\n")
     trace_summary(trace_path)
     print("\nThe decode average agrees with the HIP-event figure of bench.py (the profiler adds a little "
-          "per-launch overhead to the event bracket). Chunked prefill runs in attention_prefill_lds_kernel.\n")
+          "per-launch overhead to the event bracket). Chunked prefill runs in attention_prefill_kernel.\n")
     print("| kernel | calls | total ms | avg us | % |\n|---|---|---|---|---|")
     with open(stats_path, newline="") as f:
         for x in csv.DictReader(f):

@@ -121,6 +121,30 @@ def test_decode_attention_cuts_and_merges(name, lens):
     a.close(), b.close()
 
 
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (8, 1), (16, 1)])
+def test_prefill_attention_items_and_page_pairs(heads):
+    # chunks on top of cached contexts: items of one row to 4 * 32 / G rows and one more, first and last row around the edges of
+    # pages and of the pairs of pages that a stage holds, waves without rows, groups of 1 to 16 heads (G), against the
+    # shape-generic kernels (two bf16 paths, the bound of the parity tests)
+    shape = SHAPES["small-d128"].replace(n_q_heads=heads[0], n_kv_heads=heads[1], hidden=256, intermediate=512, vocab=4096, n_layers=2)
+    blob = make_weight_blob(shape, seed=4, weight_std=0.03, gain_std=0.1)
+    rows = 4 * 32 * heads[1] // heads[0]
+    contexts = [0, 1, 15, 16, 17, 31, 32, 33, 64, 100]
+    chunks = [1, 2, rows // 4, rows // 4 + 1, rows - 1, rows, rows + 1, 2 * rows + 5, 33, 300]
+    kw = dict(max_context=512, max_trajectories=10, kv_pool_pages=300)
+    a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, flags=rl.FLAG_GENERIC_KERNELS, **kw)
+    rng = np.random.default_rng(heads[0])
+    first, more, forced = (rng.integers(0, shape.vocab, n) for n in (sum(contexts), sum(chunks), len(chunks)))
+    got = []
+    for e in (a, b):
+        e.append_observation(range(1, 10), first, contexts[1:])
+        e.append_observation(range(10), more, chunks)
+        e.decode_step_forced(range(10), 1.0, forced)
+        got.append(np.stack([e.debug_logits(i) for i in range(10)]))
+        e.close()
+    assert np.abs(got[0] - got[1]).max() < 3e-2
+
+
 @pytest.mark.parametrize("change", [dict(), dict(hidden=260, intermediate=700, vocab=4100), dict(hidden=250, head_dim=62, vocab=4090),
                                     dict(head_dim=68), dict(head_dim=128, n_q_heads=2), dict(n_kv_heads=4, head_dim=6)])
 @pytest.mark.parametrize("lens", [[1], [16, 1], [65], [17, 64, 130], [2] * 17])
