@@ -91,9 +91,8 @@ struct rl_model {
   SamplerScratch ss{};
   int32_t* h_ids = nullptr;
   // several decode steps in one call: per-step ids / log-probs on the device and pinned, and one
-  // event per staging region (the host runs that many steps ahead of the GPU)
-  int32_t *d_ids_hist = nullptr, *h_ids_hist = nullptr;
-  float *d_lp_hist = nullptr, *h_lp_hist = nullptr;
+  // event per group of staging regions (the host runs up to that many steps ahead of the GPU)
+  int32_t *d_hist = nullptr, *h_hist = nullptr;      // per step: n ids, then n log-probs
   std::vector<hipEvent_t> ev_region;
   float *d_lp = nullptr, *h_lp = nullptr;
   int32_t* hd_ids = nullptr;   // device addresses of h_ids and h_lp
@@ -430,9 +429,8 @@ struct DevMeta {
 int check_pass(rl_model* m, const Staging& st, int slots_used);
 int flush_page_updates(rl_model* m);
 
-// at: offset (in ints) of the region of the staging buffers this pass uses (0 unless several
-// passes are staged ahead of the GPU)
-int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
+// Fills the staging buffer of one pass from offset `at` (in ints) on; *used: ints that have to be copied from there.
+int stage_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at, size_t* used) {
   size_t M = st.tok.size();
   {
     int slots = 0;
@@ -441,14 +439,7 @@ int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
     if (crc) return crc;
   }
   static_assert(sizeof(AttnItem) == 32 && sizeof(AttnMerge) == 32, "metadata records are 8 ints");
-  size_t need = 6 * M + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size();
-  const size_t n_upd = m->page_upd.size();
-  if (n_upd > 0 && (at > 0 || need + n_upd > m->meta_ints)) {
-    int frc = flush_page_updates(m);
-    if (frc) return frc;
-  }
-  const size_t upd_at = need;
-  need += m->page_upd.size();
+  const size_t need = 6 * M + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size();
   if (at + need > m->meta_ints) return fail(RL_E_ARG, "internal: metadata staging too small");
   int32_t* h = m->h_meta + at;
   int32_t* d = m->d_meta + at;
@@ -461,17 +452,37 @@ int upload_meta(rl_model* m, const Staging& st, DevMeta* dm, size_t at = 0) {
   if (!st.merges.empty())
     memcpy(h + 6 * M + 8 * st.items.size(), st.merges.data(), st.merges.size() * sizeof(AttnMerge));
   put(st.rowlist, 6 * M + 8 * st.items.size() + 8 * st.merges.size());
-  put(m->page_upd, upd_at);
-  HIPCHECK(hipMemcpyAsync(d, h, need * 4, hipMemcpyHostToDevice, m->stream));
-  if (!m->page_upd.empty()) {
-    launch_page_table_update(m->stream, m->page_table, d + upd_at, (int)(m->page_upd.size() / 3), m->md.max_pages_per_traj);
-    m->page_upd.clear();
-  }
   dm->tok = d; dm->pos = d + M; dm->slot = d + 2 * M;
   dm->traj = d + 3 * M; dm->newpos = d + 4 * M; dm->forced = d + 5 * M;
   dm->items = (AttnItem*)(d + 6 * M);
   dm->merges = (AttnMerge*)(d + 6 * M + 8 * st.items.size());
   dm->rowlist = d + 6 * M + 8 * st.items.size() + 8 * st.merges.size();
+  *used = need;
+  return RL_OK;
+}
+int copy_meta(rl_model* m, size_t at, size_t n) {
+  HIPCHECK(hipMemcpyAsync(m->d_meta + at, m->h_meta + at, n * 4, hipMemcpyHostToDevice, m->stream));
+  return RL_OK;
+}
+
+// The metadata of a pass and the pending page-table entries -> device.
+int upload_meta(rl_model* m, const Staging& st, DevMeta* dm) {
+  size_t need = 0;
+  int rc = stage_meta(m, st, dm, 0, &need);
+  if (rc) return rc;
+  if (!m->page_upd.empty() && need + m->page_upd.size() > m->meta_ints) {
+    rc = flush_page_updates(m);            // through the staging buffer, which is then filled again
+    if (!rc) rc = stage_meta(m, st, dm, 0, &need);
+    if (rc) return rc;
+  }
+  const size_t n_upd = m->page_upd.size();
+  if (n_upd > 0) memcpy(m->h_meta + need, m->page_upd.data(), n_upd * 4);
+  rc = copy_meta(m, 0, need + n_upd);
+  if (rc) return rc;
+  if (n_upd > 0) {
+    launch_page_table_update(m->stream, m->page_table, m->d_meta + need, (int)(n_upd / 3), m->md.max_pages_per_traj);
+    m->page_upd.clear();
+  }
   if (!st.mask.empty())
     HIPCHECK(hipMemcpyAsync(m->d_mask, st.mask.data(), st.mask.size(), hipMemcpyHostToDevice, m->stream));
   return RL_OK;
@@ -886,7 +897,7 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
 // the staging buffers, and the host runs up to one region per step ahead of the GPU instead of
 // waiting for every step's ids.  Pages for the whole call are reserved up front, in the order the
 // single steps would have taken them.
-const int kMaxStepsPerChunk = 1024;
+const int kMaxStepsPerChunk = 1024, kStepsPerCopy = 8;
 
 int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, float temperature,
                  uint64_t seed, int32_t* ids_out, float* lp_out) {
@@ -918,14 +929,23 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
           m->page_upd.insert(m->page_upd.end(), {t->slot, (int32_t)t->pages.size(), p});
           t->pages.push_back(p);
         }
-    rc = flush_page_updates(m);     // on their own: the passes below are staged in regions of fixed size
+  }
+  // one staging region per step, behind the page-table entries of the call (more than a quarter of the buffer: on their own); the
+  // host may run as many steps ahead as there are regions
+  const size_t region_ints = 7 * (size_t)n + 8 * (size_t)(2 * n + m->attn_slots + 8);
+  if (m->page_upd.size() > m->meta_ints / 4) {
+    rc = flush_page_updates(m);
     if (rc) return rc;
   }
-  // one staging region per step; the host may run as many steps ahead as there are regions
-  const size_t region_ints = 7 * (size_t)n + 8 * (size_t)(2 * n + m->attn_slots + 8);
-  const int n_regions = (int)std::min<size_t>(m->meta_ints / region_ints, 64);
+  const size_t n_upd = m->page_upd.size(), regions_at = (n_upd + 3) / 4 * 4;
+  int n_regions = (int)std::min<size_t>((m->meta_ints - regions_at) / region_ints, 64);
   if (n_regions < 1) return fail(RL_E_ARG, "internal: metadata staging too small");
-  while ((int)m->ev_region.size() < n_regions) {
+  // The metadata of kStepsPerCopy steps goes over in one copy, packed into the front of their regions (the first step's with the
+  // page-table entries, so that the GPU starts at once).  A small fp32 rollout (51 passes) takes 3.17 ms; with a copy and an event
+  // per step, a wait for the entries and two copies at the end it took 3.50.
+  const int group = n_regions >= kStepsPerCopy ? kStepsPerCopy : 1;
+  n_regions -= n_regions % group;
+  while ((int)m->ev_region.size() < n_regions / group) {
     hipEvent_t e = nullptr;
     HIPCHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     m->ev_region.push_back(e);
@@ -938,42 +958,67 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
     const int C = std::min(kMaxStepsPerChunk, n_steps - s0);
     std::vector<int> len0(n);
     for (int i = 0; i < n; i++) len0[i] = (int)ts[i]->tokens.size();
+    struct StepMeta { DevMeta dm; int n_items, n_merges; double kvb; };
+    std::vector<StepMeta> staged;          // of the steps from first_staged on
+    int first_staged = 0;
     for (int sc = 0; sc < C; sc++) {
       const int region = sc % n_regions;
-      if (sc >= n_regions) HIPCHECK(hipEventSynchronize(m->ev_region[region]));
-      st.clear();
-      double kvb = 0.0;
-      for (int i = 0; i < n; i++) {
-        const int nt = len0[i] + sc;              // context length at this step
-        st.tok.push_back(sc == 0 ? ts[i]->tokens[nt - 1] : 0);   // later steps: the id sampled on the device
-        st.pos.push_back(nt - 1);
-        st.slot.push_back(ts[i]->slot);
-        st.traj.push_back(ids[i]);
-        st.newpos.push_back(nt);
-        kvb += (double)nt * tokb;
+      if (sc == first_staged + (int)staged.size()) {
+        staged.clear();
+        first_staged = sc;
+        const int k = std::min(sc == 0 ? 1 : group - sc % group, C - sc);
+        // the steps that used this group's regions before are over when the last of them is
+        if (sc >= n_regions) HIPCHECK(hipEventSynchronize(m->ev_region[region / group]));
+        const size_t at = regions_at + (size_t)region * region_ints;
+        size_t filled = 0;
+        for (int j = sc; j < sc + k; j++) {
+          st.clear();
+          double kvb = 0.0;
+          for (int i = 0; i < n; i++) {
+            const int nt = len0[i] + j;               // context length at this step
+            st.tok.push_back(j == 0 ? ts[i]->tokens[nt - 1] : 0);    // later steps: the id sampled on the device
+            st.pos.push_back(nt - 1);
+            st.slot.push_back(ts[i]->slot);
+            st.traj.push_back(ids[i]);
+            st.newpos.push_back(nt);
+            kvb += (double)nt * tokb;
+          }
+          add_decode_items(m, st, ts);
+          StepMeta sm{{}, (int)st.items.size(), (int)st.merges.size(), kvb};
+          size_t used = 0;
+          if (6 * (size_t)n + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size() + 3 > region_ints)
+            return fail(RL_E_ARG, "internal: staging region too small");
+          rc = stage_meta(m, st, &sm.dm, at + filled, &used);
+          if (rc) return rc;
+          filled += (used + 3) / 4 * 4;            // 16-byte records stay aligned
+          staged.push_back(sm);
+        }
+        const bool entries = !m->page_upd.empty();
+        if (entries) memcpy(m->h_meta, m->page_upd.data(), n_upd * 4);
+        rc = entries ? copy_meta(m, 0, at + filled) : copy_meta(m, at, filled);
+        if (rc) return rc;
+        if (entries) {
+          launch_page_table_update(m->stream, m->page_table, m->d_meta, (int)(n_upd / 3), m->md.max_pages_per_traj);
+          m->page_upd.clear();
+        }
       }
-      add_decode_items(m, st, ts);
-      {
-        const size_t need_ints = 6 * (size_t)n + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size();
-        if (need_ints > region_ints) return fail(RL_E_ARG, "internal: staging region too small");
-      }
-      DevMeta dm;
-      rc = upload_meta(m, st, &dm, (size_t)region * region_ints);
-      if (rc) return rc;
+      const DevMeta& dm = staged[sc - first_staged].dm;
+      const int n_items = staged[sc - first_staged].n_items, n_merges = staged[sc - first_staged].n_merges;
+      const double kvb = staged[sc - first_staged].kvb;
       const bool timed = m->timing_every > 0 && (m->decode_steps % m->timing_every) == 0;
       m->decode_steps++;
-      const int32_t* tok = sc == 0 ? dm.tok : m->d_ids_hist + (size_t)(sc - 1) * n;
-      RowMeta r{tok, dm.pos, dm.slot, dm.items, (int)st.items.size(), dm.merges, (int)st.merges.size(),
+      const int32_t* tok = sc == 0 ? dm.tok : m->d_hist + (size_t)(sc - 1) * 2 * n;
+      RowMeta r{tok, dm.pos, dm.slot, dm.items, n_items, dm.merges, n_merges,
                 dm.rowlist, nullptr, 0, false, kvb, timed};
       if (timed) (void)hipEventRecord(m->ev_step[0], m->stream);
       forward_rows(m, n, r);
       lm_head_rows(m, n, 0, n, false, n, !greedy);
       launch_sampler(m->stream, m->logits, (size_t)m->md.V, n, m->md.V, c, greedy ? 1 : 0, nullptr, seed,
-                     dm.traj, dm.newpos, nullptr, nullptr, m->ss, m->d_ids_hist + (size_t)sc * n,
-                     m->d_lp_hist + (size_t)sc * n, drawn_maxima(m, !greedy), m->md.V / 32);
+                     dm.traj, dm.newpos, nullptr, nullptr, m->ss, m->d_hist + (size_t)sc * 2 * n,
+                     (float*)(m->d_hist + (size_t)(2 * sc + 1) * n), drawn_maxima(m, !greedy), m->md.V / 32);
       HIPCHECK(hipGetLastError());
       if (timed) (void)hipEventRecord(m->ev_step[1], m->stream);
-      HIPCHECK(hipEventRecord(m->ev_region[region], m->stream));
+      if ((region + 1) % group == 0) HIPCHECK(hipEventRecord(m->ev_region[region / group], m->stream));
       double kvu = 0.0;
       if (m->timing_every > 0) {    // byte accounting, while the GPU works (as in the single step)
         if (m->page_stamp.size() != m->refcount.size()) m->page_stamp.assign(m->refcount.size(), 0);
@@ -1009,14 +1054,14 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
         }
       }
     }
-    HIPCHECK(hipMemcpyAsync(m->h_ids_hist, m->d_ids_hist, (size_t)C * n * 4, hipMemcpyDeviceToHost, m->stream));
-    HIPCHECK(hipMemcpyAsync(m->h_lp_hist, m->d_lp_hist, (size_t)C * n * 4, hipMemcpyDeviceToHost, m->stream));
+    HIPCHECK(hipMemcpyAsync(m->h_hist, m->d_hist, (size_t)C * 2 * n * 4, hipMemcpyDeviceToHost, m->stream));
     HIPCHECK(hipStreamSynchronize(m->stream));
     for (int sc = 0; sc < C; sc++)
       for (int i = 0; i < n; i++) {
         Traj* t = ts[i];
-        const int32_t id = m->h_ids_hist[(size_t)sc * n + i];
-        const float lp = m->h_lp_hist[(size_t)sc * n + i];
+        const int32_t id = m->h_hist[(size_t)sc * 2 * n + i];
+        float lp;
+        memcpy(&lp, m->h_hist + (size_t)(2 * sc + 1) * n + i, 4);
         t->tokens.push_back(id);
         t->mask.push_back(0);
         t->logp.push_back(lp);
@@ -1220,10 +1265,8 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   TRY(m->dalloc((void**)&m->ss.segw, (size_t)m->Rl * nseg * 8));
   TRY(m->dalloc((void**)&m->ss.sege, (size_t)m->Rl * nseg * 4));
   if (m->mfma) TRY(m->dalloc((void**)&m->d_stripmax, (size_t)m->Rl * (V / 32) * 4));
-  TRY(m->dalloc((void**)&m->d_ids_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
-  TRY(m->dalloc((void**)&m->d_lp_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
-  HIPTRY(hipHostMalloc((void**)&m->h_ids_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
-  HIPTRY(hipHostMalloc((void**)&m->h_lp_hist, (size_t)kMaxStepsPerChunk * m->Rl * 4));
+  TRY(m->dalloc((void**)&m->d_hist, (size_t)kMaxStepsPerChunk * m->Rl * 8));
+  HIPTRY(hipHostMalloc((void**)&m->h_hist, (size_t)kMaxStepsPerChunk * m->Rl * 8));
   TRY(m->dalloc((void**)&m->d_lp, (size_t)m->Rl * 4));
   TRY(m->dalloc((void**)&m->d_mask, Mc));
   TRY(m->dalloc((void**)&m->d_zt, Mc * 4));
@@ -1268,8 +1311,7 @@ extern "C" void rl_model_free(rl_model* m) {
   for (void* p : m->allocs) (void)hipFree(p);
   if (m->h_meta) (void)hipHostFree(m->h_meta);
   if (m->h_ids) (void)hipHostFree(m->h_ids);
-  if (m->h_ids_hist) (void)hipHostFree(m->h_ids_hist);
-  if (m->h_lp_hist) (void)hipHostFree(m->h_lp_hist);
+  if (m->h_hist) (void)hipHostFree(m->h_hist);
   for (auto e : m->ev_region) if (e) (void)hipEventDestroy(e);
   if (m->h_lp) (void)hipHostFree(m->h_lp);
   if (m->h_lp_rows) (void)hipHostFree(m->h_lp_rows);

@@ -307,3 +307,20 @@ def test_fp32_products_with_the_norm_inside(hidden, head_dim, heads, intermediat
     assert np.abs(o.debug_logits(k) - g.debug_logits(k)).max() < 1e-4
     assert np.abs(np.asarray(o.recompute_logprobs([k], 1.0)) - g.recompute_logprobs([k], 1.0)).max() < 1e-4
     g.close()
+
+
+@pytest.mark.parametrize("n,steps", [(700, 20), (2000, 12), (2000, 330)])
+def test_decode_steps_of_batches_that_leave_few_staging_regions(n, steps):
+    # 12 regions (one group of eight, used again), four (a copy per step), and 42 000 page-table entries, more than a quarter of
+    # the staging buffer: the single steps' bits
+    shape = SHAPES["tiny"].replace(n_layers=1, hidden=64, n_q_heads=1, n_kv_heads=1, intermediate=64, vocab=128)
+    blob = make_weight_blob(shape, seed=5, weight_std=0.05)
+    kw = dict(max_context=352, max_trajectories=n, kv_pool_pages=n * 22)
+    a, b = rl.RolloutEngine(blob, **kw), rl.RolloutEngine(blob, **kw)
+    ids = np.arange(n, dtype=np.int32)
+    for e in (a, b):
+        e.append_observation(ids, np.arange(n) % 128, np.ones(n, np.int32))
+    single = [a.decode_step(ids, 1.0, 5) for _ in range(steps)]
+    got_ids, got_lps = b.decode_steps(ids, steps, 1.0, 5)
+    assert np.array_equal(got_ids, np.stack([x[0] for x in single])) and np.array_equal(got_lps, np.stack([x[1] for x in single]))
+    assert a.n_free_pages() == b.n_free_pages()
