@@ -9,7 +9,7 @@
 // The log-prob is t_id * ln 2 - ln(sum e_i).  This file must be compiled with
 // -ffp-contract=off: a fused multiply-add would change the weights' bits.
 //
-// Launches: per-segment maxima (segments of RL_SAMPLER_SEG logits; left out where the lm-head has left
+// Launches: maxima (of segments of RL_SAMPLER_SEG logits, or of a workgroup's; left out where the lm-head has left
 // maxima of its own), weight sums of the segments, then one workgroup per row that locates the segment
 // and the token inside it.
 #include "../../include/rl_rollout.h"
@@ -122,23 +122,52 @@ __global__ __launch_bounds__(256) void seg_max_kernel(const float* __restrict__ 
   }
 }
 
-// grid (ceil(nseg / spw), rows), block 256: weight sums of up to spw consecutive segments of a row.
-// The row maximum is first reduced from `maxima` (nmax per row: the lm-head's strip maxima, or the
-// segment maxima): several segments per workgroup, so that reading the maxima stays a small part of
+// grid (ceil(nseg / spw), rows), block 256: the maximum of up to spw consecutive segments of a row (drawn rows: no arg-max).  The next
+// segment's logits are requested before the current one's are compared: 128 x 151 936 logits 12.3 us (14.1 with a
+// workgroup, its reduction and its two entries per segment, which the arg-max needs).
+template <bool VEC>
+__global__ __launch_bounds__(256) void row_max_kernel(const float* __restrict__ z, size_t ldz, int V, int spw, int nseg,
+                                                      float* __restrict__ maxima) {
+  __shared__ float sm[4];
+  const int row = blockIdx.y, tid = threadIdx.x;
+  const int s0 = blockIdx.x * spw, s1 = min(s0 + spw, nseg);
+  const float* zr = z + (size_t)row * ldz;
+  float v[16], m = -INFINITY;
+  seg_load<VEC>(zr, V, s0, tid, v);
+  for (int seg = s0; seg < s1; seg++) {
+    float nx[16];
+    if (seg + 1 < s1) seg_load<VEC>(zr, V, seg + 1, tid, nx);
+#pragma unroll
+    for (int i = 0; i < 16; i++) m = fmaxf(m, seg_index<VEC>(seg, tid, i) < V ? v[i] : -INFINITY);
+    if (seg + 1 < s1) {
+#pragma unroll
+      for (int i = 0; i < 16; i++) v[i] = nx[i];
+    }
+  }
+  m = wave_max(m);
+  if ((tid & 63) == 0) sm[tid >> 6] = m;
+  __syncthreads();
+  if (tid == 0) maxima[(size_t)row * gridDim.x + blockIdx.x] = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+}
+
+// grid (ceil(nseg / spw), rows), block 256: weight sums of up to spw <= 8 consecutive segments of a row.
+// The row maximum is first reduced from `maxima` (nmax per row: the lm-head's strip maxima, or those of the kernel
+// above): several segments per workgroup, so that reading the maxima stays a small part of
 // its work and needs no launch of its own.  The next segment's logits are requested before the
-// current one's arithmetic.  128 x 151 936 logits: 18.5 us from segment maxima, 21 us from 4748 strip
-// maxima (30 us, and 38 + 8 us with a launch of its own for the maxima, before); bound by about 25
-// vector instructions per logit.  put_max: the maximum is left in the row's segmax entries for the last
-// kernel (strip maxima; with segment maxima they hold it already).
+// current one's arithmetic.  A thread leaves its sums of a segment in LDS and goes on; behind the last one a wave adds up
+// every fourth segment, so that the chains of lane exchanges and the barriers come once per workgroup and not per segment: 128 x 151 936
+// logits 16.2 us (18.4 with a reduction and two barriers per segment; 30 us, and 38 + 8 us with a launch of its own for the maxima,
+// before).  put_max: the maximum is left in the row's segmax entries for the last kernel (arg-max: they hold every segment's own).
+constexpr int kMaxSpw = 8;
 template <bool VEC>
 __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict__ z, size_t ldz, int V, float c,
                                                          const float* maxima, int nmax, int spw, int nseg, int put_max,
                                                          float* segmax, uint64_t* __restrict__ segw,
                                                          float* __restrict__ sege) {
   __shared__ float sm[4];
-  __shared__ uint64_t sw[4];
-  __shared__ float se[4];
-  const int row = blockIdx.y, tid = threadIdx.x;
+  __shared__ uint64_t sw[kMaxSpw][256];
+  __shared__ float se[kMaxSpw][256];
+  const int row = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int s0 = blockIdx.x * spw, s1 = min(s0 + spw, nseg);
   const float* zr = z + (size_t)row * ldz;
   float v[16];
@@ -153,7 +182,7 @@ __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict
     for (int j = 0; j < 8; j++) m = fmaxf(m, q[j]);
   }
   m = wave_max(m);
-  if ((tid & 63) == 0) sm[tid >> 6] = m;
+  if (lane == 0) sm[wave] = m;
   __syncthreads();
   m = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
   for (int seg = s0; seg < s1; seg++) {
@@ -196,45 +225,63 @@ __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict
         if (x >= kTwo32 && seg_index<VEC>(seg, tid, i) < V) ws += kTop;
       }
     }
+    sw[seg - s0][tid] = ws;
+    se[seg - s0][tid] = es;
     if (seg + 1 < s1) {
 #pragma unroll
       for (int i = 0; i < 16; i++) v[i] = nx[i];
     }
+  }
+  __syncthreads();
+  for (int seg = s0 + wave; seg < s1; seg += 4) {
+    const uint64_t* pw = sw[seg - s0] + lane;
+    const float* pe = se[seg - s0] + lane;
+    uint64_t ws = (pw[0] + pw[64]) + (pw[128] + pw[192]);
+    float es = __fadd_rn(__fadd_rn(pe[0], pe[64]), __fadd_rn(pe[128], pe[192]));
     for (int o = 32; o > 0; o >>= 1) {
       ws += __shfl_xor(ws, o, 64);
       es = __fadd_rn(es, __shfl_xor(es, o, 64));
     }
-    if (seg > s0) __syncthreads();      // the previous segment's sums have been read
-    if ((tid & 63) == 0) { sw[tid >> 6] = ws; se[tid >> 6] = es; }
-    __syncthreads();
-    if (tid == 0) {
-      segw[(size_t)row * nseg + seg] = sw[0] + sw[1] + sw[2] + sw[3];
-      sege[(size_t)row * nseg + seg] = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3])) * 0x1p-32f;
+    if (lane == 0) {
+      segw[(size_t)row * nseg + seg] = ws;
+      sege[(size_t)row * nseg + seg] = es * 0x1p-32f;
       if (put_max) segmax[(size_t)row * nseg + seg] = m;
     }
   }
 }
 
-// Inclusive sum over the workgroup's 256 threads; *total gets the sum of all.  tmp: 4 entries of LDS.
-__device__ __forceinline__ uint64_t block_scan(uint64_t x, uint64_t* tmp, uint64_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Sums over a wave's lanes up to and including this one.
+__device__ __forceinline__ uint64_t wave_scan(uint64_t x) {
+  const int lane = threadIdx.x & 63;
   for (int o = 1; o < 64; o <<= 1) {
-    uint64_t y = __shfl_up(x, o, 64);
+    const uint64_t y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
+  return x;
+}
+
+// Inclusive sum over the workgroup's threads; *total gets the sum of all.  tmp: an entry of LDS per wave.
+__device__ __forceinline__ uint64_t block_scan(uint64_t x, uint64_t* tmp, int waves, uint64_t* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  x = wave_scan(x);
   __syncthreads();                      // an earlier use of tmp is over
   if (lane == 63) tmp[wave] = x;
   __syncthreads();
-  uint64_t before = 0;
-  for (int k = 0; k < wave; k++) before += tmp[k];
-  *total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  uint64_t before = 0, all = 0;
+  for (int k = 0; k < waves; k++) {
+    const uint64_t y = tmp[k];
+    before += k < wave ? y : 0;
+    all += y;
+  }
+  *total = all;
   return x + before;
 }
 
-// grid rows, block 256.  A chain of three dependent reads (segment sums, the chosen segment's logits,
-// none for the log-prob): the sums over segments and the two searches are spread over the lanes (128
-// rows: 15.1 -> 6.6 us).
-template <bool VEC>
+// grid rows, block 256.  A chain of two dependent reads (segment sums and the draw; the chosen segment's logits).  FEW (at most 64
+// segments): every wave holds all segments, one a lane, and finds the segment by itself; the only barriers are those of the
+// search among the segment's logits (1 / 128 rows of 151 936 logits 5.4 / 6.7 us with the segments joined through LDS and the draw read
+// behind their sums, now 4.8 / 5.8; 1024 threads of four logits 5.5 / 6.3; 15.1 with one thread's loops).
+template <bool VEC, bool FEW>
 __global__ __launch_bounds__(256) void sample_final_kernel(
     const float* __restrict__ z, size_t ldz, int V, float c, int greedy, int nseg,
     const float* __restrict__ segmax, const int32_t* __restrict__ segarg, const uint64_t* __restrict__ segw,
@@ -242,16 +289,22 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
     const int32_t* __restrict__ row_traj, const int32_t* __restrict__ row_newpos,
     const int32_t* __restrict__ forced, const uint8_t* __restrict__ out_mask, int32_t* __restrict__ ids_out,
     float* __restrict__ logp_out) {
-  __shared__ uint64_t tmp[4], s_pre;
-  __shared__ float sm[4], se[4], s_z;
-  __shared__ int sa[4], s_seg, s_id;
-  const int row = blockIdx.x, tid = threadIdx.x;
+  constexpr int T = 256, NW = T / 64, PER = RL_SAMPLER_SEG / T;      // consecutive logits per thread
+  __shared__ uint64_t tmp[NW], s_pre;
+  __shared__ float sm[NW], se[NW], s_z;
+  __shared__ int sa[NW], s_seg, s_id;
+  const int row = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* zr = z + (size_t)row * ldz;
   const size_t r0 = (size_t)row * nseg;
+  const bool drawn = !(forced || greedy);
+  // asked for ahead of the sums that they are used behind
+  const int want = forced ? forced[row] : 0;
+  const uint32_t u = !drawn ? 0u : u32 ? u32[row] : splitmix_u32(seed, row_traj[row], row_newpos[row]);
+  const bool masked = out_mask && out_mask[row];
   float m = -INFINITY, E = 0.f;
   int arg = 0x7fffffff;
-  uint64_t W = 0;
-  for (int k = tid; k < nseg; k += 256) {
+  uint64_t W = 0, own = 0;
+  for (int k = FEW ? lane : tid; k < nseg; k += FEW ? 64 : T) {
     const float v = segmax[r0 + k];
     if (greedy) {
       const int a = segarg[r0 + k];
@@ -259,49 +312,61 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
     } else {
       m = fmaxf(m, v);
     }
-    W += segw[r0 + k];
+    own = segw[r0 + k];
+    W += own;
     E = __fadd_rn(E, sege[r0 + k]);
   }
+  if (tid == 0) { s_seg = nseg - 1; s_id = -1; }
+  const uint64_t incl = FEW ? wave_scan(W) : 0;
   for (int o = 32; o > 0; o >>= 1) {
     const float ov = __shfl_xor(m, o, 64);
     const int oa = __shfl_xor(arg, o, 64);
     if (greedy ? (ov > m || (ov == m && oa < arg)) : ov > m) { m = ov; arg = oa; }
     E = __fadd_rn(E, __shfl_xor(E, o, 64));
-    W += __shfl_xor(W, o, 64);
+    if (!FEW) W += __shfl_xor(W, o, 64);
   }
-  if ((tid & 63) == 0) { sm[tid >> 6] = m; sa[tid >> 6] = arg; se[tid >> 6] = E; tmp[tid >> 6] = W; }
-  if (tid == 0) { s_seg = nseg - 1; s_id = -1; }
-  __syncthreads();
-  m = sm[0];
-  arg = sa[0];
-  for (int k = 1; k < 4; k++)
-    if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
-  E = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3]));
-  W = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  if (FEW) {
+    W = __shfl(incl, 63, 64);
+  } else {
+    if (lane == 0) { sm[wave] = m; sa[wave] = arg; se[wave] = E; tmp[wave] = W; }
+    __syncthreads();
+    m = sm[0];
+    arg = sa[0];
+    for (int k = 1; k < NW; k++)
+      if (sm[k] > m || (sm[k] == m && sa[k] < arg)) { m = sm[k]; arg = sa[k]; }
+    E = __fadd_rn(__fadd_rn(se[0], se[1]), __fadd_rn(se[2], se[3]));
+    W = tmp[0] + tmp[1] + tmp[2] + tmp[3];
+  }
   int id;
   float zid = 0.f;
-  if (forced || greedy) {
-    id = forced ? forced[row] : (arg == 0x7fffffff ? 0 : arg);   // a row without any number: token 0
+  if (!drawn) {
+    id = forced ? want : (arg == 0x7fffffff ? 0 : arg);   // a row without any number: token 0
     if (id >= 0 && id < V) zid = zr[id];
   } else {
-    const uint32_t u = u32 ? u32[row] : splitmix_u32(seed, row_traj[row], row_newpos[row]);
     const uint64_t hi = __umul64hi(W, (uint64_t)u), lo = W * (uint64_t)u;
     const uint64_t r = (hi << 32) | (lo >> 32);          // floor(u * W / 2^32) < W
     // first segment whose inclusive sum exceeds r (the last one if none does)
-    uint64_t carry = 0;
-    for (int k0 = 0; k0 < nseg; k0 += 256) {
-      const int k = k0 + tid;
-      const uint64_t w = k < nseg ? segw[r0 + k] : 0;
-      uint64_t total;
-      const uint64_t incl = carry + block_scan(w, tmp, &total);
-      if (k < nseg - 1 && incl > r && incl - w <= r) { s_seg = k; s_pre = incl - w; }
-      if (k == nseg - 1 && incl - w <= r) s_pre = incl - w;
-      carry += total;
+    int s;
+    uint64_t rl;                                         // target inside segment s
+    if (FEW) {
+      const uint64_t above = __ballot(lane < nseg - 1 && incl > r);
+      s = above ? __builtin_ctzll(above) : nseg - 1;
+      rl = r - (__shfl(incl, s, 64) - __shfl(own, s, 64));
+    } else {
+      uint64_t carry = 0;
+      for (int k0 = 0; k0 < nseg; k0 += T) {
+        const int k = k0 + tid;
+        const uint64_t w = k < nseg ? segw[r0 + k] : 0;
+        uint64_t total;
+        const uint64_t in = carry + block_scan(w, tmp, NW, &total);
+        if (k < nseg - 1 && in > r && in - w <= r) { s_seg = k; s_pre = in - w; }
+        if (k == nseg - 1 && in - w <= r) s_pre = in - w;
+        carry += total;
+      }
+      __syncthreads();
+      s = s_seg;
+      rl = r - s_pre;
     }
-    __syncthreads();
-    const int s = s_seg;
-    const uint64_t rl = r - s_pre;                       // target inside segment s
-    const int PER = RL_SAMPLER_SEG / 256;                // 16 consecutive logits per thread
     const int base = s * RL_SAMPLER_SEG + tid * PER;
     float zl[PER];
     if (VEC) {
@@ -325,7 +390,7 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
       mine += wloc[j];
     }
     uint64_t total;
-    const uint64_t before = block_scan(mine, tmp, &total) - mine;
+    const uint64_t before = block_scan(mine, tmp, NW, &total) - mine;
     if (before <= rl && rl < before + mine) {
       uint64_t acc = before;
       bool found = false;
@@ -343,7 +408,7 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
   }
   if (tid == 0) {
     float lp = 0.f;
-    if (!(out_mask && out_mask[row])) {
+    if (!masked) {
       float t = __fmul_rn(__fsub_rn(zid, m), c);
       lp = t * 0.6931471805599453f - logf(E);
     }
@@ -423,11 +488,7 @@ __global__ __launch_bounds__(T) void sample_row_kernel(
     }
     e = __fadd_rn(e, in ? x : 0.f);
   }
-  uint64_t incl = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
+  const uint64_t incl = wave_scan(mine);
   for (int o = 32; o > 0; o >>= 1) e = __fadd_rn(e, __shfl_xor(e, o, 64));
   if (lane == 63) sw[wave] = incl;
   if (lane == 0) se[wave] = e;
@@ -499,29 +560,27 @@ void launch_sampler(hipStream_t s, const float* logits, size_t ldz, int rows, in
     return;
   }
   if (greedy || nstrips <= 0) stripmax = nullptr;   // the arg-max needs the pass over the logits
-  if (!stripmax) {
-    if (vec) seg_max_kernel<true><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
-    else seg_max_kernel<false><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
-  }
   // about five workgroups per CU, each with at most eight segments (rl_sample on 128 rows of 151936 / 40000 logits: four 38.0 /
   // 20.8 us, five 37.7 / 18.5, eight 38.9 / 18.6)
-  const int spw = (int)std::min<int64_t>(8, std::max<int64_t>(1, ((int64_t)nseg * rows + 1279) / 1280));
+  const int spw = (int)std::min<int64_t>(kMaxSpw, std::max<int64_t>(1, ((int64_t)nseg * rows + 1279) / 1280));
   const dim3 wgrid((nseg + spw - 1) / spw, rows);
-  const float* maxima = stripmax ? stripmax : sc.segmax;
-  const int nmax = stripmax ? nstrips : nseg, put = stripmax ? 1 : 0;
-  if (vec) {
-    seg_weight_kernel<true><<<wgrid, 256, 0, s>>>(logits, ldz, V, scale_c, maxima, nmax, spw, nseg, put, sc.segmax,
-                                                  sc.segw, sc.sege);
-    sample_final_kernel<true><<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax, sc.segarg, sc.segw,
-                                                   sc.sege, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out,
-                                                   logp_out);
-  } else {
-    seg_weight_kernel<false><<<wgrid, 256, 0, s>>>(logits, ldz, V, scale_c, maxima, nmax, spw, nseg, put, sc.segmax,
-                                                   sc.segw, sc.sege);
-    sample_final_kernel<false><<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax, sc.segarg, sc.segw,
-                                                    sc.sege, u32, seed, row_traj, row_newpos, forced, out_mask, ids_out,
-                                                    logp_out);
-  }
+  // of drawn rows the workgroups' maxima go where the arg-max would: the weights' kernel writes segmax while others still read
+  const float* maxima = stripmax ? stripmax : greedy ? sc.segmax : (const float*)sc.segarg;
+  const int nmax = stripmax ? nstrips : greedy ? nseg : (int)wgrid.x;
+  auto go = [&](auto vec_) {
+    constexpr bool VEC = decltype(vec_)::value;
+    if (greedy) seg_max_kernel<VEC><<<grid, 256, 0, s>>>(logits, ldz, V, sc.segmax, sc.segarg);
+    else if (!stripmax) row_max_kernel<VEC><<<wgrid, 256, 0, s>>>(logits, ldz, V, spw, nseg, (float*)sc.segarg);
+    seg_weight_kernel<VEC><<<wgrid, 256, 0, s>>>(logits, ldz, V, scale_c, maxima, nmax, spw, nseg, greedy ? 0 : 1, sc.segmax, sc.segw, sc.sege);
+    auto last = [&](auto kernel) {
+      kernel<<<rows, 256, 0, s>>>(logits, ldz, V, scale_c, greedy, nseg, sc.segmax, sc.segarg, sc.segw, sc.sege, u32, seed, row_traj, row_newpos,
+                                  forced, out_mask, ids_out, logp_out);
+    };
+    if (nseg <= 64) last(sample_final_kernel<VEC, true>);
+    else last(sample_final_kernel<VEC, false>);
+  };
+  if (vec) go(std::true_type());
+  else go(std::false_type());
 }
 
 // ---------------------------------------------------------------------------------------------
