@@ -311,6 +311,8 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
   int H = md.H, qw = md.nq * md.d, kvw = md.nkv * md.d, I = md.I, QW = qw + 2 * kvw;
   const PassPlan plan = plan_pass(md, M, m->part_rows);
   float *const co = plan.eo == EPI_ADD ? m->h : m->ph, *const cd = plan.ed == EPI_ADD ? m->h : m->ph;
+  // norm, RoPE and the cache write inside the attention: decode rows alone, none of them through a shared-prefix item
+  const bool rope_inside = !plan.fused_qkv && !r.prefill && r.n_pf_items == 0 && !m->cascade && attention_takes_rope(r.kv_bytes, md);
   int pend = 0;
   const float *so_q = nullptr, *so_g;       // sums of squares, where the norm's division is left to the consumer
   for (int l = 0; l < md.L; l++) {
@@ -319,6 +321,7 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
     const bf16_t* g_next = (const bf16_t*)(l + 1 < md.L ? m->layers[l + 1].g_in : m->g_final);
     if (l == 0) launch_embed_rmsnorm(s, (const bf16_t*)m->embed, r.tok, m->h, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
     else if (!so_q) launch_add_rmsnorm(s, m->h, m->ph, pend, (size_t)M * H, (const bf16_t*)w.g_in, (bf16_t*)m->xa, M, H, md.eps);
+    RopeArgs rope{};
     if (plan.fused_qkv) {
       const QkvArgs qa{(const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, r.pos, r.slot, m->page_table,
                        (bf16_t*)m->qb, m->pools[l].k, m->pools[l].v, md.nq, md.nkv, md.qk_norm,
@@ -326,12 +329,13 @@ void forward_mfma(rl_model* m, int M, const RowMeta& r) {
       launch_gemm_qkv(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, M, QW, H, md.kv_fp8 != 0, plan.q, qa);
     } else {
       int sq = launch_gemm_mfma(s, (const bf16_t*)m->xa, (const bf16_t*)w.wqkv, m->qkv, M, QW, H, EPI_STORE, plan.q);
-      launch_qkrope128(s, m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs,
-                       r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M, so_q);
+      rope = RopeArgs{m->qkv, sq, (size_t)M * QW, (const bf16_t*)w.gq, (const bf16_t*)w.gk, m->rope_cs, md.nq, md.nkv, md.qk_norm, md.eps,
+                      so_q, H / 16, (M + 15) / 16 * 16, H};
+      if (!rope_inside) launch_qkrope128(s, rope, r.pos, r.slot, m->page_table, (bf16_t*)m->qb, m->pools[l], md, M);
     }
     if (r.time_attn) (void)hipEventRecord(m->ev[2 * l], s);
     launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.items, r.n_items, r.merges, r.n_merges,
-                          r.rowlist, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, r.prefill);
+                          r.rowlist, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, r.prefill, rope_inside ? &rope : nullptr);
     if (r.n_pf_items > 0)
       launch_attention_mfma(s, (const bf16_t*)m->qb, m->pools[l], r.pf_items, r.n_pf_items, nullptr, 0,
                             nullptr, m->page_table, (bf16_t*)m->xo, m->attn_scratch, md, true);

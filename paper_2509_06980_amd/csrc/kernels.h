@@ -65,12 +65,21 @@ void launch_qkrope(hipStream_t s, const float* qkv, const TW* gq, const TW* gk, 
                    const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table, TA* qout,
                    KvPool pool, const ModelDims& md, int M);
 // The same for the MFMA path (head_dim 128, operand-order cache blocks).  The projection arrives as
-// n_part <= 8 split-K partial sums (qkv + p * part_stride), added here in ascending order.  ssq: the input rows of the
-// projection came from launch_gemm_residual; its rows are divided by their rms here.
-void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const bf16_t* gq,
-                      const bf16_t* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
-                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M,
-                      const float* ssq = nullptr);
+// n_part <= 8 split-K partial sums (qkv + p * part_stride), added in ascending order.  ssq: the input rows of the
+// projection came from launch_gemm_residual; its rows are divided by their rms.
+struct RopeArgs {
+  const float* qkv;
+  int n_part;
+  size_t part_stride;
+  const bf16_t *gq, *gk;
+  const float* rope_cs;
+  int nq, nkv, qk_norm;
+  float eps;
+  const float* ssq;              // null: the rows are divided already
+  int n16, ss_stride, hidden;    // sums of squares per row, their stride, and what they are the mean of
+};
+void launch_qkrope128(hipStream_t s, const RopeArgs& a, const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table,
+                      bf16_t* qout, KvPool pool, const ModelDims& md, int M);
 
 // h += sum of n_part split-K partial sums (ascending order), then out = rmsnorm(h) * g in A-tile
 // layout (bf16 MFMA path).  rows != null: gather: output row i is made from row rows[i] of h /
@@ -164,7 +173,9 @@ const int kPrefillColumns = 32;      // (row, head of the group) pairs of a wave
 void launch_attention_mfma(hipStream_t s, const bf16_t* q, KvPool pool, const AttnItem* items,
                            int n_items, const AttnMerge* merges, int n_merges,
                            const int32_t* rowlist, const int32_t* page_table, bf16_t* o,
-                           float* scratch, const ModelDims& md, bool prefill);
+                           float* scratch, const ModelDims& md, bool prefill, const RopeArgs* rope = nullptr);
+// Whether the decode attention of single rows takes their norm, RoPE and cache write along (rope).
+bool attention_takes_rope(double kv_bytes, const ModelDims& md);
 
 // ---- sampler ---------------------------------------------------------------------------------
 struct SamplerScratch {

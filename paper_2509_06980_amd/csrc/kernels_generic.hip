@@ -4,6 +4,7 @@
 //   h += W_down (silu(W_gate b) * W_up b),                       b = rmsnorm(h)
 // Each kernel below is one of those pieces; accumulation is always fp32.
 #include "kernels.h"
+#include "qkrope.h"
 
 template <typename TW>
 __global__ void embed_kernel(const TW* __restrict__ E, const int32_t* __restrict__ tok,
@@ -748,144 +749,36 @@ void launch_norm_qkv32(hipStream_t s, float* h, const float* E, const int32_t* t
   else tok ? go(norm_qkv32_kernel<128, true>) : go(norm_qkv32_kernel<128, false>);
 }
 
-// head_dim 128, bf16, MFMA cache layout: grid (M, ceil(heads / 16)), block 256.  Sixteen lanes
-// own one head: lane `sub` holds dims 4 sub .. 4 sub + 3 and their rotate-half partners 64 + ...,
-// so partial sums arrive as 16-byte loads (all issued before the first add) and q, k leave as
-// 8-byte stores.  FP8: keys and values go from fp32 straight to E4M3 codes (8-bit cache layout).
-// UNDIV: the row is still to be divided by the rms of the projection's input, ssq holds that input's sums of squares.  A
-// choice at compile time: tested at run time the plain form with the 8-bit cache took 101 registers instead of 84, 4 waves
-// a SIMD instead of 5.  The bound holds the dividing forms at five (93 registers; 101 without it).
+// head_dim 128, bf16, MFMA cache layout: grid (M, ceil(heads / 16)), block 256; qkrope_head128 for sixteen lanes a head.
+// The bound holds the dividing forms at five waves a SIMD (93 registers; 101 without it).
 template <bool FP8, bool UNDIV>
-__global__ __launch_bounds__(256, 5) void qkrope128_kernel(
-    const float* __restrict__ qkv, int n_part, size_t part_stride, const bf16_t* __restrict__ gq,
-    const bf16_t* __restrict__ gk, const float* __restrict__ rope_cs,
-    const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_slot,
-    const int32_t* __restrict__ page_table, bf16_t* __restrict__ qout, bf16_t* __restrict__ kpool,
-    bf16_t* __restrict__ vpool, int nq, int nkv, float eps, int qk_norm, int pt_stride, const float* __restrict__ ssq,
-    int n16, int ss_stride, int hidden) {
+__global__ __launch_bounds__(256, 5) void qkrope128_kernel(const RopeArgs a, const int32_t* __restrict__ row_pos,
+                                                           const int32_t* __restrict__ row_slot,
+                                                           const int32_t* __restrict__ page_table, bf16_t* __restrict__ qout,
+                                                           bf16_t* __restrict__ kpool, bf16_t* __restrict__ vpool, int pt_stride) {
   const int row = blockIdx.x, sub = threadIdx.x & 15;
-  const int hd = blockIdx.y * 16 + (threadIdx.x >> 4), NH = nq + 2 * nkv;
-  if (hd >= NH) return;          // whole 16-lane groups leave together; no barrier below
+  const int hd = blockIdx.y * 16 + (threadIdx.x >> 4);
+  if (hd >= a.nq + 2 * a.nkv) return;          // whole 16-lane groups leave together; no barrier below
   const int pos = row_pos[row];
-  const float* x = qkv + ((size_t)row * NH + hd) * 128 + sub * 4;
-  float4 lo[8], hi[8];
-#pragma unroll
-  for (int p = 0; p < 8; p++) {
-    lo[p] = p < n_part ? *(const float4*)(x + (size_t)p * part_stride) : make_float4(0.f, 0.f, 0.f, 0.f);
-    hi[p] = p < n_part ? *(const float4*)(x + (size_t)p * part_stride + 64) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  float sq = 0.f;            // the row's sum of squares where its norm is still to be applied: n16 partial sums
-  if (UNDIV)
-    for (int x = sub; x < n16; x += 16 * 8) {      // eight reads in flight: one at a time cost 2.6 us (160 sums) to 4 us
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) v[u] = ssq[min(x + 16 * u, n16 - 1) * ss_stride + row];
-#pragma unroll
-      for (int u = 0; u < 8; u++) sq += x + 16 * u < n16 ? v[u] : 0.f;
-    }
-  const bool is_q = hd < nq, is_v = hd >= nq + nkv;
-  const bf16_t* g = is_q ? gq : gk;
-  const uint2 glo = *(const uint2*)(g + sub * 4), ghi = *(const uint2*)(g + 64 + sub * 4);
-  const float* cs = rope_cs + ((size_t)pos * 64 + sub * 4) * 2;     // (cos, sin) pairs of 4 dims
-  const float4 cs0 = *(const float4*)cs, cs1 = *(const float4*)(cs + 4);
-  float a[4] = {lo[0].x, lo[0].y, lo[0].z, lo[0].w}, b[4] = {hi[0].x, hi[0].y, hi[0].z, hi[0].w};
-#pragma unroll
-  for (int p = 1; p < 8; p++)
-    if (p < n_part) {
-      a[0] += lo[p].x; a[1] += lo[p].y; a[2] += lo[p].z; a[3] += lo[p].w;
-      b[0] += hi[p].x; b[1] += hi[p].y; b[2] += hi[p].z; b[3] += hi[p].w;
-    }
-  if (UNDIV) {
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 16);
-    const float inv = 1.0f / sqrtf(sq / (float)hidden + eps);
-#pragma unroll
-    for (int e = 0; e < 4; e++) { a[e] *= inv; b[e] *= inv; }
-  }
-  float ss = 0.f;
-#pragma unroll
-  for (int e = 0; e < 4; e++) ss += a[e] * a[e] + b[e] * b[e];
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 16);
-  bf16_t* blk = nullptr;
-  const int tok = pos & (RL_PAGE - 1);
-  int page_id = 0, kvh_id = 0;
-  if (!is_q) {
-    page_id = page_table[(size_t)row_slot[row] * pt_stride + (pos >> 4)];
-    kvh_id = is_v ? hd - nq - nkv : hd - nq;
-    blk = (is_v ? vpool : kpool) + ((size_t)page_id * nkv + kvh_id) * (RL_PAGE * 128);
-  }
-  if (is_v) {
-    if constexpr (FP8) {
-      uint8_t* blk8 = (uint8_t*)(is_v ? vpool : kpool) + ((size_t)page_id * nkv + kvh_id) * (RL_PAGE * 128);
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        blk8[vswz8_off(tok, sub * 4 + e)] = f2e4m3(a[e]);
-        blk8[vswz8_off(tok, 64 + sub * 4 + e)] = f2e4m3(b[e]);
-      }
-      return;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      blk[vswz_off(tok, sub * 4 + e)] = f2bf(a[e]);
-      blk[vswz_off(tok, 64 + sub * 4 + e)] = f2bf(b[e]);
-    }
-    return;
-  }
-  if (qk_norm) {
-    const float inv = 1.0f / sqrtf(ss / 128.0f + eps);
-    const float gl[4] = {bf2f((bf16_t)(glo.x & 0xffff)), bf2f((bf16_t)(glo.x >> 16)),
-                         bf2f((bf16_t)(glo.y & 0xffff)), bf2f((bf16_t)(glo.y >> 16))};
-    const float gh[4] = {bf2f((bf16_t)(ghi.x & 0xffff)), bf2f((bf16_t)(ghi.x >> 16)),
-                         bf2f((bf16_t)(ghi.y & 0xffff)), bf2f((bf16_t)(ghi.y >> 16))};
-#pragma unroll
-    for (int e = 0; e < 4; e++) { a[e] = a[e] * inv * gl[e]; b[e] = b[e] * inv * gh[e]; }
-  }
-  const float c[4] = {cs0.x, cs0.z, cs1.x, cs1.z}, sn[4] = {cs0.y, cs0.w, cs1.y, cs1.w};
-  if constexpr (FP8) {
-    if (!is_q) {   // 4 consecutive dims = 4 consecutive bytes of one lane slot
-      uint8_t* blk8 = (uint8_t*)kpool + ((size_t)page_id * nkv + kvh_id) * (RL_PAGE * 128);
-      float r1[4], r2[4];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        r1[e] = a[e] * c[e] - b[e] * sn[e];
-        r2[e] = b[e] * c[e] + a[e] * sn[e];
-      }
-      *(uint32_t*)(blk8 + kswz8_off(tok, sub * 4)) = f2e4m3x4(r1[0], r1[1], r1[2], r1[3]);
-      *(uint32_t*)(blk8 + kswz8_off(tok, 64 + sub * 4)) = f2e4m3x4(r2[0], r2[1], r2[2], r2[3]);
-      return;
-    }
-  }
-  uint32_t y1[4], y2[4];
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    y1[e] = f2bf(a[e] * c[e] - b[e] * sn[e]);
-    y2[e] = f2bf(b[e] * c[e] + a[e] * sn[e]);
-  }
-  const uint2 w1 = make_uint2(y1[0] | (y1[1] << 16), y1[2] | (y1[3] << 16));
-  const uint2 w2 = make_uint2(y2[0] | (y2[1] << 16), y2[2] | (y2[3] << 16));
-  if (is_q) {
-    bf16_t* dst = qout + ((size_t)row * nq + hd) * 128 + sub * 4;
+  uint2 w1, w2;
+  qkrope_head128<FP8, UNDIV>(a, row, hd, sub, pos, [&] { return page_table[(size_t)row_slot[row] * pt_stride + (pos >> 4)]; }, kpool,
+                             vpool, &w1, &w2);
+  if (hd < a.nq) {
+    bf16_t* dst = qout + ((size_t)row * a.nq + hd) * 128 + sub * 4;
     *(uint2*)dst = w1;
     *(uint2*)(dst + 64) = w2;
-  } else {   // 4 consecutive dims lie in one 8-element lane slot of the swizzled key block
-    *(uint2*)(blk + kswz_off(tok, sub * 4)) = w1;
-    *(uint2*)(blk + kswz_off(tok, 64 + sub * 4)) = w2;
   }
 }
 
-void launch_qkrope128(hipStream_t s, const float* qkv, int n_part, size_t part_stride, const bf16_t* gq,
-                      const bf16_t* gk, const float* rope_cs, const int32_t* row_pos, const int32_t* row_slot,
-                      const int32_t* page_table, bf16_t* qout, KvPool pool, const ModelDims& md, int M, const float* ssq) {
+void launch_qkrope128(hipStream_t s, const RopeArgs& a, const int32_t* row_pos, const int32_t* row_slot, const int32_t* page_table,
+                      bf16_t* qout, KvPool pool, const ModelDims& md, int M) {
   if (M <= 0) return;
   const dim3 grid(M, (md.nq + 2 * md.nkv + 15) / 16);
   auto go = [&](auto kernel) {
-    kernel<<<grid, 256, 0, s>>>(qkv, n_part, part_stride, gq, gk, rope_cs, row_pos, row_slot, page_table, qout,
-                                (bf16_t*)pool.k, (bf16_t*)pool.v, md.nq, md.nkv, md.eps, md.qk_norm,
-                                md.max_pages_per_traj, ssq, md.H / 16, (M + 15) / 16 * 16, md.H);
+    kernel<<<grid, 256, 0, s>>>(a, row_pos, row_slot, page_table, qout, (bf16_t*)pool.k, (bf16_t*)pool.v, md.max_pages_per_traj);
   };
-  if (md.kv_fp8) ssq ? go(qkrope128_kernel<true, true>) : go(qkrope128_kernel<true, false>);
-  else ssq ? go(qkrope128_kernel<false, true>) : go(qkrope128_kernel<false, false>);
+  if (md.kv_fp8) a.ssq ? go(qkrope128_kernel<true, true>) : go(qkrope128_kernel<true, false>);
+  else a.ssq ? go(qkrope128_kernel<false, true>) : go(qkrope128_kernel<false, false>);
 }
 
 template <typename TW, typename TA, typename TKV>

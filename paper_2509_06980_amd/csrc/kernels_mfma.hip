@@ -2,6 +2,7 @@
 // They implement the same decoder pieces as the generic kernels (policy forward of the paper's
 // Generate / Update steps, Section 2.3.2) for head_dim 128 and tile-aligned widths.
 #include "kernels.h"
+#include "qkrope.h"
 
 #include <algorithm>
 #include <atomic>
@@ -1499,12 +1500,16 @@ __device__ __forceinline__ void attn_merge_store(const float* __restrict__ pm,
   *l_out = L;
 }
 
-template <bool FP8>
+// ROPE (single-row items, one row of a trajectory): 0, or the kernel starts from the projection's partial sums (2: rows not yet divided
+// by their rms): sixteen lanes per head form the group's queries, and in the workgroup that reads the row's last page also its key and
+// value, which go to that page before that workgroup, the only one to use them, reads it.  Every part of a row forms the same
+// queries.  See attention_takes_rope.
+template <bool FP8, int ROPE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void attention_mfma_kernel(
-    const bf16_t* __restrict__ q, const char* __restrict__ kpool, const char* __restrict__ vpool,
+    const bf16_t* __restrict__ q, char* kpool, char* vpool,
     const AttnItem* __restrict__ items, const int32_t* __restrict__ rowlist,
     const int32_t* __restrict__ page_table, bf16_t* __restrict__ o, float* __restrict__ scratch,
-    int nq, int nkv, int gshift, int pt_stride, float scale2) {
+    int nq, int nkv, int gshift, int pt_stride, float scale2, RopeArgs rope) {
   // a column's 128 outputs are padded to 132 floats: with a stride of 128 the 16 lanes that hold
   // one token group's 16 columns would all store into the same 4 banks
   constexpr int AST = 132;
@@ -1529,11 +1534,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int32_t* pt = page_table + (size_t)it.slot * pt_stride;
 
   u32x4 qreg[4];
+  if constexpr (ROPE != 0) {
+    __shared__ __align__(16) bf16_t s_q[8][128];
+    const int grp = tid >> 4, sub = tid & 15, G = 1 << gshift, last = it.pos0 / RL_PAGE;
+    const int hd = grp < G ? (kvh << gshift) + grp : nq + (grp - G) * nkv + kvh;      // the group's queries, then its key and its value
+    if (grp < G || (grp < G + 2 && it.pg_hi > last)) {
+      uint2 w1, w2;
+      qkrope_head128<FP8, ROPE == 2>(rope, it.row0, hd, sub, it.pos0, [&] { return pt[last]; }, (bf16_t*)kpool, (bf16_t*)vpool, &w1, &w2);
+      if (grp < G) {
+        *(uint2*)&s_q[grp][sub * 4] = w1;
+        *(uint2*)&s_q[grp][64 + sub * 4] = w2;
+      }
+    }
+    __syncthreads();      // the key and the value are stored, too
 #pragma unroll
-  for (int c = 0; c < 4; c++) {
-    qreg[c] = (u32x4){0u, 0u, 0u, 0u};
-    if (colvalid)
-      qreg[c] = *(const u32x4*)(q + ((size_t)qrow * nq + ((kvh << gshift) + hq)) * 128 + c * 32 + g * 8);
+    for (int c = 0; c < 4; c++) {
+      qreg[c] = (u32x4){0u, 0u, 0u, 0u};
+      if (colvalid) qreg[c] = *(const u32x4*)&s_q[hq][c * 32 + g * 8];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      qreg[c] = (u32x4){0u, 0u, 0u, 0u};
+      if (colvalid)
+        qreg[c] = *(const u32x4*)(q + ((size_t)qrow * nq + ((kvh << gshift) + hq)) * 128 + c * 32 + g * 8);
+    }
   }
   f32x4 acc[8];
 #pragma unroll
@@ -1876,10 +1901,17 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
       make_uint4(wv[0], wv[1], wv[2], wv[3]);
 }
 
+// Norm, RoPE and the cache write inside the decode attention: a launch less and the queries' way through memory, 1.4 to 2.8 us a layer
+// where the keys and values of all rows take less time than that chain (16 heads over 8: 1 row 1.4 to 2.5 us, 16 rows over 3000 keys
+// 2.9, 96 over 1000 1.4).  Where they are more than 400 MB the memory is busy from the first workgroup on, the prologue's
+// dependent reads wait behind the pages of the others, and the kernel of its own is the better one: 48 rows over 3000 keys (590 MB) 0.2 us
+// a layer in favour of this, 128 over 1000 (524 MB) 0.2, 64 over 3000 (786 MB) 2.4 against it (8-bit cache, 393 MB: 0.6 for).
+// The prologue has lanes for ten heads: groups of up to eight queries, a key and a value.
+bool attention_takes_rope(double kv_bytes, const ModelDims& md) { return md.nq / md.nkv <= 8 && kv_bytes <= 400e6; }
 void launch_attention_mfma(hipStream_t s, const bf16_t* q, KvPool pool, const AttnItem* items,
                            int n_items, const AttnMerge* merges, int n_merges,
                            const int32_t* rowlist, const int32_t* page_table, bf16_t* o,
-                           float* scratch, const ModelDims& md, bool prefill) {
+                           float* scratch, const ModelDims& md, bool prefill, const RopeArgs* rope) {
   if (n_items <= 0) return;
   float scale2 = 1.4426950408889634f / sqrtf((float)md.d);
   int gshift = 0;
@@ -1894,12 +1926,12 @@ void launch_attention_mfma(hipStream_t s, const bf16_t* q, KvPool pool, const At
       attention_prefill_kernel<false><<<grid, 256, 0, s>>>(q, kp, vp, items, page_table, o, md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
     return;
   }
-  if (md.kv_fp8)
-    attention_mfma_kernel<true><<<grid, 256, 0, s>>>(q, kp, vp, items, rowlist, page_table, o, scratch,
-                                                     md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
-  else
-    attention_mfma_kernel<false><<<grid, 256, 0, s>>>(q, kp, vp, items, rowlist, page_table, o, scratch,
-                                                      md.nq, md.nkv, gshift, md.max_pages_per_traj, scale2);
+  auto go = [&](auto kernel) {
+    kernel<<<grid, 256, 0, s>>>(q, (char*)pool.k, (char*)pool.v, items, rowlist, page_table, o, scratch, md.nq, md.nkv, gshift,
+                                md.max_pages_per_traj, scale2, rope ? *rope : RopeArgs{});
+  };
+  if (md.kv_fp8) !rope ? go(attention_mfma_kernel<true, 0>) : rope->ssq ? go(attention_mfma_kernel<true, 2>) : go(attention_mfma_kernel<true, 1>);
+  else !rope ? go(attention_mfma_kernel<false, 0>) : rope->ssq ? go(attention_mfma_kernel<false, 2>) : go(attention_mfma_kernel<false, 1>);
   if (n_merges > 0)
     attention_merge_kernel<<<dim3(n_merges, md.nkv), 256, 0, s>>>(scratch, merges, o, md.nq, md.nkv,
                                                                   gshift);

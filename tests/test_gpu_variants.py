@@ -145,6 +145,47 @@ def test_prefill_attention_items_and_page_pairs(heads):
     assert np.abs(got[0] - got[1]).max() < 3e-2
 
 
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (8, 1), (16, 1)])
+def test_norm_rope_and_cache_write_inside_the_decode_attention(heads, kv8):
+    # positions first and last in their page and around it, rows in one part and in several (the last part writes the page), groups of
+    # 1 to 8 heads and of 16 (not taken); the oracle and the bound of the 8-bit parity tests for both caches
+    shape = SHAPES["small-d128"].replace(n_q_heads=heads[0], n_kv_heads=heads[1], hidden=256, intermediate=512, vocab=4096, n_layers=2)
+    blob = make_weight_blob(shape, seed=8, weight_std=0.03, gain_std=0.1)
+    lens = [1, 15, 16, 17, 31, 33, 64, 255, 256, 700]
+    kw = dict(max_context=720, max_trajectories=len(lens), kv_pool_pages=120)
+    g = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, **kw)
+    o = OracleEngine(blob, kv_cache_dtype="fp8_e4m3" if kv8 else None, **kw)
+    rng = np.random.default_rng(heads[0])
+    ids, toks = np.arange(len(lens)), rng.integers(0, shape.vocab, sum(lens))
+    for e in (g, o):
+        e.append_observation(ids, toks, lens)
+    seen = [toks[:1], toks[-700:]]
+    bound = 8.0 * max(float(np.sqrt(np.mean((forward_bf16_model(o.model, t) - forward_full(o.model, t)) ** 2))) for t in seen)
+    for rows in (ids, ids[-1:], ids):
+        forced = rng.integers(0, shape.vocab, len(rows))
+        assert np.abs(g.decode_step_forced(rows, 1.0, forced) - o.decode_step_forced(rows, 1.0, forced)).max() < bound
+    for i in ids:
+        assert np.abs(g.debug_logits(i) - o.debug_logits(i)).max() < bound
+    g.close()
+
+
+def test_decode_attention_of_many_keys_leaves_the_norm_and_rope_outside():
+    # 90 and 128 forks of 4000 tokens: 369 and 525 MB of keys and values, either side of the limit
+    shape = SHAPES["small-g1"]
+    blob = make_weight_blob(shape, seed=9, weight_std=0.03, gain_std=0.1)
+    rng = np.random.default_rng(9)
+    toks, forced = rng.integers(0, shape.vocab, 4000), rng.integers(0, shape.vocab, (2, 128))
+    got = []
+    for n in (90, 128):
+        e = rl.RolloutEngine(blob, max_context=4016, max_trajectories=128, kv_pool_pages=520)
+        e.append_observation([0], toks, [4000])
+        e.fork(0, list(range(1, 128)))
+        got.append([e.decode_step_forced(list(range(n)), 1.0, f[:n])[:90] for f in forced])
+        e.close()
+    assert np.abs(np.stack(got[0]) - np.stack(got[1])).max() < 3e-2          # two bf16 paths, the bound of the parity tests
+
+
 @pytest.mark.parametrize("change", [dict(), dict(hidden=260, intermediate=700, vocab=4100), dict(hidden=250, head_dim=62, vocab=4090),
                                     dict(head_dim=68), dict(head_dim=128, n_q_heads=2), dict(n_kv_heads=4, head_dim=6)])
 @pytest.mark.parametrize("lens", [[1], [16, 1], [65], [17, 64, 130], [2] * 17])
