@@ -1345,20 +1345,22 @@ void launch_lm_head_logprob(hipStream_t s, const bf16_t* A, const bf16_t* Wp, in
 // loads into one and drop the hint.
 // kpool / vpool are byte pointers; a (page, kv head) block is BLK bytes (4096: bf16, 2048: 8-bit
 // cache) that a wave reads as NLD 16-byte slots per lane (head_off = kv head * BLK + lane * 16).
-#define ATT_LOAD_PLAIN(KR, VR, PAGEID)                                        \
+#define ATT_LOAD_PLAIN(KR, VR, IDX, ORDER)                                     \
   {                                                                           \
-    const size_t base_ = (size_t)(PAGEID) * nkv * BLK + head_off;             \
+    const size_t base_ = (size_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, IDX) * (uint32_t)(nkv * BLK)); \
     _Pragma("unroll") for (int c = 0; c < NLD; c++) {                         \
-      KR[c] = *(const u32x4*)(kpool + base_ + c * 1024);                      \
-      VR[c] = *(const u32x4*)(vpool + base_ + c * 1024);                      \
+      KR[c] = *(const u32x4*)(khead + base_ + (lane16 + c * 1024));           \
+      VR[c] = *(const u32x4*)(vhead + base_ + (lane16 + c * 1024));           \
+      ORDER                                                                   \
     }                                                                         \
   }
-#define ATT_LOAD_STREAM(KR, VR, PAGEID)                                       \
+#define ATT_LOAD_STREAM(KR, VR, IDX, ORDER)                                    \
   {                                                                           \
-    const size_t base_ = (size_t)(PAGEID) * nkv * BLK + head_off;             \
+    const size_t base_ = (size_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, IDX) * (uint32_t)(nkv * BLK)); \
     _Pragma("unroll") for (int c = 0; c < NLD; c++) {                         \
-      KR[c] = __builtin_nontemporal_load((const u32x4*)(kpool + base_ + c * 1024)); \
-      VR[c] = __builtin_nontemporal_load((const u32x4*)(vpool + base_ + c * 1024)); \
+      KR[c] = __builtin_nontemporal_load((const u32x4*)(khead + base_ + (lane16 + c * 1024))); \
+      VR[c] = __builtin_nontemporal_load((const u32x4*)(vhead + base_ + (lane16 + c * 1024))); \
+      ORDER                                                                   \
     }                                                                         \
   }
 // Operand register i of a page buffer: the 16-byte slot itself (bf16 cache), or half a raw slot
@@ -1423,27 +1425,37 @@ __device__ __forceinline__ u32x4 att_operand(const u32x4 (&R)[N], int i) {
   __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          \
   __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);                          \
   __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-// The decode kernel's page loop (uses pt, pg0, pg1, pglast, head_off, kpool, vpool, nkv and the
+// The decode kernel's page loop (uses pt, pg0, pg1, pglast, lane, lane16, khead, vhead, nkv and the
 // buffers kA, vA, kB, vB of the enclosing kernel); LOAD is one of the two load macros.
+// The wave's page-table entries lie in one register, entry i of 64 in lane i (ATT_IDS).  Requested page by page, an entry's sign
+// extension stood right behind its load, and every second page waited for all that was in flight: 16 rows over 1000 keys (16 heads
+// over 8) 14.8 -> 11.6 us a launch, over 3000 with the 8-bit cache (32 over 8) 18.5 -> 16, 4 over 3000 13.4 -> 12; from 32 rows over 3000
+// on, where the memory is busy all the time, within 1 %.
+// Loads in the order written, ahead of the loop as in it: where the compiler had turned the first page's around, the wait for a page's
+// first key block, the longer one of both ways into the loop, was a wait for its last value block.
+#define ATT_ORDER __builtin_amdgcn_sched_barrier(0);
+#define ATT_IDS(PG)                                                           \
+  {                                                                           \
+    pgb = (PG);                                                               \
+    ids = pt[min(pgb + lane, pglast)];                                        \
+    asm volatile("" : "+v"(ids));   /* arrives here, not at every use */      \
+  }
 #define ATT_PAGE_LOOP(LOAD)                                                   \
   if (pg0 < pg1) {                                                            \
-    int id_cur = pt[pg0];                                                     \
-    int id_nxt = pt[min(pg0 + 1, pglast)];                                    \
-    LOAD(kA, vA, id_cur)                                                      \
+    int pgb, ids;                                                             \
+    ATT_IDS(pg0)                                                              \
+    LOAD(kA, vA, 0, ATT_ORDER)                                                           \
     for (int pg = pg0; pg < pg1; pg += 2) {                                   \
-      /* page pg is in A; request the table entry of pg+2 (first: the counter of outstanding \
-         loads is in order, and its consumer must not wait for the page behind it), then pg+1 -> B. \
-         The eight loads of a page are issued two at a time between the four score MFMAs of the \
-         page being consumed (ATT_SPREAD) rather than in one burst: +0.5-2 % bandwidth. */ \
-      int id_n2 = pt[min(pg + 2, pglast)];                                    \
+      if (pg - pgb > 64 - 3) ATT_IDS(pg)                                      \
       __builtin_amdgcn_sched_barrier(0);                                      \
-      LOAD(kB, vB, id_nxt)                                                    \
+      /* page pg is in A; pg+1 -> B.  The eight loads of a page are issued two at a time between the four score MFMAs of the \
+         page being consumed (ATT_SPREAD) rather than in one burst: +0.5-2 % bandwidth. */ \
+      LOAD(kB, vB, pg + 1 - pgb, )                                              \
       ATT_PAGE(kA, vA, pg)                                                \
       ATT_SPREAD                                                              \
       __builtin_amdgcn_sched_barrier(0);                                      \
-      /* page pg+1 is in B; request the table entry of pg+3, then pg+2 -> A */ \
-      id_nxt = pt[min(pg + 3, pglast)];                                       \
-      LOAD(kA, vA, id_n2)                                                     \
+      /* page pg+1 is in B; pg+2 -> A */                                      \
+      LOAD(kA, vA, pg + 2 - pgb, )                                              \
       ATT_PAGE(kB, vB, pg + 1)                                            \
       ATT_SPREAD                                                              \
       __builtin_amdgcn_sched_barrier(0);                                      \
@@ -1455,25 +1467,24 @@ __device__ __forceinline__ u32x4 att_operand(const u32x4 (&R)[N], int i) {
 // covers the memory latency.
 #define ATT_PAGE_LOOP3(LOAD)                                                  \
   if (pg0 < pg1) {                                                            \
-    int i0 = pt[pg0], i1 = pt[min(pg0 + 1, pglast)], i2 = pt[min(pg0 + 2, pglast)]; \
-    LOAD(kA, vA, i0)                                                          \
-    LOAD(kB, vB, i1)                                                          \
+    int pgb, ids;                                                             \
+    ATT_IDS(pg0)                                                              \
+    LOAD(kA, vA, 0, ATT_ORDER)                                                           \
+    LOAD(kB, vB, 1, ATT_ORDER)                                                           \
     for (int pg = pg0; pg < pg1; pg += 3) {                                   \
-      const int j0 = pt[min(pg + 3, pglast)], j1 = pt[min(pg + 4, pglast)];   \
-      const int j2 = pt[min(pg + 5, pglast)];                                 \
-      LOAD(kC, vC, i2)                                                        \
+      if (pg - pgb > 64 - 5) ATT_IDS(pg)                                      \
+      LOAD(kC, vC, pg + 2 - pgb, ATT_ORDER)                                              \
       __builtin_amdgcn_sched_barrier(0);                                      \
       ATT_PAGE(kA, vA, pg)                                                \
       __builtin_amdgcn_sched_barrier(0);                                      \
-      LOAD(kA, vA, j0)                                                        \
+      LOAD(kA, vA, pg + 3 - pgb, ATT_ORDER)                                              \
       __builtin_amdgcn_sched_barrier(0);                                      \
       ATT_PAGE(kB, vB, pg + 1)                                            \
       __builtin_amdgcn_sched_barrier(0);                                      \
-      LOAD(kB, vB, j1)                                                        \
+      LOAD(kB, vB, pg + 4 - pgb, ATT_ORDER)                                              \
       __builtin_amdgcn_sched_barrier(0);                                      \
       ATT_PAGE(kC, vC, pg + 2)                                            \
       __builtin_amdgcn_sched_barrier(0);                                      \
-      i2 = j2;                                                                \
     }                                                                         \
   }
 
@@ -1522,7 +1533,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int item_idx = blockIdx.x / nkv;
   const AttnItem it = items[item_idx];
   const int kvh = blockIdx.x - item_idx * nkv;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int g = lane >> 4, n = lane & 15, r = n >> gshift, hq = n & ((1 << gshift) - 1);
   const bool colvalid = r < it.nrows;
   // shared-prefix items: every page of the range lies before every member's position
@@ -1572,7 +1583,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   // written, ahead of the arithmetic.
   const int pglast = max(pg1 - 1, pg0);
   constexpr int NLD = FP8 ? 2 : 4, BLK = FP8 ? 2048 : 4096;
-  const size_t head_off = (size_t)kvh * BLK + lane * 16;
+  const char *const khead = kpool + (size_t)kvh * BLK, *const vhead = vpool + (size_t)kvh * BLK;
+  const uint32_t lane16 = lane * 16;
   u32x4 kA[NLD], vA[NLD], kB[NLD], vB[NLD];
   // a wave whose share of the pages starts behind the trajectory's shared leading pages streams
   if constexpr (FP8) {

@@ -186,6 +186,24 @@ def test_decode_attention_of_many_keys_leaves_the_norm_and_rope_outside():
     assert np.abs(np.stack(got[0]) - np.stack(got[1])).max() < 3e-2          # two bf16 paths, the bound of the parity tests
 
 
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("n", [3900, 3970, 8200])
+def test_decode_attention_waves_of_more_pages_than_lanes(n, kv8):
+    # 128 rows are not cut: 61, 63 and 129 pages a wave, whose table entries are read 64 at a time; the row alone is, and needs one read
+    shape = SHAPES["small-g1"]
+    blob = make_weight_blob(shape, seed=9, weight_std=0.03, gain_std=0.1)
+    rng = np.random.default_rng(n)
+    e = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, max_context=n + 16, max_trajectories=130, kv_pool_pages=n // 16 + 270)
+    e.append_observation([0], rng.integers(0, shape.vocab, n), [n])
+    e.fork(0, list(range(1, 130)))
+    for forced in rng.integers(0, shape.vocab, 2):
+        many = e.decode_step_forced(list(range(128)), 1.0, [forced] * 128)
+        alone = e.decode_step_forced([128], 1.0, [forced])
+        assert np.abs(many - alone).max() < 3e-2          # two bf16 paths, the bound of the parity tests
+    assert np.abs(e.debug_logits(5) - e.debug_logits(128)).max() < 3e-2
+    e.close()
+
+
 @pytest.mark.parametrize("change", [dict(), dict(hidden=260, intermediate=700, vocab=4100), dict(hidden=250, head_dim=62, vocab=4090),
                                     dict(head_dim=68), dict(head_dim=128, n_q_heads=2), dict(n_kv_heads=4, head_dim=6)])
 @pytest.mark.parametrize("lens", [[1], [16, 1], [65], [17, 64, 130], [2] * 17])
