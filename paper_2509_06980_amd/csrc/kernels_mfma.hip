@@ -1676,16 +1676,21 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
   // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
   // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
   constexpr float kLazy = 256.0f;
-  float p[16];
+  typedef __attribute__((__vector_size__(4))) __bf16 bf16x2;
+  union { bf16x2 pair[8]; bf16x8 P[2]; } t;
   auto vis = [&](int i) { return !MASKED || key0 + (i >> 2) * 8 + (i & 3) <= mypos; };
+  // the sum is that of the rounded terms, which the values are weighted with: eight products of pairs with ones, not fifteen additions
   auto terms = [&]() {
+    const bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
+    float s[2] = {0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-      p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], scale2, -m));
-      if (MASKED) p[i] = vis(i) ? p[i] : 0.f;
+    for (int i = 0; i < 16; i += 2) {
+      float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], scale2, -m)), p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i + 1], scale2, -m));
+      if (MASKED) { p0 = vis(i) ? p0 : 0.f; p1 = vis(i + 1) ? p1 : 0.f; }
+      t.pair[i >> 1] = (bf16x2){(__bf16)p0, (__bf16)p1};
+      s[i >> 3] = __builtin_amdgcn_fdot2_f32_bf16(t.pair[i >> 1], one, s[i >> 3], false);
     }
-    return (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) +
-           (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
+    return s[0] + s[1];
   };
   float ps = terms();
   if (__any(ps > kLazy)) {
@@ -1704,9 +1709,6 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
     ps = terms();
   }
   l += ps;
-  bf16x8 P[2];
-#pragma unroll
-  for (int i = 0; i < 16; i++) P[i >> 3][i & 7] = (__bf16)p[i];
 #pragma unroll
   for (int pp = 0; pp < 2; pp++)
 #pragma unroll
@@ -1723,7 +1725,7 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
         const uint2 lo = *(const uint2*)x, hi = *(const uint2*)(x + 512);
         v = (u32x4){lo.x, lo.y, hi.x, hi.y};
       }
-      acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), P[pp], acc[db], 0, 0, 0);
+      acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), t.P[pp], acc[db], 0, 0, 0);
     }
 }
 
