@@ -1428,9 +1428,9 @@ __device__ __forceinline__ u32x4 att_operand(const u32x4 (&R)[N], int i) {
 // The decode kernel's page loop (uses pt, pg0, pg1, pglast, lane, lane16, khead, vhead, nkv and the
 // buffers kA, vA, kB, vB of the enclosing kernel); LOAD is one of the two load macros.
 // The wave's page-table entries lie in one register, entry i of 64 in lane i (ATT_IDS).  Requested page by page, an entry's sign
-// extension stood right behind its load, and every second page waited for all that was in flight: 16 rows over 1000 keys (16 heads
-// over 8) 14.8 -> 11.6 us a launch, over 3000 with the 8-bit cache (32 over 8) 18.5 -> 16, 4 over 3000 13.4 -> 12; from 32 rows over 3000
-// on, where the memory is busy all the time, within 1 %.
+// extension stood right behind its load, and every second page waited for all that was in flight.  A decode step of 8 layers: 16 rows
+// over 1000 keys (16 heads over 8) 430 -> 403 us, 4 over 3000 402 -> 392, 8-bit cache (32 heads over 8) 32 over 3000 891 -> 867; from 32
+// rows over 3000 keys of the bf16 cache on, where the memory is busy all the time, within 1 %.
 // Loads in the order written, ahead of the loop as in it: where the compiler had turned the first page's around, the wait for a page's
 // first key block, the longer one of both ways into the loop, was a wait for its last value block.
 #define ATT_ORDER __builtin_amdgcn_sched_barrier(0);
@@ -1915,8 +1915,8 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
       make_uint4(wv[0], wv[1], wv[2], wv[3]);
 }
 
-// Norm, RoPE and the cache write inside the decode attention: a launch less and the queries' way through memory, 1.4 to 2.8 us a layer
-// where the keys and values of all rows take less time than that chain (16 heads over 8: 1 row 1.4 to 2.5 us, 16 rows over 3000 keys
+// Norm, RoPE and the cache write inside the decode attention: a launch less and the queries' way through memory, 1.4 to 2.9 us a layer
+// where the keys and values of all rows take less time than that chain (16 heads over 8: 1 row 1.6 to 2.8 us, 16 rows over 3000 keys
 // 2.9, 96 over 1000 1.4).  Where they are more than 400 MB the memory is busy from the first workgroup on, the prologue's
 // dependent reads wait behind the pages of the others, and the kernel of its own is the better one: 48 rows over 3000 keys (590 MB) 0.2 us
 // a layer in favour of this, 128 over 1000 (524 MB) 0.2, 64 over 3000 (786 MB) 2.4 against it (8-bit cache, 393 MB: 0.6 for).
