@@ -43,7 +43,7 @@ def trace_summary(path):
     acc = defaultdict(lambda: [0, 0.0])
     with open(path, newline="") as f:
         for r in csv.DictReader(f):
-            if "attention_mfma_kernel<false>" not in r["Kernel_Name"]:
+            if "attention_mfma_kernel<false," not in r["Kernel_Name"]:
                 continue
             g = int(r.get("Grid_Size_X") or r.get("Grid_Size"))
             a = acc[g]
@@ -176,7 +176,7 @@ def rollout_summary(trace_path, stats_path, bench_log):
           f"{r['avg_launch_us']} us per decode launch (HIP events around attention + merge, every 16th step), "
           f"{r['bytes_per_launch']} bytes per launch; measured streaming-read ceiling of the box "
           f"{b['measured_stream_read_GBs']} GB/s.\n")
-    print("attention_mfma_kernel<false> (the bf16-cache instance; decode launches: one workgroup per "
+    print("attention_mfma_kernel<false, ROPE> (the bf16-cache instance; decode launches: one workgroup per "
           "trajectory x kv head) by launch shape, from the kernel trace:\n")
     trace_summary(trace_path)
     print("\nThe decode average agrees with the HIP-event figure of bench.py (the profiler adds a little "
@@ -272,7 +272,7 @@ def main():
 
     kf, kw = calib(fetch), calib(write)
     grid = n_traj * n_kv * 256                      # decode launches: one workgroup per (trajectory, kv head)
-    name = "attention_mfma_kernel<false>"           # the bf16-cache instance of the decode kernel
+    name = "attention_mfma_kernel<false,"           # the bf16-cache instance of the decode kernel
     fa = fetch[name][grid]
     wa = write[name][grid]
     f_bytes = sum(fa) / len(fa) * 1024.0 * kf
