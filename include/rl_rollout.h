@@ -266,6 +266,13 @@ int rl_debug_pass_plan(const rl_model_config* cfg, int32_t rows, int32_t max_row
  * where the plan holds.  Errors: ARG.
  */
 int rl_debug_residual_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);
+/*
+ * Memory accesses of a product of many rows: C [rows, n] = A [rows, k] * W^T, of kernel 1 (256-row tiles) or 3 (128-row
+ * tiles), width, K-slices and epilogue as in rl_debug_pass_plan.  out: {stages of the ring in LDS, how many bytes the scalar
+ * offsets of the loads reach beyond the buffer of the rows, the same of the weights}.  Errors: ARG.
+ */
+int rl_debug_many_row_loads(int32_t rows, int32_t n, int32_t k, int32_t kernel, int32_t width, int32_t slices,
+                            int32_t epilogue, int64_t* out);
 
 /*
  * Kernel timing for benchmarks: when enabled, every `every`-th decode step brackets its

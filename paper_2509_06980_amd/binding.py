@@ -13,7 +13,7 @@ EXPORTED_SYMBOLS = [
     "rl_decode_step_forced", "rl_sample_from_logits", "rl_sample_device_logits", "rl_uniform_u32", "rl_timing_enable",
     "rl_timing_read", "rl_timing_read_steps", "rl_timing_read_decode_bytes", "rl_measure_stream_read",
     "rl_decode_step_with_appends", "rl_decode_step_forced_with_appends", "rl_grpo_objective", "rl_debug_pass_plan",
-    "rl_debug_residual_plan",
+    "rl_debug_residual_plan", "rl_debug_many_row_loads",
 ]
 
 
@@ -82,6 +82,7 @@ def load_library():
                                       C.POINTER(C.c_int64), C.POINTER(C.c_double)]
     lib.rl_debug_pass_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
     lib.rl_debug_residual_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
+    lib.rl_debug_many_row_loads.argtypes = [C.c_int32] * 7 + [C.POINTER(C.c_int64)]
     lib.rl_debug_logits.argtypes = [C.c_void_p, C.c_int32, _F32P]
     lib.rl_sample_from_logits.argtypes = [_F32P, C.c_int32, C.c_int32, C.c_float, _U32P, _I32P, _F32P]
     lib.rl_sample_device_logits.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_float, C.c_void_p,
@@ -120,14 +121,17 @@ def measure_stream_read(nbytes=1 << 31, iters=10):
     return out.value
 
 
+_GEMM_KERNELS = ("tile128", "tile256", "decode", "wide128")
+_GEMM_EPILOGUES = {0: "store", 2: "swiglu", 3: "logprob", 5: "qkv", 7: "add"}
+
+
 def debug_pass_plan(shape, rows, max_rows=8192):
     """{product: (kernel, width, K-slices, epilogue)} of a forward pass over `rows` rows on the MFMA path; `shape`: an
     object with the fields of the model configuration."""
     cfg = _ModelConfig(*[getattr(shape, n) for n, _ in _ModelConfig._fields_])
     out = (C.c_int32 * 24)()
     _check(load_library().rl_debug_pass_plan(C.byref(cfg), int(rows), max(int(rows), int(max_rows)), out))
-    kernels, epilogues = ("tile128", "tile256", "decode", "wide128"), {0: "store", 2: "swiglu", 3: "logprob", 5: "qkv", 7: "add"}
-    return {name: (kernels[out[4 * i]], out[4 * i + 1], out[4 * i + 2], epilogues[out[4 * i + 3]])
+    return {name: (_GEMM_KERNELS[out[4 * i]], out[4 * i + 1], out[4 * i + 2], _GEMM_EPILOGUES[out[4 * i + 3]])
             for i, name in enumerate(("qkv", "o", "gate_up", "down", "score_head", "logits_head"))}
 
 
@@ -138,6 +142,16 @@ def debug_residual_plan(shape, rows, max_rows=8192):
     out = (C.c_int32 * 4)()
     _check(load_library().rl_debug_residual_plan(C.byref(cfg), int(rows), max(int(rows), int(max_rows)), out))
     return {name: (out[2 * i], out[2 * i + 1]) for i, name in enumerate(("o", "down")) if out[2 * i]}
+
+
+def debug_many_row_loads(rows, n, k, plan):
+    """(stages of the ring in LDS, bytes that the loads' scalar offsets reach beyond the rows' buffer, the same of the weights')
+    of a product of many rows; plan: (kernel, width, K-slices, epilogue) as in debug_pass_plan, kernel "tile256" or "wide128"."""
+    kernel, width, slices, epilogue = plan
+    out = (C.c_int64 * 3)()
+    _check(load_library().rl_debug_many_row_loads(int(rows), int(n), int(k), _GEMM_KERNELS.index(kernel), int(width), int(slices),
+                                                  {v: k for k, v in _GEMM_EPILOGUES.items()}[epilogue], out))
+    return tuple(out)
 
 
 def sample_from_logits(logits, temperature, u32):

@@ -1850,6 +1850,16 @@ extern "C" int rl_debug_pass_plan(const rl_model_config* c, int32_t rows, int32_
   return RL_OK;
 }
 
+extern "C" int rl_debug_many_row_loads(int32_t rows, int32_t n, int32_t k, int32_t kernel, int32_t width, int32_t slices,
+                                       int32_t epilogue, int64_t* out) {
+  const bool t256 = kernel == GEMM_TILE256;
+  if (!out || rows <= 0 || n <= 0 || n % 32 != 0 || k <= 0 || k % 64 != 0 || (!t256 && kernel != GEMM_WIDE128) ||
+      (width != 4 && !(t256 && width == 5)) || slices < 1 || slices > kMaxSplits || (int64_t)n * k * 2 >= 0x7fff0000)
+    return fail(RL_E_ARG, "bad argument");
+  debug_many_row_loads(rows, n, k, t256 ? 4 : 2, width, slices, epilogue, out);
+  return RL_OK;
+}
+
 extern "C" int rl_timing_enable(rl_model* m, int32_t every) {
   if (!m || every < 0) return fail(RL_E_ARG, "bad argument");
   m->timing_every = every;

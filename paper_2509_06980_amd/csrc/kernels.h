@@ -129,6 +129,9 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, size_t part_rows);
 // are divided by their rms here.
 int launch_gemm_mfma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int epilogue,
                      const GemmPlan& plan, const float* ssq = nullptr, float eps = 0.f);
+// Host arithmetic of the 256- and 128-row tiles' launch (mb 4 or 2) of nbw 64-column groups: out = {stages of the ring, how many
+// bytes the loads' scalar offsets reach beyond the rows' buffer, the same of the weights'}.
+void debug_many_row_loads(int M, int N, int K, int mb, int nbw, int splits, int epilogue, int64_t* out);
 // O or down of at most kResidualRows rows with the residual add and the norm behind it: h [M, N] += A * W^T; out = bf16(h * g) in
 // A-tile layout, its rows not yet divided by their rms; ssq[N / 16][M rounded up to 16]: sums of squares of 16 columns.
 const int kResidualRows = 512;

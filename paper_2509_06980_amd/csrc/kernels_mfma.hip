@@ -536,6 +536,22 @@ __device__ __forceinline__ void load_to_lds(unsigned lds, int voff, u32x4 rsrc, 
                : "memory", "m0");
 }
 
+// Scalar offsets of a workgroup's 1 KB loads: inside the two buffers whatever is asked for.  The hardware compares a lane's
+// offset with the buffer's size less the scalar one, so only a lane's offset may lie behind the end.
+struct ManyRowLoads {
+  int c1, NB, strip0;        // end of the K-slice in chunks of 32 k, strips of the weights, first strip of the tile
+  unsigned tile1;            // of the second 128-row tile of the rows, 0 where there is none
+  __host__ __device__ int inside(int chunk) const { return chunk < c1 ? chunk : c1 - 1; }
+  __host__ __device__ unsigned rows(int chunk, int tile, int kb, int wave) const {
+    return (tile ? tile1 : 0u) + (unsigned)((2 * inside(chunk) + kb) * 4 + wave) * 1024u;
+  }
+  // strips past the end (N not a multiple of the tile): the last one again, results dropped
+  __host__ __device__ unsigned weights(int chunk, int j, int wave) const {
+    const int c = inside(chunk), s = strip0 + 2 * j + (wave >> 1), st = s < NB ? s : NB - 1;
+    return ((unsigned)(c >> 1) * NB + st) * 4096u + (c & 1) * 2048u + (wave & 1) * 1024u;
+  }
+};
+
 template <int EPI, int MB, int NBW, int R>
 __global__ __launch_bounds__(256, MB == 2 && R == 3 ? 2 : 1) void gemm_dma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Wp,
                                                        void* __restrict__ Cv, int M, int N, int K,
@@ -547,7 +563,7 @@ __global__ __launch_bounds__(256, MB == 2 && R == 3 ? 2 : 1) void gemm_dma_kerne
   constexpr int PW = MB + NBW;                // 1 KB pieces per wave and chunk
   constexpr int BUF = (NA + 4 * NBW) * 1024;  // bytes of a stage: the row pieces, then [strip][kb]
   constexpr int F = PW / 2;                   // MB = 4: pieces of a chunk that are asked for half a chunk ahead of the others
-  constexpr int kFar = 0x7fff0000;            // behind every buffer's end: zeros, no memory traffic
+  constexpr int kFar = 0x7fff0000;            // a lane's offset behind every buffer's end: zeros, no memory traffic
   extern __shared__ u32x4 smem[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
@@ -559,24 +575,20 @@ __global__ __launch_bounds__(256, MB == 2 && R == 3 ? 2 : 1) void gemm_dma_kerne
   const int mt0 = blk0 >> 2, mts = min((r32 + 3) / 4 - mt0, MB == 4 ? 2 : 1);      // its 128-row tiles of A
   const u32x4 ra = buffer_rsrc(A + (size_t)mt0 * K * 128, (unsigned)mts * (unsigned)K * 256u);
   const u32x4 rb = buffer_rsrc(Wp, (unsigned)N * (unsigned)K * 2u);
+  const ManyRowLoads at{c1, NB, strip0, mts > 1 ? (unsigned)K * 256u : 0u};
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
   const int voff = lane * 16;
   int avoff[2];                               // MB = 4: of this wave's row block in either 128-row tile
 #pragma unroll
   for (int t = 0; t < 2; t++) avoff[t] = blk0 + 4 * t + wave < r32 ? voff : kFar;
-  // piece j of this wave of chunk c into stage buf; far: 0, or kFar for chunks behind the slice (MB = 4: the last chunk again, never
-  // read, as the registers that the choice takes would spill)
+  // piece j of this wave of a chunk into stage buf; chunks behind the slice: the last one's offset, and far = kFar (MB = 4: the last
+  // chunk again, never read, as the registers that the choice takes would spill)
   auto dma = [&](int chunk, int j, int buf, int far) {
-    const int c = MB == 4 ? min(chunk, c1 - 1) : chunk;
     const unsigned dst = lds0 + (unsigned)buf * BUF + (unsigned)(j * 4 + wave) * 1024u;
-    if (j < MB) {
-      const int tile = j >> 1, kb = j & 1;
-      load_to_lds(dst, MB == 4 ? avoff[tile] : voff | (blk0 + wave < r32 ? far : kFar), ra,
-                  (unsigned)tile * (unsigned)K * 256u + (unsigned)((2 * c + kb) * 4 + wave) * 1024u);
-    } else {     // strips past the end (N not a multiple of the tile): the last one again, results dropped
-      const int st = min(strip0 + 2 * (j - MB) + (wave >> 1), NB - 1);
-      load_to_lds(dst, voff | far, rb, ((unsigned)(c >> 1) * NB + st) * 4096u + (c & 1) * 2048u + (wave & 1) * 1024u);
-    }
+    if (j < MB)
+      load_to_lds(dst, MB == 4 ? avoff[j >> 1] : voff | (blk0 + wave < r32 ? far : kFar), ra, at.rows(chunk, j >> 1, j & 1, wave));
+    else
+      load_to_lds(dst, voff | far, rb, at.weights(chunk, j - MB, wave));
   };
   auto behind = [&](int c) { return MB == 4 || c < c1 ? 0 : kFar; };
   f32x16 acc[MB][4], acc5[MB];
@@ -778,11 +790,42 @@ static void set_lds_limit(std::atomic<uint64_t>& done, const void* kernel, int b
   done.fetch_or(bit, std::memory_order_release);
 }
 
+// Stages of the ring, and the grid of a launch.
+static int dma_stages(int mb, int epilogue, const dim3& grid, int chunks_per_split) {
+  if (mb == 4) return 4;
+  return epilogue != EPI_QKV && epilogue != EPI_QKV8 && grid.x * grid.y * grid.z <= 256 && chunks_per_split >= 48 ? 4 : 3;
+}
+static dim3 dma_grid(int mb, int nbw, int M, int N, int splits) {
+  return dim3((N / 32 + 2 * nbw - 1) / (2 * nbw), (M + 64 * mb - 1) / (64 * mb), splits);
+}
+
+void debug_many_row_loads(int M, int N, int K, int mb, int nbw, int splits, int epilogue, int64_t* out) {
+  const int cps = (K / 32 + splits - 1) / splits, tiles128 = (M + 127) / 128;
+  const dim3 grid = dma_grid(mb, nbw, M, N, splits);
+  const int stages = dma_stages(mb, epilogue, grid, cps);
+  int64_t far_rows = 0, far_weights = 0;
+  for (int z = 0; z < splits; z++)
+    for (unsigned y = 0; y < grid.y; y++)
+      for (unsigned x = 0; x < grid.x; x++) {
+        const int mts = std::min(tiles128 - (int)y * mb / 2, mb / 2), c1 = std::min((z + 1) * cps, K / 32);
+        const ManyRowLoads at{c1, N / 32, (int)x * 2 * nbw, mts > 1 ? (unsigned)K * 256u : 0u};
+        for (int c = z * cps; c < c1 + stages; c++)
+          for (int j = 0; j < mb + nbw; j++)
+            for (int wave = 0; wave < 4; wave++) {
+              if (j < mb) far_rows = std::max(far_rows, at.rows(c, j >> 1, j & 1, wave) + 1024 - (int64_t)mts * K * 256);
+              else far_weights = std::max(far_weights, at.weights(c, j - mb, wave) + 1024 - (int64_t)N * K * 2);
+            }
+      }
+  out[0] = stages;
+  out[1] = far_rows;
+  out[2] = far_weights;
+}
+
 template <int EPI, int MB, int NBW>
 static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C, int M, int N, int K, int splits,
                        const int32_t* tgt, float* zt, float scale_c, const QkvArgs& q) {
   const int cps = (K / 32 + splits - 1) / splits;
-  const dim3 grid((N / 32 + 2 * NBW - 1) / (2 * NBW), (M + 64 * MB - 1) / (64 * MB), splits);
+  const dim3 grid = dma_grid(MB, NBW, M, N, splits);
   static std::atomic<uint64_t> done[2];
   auto go = [&](auto kernel, int stages) {
     const int lds = stages * (4 * MB + 4 * NBW) * 1024;
@@ -793,7 +836,7 @@ static void launch_dma(hipStream_t s, const bf16_t* A, const bf16_t* Wp, void* C
     go(gemm_dma_kernel<EPI, 4, NBW, 4>, 4);
   } else {
     if constexpr (EPI != EPI_QKV && EPI != EPI_QKV8) {
-      if (grid.x * grid.y * grid.z <= 256 && cps >= 48) return go(gemm_dma_kernel<EPI, 2, 4, 4>, 4);
+      if (dma_stages(MB, EPI, grid, cps) == 4) return go(gemm_dma_kernel<EPI, 2, 4, 4>, 4);
     }
     go(gemm_dma_kernel<EPI, 2, 4, 3>, 3);
   }

@@ -182,3 +182,37 @@ def test_residual_products_tiles_and_bounds():
 def test_residual_products_of_more_than_128_rows_where_they_are_faster(shape, rows, inside):
     s = SHAPES["small-d128"].replace(**dict(zip(("hidden", "n_q_heads", "n_kv_heads", "intermediate"), shape)))
     assert set(rl.debug_residual_plan(s, rows)) == inside
+
+
+def test_many_row_loads_stay_inside_their_buffers():
+    # the scalar part of every load's offset, also of chunks behind a K-slice, strips behind the last and the second 128-row tile of
+    # 256 rows that is not there: at every plan's rows, widths that end inside a tile, slices of odd and unequal length
+    rng = random.Random(7)
+    cases = [(587, 2560, 9728, "down"), (8192 - 100, 2560, 9728, "down"), (129, 32, 64, "o"), (385, 1056, 2112, "o")]
+    cases += [(rng.randint(129, 1400), 32 * rng.randint(1, 40), 64 * rng.randint(1, 50), "o") for _ in range(60)]
+    for rows, n, k, name in cases:
+        for kernel, width in (("wide128", 4), ("tile256", 4), ("tile256", 5)):
+            for slices in (1, 2, 3, 5, 8):
+                if (slices - 1) * -(-(k // 32) // slices) < k // 32:          # no slice is empty
+                    for epilogue in ("store", "add", "swiglu"):
+                        stages, beyond_rows, beyond_weights = rl.debug_many_row_loads(rows, n, k, (kernel, width, slices, epilogue))
+                        assert stages in (3, 4) and (beyond_rows, beyond_weights) == (0, 0), (rows, n, k, kernel, width, slices)
+
+
+@pytest.mark.parametrize("rows,n,k,slices,epilogue,stages", [
+    (587, 2560, 9728, 5, "store", 4), (587, 2560, 4096, 1, "add", 4),      # 250 workgroups of 61 chunks, 50 of 128: one to a CU
+    (587, 2560, 9728, 8, "store", 3),                                      # 400 workgroups: two share one
+    (587, 2560, 7616, 5, "store", 4), (587, 2560, 7488, 5, "store", 3),    # 48 and 47 chunks
+    (300, 19456, 2560, 1, "swiglu", 4), (300, 6144, 2560, 1, "qkv", 3),    # the norm's epilogue has no room for a fourth
+])
+def test_stages_of_the_128_row_tiles(rows, n, k, slices, epilogue, stages):
+    assert rl.debug_many_row_loads(rows, n, k, ("wide128", 4, slices, epilogue))[0] == stages
+
+
+@pytest.mark.parametrize("bad", [(0, 32, 64, ("wide128", 4, 1, "store")), (200, 33, 64, ("wide128", 4, 1, "store")),
+                                 (200, 32, 96, ("wide128", 4, 1, "store")), (200, 32, 64, ("decode", 4, 1, "store")),
+                                 (200, 32, 64, ("wide128", 5, 1, "store")), (200, 32, 64, ("tile256", 4, 9, "store")),
+                                 (200, 262144, 4096, ("tile256", 4, 1, "store"))])
+def test_many_row_loads_refuse_what_the_kernel_does_not_take(bad):
+    with pytest.raises(rl.RolloutError):
+        rl.debug_many_row_loads(*bad)
