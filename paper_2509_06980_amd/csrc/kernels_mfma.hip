@@ -1679,9 +1679,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // there directly in the pool's operand order (no registers, no LDS stores), two pairs ahead in a ring of three:
 //   S^T[32 keys, 32 columns] = K . Q^T, 8 steps of 16 dims: lane (key, half) reads its 8 dims of a step as 16 bytes (8-bit cache:
 //   of two steps), 16 keys of a page being 256 contiguous bytes;
-//   O^T[32 dims, 32 columns] += V^T . P^T per page and block of 32 dims: lane l of the scores holds, for column l % 32, keys
-//   8 j + 4 (l / 32) + 0 .. 3 (j = 0 .. 3), so operand slot 4 x + e of a page is key 8 x + 4 (l / 32) + e on both sides, and the values
-//   are two 8-byte reads 512 bytes apart, 64 lanes covering 512 contiguous bytes.
+//   O^T[32 dims, 32 columns] += V^T . P^T in two steps of 16 keys, per block of 32 dims: lane l of the scores holds, for column
+//   l % 32, keys 8 j + 4 (l / 32) + 0 .. 3 (j = 0, 1: first page, 2, 3: second).  Step x takes j = x and j = 2 + x, so a lane's eight
+//   slots are four keys of either page on both sides, and the values are two 8-byte reads a page apart, 64 lanes covering 512
+//   contiguous bytes.  Key group 2 x + l / 32, these eight keys, has its own fp32 sum of the terms before they are rounded.
 // Nothing is moved between registers to put an operand together.  One barrier per pair: behind it the pair is complete for
 // every wave and the stage of the pair before is free for the pair after the next.
 // What bounds it: a wave's matrix and vector work take turns (32 keys x 32 columns: 512 cycles of MFMA, 60 vector instructions
@@ -1695,7 +1696,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // behind every row of the item); the pool is cleared at load, so such blocks hold finite values.
 template <bool FP8, bool MASKED>
 __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int key0, const u32x4 (&q)[8], f32x16 (&acc)[4],
-                                             float& m, float& l, int mypos, float scale2) {
+                                             float& m, float (&l)[2], int mypos, float scale2, int lane) {
   f32x16 S;
 #pragma unroll
   for (int i = 0; i < 16; i++) S[i] = 0.f;
@@ -1704,72 +1705,92 @@ __device__ __forceinline__ void prefill_pair(const char* kb, const char* vb, int
   };
   if constexpr (FP8) {
 #pragma unroll
-    for (int x = 0; x < 4; x++) {      // a slot holds the lane's dims of steps ks and ks + 2
-      const u32x4 raw[1] = {*(const u32x4*)(kb + (x >> 1) * 1024 + (x & 1) * 512)};
-      score(att_operand<true>(raw, 0), 4 * (x >> 1) + (x & 1));
-      score(att_operand<true>(raw, 1), 4 * (x >> 1) + (x & 1) + 2);
+    for (int x = 0; x < 2; x++) {      // a slot holds the lane's dims of steps ks and ks + 2; steps in ascending order
+      const u32x4 raw[2] = {*(const u32x4*)(kb + x * 1024), *(const u32x4*)(kb + x * 1024 + 512)};
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++) {
+        const u32x4 one[1] = {raw[ks & 1]};
+        score(att_operand<true>(one, ks >> 1), 4 * x + ks);
+      }
     }
   } else {
 #pragma unroll
     for (int ks = 0; ks < 8; ks++) score(*(const u32x4*)(kb + ks * 512), ks);
   }
   // m (in scaled units: score * scale2, scale2 > 0) is the reference point of the exponents, not
-  // necessarily the running maximum: it only moves, to the column's maximum so far, when the sixteen terms
-  // of some lane of the wave sum to more than kLazy = 2^8.  The ratio acc / l does not depend on m, and the common
-  // case needs neither a maximum nor a rescaling: the terms are formed first, and their sum, which
-  // is needed anyway, shows whether one of them was that large (or infinite: they are formed again).
+  // necessarily the running maximum: it only moves, to the column's maximum so far, when the eight terms of a key group
+  // in some column of the 16 around it sum to more than kLazy = 2^8.  The ratio acc / l does not depend on m, and the common
+  // case needs neither a maximum nor a rescaling: the terms are formed first, and their sums, which
+  // are needed anyway, show whether one of them was that large (or infinite: they are formed again).
   constexpr float kLazy = 256.0f;
   typedef __attribute__((__vector_size__(4))) __bf16 bf16x2;
   union { bf16x2 pair[8]; bf16x8 P[2]; } t;
+  float ps[2];
   auto vis = [&](int i) { return !MASKED || key0 + (i >> 2) * 8 + (i & 3) <= mypos; };
-  // the sum is that of the rounded terms, which the values are weighted with: eight products of pairs with ones, not fifteen additions
   auto terms = [&]() {
-    const bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
-    float s[2] = {0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 16; i += 2) {
-      float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], scale2, -m)), p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i + 1], scale2, -m));
-      if (MASKED) { p0 = vis(i) ? p0 : 0.f; p1 = vis(i + 1) ? p1 : 0.f; }
-      t.pair[i >> 1] = (bf16x2){(__bf16)p0, (__bf16)p1};
-      s[i >> 3] = __builtin_amdgcn_fdot2_f32_bf16(t.pair[i >> 1], one, s[i >> 3], false);
+    for (int x = 0; x < 2; x++) {
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const int i = (e >> 2) * 8 + 4 * x + (e & 3);
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[i], scale2, -m));
+        if (MASKED) p[e] = vis(i) ? p[e] : 0.f;
+      }
+      ps[x] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+#pragma unroll
+      for (int e = 0; e < 4; e++) t.pair[4 * x + e] = (bf16x2){(__bf16)p[2 * e], (__bf16)p[2 * e + 1]};
     }
-    return s[0] + s[1];
   };
-  float ps = terms();
-  if (__any(ps > kLazy)) {
+  terms();
+  if (const uint64_t hit = __ballot(ps[0] > kLazy || ps[1] > kLazy)) {
+    const bool moves = hit & ((lane & 16) ? 0xffff0000ffff0000ull : 0x0000ffff0000ffffull);
     float mx = ATT_NEG;
 #pragma unroll
     for (int i = 0; i < 16; i++) mx = fmaxf(mx, vis(i) ? S[i] : ATT_NEG);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx * scale2);
+    const float mn = moves ? fmaxf(m, mx * scale2) : m;
     const float alpha = exp2f(m - mn);
-    l *= alpha;
+    l[0] *= alpha;
+    l[1] *= alpha;
 #pragma unroll
     for (int j = 0; j < 4; j++)
 #pragma unroll
       for (int i = 0; i < 16; i++) acc[j][i] *= alpha;
     m = mn;
-    ps = terms();
+    terms();
   }
-  l += ps;
-#pragma unroll
-  for (int pp = 0; pp < 2; pp++)
-#pragma unroll
-    for (int db = 0; db < 4; db++) {
-      u32x4 v;
-      if constexpr (FP8) {
-        const char* x = vb + pp * 2048 + (db >> 1) * 1024 + (db & 1) * 8;
-        uint32_t a, b, c, d;
-        e4m3x4_to_bf16(*(const uint32_t*)x, &a, &b);
-        e4m3x4_to_bf16(*(const uint32_t*)(x + 512), &c, &d);
-        v = (u32x4){a, b, c, d};
-      } else {
-        const char* x = vb + pp * 4096 + db * 1024;
-        const uint2 lo = *(const uint2*)x, hi = *(const uint2*)(x + 512);
-        v = (u32x4){lo.x, lo.y, hi.x, hi.y};
-      }
-      acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), t.P[pp], acc[db], 0, 0, 0);
+  l[0] += ps[0];
+  l[1] += ps[1];
+  auto value = [&](int x, int db) {
+    if constexpr (FP8) {
+      const char* at = vb + x * 512 + (db >> 1) * 1024 + (db & 1) * 8;
+      uint32_t a, b, c, d;
+      e4m3x4_to_bf16(*(const uint32_t*)at, &a, &b);
+      e4m3x4_to_bf16(*(const uint32_t*)(at + 2048), &c, &d);
+      return (u32x4){a, b, c, d};
+    } else {
+      const char* at = vb + x * 512 + db * 1024;
+      const uint2 lo = *(const uint2*)at, hi = *(const uint2*)(at + 4096);
+      asm volatile("" ::: "memory");      // joined with another read's, the halves would have to be moved (24 moves)
+      return (u32x4){lo.x, lo.y, hi.x, hi.y};
     }
+  };
+  auto add = [&](const u32x4& v, int x, int db) {
+    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), t.P[x], acc[db], 0, 0, 0);
+  };
+  u32x4 v[2][4];
+#pragma unroll
+  for (int db = 0; db < 4; db++) v[0][db] = value(0, db);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int db = 0; db < 4; db++) {
+    v[1][db] = value(1, db);
+    add(v[0][db], 0, db);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int db = 0; db < 4; db++) add(v[1][db], 1, db);
 }
 
 template <bool FP8>
@@ -1826,7 +1847,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   for (int j = 0; j < 4; j++)
 #pragma unroll
     for (int i = 0; i < 16; i++) acc[j][i] = 0.f;
-  float m = ATT_NEG, l = 0.f;
+  float m = ATT_NEG, l[2] = {0.f, 0.f};
   load(0, block(0), block(1));
   load(1, block(2), block(3));
   size_t n0 = block(4), n1 = block(5);
@@ -1845,20 +1866,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   const int nfull = full_pages >> 1;
   for (int s = 0; s < nfull; s++) {
     advance(s);
-    prefill_pair<FP8, false>(kl + buf * STAGE, vl + buf * STAGE, 0, qr, acc, m, l, mypos, scale2);
+    prefill_pair<FP8, false>(kl + buf * STAGE, vl + buf * STAGE, 0, qr, acc, m, l, mypos, scale2, lane);
     buf = buf == 2 ? 0 : buf + 1;
   }
   for (int s = nfull; s < nst; s++) {
     advance(s);
     if (2 * s < pg1)
-      prefill_pair<FP8, true>(kl + buf * STAGE, vl + buf * STAGE, 2 * s * RL_PAGE + 4 * half, qr, acc, m, l, mypos, scale2);
+      prefill_pair<FP8, true>(kl + buf * STAGE, vl + buf * STAGE, 2 * s * RL_PAGE + 4 * half, qr, acc, m, l, mypos, scale2, lane);
     buf = buf == 2 ? 0 : buf + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  l += __shfl_xor(l, 32, 64);
+  const float sum = (l[0] + __shfl_xor(l[0], 32, 64)) + (l[1] + __shfl_xor(l[1], 32, 64));
   if (r >= it.nrows) return;
   // acc[db][i] is O[row r][head][d = 32 db + (i / 4) * 8 + 4 half + i % 4]: four consecutive dims = one 8-byte store
-  const float inv = 1.0f / l;
+  const float inv = 1.0f / sum;
 #pragma unroll
   for (int db = 0; db < 4; db++)
 #pragma unroll

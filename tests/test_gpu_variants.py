@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
+from crafted import ManySmallWeights
 from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from oracle import OracleEngine
 from oracle.bf16_error_model import forward_bf16_model
@@ -143,6 +144,22 @@ def test_prefill_attention_items_and_page_pairs(heads):
         got.append(np.stack([e.debug_logits(i) for i in range(10)]))
         e.close()
     assert np.abs(got[0] - got[1]).max() < 3e-2
+
+
+@pytest.mark.parametrize("heads", [(2, 2), (2, 1)])
+def test_softmax_denominator_is_the_sum_of_unrounded_weights(heads):
+    # up to 600 weights that bf16 would round down by 0.375 % each, in decode rows and in appended rows.  With a rounded
+    # denominator the log-probs are 0.0015 to 0.0079 too high; the roundings behind it average to less than a tenth of that.
+    m = ManySmallWeights(heads, 600)
+    e = rl.RolloutEngine(m.blob, max_context=640, max_trajectories=1, kv_pool_pages=40)
+    e.append_observation([0], [1, 0], [2])
+    exact = m.logprobs(601)
+    off = (m.logprobs(601, m.rounded) - exact)[100:].mean()
+    decoded = np.concatenate([e.decode_step_forced([0], 1.0, [0]) for _ in range(600)])
+    appended = e.recompute_logprobs([0], 1.0)[2:]
+    for got in (decoded, appended):
+        assert abs((got - exact)[100:].mean()) < 0.1 * off
+    e.close()
 
 
 @pytest.mark.parametrize("kv8", [False, True])
