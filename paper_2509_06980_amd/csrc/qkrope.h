@@ -48,9 +48,11 @@ __device__ __forceinline__ void qkrope_head128(const RopeArgs& a, int row, int h
 #pragma unroll
     for (int e = 0; e < 4; e++) { u[e] *= inv; w[e] *= inv; }
   }
+  // fused multiply-adds as written, here and in the rotation: left to the compiler, which of two products it rounds differs from kernel to
+  // kernel, and with it a key's last bit
   float ss = 0.f;
 #pragma unroll
-  for (int e = 0; e < 4; e++) ss += u[e] * u[e] + w[e] * w[e];
+  for (int e = 0; e < 4; e++) ss += __builtin_fmaf(u[e], u[e], w[e] * w[e]);
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 16);
   const int tok = pos & (RL_PAGE - 1);
@@ -87,8 +89,8 @@ __device__ __forceinline__ void qkrope_head128(const RopeArgs& a, int row, int h
   float r1[4], r2[4];
 #pragma unroll
   for (int e = 0; e < 4; e++) {
-    r1[e] = u[e] * c[e] - w[e] * sn[e];
-    r2[e] = w[e] * c[e] + u[e] * sn[e];
+    r1[e] = __builtin_fmaf(u[e], c[e], -(w[e] * sn[e]));
+    r2[e] = __builtin_fmaf(w[e], c[e], u[e] * sn[e]);
   }
   if constexpr (FP8) {
     if (!is_q) {   // 4 consecutive dims = 4 consecutive bytes of one lane slot

@@ -65,4 +65,62 @@ s ManySmallWeights:
         return z - np.log(np.exp(z) + s.vocab - 1)
 
 
-def
+def _fma(a, b, c):
+    return (np.float64(a) * np.float64(b) + np.float64(c)).astype(np.float32)
+
+
+def normed_keys(x, first):
+    """Rows of 128 fp32 numbers divided by their rms, in bf16, with the roundings of the kernels: sixteen lanes of four dims and their
+    partners 64 further on, whose squares are added with one fused multiply-add; first: the dim's own square is the fused one."""
+    lo, hi = x[:, :64], x[:, 64:]
+    t = (_fma(lo, lo, hi * hi) if first else _fma(hi, hi, lo * lo)).reshape(-1, 16, 4)
+    s = ((t[..., 0] + t[..., 1]) + t[..., 2]) + t[..., 3]
+    for o in (8, 4, 2, 1):
+        s = s + s[:, np.arange(16) ^ o]
+    return _bf16(x * (np.float32(1) / np.sqrt(_fma(s[:, :1], np.float32(1 / 128), np.float32(1e-6)))))
+
+
+class KeyBits:
+    """Pairs of tokens whose keys agree in the one dim that a query token looks at, to the bit, and no longer do if the sum of
+    squares of the first one's key is rounded the other way: one bf16 step of the key is then eight units of the score."""
+
+    def __init__(self):
+        s = self.shape = SHAPES["small-d128"].replace(n_layers=1, hidden=256, intermediate=64, vocab=4096, n_q_heads=2, n_kv_heads=2, rope_theta=1e30)
+        dims = np.r_[32:64, 96:128]                    # those that do not rotate
+        pairs = []                                     # (dim, its key, parts of the two rows)
+        for seed in range(12):
+            rng = np.random.default_rng(seed)
+            part = _bf16(rng.uniform(1, 2, (2, 20000, 64)) * rng.choice([-1, 1], (2, 20000, 64)))
+            x = np.zeros((20000, 128), np.float32)
+            x[:, dims] = 16 * part[0] + part[1] / 16   # exact in fp32, their squares are not
+            a, b = normed_keys(x, True), normed_keys(x, False)
+            for r, c in zip(*np.nonzero(a != b)):
+                same = np.nonzero((a[:, c] == a[r, c]) & (b[:, c] == a[r, c]))[0]
+                pairs.append((c, a[r, c], part[:, r], part[:, same[0]]))
+        self.pairs = len(pairs)
+        tokens = 1 + 3 * self.pairs                    # token 0: no key; then first, second and query of every pair
+        assert self.pairs >= 8 and 2 * tokens <= s.hidden
+        embed = np.zeros((s.vocab, s.hidden))
+        wq, wk = np.zeros((2, 128, s.hidden)), np.zeros((2, 128, s.hidden))
+        for t in range(tokens):                        # divided by their rms: 16 and 1 / 16
+            embed[t, 2 * t], embed[t, 2 * t + 1] = 1.0, 2.0 ** -8
+        for i, (c, key, first, second) in enumerate(pairs):
+            for t, part in ((1 + 3 * i, first), (2 + 3 * i, second)):
+                wk[:, dims, 2 * t], wk[:, dims, 2 * t + 1] = part
+            wq[:, c, 2 * (3 + 3 * i)] = np.sign(key)
+        rng = np.random.default_rng(1)
+        wv = np.zeros((2, 128, s.hidden))
+        wv[:, :, 0:2 * tokens:2] = rng.standard_normal((2, 128, tokens)) / 16
+        self.wv, self.wo = _bf16(wv), _bf16(rng.standard_normal((s.hidden, 256)) / 11)
+        self.head = _bf16(rng.standard_normal((s.vocab, s.hidden)) / 16)
+        self.blob = set_tensors(s, {"embed": embed, "l0.w_q": wq.reshape(-1, s.hidden), "l0.w_k": wk.reshape(-1, s.hidden), "l0.g_q": np.full(128, 1024.0),
+                                    "l0.w_v": self.wv.reshape(-1, s.hidden), "l0.w_o": self.wo, "lm_head": self.head})
+
+    def logits(self, i, share=0.5):
+        """Behind the tokens of pair i in float64; share: of the first one."""
+        t = 1 + 3 * i
+        values = 16.0 * (share * self.wv[:, :, 2 * t] + (1 - share) * self.wv[:, :, 2 * t + 2]).astype(np.float64)
+        h = self.wo.astype(np.float64) @ values.reshape(-1)
+        h[2 * t + 4] += 1.0
+        h[2 * t + 5] += 2.0 ** -8
+        return self.head.astype(np.float64) @ (h / np.sqrt(np.mean(h * h) + 1e-6))

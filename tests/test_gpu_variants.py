@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
-from crafted import ManySmallWeights
+from crafted import KeyBits, ManySmallWeights
 from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from oracle import OracleEngine
 from oracle.bf16_error_model import forward_bf16_model
@@ -185,6 +185,52 @@ def test_norm_rope_and_cache_write_inside_the_decode_attention(heads, kv8):
     for i in ids:
         assert np.abs(g.debug_logits(i) - o.debug_logits(i)).max() < bound
     g.close()
+
+
+@pytest.mark.parametrize("flags", [0, rl.FLAG_SHARED_PREFIX_ATTENTION])
+@pytest.mark.parametrize("appended", [True, False])
+def test_keys_are_rounded_as_written(flags, appended):
+    # keys formed in a pass of appended rows and in decode rows, there inside the attention and by the kernel of their own.  A
+    # sum of squares with the other square fused moves all weight to one of two tokens that share it: logits by 1 and more.
+    k = KeyBits()
+    e = rl.RolloutEngine(k.blob, flags=flags, max_context=64, max_trajectories=k.pairs, kv_pool_pages=k.pairs)
+    ids = np.arange(k.pairs)
+    toks = np.stack([[0, 0, 1 + 3 * i, 2 + 3 * i, 3 + 3 * i] for i in ids])
+    if appended:
+        e.append_observation(ids, toks.reshape(-1), [5] * k.pairs)
+    else:
+        e.append_observation(ids, toks[:, :2].reshape(-1), [2] * k.pairs)
+        for j in range(2, 5):
+            e.decode_step_forced(ids, 1.0, toks[:, j])
+    for i in ids:
+        want = k.logits(i)
+        assert min(np.abs(k.logits(i, share) - want).max() for share in (0.0, 1.0)) > 1.0
+        assert np.abs(e.debug_logits(i) - want).max() < 0.05            # bf16 roundings of logits of deviation 1
+    e.close()
+
+
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("heads", [(2, 2), (8, 2), (8, 1)])
+@pytest.mark.parametrize("change", [dict(hidden=256, intermediate=512), dict(hidden=2560, intermediate=640)])
+def test_norm_and_rope_inside_and_outside_the_attention_have_the_same_bits(change, heads, kv8):
+    # an engine that may read shared pages once leaves them to the kernel of their own; nothing else differs where no trajectory is
+    # forked.  Rows divided by their rms and rows still to be divided (the second layer's, behind a down product with the norm inside)
+    shape = SHAPES["small-d128"].replace(n_q_heads=heads[0], n_kv_heads=heads[1], vocab=4096, n_layers=2, **change)
+    blob = make_weight_blob(shape, seed=8, weight_std=0.03, gain_std=0.1)
+    lens = [1, 15, 16, 17, 31, 33, 64, 255, 256, 700]
+    kw = dict(max_context=720, max_trajectories=len(lens), kv_pool_pages=120)
+    kv = rl.FLAG_FP8_KV_CACHE if kv8 else 0
+    a, b = rl.RolloutEngine(blob, flags=kv, **kw), rl.RolloutEngine(blob, flags=kv | rl.FLAG_SHARED_PREFIX_ATTENTION, **kw)
+    rng = np.random.default_rng(heads[0])
+    ids, toks = np.arange(len(lens)), rng.integers(0, shape.vocab, sum(lens))
+    for e in (a, b):
+        e.append_observation(ids, toks, lens)
+    for _ in range(8):
+        forced = rng.integers(0, shape.vocab, len(lens))
+        assert np.array_equal(a.decode_step_forced(ids, 1.0, forced), b.decode_step_forced(ids, 1.0, forced))
+    for i in ids:
+        assert np.array_equal(a.debug_logits(i), b.debug_logits(i))
+    a.close(), b.close()
 
 
 def test_decode_attention_of_many_keys_leaves_the_norm_and_rope_outside():
