@@ -4,8 +4,25 @@ All models have one layer, an MLP of zeros and a RoPE base so large that the upp
 """
 import numpy as np
 
+from oracle.fp8 import e4m3_round
 from synthetic import SHAPES, make_weight_blob
 from synthetic.weights import BLOB_HEADER_BYTES, _to_bf16_bits, tensor_table
+
+KINDS = 30                       # key dims 32 .. 61 of a head; dim 62: the filler's key, dim 63: a query that meets no key
+FILLER = 0
+
+
+def KEY(j):                      # tokens with key j that look for nothing, that look for key j, and both
+    return 1 + j
+
+
+def QUERY(j):
+    return 1 + KINDS + j
+
+
+def SELF(j):
+    return 1 + 2 * KINDS + j
+
 
 def set_tensors(shape, tensors, like=None):
     """Blob of a bf16 model with the named tensors set; the others as in `like`, or gains of one and zeros."""
@@ -25,7 +42,50 @@ def _bf16(a):
     return (_to_bf16_bits(np.ascontiguousarray(a, np.float32).reshape(-1)).astype(np.uint32) << 16).view(np.float32).reshape(np.shape(a))
 
 
-s ManySmallWeights:
+class Peaked:
+    """Tokens are one-hot, so a token's query and key are single dims of 128^0.5: a query meets its own kind of key with a score of
+    11.3 and e^11.3 = 82 000 times the weight of any other.  Values are random per kind and kv head."""
+
+    def __init__(self, heads, kv8=False, seed=1):
+        s = self.shape = SHAPES["small-d128"].replace(n_layers=1, hidden=256, intermediate=64, vocab=4096, n_q_heads=heads[0], n_kv_heads=heads[1],
+                                                      rope_theta=1e30)
+        rng = np.random.default_rng(seed)
+        tokens = 1 + 3 * KINDS
+        embed = np.zeros((s.vocab, s.hidden))
+        embed[np.arange(tokens), np.arange(tokens)] = 1.0
+        wq, wk = np.zeros((s.n_q_heads, 128, s.hidden)), np.zeros((s.n_kv_heads, 128, s.hidden))
+        wq[:, 63, FILLER] = wk[:, 62, FILLER] = 1.0
+        for j in range(KINDS):
+            wq[:, 63, KEY(j)] = wq[:, 32 + j, QUERY(j)] = wq[:, 32 + j, SELF(j)] = 1.0
+            wk[:, 32 + j, KEY(j)] = wk[:, 62, QUERY(j)] = wk[:, 32 + j, SELF(j)] = 1.0
+        wv = _bf16(np.where(np.arange(s.hidden) < tokens, rng.standard_normal((s.n_kv_heads, 128, s.hidden)) / 16, 0.0))
+        self.values, self.score = 16.0 * wv.astype(np.float64), 128 ** 0.5       # a one-hot row divided by its rms is 16
+        if kv8:
+            self.values, self.score = e4m3_round(self.values), float(e4m3_round(self.score))
+        self.wo = _bf16(rng.standard_normal((s.hidden, s.n_q_heads * 128)) * (2.0 / (s.n_q_heads * 128)) ** 0.5)
+        self.head = _bf16(rng.standard_normal((s.vocab, s.hidden)) / 16)
+        self.key_of = np.full(tokens, 62)
+        self.looks_for = np.full(tokens, 63)
+        for j in range(KINDS):
+            self.key_of[[KEY(j), SELF(j)]] = self.looks_for[[QUERY(j), SELF(j)]] = 32 + j
+        self.blob = set_tensors(s, {"embed": embed, "l0.w_q": wq.reshape(-1, s.hidden), "l0.w_k": wk.reshape(-1, s.hidden),
+                                    "l0.w_v": wv.reshape(-1, s.hidden), "l0.w_o": self.wo, "lm_head": self.head})
+
+    def logits(self, tokens):
+        """Of the last of `tokens`, in float64 from the closed form."""
+        s, tokens = self.shape, np.asarray(tokens)
+        w = np.where(self.key_of[tokens] == self.looks_for[tokens[-1]], np.exp(self.score), 1.0)
+        values = self.values[:, :, tokens] @ (w / w.sum())
+        h = self.wo.astype(np.float64) @ np.repeat(values, s.n_q_heads // s.n_kv_heads, 0).reshape(-1)
+        h[tokens[-1]] += 1.0
+        return self.head.astype(np.float64) @ (h / np.sqrt(np.mean(h * h) + 1e-6))
+
+    def logprobs(self, tokens):
+        z = self.logits(tokens)
+        return z - z.max() - np.log(np.exp(z - z.max()).sum())
+
+
+class ManySmallWeights:
     """One token of large weight, then any number whose softmax weight of an eighth lies just below half way to the next bf16 number:
     rounded, every one of them is too small by 0.375 %.  All others' values are zero, so that the output is the first
     one's value divided by the denominator.  Token 0: the many, token 1: the first."""

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
-from crafted import KeyBits, ManySmallWeights
+from crafted import FILLER, KEY, KINDS, QUERY, SELF, KeyBits, ManySmallWeights, Peaked
 from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from oracle import OracleEngine
 from oracle.bf16_error_model import forward_bf16_model
@@ -187,6 +187,36 @@ def test_norm_rope_and_cache_write_inside_the_decode_attention(heads, kv8):
     g.close()
 
 
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (8, 2), (8, 1), (16, 1)])
+def test_decode_rows_meet_their_own_key(heads, kv8):
+    # every row looks for its own key and no earlier one has it: a part that reads its last page before the key and the value are there
+    # moves the log-probs by 1 and more and the logits by 2 and more.  Rows in one part and in several, first and last in a page.
+    # Bound: bf16 roundings of outputs and rows of logits of deviation 1, 2^-9 each, of 4096 logits the largest; measured 0.012.
+    p = Peaked(heads, kv8)
+    lens = [1, 15, 16, 17, 31, 33, 64, 255, 256, 700]
+    g = rl.RolloutEngine(p.blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, max_context=720, max_trajectories=len(lens), kv_pool_pages=120)
+    seen = [[FILLER] * (n - 1) + [SELF(i)] for i, n in enumerate(lens)]
+    g.append_observation(np.arange(len(lens)), np.concatenate(seen), lens)
+
+    def without(t):                                  # its own key like all others
+        return t[:-1] + [QUERY(t[-1] - SELF(0))]
+    for step, rows in enumerate((range(len(lens)), [len(lens) - 1], range(len(lens)))):
+        new = [SELF(j) for j in range(len(lens) + 6 * step, len(lens) + 6 * step + 6)]
+        want, apart = (np.stack([p.logprobs(t(seen[i]))[new] for i in rows]) for t in (lambda t: t, without))
+        pick = np.abs(want - apart).argmax(1)
+        at = np.arange(len(rows))
+        assert (np.abs(want - apart)[at, pick][[len(seen[i]) > 1 for i in rows]] > 0.5).all()
+        got = g.decode_step_forced(list(rows), 1.0, [new[k] for k in pick])
+        assert np.abs(got - want[at, pick]).max() < 0.05
+        for i, k in zip(rows, pick):
+            seen[i].append(new[k])
+    for i, t in enumerate(seen):
+        assert np.abs(g.debug_logits(i) - p.logits(t)).max() < 0.05
+        assert np.abs(p.logits(without(t)) - p.logits(t)).max() > 1.0
+    g.close()
+
+
 @pytest.mark.parametrize("flags", [0, rl.FLAG_SHARED_PREFIX_ATTENTION])
 @pytest.mark.parametrize("appended", [True, False])
 def test_keys_are_rounded_as_written(flags, appended):
@@ -250,20 +280,33 @@ def test_decode_attention_of_many_keys_leaves_the_norm_and_rope_outside():
 
 
 @pytest.mark.parametrize("kv8", [False, True])
-@pytest.mark.parametrize("n", [3900, 3970, 8200])
+@pytest.mark.parametrize("n", [3900, 3970, 4090, 4150, 4220, 4290, 8200])
 def test_decode_attention_waves_of_more_pages_than_lanes(n, kv8):
-    # 128 rows are not cut: 61, 63 and 129 pages a wave, whose table entries are read 64 at a time; the row alone is, and needs one read
-    shape = SHAPES["small-g1"]
-    blob = make_weight_blob(shape, seed=9, weight_std=0.03, gain_std=0.1)
+    # 128 rows are not cut: 61, 63, 64, 65, 66, 68 and 129 pages a wave, whose table entries are read 64 at a time.  Every row looks for
+    # one key, which lies in one page: first and last of a wave, and around the entries at which the next 64 are read.  A wave that
+    # takes another page for it moves the row's log-prob by 0.5 at least (all but the looked-for key weigh next to nothing).
+    # 2^-9 roundings of logits of deviation 1: 0.05, as above.
+    p = Peaked((2, 2), kv8)
+    pages = (n + 2 + 15) // 16                       # of the second step's rows
+    per = (pages + 3) // 4
+    places = [(w, k) for w in range(4) for k in sorted({0, 57, 58, 59, 60, 61, 62, 63, 64, 65, 119, 120, 122, 123, 126, per - 1}) if k < per and w * per + k < pages - 1]
     rng = np.random.default_rng(n)
-    e = rl.RolloutEngine(blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, max_context=n + 16, max_trajectories=130, kv_pool_pages=n // 16 + 270)
-    e.append_observation([0], rng.integers(0, shape.vocab, n), [n])
-    e.fork(0, list(range(1, 130)))
-    for forced in rng.integers(0, shape.vocab, 2):
-        many = e.decode_step_forced(list(range(128)), 1.0, [forced] * 128)
-        alone = e.decode_step_forced([128], 1.0, [forced])
-        assert np.abs(many - alone).max() < 3e-2          # two bf16 paths, the bound of the parity tests
-    assert np.abs(e.debug_logits(5) - e.debug_logits(128)).max() < 3e-2
+    toks = np.zeros(n, np.int64)
+    used = min(KINDS, len(places))
+    for j, x in enumerate(rng.permutation(len(places))[:used]):
+        w, k = places[x]
+        toks[(w * per + k) * 16 + rng.integers(0, 16)] = KEY(j)
+    e = rl.RolloutEngine(p.blob, flags=rl.FLAG_FP8_KV_CACHE if kv8 else 0, max_context=n + 16, max_trajectories=128, kv_pool_pages=n // 16 + 270)
+    e.append_observation([0], toks, [n])
+    e.fork(0, list(range(1, 128)))
+    kinds = np.arange(128) % used
+    e.decode_step_forced(np.arange(128), 1.0, [QUERY(j) for j in kinds])
+    want = np.stack([p.logprobs(np.append(toks, QUERY(j))) for j in range(used)])
+    missed = np.stack([p.logprobs(np.append(np.where(toks == KEY(j), FILLER, toks), QUERY(j))) for j in range(used)])
+    forced = np.abs(want - missed).argmax(1)
+    assert np.abs(want - missed).max(1).min() > 0.5
+    got = e.decode_step_forced(np.arange(128), 1.0, forced[kinds])
+    assert np.abs(got - want[kinds, forced[kinds]]).max() < 0.05
     e.close()
 
 
