@@ -267,6 +267,14 @@ int rl_debug_pass_plan(const rl_model_config* cfg, int32_t rows, int32_t max_row
  */
 int rl_debug_residual_plan(const rl_model_config* cfg, int32_t rows, int32_t max_rows, int32_t* out);
 /*
+ * How rl_decode_steps shares out its staging buffer: n rows a step, new_pages pages taken in the call, runtime
+ * configuration as given to rl_model_load, n_kv_heads 0 for models outside the MFMA path.  out: {page-table entries go
+ * over on their own, regions of one step each, steps per copy}; no region: the call is refused.  Errors: ARG.
+ */
+int rl_debug_staging_plan(int32_t n, int32_t n_kv_heads, int32_t max_trajectories, int32_t max_batch_rows,
+                          int32_t new_pages, int32_t* out);
+
+/*
  * Memory accesses of a product of many rows: C [rows, n] = A [rows, k] * W^T, of kernel 1 (256-row tiles) or 3 (128-row
  * tiles), width, K-slices and epilogue as in rl_debug_pass_plan.  out: {stages of the ring in LDS, how many bytes the scalar
  * offsets of the loads reach beyond the buffer of the rows, the same of the weights}.  Errors: ARG.

@@ -13,7 +13,7 @@ EXPORTED_SYMBOLS = [
     "rl_decode_step_forced", "rl_sample_from_logits", "rl_sample_device_logits", "rl_uniform_u32", "rl_timing_enable",
     "rl_timing_read", "rl_timing_read_steps", "rl_timing_read_decode_bytes", "rl_measure_stream_read",
     "rl_decode_step_with_appends", "rl_decode_step_forced_with_appends", "rl_grpo_objective", "rl_debug_pass_plan",
-    "rl_debug_residual_plan", "rl_debug_many_row_loads",
+    "rl_debug_residual_plan", "rl_debug_many_row_loads", "rl_debug_staging_plan",
 ]
 
 
@@ -82,6 +82,7 @@ def load_library():
                                       C.POINTER(C.c_int64), C.POINTER(C.c_double)]
     lib.rl_debug_pass_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
     lib.rl_debug_residual_plan.argtypes = [C.POINTER(_ModelConfig), C.c_int32, C.c_int32, _I32P]
+    lib.rl_debug_staging_plan.argtypes = [C.c_int32] * 5 + [_I32P]
     lib.rl_debug_many_row_loads.argtypes = [C.c_int32] * 7 + [C.POINTER(C.c_int64)]
     lib.rl_debug_logits.argtypes = [C.c_void_p, C.c_int32, _F32P]
     lib.rl_sample_from_logits.argtypes = [_F32P, C.c_int32, C.c_int32, C.c_float, _U32P, _I32P, _F32P]
@@ -152,6 +153,13 @@ def debug_many_row_loads(rows, n, k, plan):
     _check(load_library().rl_debug_many_row_loads(int(rows), int(n), int(k), _GEMM_KERNELS.index(kernel), int(width), int(slices),
                                                   {v: k for k, v in _GEMM_EPILOGUES.items()}[epilogue], out))
     return tuple(out)
+
+
+def debug_staging_plan(n, n_kv_heads, max_trajectories, max_batch_rows=0, new_pages=0):
+    """(page-table entries sent ahead, regions, steps per copy) of a call of several decode steps of n rows."""
+    out = (C.c_int32 * 3)()
+    _check(load_library().rl_debug_staging_plan(int(n), int(n_kv_heads), int(max_trajectories), int(max_batch_rows), int(new_pages), out))
+    return bool(out[0]), out[1], out[2]
 
 
 def sample_from_logits(logits, temperature, u32):

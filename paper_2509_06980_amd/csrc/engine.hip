@@ -567,6 +567,13 @@ void add_items(rl_model* m, Staging& st, int row0, int cnt, int slot, int pos0) 
 // then covers only its own remainder and a merge record joins the two.
 const int kAttnTargetWgs = 1024;
 const int kMinSharedPages = 8;
+// Sizes of buffers that a model of this many trajectories gets (n_kv_heads 0: not on the MFMA path, no scratch for parts).
+const int kDefaultBatchRows = 8192;
+int row_capacity(int max_batch_rows, int max_trajectories) {
+  return round_up(std::max(max_batch_rows ? max_batch_rows : kDefaultBatchRows, max_trajectories), 128);
+}
+int attention_slots(int n_kv_heads, int max_trajectories) { return n_kv_heads ? kAttnTargetWgs / n_kv_heads + 3 * max_trajectories + 64 : 0; }
+size_t staging_ints(int max_batch_rows, int max_trajectories) { return 32 * (size_t)row_capacity(max_batch_rows, max_trajectories) + 3 * 65536; }
 int add_decode_items(rl_model* m, Staging& st, const std::vector<Traj*>& ts) {   // returns scratch slots used
   int n = (int)st.pos.size();
   const int rpb = std::max(1, 16 / (m->md.nq / m->md.nkv));   // member rows per gather item
@@ -903,6 +910,23 @@ int decode_impl(rl_model* m, const int32_t* ids, int32_t n, float temperature, u
 // single steps would have taken them.
 const int kMaxStepsPerChunk = 1024, kStepsPerCopy = 8;
 
+// How the staging buffer is shared out over the steps of such a call.  flush: its page-table entries go over first, on their own and
+// waited for, instead of in front of the regions.  group: steps whose metadata goes over in one copy, packed into the front
+// of their regions (the first step's alone, with the entries, so that the GPU starts at once); regions: a multiple of it.
+// A small fp32 rollout (51 passes) takes 3.17 ms in groups of eight; with a copy and an event per step, a wait for the
+// entries and two copies at the end it took 3.50.
+struct StagingPlan { bool flush; int regions, group; };
+size_t staging_region_ints(int n, int attn_slots) { return 7 * (size_t)n + 8 * (size_t)(2 * n + attn_slots + 8); }
+StagingPlan plan_staging(size_t meta_ints, size_t region_ints, size_t entry_ints) {
+  auto fit = [&](size_t taken) { return taken >= meta_ints ? 0 : (int)std::min<size_t>((meta_ints - taken) / region_ints, 64); };
+  StagingPlan p{};
+  p.flush = entry_ints > meta_ints / 4 || fit(entry_ints) < 1;
+  p.regions = fit(p.flush ? 0 : entry_ints);
+  p.group = p.regions >= kStepsPerCopy ? kStepsPerCopy : 1;
+  p.regions -= p.regions % p.group;
+  return p;
+}
+
 int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, float temperature,
                  uint64_t seed, int32_t* ids_out, float* lp_out) {
   std::vector<Traj*> ts;
@@ -922,6 +946,10 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
   }
   if (need > m->n_free) return fail(RL_E_NOPAGES, "page pool exhausted");
   if (n == 0 || n_steps == 0) return RL_OK;
+  // one staging region per step, behind the page-table entries of the call; the host may run as many steps ahead as there are regions
+  const size_t region_ints = staging_region_ints(n, m->attn_slots);
+  const StagingPlan plan = plan_staging(m->meta_ints, region_ints, m->page_upd.size() + 3 * (size_t)need);
+  if (plan.regions < 1) return fail(RL_E_ARG, "internal: metadata staging too small");
   {
     std::vector<size_t> len0(n);
     for (int i = 0; i < n; i++) len0[i] = ts[i]->tokens.size();
@@ -934,21 +962,12 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
           t->pages.push_back(p);
         }
   }
-  // one staging region per step, behind the page-table entries of the call (more than a quarter of the buffer: on their own); the
-  // host may run as many steps ahead as there are regions
-  const size_t region_ints = 7 * (size_t)n + 8 * (size_t)(2 * n + m->attn_slots + 8);
-  if (m->page_upd.size() > m->meta_ints / 4) {
+  if (plan.flush) {
     rc = flush_page_updates(m);
     if (rc) return rc;
   }
-  const size_t n_upd = m->page_upd.size(), regions_at = (n_upd + 3) / 4 * 4;
-  int n_regions = (int)std::min<size_t>((m->meta_ints - regions_at) / region_ints, 64);
-  if (n_regions < 1) return fail(RL_E_ARG, "internal: metadata staging too small");
-  // The metadata of kStepsPerCopy steps goes over in one copy, packed into the front of their regions (the first step's with the
-  // page-table entries, so that the GPU starts at once).  A small fp32 rollout (51 passes) takes 3.17 ms; with a copy and an event
-  // per step, a wait for the entries and two copies at the end it took 3.50.
-  const int group = n_regions >= kStepsPerCopy ? kStepsPerCopy : 1;
-  n_regions -= n_regions % group;
+  const size_t n_upd = m->page_upd.size(), regions_at = n_upd;
+  const int group = plan.group, n_regions = plan.regions;
   while ((int)m->ev_region.size() < n_regions / group) {
     hipEvent_t e = nullptr;
     HIPCHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -990,11 +1009,11 @@ int decode_multi(rl_model* m, const int32_t* ids, int32_t n, int32_t n_steps, fl
           add_decode_items(m, st, ts);
           StepMeta sm{{}, (int)st.items.size(), (int)st.merges.size(), kvb};
           size_t used = 0;
-          if (6 * (size_t)n + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size() + 3 > region_ints)
+          if (6 * (size_t)n + 8 * st.items.size() + 8 * st.merges.size() + st.rowlist.size() > region_ints)
             return fail(RL_E_ARG, "internal: staging region too small");
           rc = stage_meta(m, st, &sm.dm, at + filled, &used);
           if (rc) return rc;
-          filled += (used + 3) / 4 * 4;            // 16-byte records stay aligned
+          filled += used;
           staged.push_back(sm);
         }
         const bool entries = !m->page_upd.empty();
@@ -1125,7 +1144,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   rl_model* m = new rl_model();
   m->cfg = c;
   m->rt = *rt;
-  if (m->rt.max_batch_rows == 0) m->rt.max_batch_rows = 8192;
+  if (m->rt.max_batch_rows == 0) m->rt.max_batch_rows = kDefaultBatchRows;
   m->bf16 = c.weight_dtype == 1;
   m->el = el;
   m->mfma = m->bf16 && mfma_shape_ok(c) && !(rt->flags & RL_FLAG_GENERIC_KERNELS);
@@ -1242,7 +1261,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   m->n_free = pool_pages;
   for (int s = rt->max_trajectories - 1; s >= 0; s--) m->free_slots.push_back(s);
   // ---- work buffers ----
-  m->Mcap = round_up(std::max(m->rt.max_batch_rows, rt->max_trajectories), 128);
+  m->Mcap = row_capacity(m->rt.max_batch_rows, rt->max_trajectories);
   m->Rl = round_up(std::max(rt->max_trajectories, 256), 128);
   size_t Mc = m->Mcap;
   size_t ael = m->bf16 ? 2 : 4;
@@ -1259,7 +1278,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
   if (!m->mfma) TRY(m->dalloc((void**)&m->gu, Mc * 2 * I * 4, true));
   TRY(m->dalloc((void**)&m->logits, (size_t)m->Rl * V * 4));
   if (m->mfma) {
-    m->attn_slots = kAttnTargetWgs / c.n_kv_heads + 3 * rt->max_trajectories + 64;
+    m->attn_slots = attention_slots(c.n_kv_heads, rt->max_trajectories);
     TRY(m->dalloc((void**)&m->attn_scratch,   // one slot per part of a cut decode row
                   (size_t)m->attn_slots * c.n_kv_heads * 16 * 130 * 4));
   }
@@ -1283,7 +1302,7 @@ extern "C" int rl_model_load(const rl_runtime_config* rt, const void* weights, s
     TRY(m->dalloc((void**)&m->d_gout, 3 * 8));
     HIPTRY(hipHostMalloc((void**)&m->h_gaux, (3 * Mc + 4 * T + 4) * 4));
   }
-  m->meta_ints = 32 * Mc + 3 * 65536;
+  m->meta_ints = staging_ints(m->rt.max_batch_rows, rt->max_trajectories);
   TRY(m->dalloc((void**)&m->d_meta, m->meta_ints * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_meta, m->meta_ints * 4));
   HIPTRY(hipHostMalloc((void**)&m->h_ids, (size_t)m->Rl * 4));
@@ -1847,6 +1866,15 @@ extern "C" int rl_debug_pass_plan(const rl_model_config* c, int32_t rows, int32_
   put(3, p.d, p.ed);
   put(4, plan_gemm(rows, md.V, md.H, EPI_LSE, 0), EPI_LSE);
   put(5, plan_gemm(rows, md.V, md.H, EPI_STORE, 0), EPI_STORE);
+  return RL_OK;
+}
+
+extern "C" int rl_debug_staging_plan(int32_t n, int32_t n_kv_heads, int32_t max_trajectories, int32_t max_batch_rows, int32_t new_pages,
+                                     int32_t* out) {
+  if (!out || n <= 0 || n > max_trajectories || n_kv_heads < 0 || max_batch_rows < 0 || new_pages < 0) return fail(RL_E_ARG, "bad argument");
+  const StagingPlan p = plan_staging(staging_ints(max_batch_rows, max_trajectories), staging_region_ints(n, attention_slots(n_kv_heads, max_trajectories)),
+                                     3 * (size_t)new_pages);
+  out[0] = p.flush; out[1] = p.regions; out[2] = p.group;
   return RL_OK;
 }
 

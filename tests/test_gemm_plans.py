@@ -216,3 +216,21 @@ def test_stages_of_the_128_row_tiles(rows, n, k, slices, epilogue, stages):
 def test_many_row_loads_refuse_what_the_kernel_does_not_take(bad):
     with pytest.raises(rl.RolloutError):
         rl.debug_many_row_loads(*bad)
+
+
+def test_staging_of_several_decode_steps():
+    # a call that fits without its page-table entries is taken
+    rng = random.Random(8)
+    for _ in range(4000):
+        T = int(round(2 ** rng.uniform(0, 15)))
+        n, nkv, rows = rng.randint(1, T), rng.choice([0, 1, 2, 4, 8, 16]), rng.choice([0, 128, 2048, 16384])
+        pages = int(n * rng.choice([0, 0.1, 1, 4, 64, 300]))
+        cap = -(-max(rows or 8192, T) // 128) * 128
+        room = 32 * cap + 3 * 65536
+        region = 7 * n + 8 * (2 * n + (1024 // nkv + 3 * T + 64 if nkv else 0) + 8)
+        ahead, regions, group = rl.debug_staging_plan(n, nkv, T, rows, pages)
+        bare = min(room // region, 64)
+        assert (regions >= 1) == (bare >= 1)
+        assert regions * region + (0 if ahead else 3 * pages) <= room
+        assert 1 <= group <= 8 and regions % group == 0
+    assert rl.debug_staging_plan(128, 8, 128, 0, 600) == (False, 56, 8)

@@ -489,3 +489,38 @@ def test_decode_steps_of_batches_that_leave_few_staging_regions(n, steps):
     got_ids, got_lps = b.decode_steps(ids, steps, 1.0, 5)
     assert np.array_equal(got_ids, np.stack([x[0] for x in single])) and np.array_equal(got_lps, np.stack([x[1] for x in single]))
     assert a.n_free_pages() == b.n_free_pages()
+
+
+def test_decode_steps_of_eight_thousand_trajectories():
+    # parts of cut rows need room in every region: one fits the staging buffer, and only without the call's page-table entries
+    shape = SHAPES["small-d128"].replace(n_layers=1, hidden=256, n_q_heads=8, n_kv_heads=8, intermediate=64, vocab=4096)
+    blob = make_weight_blob(shape, seed=5, weight_std=0.05)
+    n, steps = 8000, 64
+    assert rl.debug_staging_plan(n, 8, n, 0, 4 * n) == (True, 1, 1) and rl.debug_staging_plan(n, 8, n) == (False, 1, 1)
+    ids = np.arange(n, dtype=np.int32)
+    got = []
+    for several in (False, True):
+        e = rl.RolloutEngine(blob, max_context=80, max_trajectories=n, kv_pool_pages=5 * n)
+        e.append_observation(ids, np.arange(n) % 4096, np.ones(n, np.int32))
+        r = e.decode_steps(ids, steps, 1.0, 5) if several else [np.stack(x) for x in zip(*[e.decode_step(ids, 1.0, 5) for _ in range(steps)])]
+        got.append((*r, *e.decode_step(ids, 1.0, 6), e.n_free_pages()))
+        e.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*got))
+
+
+def test_decode_steps_that_do_not_fit_take_no_pages():
+    # more trajectories than the staging buffer has room for, at the end of their pages: refused, and a single step goes on as if nothing had been
+    shape = SHAPES["small-d128"].replace(n_layers=1, hidden=256, n_q_heads=8, n_kv_heads=8, intermediate=64, vocab=4096)
+    n = 14000
+    assert rl.debug_staging_plan(n, 8, n)[1] == 0
+    e = rl.RolloutEngine(make_weight_blob(shape, seed=5, weight_std=0.05), max_context=64, max_trajectories=n, kv_pool_pages=2 * n)
+    ids = np.arange(n, dtype=np.int32)
+    e.append_observation([0, n - 1], np.arange(32), [16, 16])
+    e.append_observation(ids[1:-1], np.ones(n - 2, np.int32), np.ones(n - 2, np.int32))
+    before = e.n_free_pages(), e.traj_read(0)[3].tolist()
+    with pytest.raises(rl.RolloutError):
+        e.decode_steps(ids, 3, 1.0, 5)
+    assert (e.n_free_pages(), e.traj_read(0)[3].tolist()) == before
+    want = e.decode_step([n - 1], 1.0, 7), e.decode_step([0], 1.0, 7)
+    assert e.n_free_pages() == before[0] - 2 and len(e.traj_read(0)[3]) == 2 and np.isfinite([w[1] for w in want]).all()
+    e.close()
