@@ -914,15 +914,17 @@ const int kMaxStepsPerChunk = 1024, kStepsPerCopy = 8;
 // waited for, instead of in front of the regions.  group: steps whose metadata goes over in one copy, packed into the front
 // of their regions (the first step's alone, with the entries, so that the GPU starts at once); regions: a multiple of it.
 // A small fp32 rollout (51 passes) takes 3.17 ms in groups of eight; with a copy and an event per step, a wait for the
-// entries and two copies at the end it took 3.50.
+// entries and two copies at the end it took 3.50.  Two groups at least, so that one is filled while the GPU works on the other's
+// steps; and where the entries would leave room for fewer regions than that takes they go first, which costs tens of us a call
+// whose steps have hundreds of rows.
 struct StagingPlan { bool flush; int regions, group; };
 size_t staging_region_ints(int n, int attn_slots) { return 7 * (size_t)n + 8 * (size_t)(2 * n + attn_slots + 8); }
 StagingPlan plan_staging(size_t meta_ints, size_t region_ints, size_t entry_ints) {
   auto fit = [&](size_t taken) { return taken >= meta_ints ? 0 : (int)std::min<size_t>((meta_ints - taken) / region_ints, 64); };
   StagingPlan p{};
-  p.flush = entry_ints > meta_ints / 4 || fit(entry_ints) < 1;
+  p.flush = entry_ints > meta_ints / 4 || fit(entry_ints) < std::min(fit(0), 2 * kStepsPerCopy);
   p.regions = fit(p.flush ? 0 : entry_ints);
-  p.group = p.regions >= kStepsPerCopy ? kStepsPerCopy : 1;
+  p.group = std::max(1, std::min(kStepsPerCopy, p.regions / 2));
   p.regions -= p.regions % p.group;
   return p;
 }

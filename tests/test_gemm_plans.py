@@ -219,8 +219,10 @@ def test_many_row_loads_refuse_what_the_kernel_does_not_take(bad):
 
 
 def test_staging_of_several_decode_steps():
-    # a call that fits without its page-table entries is taken
+    # a call that fits without its page-table entries is taken; two groups wherever there are two regions, so that the host fills one
+    # while the GPU works on the other; the entries cost no regions that two groups of eight would need
     rng = random.Random(8)
+    seen = set()
     for _ in range(4000):
         T = int(round(2 ** rng.uniform(0, 15)))
         n, nkv, rows = rng.randint(1, T), rng.choice([0, 1, 2, 4, 8, 16]), rng.choice([0, 128, 2048, 16384])
@@ -233,4 +235,8 @@ def test_staging_of_several_decode_steps():
         assert (regions >= 1) == (bare >= 1)
         assert regions * region + (0 if ahead else 3 * pages) <= room
         assert 1 <= group <= 8 and regions % group == 0
+        if bare >= 2:
+            assert regions >= 2 * group and regions > min(bare, 16) - group
+        seen.add((ahead, min(regions, 2), min(group, 2)))
+    assert seen == {(a, r, g) for a in (False, True) for r, g in ((1, 1), (2, 1), (2, 2))} | {(False, 0, 1), (True, 0, 1)}
     assert rl.debug_staging_plan(128, 8, 128, 0, 600) == (False, 56, 8)

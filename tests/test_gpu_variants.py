@@ -476,8 +476,9 @@ def test_fp32_products_with_the_norm_inside(hidden, head_dim, heads, intermediat
 
 @pytest.mark.parametrize("n,steps", [(700, 20), (2000, 12), (2000, 330)])
 def test_decode_steps_of_batches_that_leave_few_staging_regions(n, steps):
-    # 12 regions (one group of eight, used again), four (a copy per step), and 42 000 page-table entries, more than a quarter of
-    # the staging buffer: the single steps' bits
+    # 28 regions (three groups of eight), eight (two groups of four, used again), and 42 000 page-table entries, more than a quarter of
+    # the staging buffer (ahead on their own): the single steps' bits
+    assert rl.debug_staging_plan(n, 0, n, 0, n * (steps // 16 + 1)) == {(700, 20): (False, 24, 8), (2000, 12): (False, 8, 4), (2000, 330): (True, 8, 4)}[n, steps]
     shape = SHAPES["tiny"].replace(n_layers=1, hidden=64, n_q_heads=1, n_kv_heads=1, intermediate=64, vocab=128)
     blob = make_weight_blob(shape, seed=5, weight_std=0.05)
     kw = dict(max_context=352, max_trajectories=n, kv_pool_pages=n * 22)
