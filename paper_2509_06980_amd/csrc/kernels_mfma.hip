@@ -1981,9 +1981,11 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 
 // Norm, RoPE and the cache write inside the decode attention: a launch less and the queries' way through memory, 1.4 to 2.9 us a layer
 // where the keys and values of all rows take less time than that chain (16 heads over 8: 1 row 1.6 to 2.8 us, 16 rows over 3000 keys
-// 2.9, 96 over 1000 1.4).  Where they are more than 400 MB the memory is busy from the first workgroup on, the prologue's
-// dependent reads wait behind the pages of the others, and the kernel of its own is the better one: 48 rows over 3000 keys (590 MB) 0.2 us
-// a layer in favour of this, 128 over 1000 (524 MB) 0.2, 64 over 3000 (786 MB) 2.4 against it (8-bit cache, 393 MB: 0.6 for).
+// 2.9, 96 over 1000 1.4).  The more keys there are, the sooner the memory is busy all the time, and then the prologue's dependent reads
+// wait behind the pages of the others.  us a layer of whole steps in favour of it, both caches, 128 / 64 / 40 rows of 32 heads over 8 and
+// 128 / 64 of 16 over 8: 262 MB 0 to 3.5 (mean 1.8), 393 MB -0.4 to 1.7 (0.6), 524 MB -1.3 to 1.8 (0.4), 655 MB -3.0 to 1.9 (-0.6),
+// 786 MB -5.3 to 0.5 (-1.6), 1049 MB -4.8 to 0.2 (-2.7).  40 long rows stay ahead to 786 MB, 128 short ones fall behind soon after
+// 400, the last at which none loses more than two runs of one side differ.
 // The prologue has lanes for ten heads: groups of up to eight queries, a key and a value.
 bool attention_takes_rope(double kv_bytes, const ModelDims& md) { return md.nq / md.nkv <= 8 && kv_bytes <= 400e6; }
 void launch_attention_mfma(hipStream_t s, const bf16_t* q, KvPool pool, const AttnItem* items,
