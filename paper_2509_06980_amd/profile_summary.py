@@ -13,15 +13,24 @@ reads back, together with the hash of the kernel source the counters belong to.
 import csv
 import hashlib
 import os
+import re
 import sys
 from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SRC = os.path.join(HERE, "csrc", "kernels_mfma.hip")
+KERNEL_SRC = [os.path.join(HERE, "csrc", name) for name in ("kernels_mfma.hip", "qkrope.h")]
 
 
 def kernel_source_hash():
-    return hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+    """Of the files that the decode attention is compiled from."""
+    return hashlib.sha256(b"".join(open(path, "rb").read() for path in KERNEL_SRC)).hexdigest()[:16]
+
+
+def decode_attention_form(name):
+    """Where norm, RoPE and cache write of its rows are done, for the bf16-cache instance of the decode attention, from a
+    kernel's name; None for any other kernel."""
+    m = re.search(r"attention_mfma_kernel<false, (\d)>", name)
+    return m and ("before", "inside", "inside, rows divided by their rms there")[int(m.group(1))]
 
 
 def read_counter(path, counter):
@@ -38,20 +47,22 @@ def read_counter(path, counter):
 
 
 def trace_summary(path):
-    """Average duration of attention_mfma_kernel per grid size from a rocprofv3 kernel trace CSV
+    """Average duration of attention_mfma_kernel per form and grid size from a rocprofv3 kernel trace CSV
     (decode launches have grid = trajectories x kv heads x 256 threads)."""
     acc = defaultdict(lambda: [0, 0.0])
     with open(path, newline="") as f:
         for r in csv.DictReader(f):
-            if "attention_mfma_kernel<false," not in r["Kernel_Name"]:
+            form = decode_attention_form(r["Kernel_Name"])
+            if not form:
                 continue
-            g = int(r.get("Grid_Size_X") or r.get("Grid_Size"))
-            a = acc[g]
+            a = acc[int(r.get("Grid_Size_X") or r.get("Grid_Size")), form]
             a[0] += 1
             a[1] += float(r["End_Timestamp"]) - float(r["Start_Timestamp"])
-    print("| attention_mfma_kernel grid (threads) | launches | avg us |\n|---|---|---|")
-    for g, (n, t) in sorted(acc.items(), key=lambda kv: -kv[1][0])[:6]:
-        print(f"| {g} | {n} | {t / n / 1e3:.2f} |")
+    if not acc:
+        raise SystemExit(f"{path}: no launch of attention_mfma_kernel with the bf16 cache")
+    print("| attention_mfma_kernel grid (threads) | norm, RoPE and cache write of its rows | launches | avg us |\n|---|---|---|---|")
+    for (g, form), (n, t) in sorted(acc.items(), key=lambda kv: -kv[1][0])[:8]:
+        print(f"| {g} | {form} | {n} | {t / n / 1e3:.2f} |")
 
 
 def decode_products():
@@ -177,9 +188,9 @@ def rollout_summary(trace_path, stats_path, bench_log):
           f"{r['bytes_per_launch']} bytes per launch; measured streaming-read ceiling of the box "
           f"{b['measured_stream_read_GBs']} GB/s.\n")
     print("attention_mfma_kernel<false, ROPE> (the bf16-cache instance; decode launches: one workgroup per "
-          "trajectory x kv head) by launch shape, from the kernel trace:\n")
+          "trajectory x kv head) by form and launch shape, from the kernel trace:\n")
     trace_summary(trace_path)
-    print("\nThe decode average agrees with the HIP-event figure of bench.py (the profiler adds a little "
+    print("\nThe HIP-event figure of bench.py averages over these forms (and the profiler adds a little "
           "per-launch overhead to the event bracket). Chunked prefill runs in attention_prefill_kernel.\n")
     print("| kernel | calls | total ms | avg us | % |\n|---|---|---|---|---|")
     with open(stats_path, newline="") as f:
@@ -272,11 +283,23 @@ def main():
 
     kf, kw = calib(fetch), calib(write)
     grid = n_traj * n_kv * 256                      # decode launches: one workgroup per (trajectory, kv head)
-    name = "attention_mfma_kernel<false,"           # the bf16-cache instance of the decode kernel
-    fa = fetch[name][grid]
-    wa = write[name][grid]
-    f_bytes = sum(fa) / len(fa) * 1024.0 * kf
-    w_bytes = sum(wa) / len(wa) * 1024.0 * kw
+    forms = {}                                      # form -> fetched, written KiB of its launches
+
+    def collect(tab, which, path):
+        for name, grids in tab.items():
+            form = decode_attention_form(name)
+            if form and grid in grids:
+                forms.setdefault(form, ([], []))[which].extend(grids[grid])
+        if not any(f[which] for f in forms.values()):
+            raise SystemExit(f"{path}: no decode launch of attention_mfma_kernel with the bf16 cache and {grid} threads")
+
+    collect(fetch, 0, sys.argv[1])
+    collect(write, 1, sys.argv[2])
+    fa, wa = (sum((f[i] for f in forms.values()), []) for i in (0, 1))
+
+    def mean(values, factor):
+        return sum(values) / len(values) * 1024.0 * factor if values else float("nan")
+    f_bytes, w_bytes = mean(fa, kf), mean(wa, kw)
     print("# HBM traffic of attention_mfma_kernel, cfg3 rollout (Qwen3-4B shape, 128 trajectories)\n")
     print("Commands (MI355X box, repository root; one counter per run):\n")
     print("    rocprofv3 --pmc FETCH_SIZE --kernel-include-regex 'attention_mfma_kernel|copyBuffer' "
@@ -287,6 +310,8 @@ def main():
     print(f"Calibration copy: embedding table, {copy_bytes} bytes read and written by `__amd_rocclr_copyBuffer`; "
           f"FETCH_SIZE factor {kf:.4f}, WRITE_SIZE factor {kw:.4f} (expected bytes / counter KiB x 1024).\n")
     print(f"Decode launches (grid {grid} threads): {len(fa)} with FETCH_SIZE, {len(wa)} with WRITE_SIZE.\n")
+    for form, (f, w) in sorted(forms.items()):
+        print(f"- norm, RoPE and cache write {form}: {len(f)} launches, {mean(f, kf) / 1e6:.1f} MB fetched, {mean(w, kw) / 1e6:.1f} MB written each")
     print(f"- fetched from HBM per launch: {f_bytes / 1e6:.1f} MB")
     print(f"- written to HBM per launch: {w_bytes / 1e6:.1f} MB")
     print(f"- traffic_bytes_per_launch: {f_bytes + w_bytes:.0f}")
