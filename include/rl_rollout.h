@@ -288,6 +288,9 @@ int rl_debug_many_row_loads(int32_t rows, int32_t n, int32_t k, int32_t kernel, 
  * the accumulated duration, the number of timed launches and the bytes of keys / values
  * those launches had to read: attn_kv_bytes sums context length x bytes per token per layer over
  * the rows; attn_kv_unique_bytes counts a page shared by several trajectories of the step once.
+ * Steps of up to 400 MB of keys and values a layer have QK-norm, RoPE and the cache write of their rows inside the attention
+ * launch (bf16 models with head_dim 128 and groups of up to eight heads): there the duration covers these too, while
+ * the bytes are the same keys and values, so bytes over duration is a bandwidth of the attention alone only above that.
  */
 int rl_timing_enable(rl_model* m, int32_t every);
 int rl_timing_read(rl_model* m, double* attn_ms, int64_t* attn_launches, double* attn_kv_bytes,
