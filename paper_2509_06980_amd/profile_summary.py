@@ -67,11 +67,11 @@ def trace_summary(path):
 
 def decode_products():
     """(kernel, threads of the launch) -> what it has to move, for the products of a decode step of 128
-    trajectories of the Qwen3-4B shape."""
+    trajectories of the Qwen3-4B shape (weights through the caches, rows divided by their rms before)."""
     from synthetic import SHAPES
     from .binding import debug_pass_plan
     s, rows = SHAPES["qwen3-4b"], 128
-    out = {("gemm_mfma_kernel<4, 4>", (s.vocab + 127) // 128 * 256):
+    out = {("gemm_mfma_kernel<4, 4, false, false>", (s.vocab + 127) // 128 * 256):
            f"lm-head: {s.vocab * s.hidden * 2 / 1e6:.1f} MB weights, {rows * s.vocab * 4 / 1e6:.1f} MB logits written"}
     dims = dict(qkv=(s.q_width + 2 * s.kv_width, s.hidden), o=(s.hidden, s.q_width),
                 gate_up=(2 * s.intermediate, s.hidden), down=(s.hidden, s.intermediate))
@@ -80,7 +80,7 @@ def decode_products():
             continue
         n, k = dims[name]
         ring = "128, 3" if width == 5 else "64, 4"
-        key = (f"gemm_decode_kernel<{2 if epilogue == 'swiglu' else 0}, 2, {width}, {ring}>", (n // 16 + width - 1) // width * slices * 256)
+        key = (f"gemm_decode_kernel<{2 if epilogue == 'swiglu' else 0}, 2, {width}, {ring}, false, false>", (n // 16 + width - 1) // width * slices * 256)
         written = rows * n / 1e6 if epilogue == "swiglu" else rows * n * 4 / 1e6      # bf16 of half the columns
         out[key] = f"{name}: {n * k * 2 / 1e6:.1f} MB weights, {slices} x {written:.1f} MB written"
     return out
@@ -118,7 +118,7 @@ def decode_step_table(fetch_path, write_path):
             rows.append((k, g, len(vals), sum(vals) / len(vals) * 1024 * kf / 1e6,
                          sum(wv) / len(wv) * 1024 * kw / 1e6 if wv else float("nan")))
     for k, g, n, fm, wm in sorted(rows, key=lambda r: -r[2] * (r[3] + r[4])):
-        print(f"| {k[:60]} | {g} | {n} | {fm:.2f} | {wm:.2f} | {expect.get((k, g), '')} |")
+        print(f"| {k[:64]} | {g} | {n} | {fm:.2f} | {wm:.2f} | {expect.get((k, g), '')} |")
 
 
 def mfma_table(counter_path, trace_path):

@@ -68,3 +68,19 @@ def test_hash_covers_every_file_of_the_decode_attention(tmp_path, monkeypatch):
     changed.write_bytes(open(ps.KERNEL_SRC[1], "rb").read() + b"\n")
     monkeypatch.setattr(ps, "KERNEL_SRC", [ps.KERNEL_SRC[0], str(changed)])
     assert ps.kernel_source_hash() != before
+
+
+def test_products_of_a_decode_step_are_named_as_in_the_library(tmp_path, capsys):
+    # what a product has to move stands beside what it moved: the table's names are those of kernels that are there
+    from test_kernel_resources import _kernels
+
+    import paper_2509_06980_amd as rl
+    there = {f"{name}<{', '.join(map(str, args))}>" for name, args in _kernels(rl.LIB_PATH)}
+    expect = ps.decode_products()
+    assert {re.match(r"\w+: ", what.replace("lm-head", "head")).group(0) for what in expect.values()} == {"head: ", "qkv: ", "o: ", "gate_up: ", "down: "}
+    for kernel, _ in expect:
+        assert kernel.replace("false", "0") in there, kernel
+    (kernel, grid), what = next(iter(expect.items()))
+    rows = [(*COPY, 151936 * 2560 * 2 / 1024)] + [(f"void {kernel}(float*)", grid, 1000.0)] * 100
+    ps.decode_step_table(_counters(tmp_path / "f.csv", "FETCH_SIZE", rows), _counters(tmp_path / "w.csv", "WRITE_SIZE", rows))
+    assert f"| {kernel} | {grid} | 100 | 1.02 | 1.02 | {what} |" in capsys.readouterr().out
