@@ -157,7 +157,8 @@ __global__ __launch_bounds__(256) void row_max_kernel(const float* __restrict__ 
 // current one's arithmetic.  A thread leaves its sums of a segment in LDS and goes on; behind the last one a wave adds up
 // every fourth segment, so that the chains of lane exchanges and the barriers come once per workgroup and not per segment: 128 x 151 936
 // logits 16.2 us (18.4 with a reduction and two barriers per segment; 30 us, and 38 + 8 us with a launch of its own for the maxima,
-// before).  put_max: the maximum is left in the row's segmax entries for the last kernel (arg-max: they hold every segment's own).
+// before).  The integer sums take any order; a log-prob's bits are those of fp32 sums over a wave's 64 threads, halves first, and then over
+// the four waves, so sixteen lanes add up one wave's (rotated in LDS so that they meet no bank twice).  put_max: the maximum is left in the row's segmax entries for the last kernel (arg-max: they hold every segment's own).
 constexpr int kMaxSpw = 8;
 template <bool VEC>
 __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict__ z, size_t ldz, int V, float c,
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict
       }
     }
     sw[seg - s0][tid] = ws;
-    se[seg - s0][tid] = es;
+    se[seg - s0][tid ^ wave << 4] = es;
     if (seg + 1 < s1) {
 #pragma unroll
       for (int i = 0; i < 16; i++) v[i] = nx[i];
@@ -235,12 +236,15 @@ __global__ __launch_bounds__(256) void seg_weight_kernel(const float* __restrict
   __syncthreads();
   for (int seg = s0 + wave; seg < s1; seg += 4) {
     const uint64_t* pw = sw[seg - s0] + lane;
-    const float* pe = se[seg - s0] + lane;
     uint64_t ws = (pw[0] + pw[64]) + (pw[128] + pw[192]);
-    float es = __fadd_rn(__fadd_rn(pe[0], pe[64]), __fadd_rn(pe[128], pe[192]));
-    for (int o = 32; o > 0; o >>= 1) {
-      ws += __shfl_xor(ws, o, 64);
-      es = __fadd_rn(es, __shfl_xor(es, o, 64));
+    const int w = lane >> 4;
+    const float* pe = se[seg - s0] + w * 64;
+    auto of = [&](int t) { return pe[t ^ w << 4]; };      // thread t of wave w
+    float es = __fadd_rn(__fadd_rn(of(lane & 15), of((lane & 15) + 32)), __fadd_rn(of((lane & 15) + 16), of((lane & 15) + 48)));
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+      ws += __shfl_xor(ws, 1 << k, 64);
+      es = __fadd_rn(es, __shfl_xor(es, k < 4 ? 8 >> k : 1 << k, 64));
     }
     if (lane == 0) {
       segw[(size_t)row * nseg + seg] = ws;

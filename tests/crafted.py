@@ -1,10 +1,11 @@
-"""Weights under which one key, one page or one rounding decides the logits (test helper).
+"""Weights under which one key, one page or one rounding decides the logits, and sums in the kernels' order (test helper).
 
 All models have one layer, an MLP of zeros and a RoPE base so large that the upper half of a head's dim pairs do not rotate.
 """
 import numpy as np
 
 from oracle.fp8 import e4m3_round
+from oracle.sampler import EXP2_POLY, scale_constant
 from synthetic import SHAPES, make_weight_blob
 from synthetic.weights import BLOB_HEADER_BYTES, _to_bf16_bits, tensor_table
 
@@ -184,3 +185,38 @@ class KeyBits:
         h[2 * t + 4] += 1.0
         h[2 * t + 5] += 2.0 ** -8
         return self.head.astype(np.float64) @ (h / np.sqrt(np.mean(h * h) + 1e-6))
+
+
+def weight_sum(z, temperature, by_lane=False):
+    """The fp32 sum of the sampler's weights over a row of more than 16384 numbers in the kernels' order: a segment of 4096 by 256 threads
+    of sixteen, a wave's 64 threads, four waves, 64 lanes of segments.  by_lane: the four waves' threads first."""
+    f, v = np.float32, len(z)
+    t = ((z - z.max()) * scale_constant(temperature)).astype(f)
+    n = np.floor(t)
+    p = np.full_like(t, EXP2_POLY[6])
+    for c in EXP2_POLY[5::-1]:
+        p = (p * (t - n)).astype(f) + c
+    e = np.zeros(-(-v // 4096) * 4096, f)
+    e[:v] = np.where(n < -40, f(0), np.ldexp(p, n.astype(np.int32) + 32))
+    seg = e.reshape(-1, 4, 256, 4).transpose(0, 2, 1, 3).reshape(-1, 256, 16) if v % 4 == 0 else e.reshape(-1, 16, 256).transpose(0, 2, 1)
+
+    def chain(x):                                # one after the other
+        out = np.zeros(x.shape[:-1], f)
+        for i in range(x.shape[-1]):
+            out = out + x[..., i]
+        return out
+
+    def tree(x):                                 # 64 lanes, halves first
+        for o in (32, 16, 8, 4, 2, 1):
+            x = x[..., :o] + x[..., o:]
+        return x[..., 0]
+
+    def four(x):
+        return (x[..., 0] + x[..., 1]) + (x[..., 2] + x[..., 3])
+    threads = chain(seg).reshape(-1, 4, 64)
+    sums = (tree(four(threads.transpose(0, 2, 1))) if by_lane else four(tree(threads))) * f(2.0 ** -32)
+    k = len(sums)
+    if k <= 64:
+        return tree(np.r_[sums, np.zeros(64 - k, f)])
+    lanes = np.r_[sums, np.zeros(-k % 256, f)].reshape(-1, 256).T
+    return four(tree(chain(lanes).reshape(4, 64)))

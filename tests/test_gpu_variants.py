@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2509_06980_amd as rl
-from crafted import FILLER, KEY, KINDS, QUERY, SELF, KeyBits, ManySmallWeights, Peaked
+from crafted import FILLER, KEY, KINDS, QUERY, SELF, KeyBits, ManySmallWeights, Peaked, weight_sum
 from gemm_cases import DECODE, DECODE_ROWS, MANY_ROWS, MANY_ROWS_ORACLE, RESIDUAL, RESIDUAL_ROWS, small
 from oracle import OracleEngine
 from oracle.bf16_error_model import forward_bf16_model
@@ -36,6 +36,22 @@ def test_sampler_segment_layouts(V, rows, T):
         assert ids[r] == tok, (r, ids[r], tok)
         # float32 sums of up to V terms in a tree over 16 x 256 and the segments: well below 1e-5
         assert abs(lps[r] - lp) < 1e-5 * max(1.0, abs(lp))
+
+
+@pytest.mark.parametrize("V,rows", [(16388, 8), (20483, 300), (151936, 128), (151937, 6), (300004, 40)])
+def test_sampler_log_probs_sum_in_one_order(V, rows):
+    # a token whose weight is all but a thousandth: its log-prob is minus the logarithm of a sum just above one, in which an fp32 step of
+    # the sum shows 2000 times over.  One to eight segments per workgroup, more than 64 in a row, rows of whole 16-byte pieces and others
+    rng = np.random.default_rng(V)
+    z = rng.standard_normal((rows, V)).astype(np.float32)
+    at = rng.integers(0, V, rows)
+    z[np.arange(rows), at] = 8.0 + np.log(V / 2.7)
+    sums = np.array([weight_sum(r, 1.0) for r in z[:40]])
+    assert (sums != [weight_sum(r, 1.0, by_lane=True) for r in z[:40]]).any() and sums.max() < 1.004
+    ids, lps = rl.sample_from_logits(z, 1.0, np.full(rows, 2**31, np.uint32))
+    assert np.array_equal(ids, at)
+    # an fp32 step of the sums is 2^-23; of a logarithm below 2^-8 it is 2^-32
+    assert np.abs(lps[:40] + np.log(sums.astype(np.float64))).max() < 2.0 ** -29
 
 
 @pytest.mark.parametrize("V", [5, 4100, 4101, 16384, 16388])
