@@ -345,9 +345,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const bf16_t* __restrict
 // What bounds it at thousands of rows is power: on operands of zeros the same instructions take 213 us instead of 295
 // (8192 x 2560 x 9728: 1.92 and 1.38 PFLOP/s), and MFMAs alone, on registers, reach 2.4 and 1.87.  (16x16x32 MFMAs
 // draw less, 2.13 PFLOP/s alone with two waves a SIMD, but one wave a SIMD cannot issue them back to back: 312 us.)
-// MB = 2: bound by what the CUs fetch from L2 (without the loads 587 x 2560 x 9728 in five slices takes 27 us of 35) and by the
-// latencies of one wave a SIMD: the operands of a whole chunk are read one chunk ahead, one read behind an MFMA, and the
-// next chunk's loads between them (587 x 2560 x 4096 undivided, 50 workgroups: 51 us with operands half a chunk ahead, reads and
+// MB = 2: bound by what the CUs fetch from L2 (without the loads 587 x 2560 x 9728 in five slices takes 27 us of 35; matrix pipes 0.36 of
+// the time busy, addressers 0.60) and by the latencies of one wave a SIMD: the operands of a whole chunk are read one chunk ahead, one
+// read behind an MFMA, and the next chunk's loads between them (587 x 2560 x 4096 undivided, 50 workgroups: 51 us with operands half a chunk ahead, reads and
 // loads in front of each group of four MFMAs; 43.5 a chunk ahead; 41.4 one by one).  Three stages let two workgroups share a CU;
 // where there is only one to a CU anyway four hide more of the weights' stream (300 x 19456 x 2560 42.6 -> 39.7 us).
 // The fifth accumulator column lives in vector registers: 320 accumulator registers exceed the 256
@@ -1685,11 +1685,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 //   contiguous bytes.  Key group 2 x + l / 32, these eight keys, has its own fp32 sum of the terms before they are rounded.
 // Nothing is moved between registers to put an operand together.  One barrier per pair: behind it the pair is complete for
 // every wave and the stage of the pair before is free for the pair after the next.
-// What bounds it: a wave's matrix and vector work take turns (32 keys x 32 columns: 512 cycles of MFMA, 60 vector instructions
-// of which 16 exponentials), so other waves of the SIMD have to fill the pipes, and three fit the registers (149); then power: on
-// operands of zeros 12 x 610 rows over 3000 keys take 329 us, on random ones 395 (1.0 PFLOP/s).  Before, with 16x16x32 MFMAs,
-// two waves a SIMD, keys and values through registers and the pages' addresses formed by every lane: 430; 16 x 512 rows over
-// none 77 -> 69 us, 24 x 340 over 2000 with two heads a group 204 -> 169.
+// What bounds it: a wave's matrix and vector work take turns (32 keys x 32 columns: 512 cycles of MFMA, 61 vector instructions
+// of which 16 exponentials), so other waves of the SIMD have to fill the pipes, and three fit the registers (155; 8-bit cache 150); then
+// power.  Over 3300 keys the matrix pipes are busy 0.48 of the time, LDS 0.60 of which 0.24 are bank conflicts, at 1.9 GHz; on operands of
+// zeros 12 x 610 rows over 3000 keys take 330 us, on random ones 421 (0.94 PFLOP/s).  Before, with 16x16x32 MFMAs, two waves a SIMD, keys
+// and values through registers and the pages' addresses formed by every lane: 418 and 502; 16 x 512 rows over none 87 -> 78 us,
+// 24 x 340 over 2000 with two heads a group 227 -> 179, 8-bit cache 515 -> 432 (all from traces of engine passes).
 // Items are taken from the last to the first: a trajectory's later rows see more keys, and short items fill the end of the launch
 // better (8 x 1024 rows over none 105 -> 99 us).
 // Page indices past the item's last page are clamped to it (their keys are masked: they lie
