@@ -408,7 +408,8 @@ def main():
                     "kernel": "attention_mfma_kernel" if eng.config["head_dim"] == 128 and
                     eng.config["weight_dtype"] == 1 else "attention_generic_kernel",
                     "avg_launch_us": round(attn_ms * 1e3 / attn_n, 2), "launches_timed": int(attn_n),
-                    "bytes_per_launch": round(attn_unique / attn_n)}
+                    "bytes_per_launch": round(attn_unique / attn_n),
+                    "note": "launches of up to 400 MB of keys and values also form their rows' QK-norm, RoPE and cache write (head_dim 128)"}
     out = {
         "metric": "rollout_generated_tokens_per_s", "value": round(n_gen / dt, 1), "unit": "tokens/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
